@@ -7,13 +7,13 @@
 // and in what is read before / written after the loop.
 //
 // Shape of the computation (d = 128, b_q = 128, bf16 in, fp32 accumulate):
-//   work-group = one query block = 4 waves x 32 query rows, two work-groups per CU
-//   (two waves per SIMD, so one wave's softmax overlaps the other's MFMAs);
-//   K/V tile   = 64 keys, double-buffered in LDS, filled by 16-byte direct-to-LDS buffer
-//   loads (no staging registers; a gathered row and a contiguous row cost the same);
+//   work-group = one query block = 4 waves x 32 query rows, three work-groups per CU
+//   (three waves per SIMD, so one wave's softmax and LDS latency overlap the others' MFMAs);
+//   K/V tile   = 64 keys, two K stages and one V stage in LDS, filled by 16-byte direct-to-LDS
+//   buffer loads (no staging registers; a gathered row and a contiguous row cost the same);
 //   S^T = K Q^T  with v_mfma_f32_32x32x16_bf16 (keys are the M dimension, query
 //   rows the N dimension, so one lane owns one query row and the row max / sum
-//   are in-lane reductions plus one exchange between the wave's halves);
+//   are in-lane reductions; the wave's halves meet only when a reference is raised);
 //   O^T = V^T P^T with the same instruction; V stays row-major in LDS and its operand
 //   is read with the transposing LDS load ds_read_b64_tr_b16.
 // LDS layout of a tile: a direct-to-LDS load writes the 64 lanes' 16 bytes to consecutive
@@ -21,9 +21,22 @@
 // sits in group kk % 16, row kk / 16; groups are padded (K: 16 B, V: 64 B) so that the 16
 // lanes of an operand read fall into different banks.
 // The running reference m of exp(s - m) is only raised when a row's maximum
-// exceeds it by more than 2^8; the accumulators (which live in AGPRs) are then
-// rescaled, otherwise they are left alone.  The true row maximum, which is the
-// anchor that stage 1 exports, is tracked separately.
+// exceeds it by more than 2^8; the accumulators are then rescaled, otherwise they are left
+// alone.  The true row maximum, which is the anchor that stage 1 exports, is tracked separately.
+//
+// What bounds it: a wave's own chain per tile (load issue, 16 score MFMAs, softmax, 16 P V MFMAs,
+// two barriers) is about 2.7 times as long as its 1024 MFMA cycles, so the matrix pipe needs three
+// waves per SIMD to stay busy.  Three fit if a wave takes at most 168 registers and a work-group a
+// third of the LDS.  V therefore has one stage: V tile t is issued when tile t - 1 has been
+// consumed and is awaited after the scores and softmax of tile t, behind which its latency hides
+// (K tile t + 1 has the whole of tile t).  At 168 registers the compiler left alone issues every LDS operand
+// read right before its MFMA, so the read-ahead is written out and pinned with scheduling fences,
+// and no load or wait stands under a condition (a path on which fewer loads are outstanding would
+// turn the waits into vmcnt(0)).
+// Measured, 131072 tokens x 32 heads, step 16: anchor computation 3.10 -> 2.80 ms (the two-per-CU form
+// with two V stages before), matrix pipe 50 -> 61 % busy; the engine clock falls from 1.70 to 1.62 GHz
+// at the same time (the card's power limit), which is why the time gains less than the cycles.  Of this the third
+// wave alone gave 5 %, the pinned order 4 %.
 #include "aa_engine_bf16_common.h"
 #include "aa_pool.h"
 
@@ -35,13 +48,13 @@ using namespace eng;
 // the other modes' branches, registers and, above all, merged control-flow paths (where paths with
 // different numbers of outstanding loads meet, the compiler's waits assume the shortest).
 template <int FLAGS>
-__global__ __launch_bounds__(256, 2) void engine_bf16_kernel(EngineArgs a) {
+__global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     constexpr int flags = FLAGS;
     constexpr int NW = 4;                            // waves per work-group
     static_assert(NW == 4, "the loader deals four groups of a tile to every wave");
     // one LDS object per stage, so that the compiler can tell that the asynchronous loads into
-    // one stage do not alias the operand reads from the other
-    __shared__ __attribute__((aligned(16))) char Ks0[KBYTES], Ks1[KBYTES], Vs0[VBYTES], Vs1[VBYTES];
+    // one stage do not alias the operand reads from the others
+    __shared__ __attribute__((aligned(16))) char Ks0[KBYTES], Ks1[KBYTES], Vs0[VBYTES];
     __shared__ float red[NW];
     __shared__ float qpart[(FLAGS & kEngStoreState) ? 4 : 1][128];   // pooled-query partial sums (stage 1)
     const KParams& p = a.p;
@@ -55,9 +68,9 @@ __global__ __launch_bounds__(256, 2) void engine_bf16_kernel(EngineArgs a) {
     const Seq sq = seq_of(p, wk.b);
     const int row0 = wk.i * BQ;
     if (row0 >= sq.len) return;
-    // Two waves share a SIMD (one from each resident work-group).  A wave raises its issue priority
-    // for its MFMA blocks and drops it for its softmax, so a wave with matrix work wins over a
-    // sibling that is in its vector-ALU part, and the pair does not settle into lockstep.
+    // Three waves share a SIMD (one from each resident work-group).  A wave raises its issue priority
+    // for its MFMA blocks and drops it for its softmax, so a wave with matrix work wins over
+    // siblings that are in their vector-ALU part, and they do not settle into lockstep.
     __builtin_amdgcn_s_setprio(2);
     const int hk = wk.h / p.grp;
     const int g = wk.i / p.step;
@@ -105,47 +118,62 @@ __global__ __launch_bounds__(256, 2) void engine_bf16_kernel(EngineArgs a) {
     auto tile_start = [&](int t) -> int {            // first key of contiguous tile t (t < nA)
         return TK * (t < T1 ? t : t2s + (t - T1));
     };
-    // Keys of a list tile come from the index list: they are fetched one step ahead into kidx.
-    // Nothing else ever writes kidx's registers: a vector-ALU write to registers that may still
+    // Keys of a list tile come from the index list.  Tile t's are fetched into kidx0 / kidx1 (by the
+    // parity of t) two steps ahead: its K rows are loaded in step t - 1, its V rows in step t.
+    // Nothing else ever writes these registers: a vector-ALU write to registers that may still
     // be the target of an outstanding load makes the compiler wait for every outstanding load,
     // the asynchronous tile loads included.  Keys of a contiguous tile are plain arithmetic.
-    intx4 kidx = {0, 0, 0, 0};
-    auto idx_prefetch = [&](int t) {
+    intx4 kidx0 = {0, 0, 0, 0}, kidx1 = {0, 0, 0, 0};
+    auto idx_prefetch = [&](int t, intx4& kidx) {
         if (t >= nA && t < nT) kidx = *(const intx4*)(a.idx + lbase + (long long)(t - nA) * TK + kq0);
     };
     // asynchronous: completion is awaited by wait_vmem()
-    auto tile_load = [&](int t, char* Kb, char* Vb) {
-        char* kd = Kb + GPW * wave * KGRP;
-        char* vd = Vb + GPW * wave * VGRP;
-        if (t < nA) {
-            const int t0 = tile_start(t) + kq0;
+    // (no branch: the byte offsets of a contiguous tile are clamped to the sequence's last row)
+    const unsigned klane = (unsigned)kq0 * kstb + 16u * lch, vlane = (unsigned)kq0 * vstb + 16u * lch;
+    const unsigned klast = (unsigned)(sq.len - 1) * kstb + 16u * lch, vlast = (unsigned)(sq.len - 1) * vstb + 16u * lch;
+    auto rows_load = [&](int t, const __amdgpu_buffer_rsrc_t& rs, unsigned stb, unsigned lane0, unsigned last, char* dst,
+                         int pitch, const intx4& kidx) {
+        const bool is_list = (FLAGS & kEngList) && t >= nA;
+        const unsigned base = (unsigned)tile_start(t) * stb;
 #pragma unroll
-            for (int j = 0; j < GPW; ++j) {
-                const unsigned key = (unsigned)min(t0 + j, sq.len - 1);
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, (lds_void*)(kd + j * KGRP), 16,
-                                                         (int)(key * kstb + 16u * lch), 0, 0, 0);
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(vrs, (lds_void*)(vd + j * VGRP), 16,
-                                                         (int)(key * vstb + 16u * lch), 0, 0, 0);
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < GPW; ++j) {
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, (lds_void*)(kd + j * KGRP), 16,
-                                                         (int)((unsigned)kidx[j] * kstb + 16u * lch), 0, 0, 0);
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(vrs, (lds_void*)(vd + j * VGRP), 16,
-                                                         (int)((unsigned)kidx[j] * vstb + 16u * lch), 0, 0, 0);
-            }
+        for (int j = 0; j < GPW; ++j) {
+            unsigned off = 0;
+            if (FLAGS & kEngAnchorRegion) off = min(lane0 + (base + j * stb), last);
+            if (FLAGS & kEngList) off = is_list ? (unsigned)kidx[j] * stb + 16u * lch : off;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(dst + j * pitch), 16, (int)off, 0, 0, 0);
         }
+    };
+    auto k_load = [&](int t, char* Kb, const intx4& kidx) {
+        rows_load(t, krs, kstb, klane, klast, Kb + GPW * wave * KGRP, KGRP, kidx);
+    };
+    auto v_load = [&](int t, const intx4& kidx) { rows_load(t, vrs, vstb, vlane, vlast, Vs0 + GPW * wave * VGRP, VGRP, kidx); };
+    // Work-group barrier that leaves vector-memory operations in flight.  LDS operand reads before it
+    // have been consumed by their MFMAs and the tile loads it publishes were awaited; the fences only
+    // keep the compiler from moving work across it.
+    auto bare_barrier = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
     };
 
     // The first list indices are requested before everything else: the first tile's loads need them,
     // and only them, so they go out while the Q fragments and the cached state are still on their way
     // (waits are in issue order: behind those loads the indices would arrive last).
-    if (nT > 0) idx_prefetch(0);
+    if (nT > 0) idx_prefetch(0, kidx0);
 
     // ---- Q fragments (B operand of S^T = K Q^T): lane (n, hf) holds Q[row][16 ks + 8 hf .. +8)
     bf16x8 qf[8];
     load_q_fragments(qf, a, sq, wk.b, wk.h, r, rok, 0, hf);
+
+    // ---- pipeline prologue: the first K tile goes out ahead of the cached state, which is not needed
+    // before the first P V block
+    if (nT > 0) {
+        k_load(0, Ks0, kidx0);
+        idx_prefetch(1, kidx1);
+    }
+    __builtin_amdgcn_sched_barrier(0);
 
     // ---- running state (see load_state)
     const float c2 = p.sigma * 1.4426950408889634f;  // exp(sigma*x) = exp2(c2*x)
@@ -156,14 +184,10 @@ __global__ __launch_bounds__(256, 2) void engine_bf16_kernel(EngineArgs a) {
     floatx16 o[4];
     if (flags & kEngLoadState) load_state(a, ri, tile, lane, hf, mref, mtrue, l, o);
     else init_state(mref, mtrue, l, o);
-
-    // ---- pipeline prologue
-    if (nT > 0) {
-        tile_load(0, Ks0, Vs0);
-        idx_prefetch(1);
-    }
-    wait_vmem();
-    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+    // K tile 0 is there; the 16 loads of the cached accumulators are younger and may still be on their way
+    if (flags & kEngLoadState) __builtin_amdgcn_s_waitcnt(0x4F70); else wait_vmem();
+    bare_barrier();
 
     // operand addresses inside a stage (bytes): K row of key 32 kb + n; V chunk read by this lane
     // in the transposing load (lane 16 G + s: key offset s / 4, 8-byte piece s % 4 of d-half G % 2)
@@ -171,13 +195,13 @@ __global__ __launch_bounds__(256, 2) void engine_bf16_kernel(EngineArgs a) {
     const int ls = lane & 15, lg = lane >> 4;
     const int voff = (4 * hf + (ls >> 2)) * VGRP + 32 * (lg & 1) + 8 * (ls & 3);
 
-    auto tile_step = [&](int t, const char* Kcur, const char* Vcur, char* Knext, char* Vnext) {
-        if (t + 1 < nT) {
-            tile_load(t + 1, Knext, Vnext);
-            idx_prefetch(t + 2);
-        }
+    auto tile_step = [&](int t, const char* Kcur, char* Knext, intx4& kcur, intx4& knext) {
+        v_load(t, kcur);
+        idx_prefetch(t + 2, kcur);
+        __builtin_amdgcn_sched_barrier(0);           // the wait below counts on this issue order
+        k_load(min(t + 1, nT - 1), Knext, knext);    // past the end: the last tile again, into a stage nobody reads
         const char* Kb = Kcur + koff;
-        const char* Vb = Vcur + voff;
+        const char* Vb = Vs0 + voff;
 
         // S^T = K Q^T : s[kb], 32 keys x 32 rows each.  Masks (tiles that touch a region
         // boundary, the diagonal or a list tail) enter as the initial accumulator: 0 for a
@@ -192,83 +216,96 @@ __global__ __launch_bounds__(256, 2) void engine_bf16_kernel(EngineArgs a) {
         }
         // a contiguous tile that starts beyond this wave's last row is hidden from all its rows
         // (the work-group still needs it for its later rows): nothing to compute
-        if (!(t < nA && t0 > rw + 31)) {
-        floatx16 s[2];
-        if (__builtin_expect(mode == 0, 1)) {
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                const bf16x8 kf = *(const bf16x8*)(Kb + 512 * kb);
-                s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[0], kZero16, 0, 0, 0);
-            }
-        } else {
-            // key j = t0 + jl is visible to row r iff j <= r and (j < ninit or j >= W);
-            // entry jl of the last list chunk is real iff jl < rem
-            const int jr = mode == 1 ? r - t0 : cnt - (t - nA) * TK - 1;
-            const int jn = mode == 1 ? ninit - t0 : TK;
-            const int jw = W - t0;
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                floatx16 bias;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int jl = 32 * kb + 8 * (v >> 2) + 4 * hf + (v & 3);
-                    const bool ok = (jl <= jr) & ((jl < jn) | (jl >= jw));
-                    bias[v] = ok ? 0.f : -INFINITY;
-                }
-                const bf16x8 kf = *(const bf16x8*)(Kb + 512 * kb);
-                s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[0], bias, 0, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int ks = 1; ks < 8; ++ks)
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                const bf16x8 kf = *(const bf16x8*)(Kb + 512 * kb + 32 * ks);
-                s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], s[kb], 0, 0, 0);
-            }
-        __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
-
-        __builtin_amdgcn_s_setprio(0);
+        const bool on = !(t < nA && t0 > rw + 31);
         bf16x8 pf[2][2];  // [kb][s16]
-        if constexpr ((FLAGS & kEngStoreState) != 0) softmax_tile(s, pf, c2, rescale_gap, mref, mtrue, l, o);
-        else softmax_tile_lazy(s, pf, c2, mref, l, o);
-
-        __builtin_amdgcn_s_setprio(2);
-        // O^T += V^T P^T
+        if (on) {
+            floatx16 s[2];
+            // K operands run four MFMAs ahead of their use; the order is pinned with scheduling fences
+            // (left alone, the compiler issues each read right before its MFMA)
+            {
+                bf16x8 kf[16];
+                auto read_k = [&](int i) { kf[i] = *(const bf16x8*)(Kb + 512 * (i & 1) + 32 * (i >> 1)); };
 #pragma unroll
-        for (int sg = 0; sg < 4; ++sg)
+                for (int i = 0; i < 4; ++i) read_k(i);
+                __builtin_amdgcn_sched_barrier(0);
+                if (__builtin_expect(mode == 0, 1)) {
 #pragma unroll
-            for (int db = 0; db < 4; ++db) {
-                // keys 16 sg + 8 rd + 4 hf + (0..3) live in groups 8 rd + 4 hf + (0..3), row sg
-                const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (__attribute__((address_space(3))) shortx4*)(Vb + sg * 256 + 64 * db));
-                const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (__attribute__((address_space(3))) shortx4*)(Vb + 8 * VGRP + sg * 256 + 64 * db));
-                const shortx8 vv = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vv), pf[sg >> 1][sg & 1],
-                                                                 o[db], 0, 0, 0);
+                    for (int kb = 0; kb < 2; ++kb)
+                        s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb], qf[0], kZero16, 0, 0, 0);
+                } else {
+                    // key j = t0 + jl is visible to row r iff j <= r and (j < ninit or j >= W);
+                    // entry jl of the last list chunk is real iff jl < rem
+                    // (jl = 32 kb + 8 (v / 4) + 4 hf + v % 4: the lane's part is taken off the limits instead)
+                    int jr = (mode == 1 ? r - t0 : cnt - (t - nA) * TK - 1) - 4 * hf;
+                    asm volatile("" : "+v"(jr));     // opaque: the 32 comparisons are not hoisted out of the loop
+                    const int jn = (mode == 1 ? ninit - t0 : TK) - 4 * hf;
+                    const int jw = W - t0 - 4 * hf;
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb) {
+                        floatx16 bias;
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) {
+                            const int jc = 32 * kb + 8 * (v >> 2) + (v & 3);
+                            bool ok = jc <= jr;
+                            if (FLAGS & kEngAnchorRegion) ok = ok & ((jc < jn) | (jc >= jw));
+                            bias[v] = ok ? 0.f : -INFINITY;
+                        }
+                        s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb], qf[0], bias, 0, 0, 0);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                read_k(4); read_k(5);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 2; i < 16; ++i) {         // MFMA i: ks = i / 2, kb = i % 2
+                    s[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i], qf[i >> 1], s[i & 1], 0, 0, 0);
+                    if (i + 4 < 16) read_k(i + 4);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
-
+            __builtin_amdgcn_s_setprio(0);
+            softmax_tile(s, pf, c2, rescale_gap, mref, mtrue, l, o);
+            __builtin_amdgcn_s_setprio(2);
         }
-        wait_vmem();                                 // next tile has landed in LDS
-        __syncthreads();
+        // V tile t has landed (vmcnt(4): the four loads of the next K tile are younger)
+        __builtin_amdgcn_s_waitcnt(0x0F74);
+        bare_barrier();
+        if (on) {
+        // O^T += V^T P^T, V operands four MFMAs ahead
+        shortx4 vlo[16], vhi[16];
+        auto read_v = [&](int i) {                 // operand of MFMA i: sg = i / 4, db = i % 4
+            // keys 16 sg + 8 rd + 4 hf + (0..3) live in groups 8 rd + 4 hf + (0..3), row sg
+            vlo[i] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (__attribute__((address_space(3))) shortx4*)(Vb + (i >> 2) * 256 + 64 * (i & 3)));
+            vhi[i] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (__attribute__((address_space(3))) shortx4*)(Vb + 8 * VGRP + (i >> 2) * 256 + 64 * (i & 3)));
+        };
+#pragma unroll
+        for (int i = 0; i < 4; ++i) read_v(i);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const shortx8 vv = __builtin_shufflevector(vlo[i], vhi[i], 0, 1, 2, 3, 4, 5, 6, 7);
+            const int sg = i >> 2, db = i & 3;
+            o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vv), pf[sg >> 1][sg & 1],
+                                                             o[db], 0, 0, 0);
+            if (i + 4 < 16) read_v(i + 4);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        }
+        wait_vmem();                                 // next K tile has landed in LDS
+        bare_barrier();
     };
     for (int t = 0; t < nT; t += 2) {
-        tile_step(t, Ks0, Vs0, Ks1, Vs1);
-        if (t + 1 < nT) tile_step(t + 1, Ks1, Vs1, Ks0, Vs0);
+        tile_step(t, Ks0, Ks1, kidx0, kidx1);
+        if (t + 1 < nT) tile_step(t + 1, Ks1, Ks0, kidx1, kidx0);
     }
 
     // ---- epilogue
     // The tile stages are free now (every wave has passed the barrier that ends the last tile):
     // each wave takes one of them as a private staging area for coalesced stores.  LDS operations
     // of one wave execute in order, so no barrier separates its writes from its reads.
-    char* const stg = wave == 0 ? Ks0 : wave == 1 ? Ks1 : wave == 2 ? Vs0 : Vs1;
+    char* const stg = wave == 0 ? Ks0 : wave == 1 ? Ks1 : Vs0 + (wave - 2) * kOutStageBytes;
     const int wave_rows = min(32, sq.len - rw);      // rows of this wave inside the sequence (<= 0: none)
     const float lt = row_sum(l);                     // row sum relative to mref
     if (flags & kEngStoreState) {

@@ -92,32 +92,9 @@ __device__ __forceinline__ void init_state(float& mref, float& mtrue, float& l, 
         for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
 }
 
-// Online softmax of one tile for this lane's query row (the other half of the row's keys is 32
-// lanes away).  s: the tile's scores, hidden pairs already at -inf.  The reference is raised only
-// when some row's maximum exceeds it by more than 2^8 (wave-uniform branch, rare after the first
-// tiles); the accumulators are then rescaled, otherwise untouched.  pf: probabilities as bf16, the
-// B operand of O^T += V^T P^T.
-__device__ __forceinline__ void softmax_tile(const floatx16 (&s)[2], bf16x8 (&pf)[2][2], float c2, float rescale_gap,
-                                             float& mref, float& mtrue, float& l, floatx16 (&o)[4]) {
-    float mx = fmaxf(s[0][0], s[1][0]);
-#pragma unroll
-    for (int v = 1; v < 16; ++v) mx = fmaxf(fmaxf(mx, s[0][v]), s[1][v]);     // v_max3_f32
-    {
-        float u, w;
-        both_halves(mx, u, w);
-        mx = fmaxf(u, w);
-    }
-    mtrue = fmaxf(mtrue, mx);
-    if (__builtin_expect(__any(mx > mref + rescale_gap), 0)) {
-        const float mnew = fmaxf(mref, mx);
-        const float alpha = (mnew == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f((mref - mnew) * c2);
-        mref = mnew;
-        l *= alpha;
-#pragma unroll
-        for (int db = 0; db < 4; ++db)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
-    }
+// Probabilities of one tile against the current reference, as bf16 (the B operand of O^T += V^T P^T);
+// returns their sum over the lane's keys.
+__device__ __forceinline__ float probabilities(const floatx16 (&s)[2], bf16x8 (&pf)[2][2], float c2, float mref) {
     const float mc = (mref == -INFINITY) ? 0.f : mref * c2;
     float rs = 0.f;
 #pragma unroll
@@ -132,7 +109,33 @@ __device__ __forceinline__ void softmax_tile(const floatx16 (&s)[2], bf16x8 (&pf
             }
             pf[kb][h8] = __builtin_convertvector(pv, bf16x8);
         }
-    l += rs;
+    return rs;
+}
+
+// Online softmax of one tile for this lane's query row (the other half of the row's keys is 32
+// lanes away).  s: the tile's scores, hidden pairs already at -inf.  The reference is raised only
+// when some row's maximum exceeds it by more than rescale_gap (2^8; wave-uniform branch, rare after
+// the first tiles); the accumulators are then rescaled, otherwise untouched.  mtrue is the maximum
+// over the keys of this lane alone (the two halves meet in store_state).
+__device__ __forceinline__ void softmax_tile(const floatx16 (&s)[2], bf16x8 (&pf)[2][2], float c2, float rescale_gap,
+                                             float& mref, float& mtrue, float& l, floatx16 (&o)[4]) {
+    float mx = fmaxf(s[0][0], s[1][0]);
+#pragma unroll
+    for (int v = 1; v < 16; ++v) mx = fmaxf(fmaxf(mx, s[0][v]), s[1][v]);     // v_max3_f32
+    mtrue = fmaxf(mtrue, mx);
+    if (__builtin_expect(__any(mx > mref + rescale_gap), 0)) {
+        float u, w;
+        both_halves(mx, u, w);
+        const float mnew = fmaxf(mref, fmaxf(u, w));
+        const float alpha = (mnew == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f((mref - mnew) * c2);
+        mref = mnew;
+        l *= alpha;
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
+    }
+    l += probabilities(s, pf, c2, mref);
 }
 
 // The same for the modes that do not export the true row maximum (stage 3, dense attention): the
@@ -143,20 +146,7 @@ __device__ __forceinline__ void softmax_tile(const floatx16 (&s)[2], bf16x8 (&pf
 // probabilities again (wave-uniform branch, rare after the first tiles).
 __device__ __forceinline__ void softmax_tile_lazy(const floatx16 (&s)[2], bf16x8 (&pf)[2][2], float c2, float& mref,
                                                   float& l, floatx16 (&o)[4]) {
-    float mc = (mref == -INFINITY) ? 0.f : mref * c2;
-    float rs = 0.f;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int h8 = 0; h8 < 2; ++h8) {
-            floatx8 pv;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                pv[e] = __builtin_amdgcn_exp2f(fmaf(s[kb][8 * h8 + e], c2, -mc));
-                rs += pv[e];
-            }
-            pf[kb][h8] = __builtin_convertvector(pv, bf16x8);
-        }
+    float rs = probabilities(s, pf, c2, mref);
     if (__builtin_expect(__any(rs > 256.f || mref == -INFINITY), 0)) {
         float mx = fmaxf(s[0][0], s[1][0]);
 #pragma unroll
@@ -174,20 +164,7 @@ __device__ __forceinline__ void softmax_tile_lazy(const floatx16 (&s)[2], bf16x8
         for (int db = 0; db < 4; ++db)
 #pragma unroll
             for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
-        mc = (mref == -INFINITY) ? 0.f : mref * c2;
-        rs = 0.f;
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int h8 = 0; h8 < 2; ++h8) {
-                floatx8 pv;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    pv[e] = __builtin_amdgcn_exp2f(fmaf(s[kb][8 * h8 + e], c2, -mc));
-                    rs += pv[e];
-                }
-                pf[kb][h8] = __builtin_convertvector(pv, bf16x8);
-            }
+        rs = probabilities(s, pf, c2, mref);
     }
     l += rs;
 }
@@ -205,6 +182,9 @@ __device__ __forceinline__ float row_sum(float l) {
 __device__ __forceinline__ float store_state(const EngineArgs& a, long long ri, long long tile, bool rok,
                                              bool wave_has_rows, int lane, int hf, float c2, float mref, float mtrue,
                                              float lt, const floatx16 (&o)[4]) {
+    float ma, mb;
+    both_halves(mtrue, ma, mb);
+    mtrue = fmaxf(ma, mb);
     const float down = (mref == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f((mref - mtrue) * c2);
     const float ms = mtrue * a.p.sigma;
     if (rok && hf == 0) { a.Mout[ri] = ms; a.Lout[ri] = lt * down; }
