@@ -208,11 +208,8 @@ std::once_flag g_attr_once;
 hipError_t g_attr_status = hipSuccess;
 hipError_t raise_lds_limits() {
     std::call_once(g_attr_once, [] {
-        g_attr_status = hipFuncSetAttribute((const void*)engine_fp32_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                            (int)engine_fp32_lds_bytes(128, 128));
-        if (g_attr_status == hipSuccess)
-            g_attr_status = hipFuncSetAttribute((const void*)mask_block_kernel,
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaskBlockLdsMax);
+        g_attr_status = hipFuncSetAttribute((const void*)mask_block_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                            (int)kMaskBlockLdsMax);
     });
     return g_attr_status;
 }
@@ -256,13 +253,11 @@ int launch_engine(const Plan& pl, const aa_params* prm, EngineArgs& ea, hipStrea
         }
         return rc;
     }
-    AA_HIP(raise_lds_limits());
-    AA_LAUNCH(engine_fp32_kernel, dim3(grid), dim3(2 * k.bq), engine_fp32_lds_bytes(k.d, k.bq), st, ea);
-    return AA_OK;
+    return engine_status(launch_engine_fp32(ea, st), "engine_fp32_kernel");
 }
 
 // sel_ws (nullable): a stripe_select workspace; the bf16 engines then also leave the pooled queries of
-// stage 2 there (run_select is told so)
+// stage 2 there, and the fp32 path leaves the pooled anchors to run_select (which is told so)
 int run_anchor(const Plan& pl, const aa_params* p, const void* q, const void* k, const void* v, float* M, float* L,
                float* Acc, float* xa, char* sel_ws, hipStream_t st) {
     EngineArgs ea;
@@ -274,14 +269,22 @@ int run_anchor(const Plan& pl, const aa_params* p, const void* q, const void* k,
     if (sel_ws && p->dtype == AA_BF16) {
         ea.qp_hi = sel_ws + pl.sel_qhi; ea.qp_lo = sel_ws + pl.sel_qlo; ea.qlo_norm = (float*)(sel_ws + pl.sel_qln);
     }
-    return launch_engine(pl, p, ea, st);
+    const int rc = launch_engine(pl, p, ea, st);
+    if (rc != AA_OK || p->dtype == AA_BF16 || sel_ws) return rc;
+    SelectArgs sa;
+    memset(&sa, 0, sizeof(sa));
+    sa.p = pl.kp;
+    sa.m_rows = M; sa.xa_out = xa;
+    AA_LAUNCH(pool_fp32_kernel, dim3(pl.kp.nblk_max, pl.kp.Hq, pl.kp.B), dim3(256), 0, st, sa);
+    return AA_OK;
 }
 
-// q_pooled: stage 1 has written the pooled queries into ws already (bf16 only)
+// fused_M (nullable): the call follows run_anchor with this workspace, M is stage 1's; bf16: the pooled queries
+// are in ws already; fp32: the pooled anchors are still to be computed, into xa
 // stats (nullable): the scan kernel also reports attended pairs and selected entries there
 int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k, const float* xa, int32_t* counts,
-               int64_t* offsets, int32_t* idx, int64_t cap, int32_t* flag, char* ws, bool q_pooled, int64_t* stats,
-               hipStream_t st) {
+               int64_t* offsets, int32_t* idx, int64_t cap, int32_t* flag, char* ws, const float* fused_M, float* xa_out,
+               int64_t* stats, hipStream_t st) {
     const KParams& kp = pl.kp;
     SelectArgs sa;
     memset(&sa, 0, sizeof(sa));
@@ -306,11 +309,12 @@ int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k,
     if (kp.packed)
         AA_LAUNCH(zero_i32_kernel, dim3((unsigned)cdiv(pl.sz.groups, 256)), dim3(256), 0, st, counts,
                   (long long)pl.sz.groups);
-    q_pooled = q_pooled && p->dtype == AA_BF16;
+    const bool q_pooled = fused_M && p->dtype == AA_BF16;
+    if (p->dtype != AA_BF16) { sa.m_rows = fused_M; sa.xa_out = xa_out; }
     sa.pool_skip_q = q_pooled;
     if (p->granularity == AA_BLOCK) {
         if (p->dtype != AA_BF16)
-            AA_LAUNCH(pool_q_fp32_kernel, gblk, dim3(128), 0, st, sa);
+            AA_LAUNCH(pool_fp32_kernel, gblk, dim3(256), 0, st, sa);
         else if (!q_pooled)
             AA_LAUNCH(pool_q_bf16_kernel, gblk, dim3(256), 0, st, sa);
         AA_LAUNCH(pool_k_kernel, dim3(kp.nblk_max, kp.Hkv, kp.B), dim3(256), 0, st, sa);
@@ -326,9 +330,9 @@ int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k,
         const dim3 gm((unsigned)(mask_per_xcd > 0 ? mask_per_xcd * 8 : 8));
         AA_LAUNCH(mask_bf16_kernel, gm, dim3(256), 0, st, sa);
     } else {
-        AA_LAUNCH(pool_q_fp32_kernel, gblk, dim3(128), 0, st, sa);
-        const dim3 gm((unsigned)cdiv(kp.N, 256), (unsigned)kp.ngrp_max, (unsigned)(kp.B * kp.Hq));
-        AA_LAUNCH(mask_fp32_kernel, gm, dim3(256), (size_t)kp.step * kp.d * 4, st, sa);
+        AA_LAUNCH(pool_fp32_kernel, gblk, dim3(256), 0, st, sa);
+        const int rc = engine_status(launch_mask_fp32(sa, st), "mask_fp32_kernel");
+        if (rc != AA_OK) return rc;
     }
     AA_LAUNCH(count_kernel, ggrp, dim3(256), 0, st, sa);
     AA_LAUNCH(scan_kernel, dim3(1), dim3(1024), 0, st, sa);
@@ -396,7 +400,7 @@ int stripe_select(const aa_params* params, const void* q, const void* k, const f
     if (idx_capacity < 0 || misaligned(q) || misaligned(k) || misaligned(idx) || misaligned(ws)) return AA_EINVAL;
     if (ws_bytes < pl.sz.select_ws_bytes) return AA_EWORKSPACE;
     return run_select(pl, params, q, k, xa_pooled, counts, offsets, idx, idx_capacity, overflow_flag, (char*)ws,
-                      false, nullptr, (hipStream_t)stream);
+                      nullptr, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int stripe_select_noalloc(const aa_params* params, const void* q, const void* k, const float* xa_pooled,
@@ -412,7 +416,7 @@ int stripe_select_noalloc(const aa_params* params, const void* q, const void* k,
     rc = scratch_of_current_device(&ws);
     if (rc != AA_OK) return rc;
     return run_select(pl, params, q, k, xa_pooled, counts, offsets, idx, idx_capacity, overflow_flag, (char*)ws,
-                      false, nullptr, (hipStream_t)stream);
+                      nullptr, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int sparse_attn(const aa_params* params, const void* q, const void* k, const void* v, const float* M, const float* L,
@@ -448,11 +452,12 @@ int anchor_attention_prefill(const aa_params* params, const void* q, const void*
     int64_t* offsets = (int64_t*)(w + pl.pf_offsets);
     int32_t* flag = (int32_t*)(w + pl.pf_flag);
     int32_t* idx = (int32_t*)(w + pl.pf_idx);
-    // the block means of Q (first step of stage 2) come out of stage 1, which holds the block's
+    // bf16: the block means of Q (first step of stage 2) come out of stage 1, which holds the block's
     // queries in registers; the stage-wise entry points compute the same bits in a kernel of their own
     rc = run_anchor(pl, params, q, k, v, M, L, Acc, xa, w + pl.pf_sel, st);
     if (rc != AA_OK) return rc;
-    rc = run_select(pl, params, q, k, xa, counts, offsets, idx, pl.sz.idx_capacity_max, flag, w + pl.pf_sel, true, stats, st);
+    rc = run_select(pl, params, q, k, xa, counts, offsets, idx, pl.sz.idx_capacity_max, flag, w + pl.pf_sel, M, xa,
+                    stats, st);
     if (rc != AA_OK) return rc;
     rc = run_sparse(pl, params, q, k, v, M, L, Acc, counts, offsets, idx, pl.sz.idx_capacity_max, out, lse, st);
     if (rc != AA_OK) return rc;

@@ -53,7 +53,7 @@ int launch_engine_bf16(const EngineArgs& ea, unsigned grid, hipStream_t st);
 // 256 query rows (two consecutive blocks) per work-group; needs dense mode or an even step
 int launch_engine_bf16_pp(const EngineArgs& ea, unsigned grid, hipStream_t st);
 
-__global__ void engine_fp32_kernel(EngineArgs a);
-size_t engine_fp32_lds_bytes(int d, int bq);
+// fp32; writes no pooled anchors (ea.xa is not read: pool_fp32_kernel does that from M)
+int launch_engine_fp32(const EngineArgs& ea, hipStream_t st);
 
 }  // namespace aa

@@ -1,45 +1,84 @@
-// fp32 tile engine: the same online-softmax walk as the bf16 engine (stage 1
+// fp32 tile engine: the same online-softmax walk as the bf16 engines (stage 1
 // anchor computation, Algorithm 1; stage 3 gathered sparse attention, Algorithm 3;
 // dense causal comparator -- arXiv 2505.23520) with fp32 inputs, fp32 products and
-// fp32 probabilities.  On gfx950 the fp32 matrix and vector pipes have the same
-// peak rate, so this instantiation uses plain vector FMAs over LDS tiles: two
-// lanes share one query row, each owning half of the head dimension.
+// fp32 probabilities, on the fp32 matrix instruction v_mfma_f32_32x32x2_f32.
+//
+// Fragments (the layout of the bf16 engines with k = 2 per instruction): lane (n, hf) = (lane % 32,
+// lane / 32).  S^T = K Q^T: keys = M, query rows = N; k slot hf of step (j, e) is column
+// 8 j + 4 hf + e, so one 16-byte piece of a K row feeds four instructions.  Score register v of lane
+// (n, hf) belongs to query row n and key 8 (v / 4) + 4 hf + v % 4 -- which is exactly the B operand
+// of O^T = V^T P^T if k slot hf of step v is that key: the probabilities never move between lanes.
+// V^T rows are columns of V in any order: row c of column block db is column T c + db (T = d / 32),
+// so a lane's T columns are one wide load and a wave reads two whole V rows at once.
+//
+// Shape: work-group = one tile of 32 query rows = 4 waves that share the rows and split the 32-key
+// blocks among them (block b belongs to wave b % 4); each keeps its own (m, l, O) and they are merged
+// once, through LDS, at the end.  At 64 matrix cycles per instruction 32 keys of K and V (32 KB at
+// d = 128) feed 8192 cycles of a wave, 16 B/clk for a CU: K and V come straight from L2 into
+// registers, the loop has no LDS stage and no barrier, and a gathered row costs what a contiguous one
+// does.  32 rows per work-group keep the chip filled at small sizes, and splitting the keys
+// shortens the chain of a short sequence.
+// Bound: the fp32 matrix pipe (157 TFLOP/s nominal; the vector ALU without packed instructions
+// reaches half of that), and on short sequences the chain of one wave's blocks.
+// Measured against vector FMAs over LDS tiles (one work-group per query block, two lanes per row):
+// prefill of 4000 tokens, 8 / 2 heads, d = 128, block 128: 918 -> 155 us; 1024 tokens, 1 head, d = 64: 201 -> 42 us
+// (both with the matching stage-2 kernels); dense causal, 2313 tokens, 2 heads, d = 64: 858 -> 61 us.
 #include "aa_common.h"
 #include "aa_engine.h"
 
 namespace aa {
 
 namespace {
-constexpr int TK = 64;  // keys per tile (one list chunk)
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+constexpr floatx16 kZero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+constexpr int KB = 32;   // keys per block
+constexpr int RT = 32;   // query rows per work-group
+constexpr int NW = 4;    // waves per work-group
 
-template <int DH>  // DH = d / 2
-__device__ __forceinline__ void engine_fp32_body(const EngineArgs& a, float* smem) {
-    constexpr int Dd = 2 * DH;
-    constexpr int STR = Dd + 4;                      // padded row stride of the K and V tiles
+template <int T> struct vcols;
+template <> struct vcols<1> { typedef float type; };
+template <> struct vcols<2> { typedef float type __attribute__((ext_vector_type(2))); };
+template <> struct vcols<4> { typedef float type __attribute__((ext_vector_type(4))); };
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ float comp(float x, int) { return x; }
+template <class V> __device__ __forceinline__ float comp(const V& x, int i) { return x[i]; }
+
+template <int D>
+__global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void engine_fp32_kernel(EngineArgs a) {
+    constexpr int T = D / 32;                        // column blocks of O
+    constexpr int NK = D / 8;                        // 16-byte pieces of a K / Q row per lane
+    constexpr int VK = 16 / NK;                      // V rows per K piece
+    constexpr int LAG = D == 128 ? NK / 2 : NK / 4;                      // K pieces (and their share of V rows) not yet in flight
+    typedef typename vcols<T>::type vec;
+    __shared__ float obuf[NW][T][16][64];            // every wave's O^T registers
+    __shared__ float mbuf[NW][RT], lbuf[NW][RT];
     const KParams& p = a.p;
-    const int tid = threadIdx.x;
-    const int lr = tid >> 1, hh = tid & 1;
-    const int BQ = p.bq;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int n = lane & 31, hf = lane >> 5;
 
     if (!engine_selected(a)) return;
-    const Work wk = decode_work(p, p.nblk_max, blockIdx.x);
+    const int rts = (p.bq + RT - 1) / RT;            // row tiles of a query block
+    const Work wk = decode_work(p, p.nblk_max * rts, blockIdx.x);
     const Seq sq = seq_of(p, wk.b);
-    const int row0 = wk.i * BQ;
-    if (row0 >= sq.len) return;
+    const int blk = wk.i / rts;
+    const int row0 = blk * p.bq + (wk.i % rts) * RT;             // first row of the tile
+    const int rend = min(min(blk * p.bq + p.bq, row0 + RT), sq.len);
+    if (row0 >= rend) return;
     const int hk = wk.h / p.grp;
-    const int g = wk.i / p.step;
-    const int rlast = min(row0 + BQ, sq.len) - 1;
-    const int r = row0 + lr;
-    const bool rok = r < sq.len;
+    const int g = blk / p.step;
+    const int r = row0 + n;
+    const bool rok = r < rend;
+    const int rlast = rend - 1;
 
+    // ---- block sequence: [initial tokens][window .. diagonal][list]
     int W = 0, ninit = 0, T1 = 0, t2s = 0, nA = 0;
     if (a.flags & kEngAnchorRegion) {
         if (!(a.flags & kEngDense)) { W = window_start(p, g); ninit = p.n_init; }
         const int e1 = min(ninit, rlast + 1);
-        T1 = (e1 + TK - 1) / TK;
-        t2s = max(T1, W / TK);
-        const int T2 = rlast / TK + 1;
-        nA = T1 + max(0, T2 - t2s);
+        T1 = (e1 + KB - 1) / KB;
+        t2s = max(T1, W / KB);
+        nA = T1 + max(0, rlast / KB + 1 - t2s);
     }
     int cnt = 0;
     long long lbase = 0;
@@ -48,154 +87,206 @@ __device__ __forceinline__ void engine_fp32_body(const EngineArgs& a, float* sme
         cnt = a.counts[t];
         lbase = a.offsets[t];
     }
-    const int nL = (cnt + TK - 1) / TK;
-    const int nT = nA + nL;
+    const int nT = nA + (cnt + KB - 1) / KB;
+    auto block_start = [&](int t) -> int { return KB * (t < T1 ? t : t2s + (t - T1)); };
+    // key of this lane's K row in block t (lists are padded to 64 entries, so every slot read exists)
+    auto key_of = [&](int t) -> int {
+        if (t >= nT) return 0;
+        return t < nA ? min(block_start(t) + n, sq.len - 1) : a.idx[lbase + (long long)(t - nA) * KB + n];
+    };
 
-    const float* kb_ = (const float*)a.k + tok_offset(p, p.ks, sq, wk.b, hk, 0);
-    const float* vb_ = (const float*)a.v + tok_offset(p, p.vs, sq, wk.b, hk, 0);
-    float* Ks = smem;
-    float* Vs = smem + TK * STR;
+    const float* kb_ = (const float*)a.k + tok_offset(p, p.ks, sq, wk.b, hk, 0) + 4 * hf;
+    const float* vb_ = (const float*)a.v + tok_offset(p, p.vs, sq, wk.b, hk, 0) + T * n;
 
-    float q[DH], acc[DH];
+    int key = key_of(wave), key_next = key_of(wave + NW);
+    floatx4 q[NK], kf[NK];
+    vec vf[16];
+    auto load_k = [&](int j, int kk) { kf[j] = *(const floatx4*)(kb_ + (long long)kk * p.ks[2] + 8 * j); };
+    auto load_v = [&](int v, int kk) {
+        int src = 16 * hf;                           // byte address of lane 4 hf, opaque: 16 sums are not kept in registers
+        asm volatile("" : "+v"(src));
+        const int row = __builtin_amdgcn_ds_bpermute(src + 4 * (8 * (v >> 2) + (v & 3)), kk);
+        vf[v] = *(const vec*)(vb_ + (long long)row * p.vs[2]);
+    };
     {
-        const float* src = (const float*)a.q + tok_offset(p, p.qs, sq, wk.b, wk.h, rok ? r : row0) + hh * DH;
+        const float* src = (const float*)a.q + tok_offset(p, p.qs, sq, wk.b, wk.h, rok ? r : row0) + 4 * hf;
 #pragma unroll
-        for (int c = 0; c < DH; c += 4) {
-            const float4 x = *(const float4*)(src + c);
-            q[c] = x.x; q[c + 1] = x.y; q[c + 2] = x.z; q[c + 3] = x.w;
-        }
+        for (int j = 0; j < NK; ++j) q[j] = *(const floatx4*)(src + 8 * j);
     }
-    const float c2 = p.sigma * 1.4426950408889634f;
-    float m, l;
-    const long long ri = row_index(p, sq, wk.b, wk.h, rok ? r : row0);
-    if (a.flags & kEngLoadState) {
-        m = a.Min[ri] / p.sigma;
-        l = a.Lin[ri];
-        const float* src = a.Accin + ri * Dd + hh * DH;
 #pragma unroll
-        for (int c = 0; c < DH; c += 4) {
-            const float4 x = *(const float4*)(src + c);
-            acc[c] = x.x; acc[c + 1] = x.y; acc[c + 2] = x.z; acc[c + 3] = x.w;
-        }
-    } else {
-        m = -INFINITY; l = 0.f;
-#pragma unroll
-        for (int c = 0; c < DH; ++c) acc[c] = 0.f;
-    }
+    for (int j = 0; j < NK - LAG; ++j) load_k(j, key);
 
-    for (int t = 0; t < nT; ++t) {
-        const bool contiguous = t < nA;
-        const int t0 = contiguous ? TK * (t < T1 ? t : t2s + (t - T1)) : 0;
-        __syncthreads();                             // previous tile fully consumed
-        for (int e = tid; e < TK * (Dd / 4); e += blockDim.x) {
-            const int kk = e / (Dd / 4), c4 = e % (Dd / 4);
-            const int key = contiguous ? min(t0 + kk, sq.len - 1) : a.idx[lbase + (long long)(t - nA) * TK + kk];
-            *(float4*)(Ks + kk * STR + 4 * c4) = *(const float4*)(kb_ + (long long)key * p.ks[2] + 4 * c4);
-            *(float4*)(Vs + kk * STR + 4 * c4) = *(const float4*)(vb_ + (long long)key * p.vs[2] + 4 * c4);
-        }
-        __syncthreads();
+    const float c2 = p.sigma * 1.4426950408889634f;  // exp(sigma*x) = exp2(c2*x)
+    float m = -INFINITY, l = 0.f;                    // l: this lane's keys only
+    floatx16 o[T];
+#pragma unroll
+    for (int db = 0; db < T; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
 
-        float s[TK];
+    // K pieces and V rows go through the registers in one stream: K pieces of a block, its V rows, K pieces
+    // of the wave's next block.  Each is requested NK - LAG pieces (half to three quarters of K's share) ahead of its use,
+    // into registers whose contents the products have just used; the order is pinned with scheduling fences.
+#pragma unroll 1
+    for (int t = wave; t < nT; t += NW) {
+        // two accumulation chains: half the rounding error of one (measured against 64 bits: d = 128 outputs
+        // 1.5e-6 off with one chain), and no product waits for the one before it
+        floatx16 s2[2] = {kZero16, kZero16};
 #pragma unroll
-        for (int jj = 0; jj < TK; ++jj) {
-            const float* kr = Ks + jj * STR + hh * DH;
-            float d0 = 0.f;
+        for (int j = 0; j < NK; ++j) {
 #pragma unroll
-            for (int c = 0; c < DH; c += 4) {
-                const float4 x = *(const float4*)(kr + c);
-                d0 = fmaf(q[c], x.x, d0); d0 = fmaf(q[c + 1], x.y, d0);
-                d0 = fmaf(q[c + 2], x.z, d0); d0 = fmaf(q[c + 3], x.w, d0);
-            }
-            s[jj] = d0 + __shfl_xor(d0, 1, 64);
+            for (int e = 0; e < 4; ++e)
+                s2[e & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][e], q[j][e], s2[e & 1], 0, 0, 0);
+#pragma unroll
+            for (int u = 0; u < VK; ++u)
+                if (j >= LAG) load_v((j - LAG) * VK + u, key);
+            if (j < LAG) load_k(j + NK - LAG, key);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        if (contiguous) {
+        floatx16 s = s2[0] + s2[1];
+        if (t < nA) {
+            // key j is visible to row r iff j <= r and (j < ninit or j >= W); the lane's part of j,
+            // 4 hf, is taken off the limits instead
+            const int t0 = block_start(t);
+            if (t0 + KB - 1 > row0 || !(t0 + KB <= ninit || t0 >= W)) {
+                int jr = r - t0 - 4 * hf;
+                asm volatile("" : "+v"(jr));         // opaque: nothing is hoisted out of the loop
+                const int jn = ninit - t0 - 4 * hf, jw = W - t0 - 4 * hf;
 #pragma unroll
-            for (int jj = 0; jj < TK; ++jj) {
-                const int j = t0 + jj;
-                if (!((j <= r) && (j < ninit || j >= W))) s[jj] = -INFINITY;
+                for (int v = 0; v < 16; ++v) {
+                    const int jc = 8 * (v >> 2) + (v & 3);
+                    if (!(jc <= jr && (jc < jn || jc >= jw))) s[v] = -INFINITY;
+                }
             }
         } else {
-            const int rem = cnt - (t - nA) * TK;
+            int jr = cnt - (t - nA) * KB - 1 - 4 * hf;
+            asm volatile("" : "+v"(jr));
+            if ((t + 1 - nA) * KB > cnt) {
 #pragma unroll
-            for (int jj = 0; jj < TK; ++jj)
-                if (jj >= rem) s[jj] = -INFINITY;
+                for (int v = 0; v < 16; ++v)
+                    if (8 * (v >> 2) + (v & 3) > jr) s[v] = -INFINITY;
+            }
         }
         float mx = s[0];
 #pragma unroll
-        for (int jj = 1; jj < TK; ++jj) mx = fmaxf(mx, s[jj]);
-        const float mnew = fmaxf(m, mx);
-        const float muse = (mnew == -INFINITY) ? 0.f : mnew;
-        const float alpha = __builtin_amdgcn_exp2f((m - muse) * c2);
-        const float mc = muse * c2;
-        m = mnew;
+        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        if (__any(mx > m)) {
+            const float mnew = fmaxf(m, mx);
+            const float alpha = (mnew == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f((m - mnew) * c2);
+            m = mnew;
+            l *= alpha;
+#pragma unroll
+            for (int db = 0; db < T; ++db)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
+        }
+        const float mc = (m == -INFINITY) ? 0.f : m * c2;
         float rs = 0.f;
 #pragma unroll
-        for (int jj = 0; jj < TK; ++jj) {
-            s[jj] = __builtin_amdgcn_exp2f(fmaf(s[jj], c2, -mc));
-            rs += s[jj];
+        for (int v = 0; v < 16; ++v) {
+            s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], c2, -mc));
+            rs += s[v];
         }
-        l = l * alpha + rs;
+        l += rs;
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int c = 0; c < DH; ++c) acc[c] *= alpha;
+        for (int v = 0; v < 16; ++v) {
 #pragma unroll
-        for (int jj = 0; jj < TK; ++jj) {
-            const float* vr = Vs + jj * STR + hh * DH;
-#pragma unroll
-            for (int c = 0; c < DH; c += 4) {
-                const float4 x = *(const float4*)(vr + c);
-                acc[c] = fmaf(s[jj], x.x, acc[c]); acc[c + 1] = fmaf(s[jj], x.y, acc[c + 1]);
-                acc[c + 2] = fmaf(s[jj], x.z, acc[c + 2]); acc[c + 3] = fmaf(s[jj], x.w, acc[c + 3]);
+            for (int db = 0; db < T; ++db)
+                o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(comp(vf[v], db), s[v], o[db], 0, 0, 0);
+            if (v + VK * (NK - LAG) < 16) load_v(v + VK * (NK - LAG), key);
+            if (v == VK * LAG - 1) {
+                key = key_next;
+                key_next = key_of(t + 2 * NW);
             }
+            if (v >= VK * LAG && v % VK == 0) load_k(v / VK - LAG, key);
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
 
-    const float ms = m * p.sigma;
-    if (a.flags & kEngStoreState) {
-        if (rok) {
-            if (hh == 0) { a.Mout[ri] = ms; a.Lout[ri] = l; }
-            if (a.Accout) {
-                float* dst = a.Accout + ri * Dd + hh * DH;
+    // ---- merge the four waves' states.  Wave w finishes O^T registers 4 w .. 4 w + 3 of every column
+    // block: of row n the columns T (8 w + 4 hf) .. + 4 T - 1.
+    l += __shfl_xor(l, 32, 64);
 #pragma unroll
-                for (int c = 0; c < DH; c += 4) *(float4*)(dst + c) = make_float4(acc[c], acc[c + 1], acc[c + 2], acc[c + 3]);
-            }
+    for (int db = 0; db < T; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) obuf[wave][db][v][lane] = o[db][v];
+    if (hf == 0) { mbuf[wave][n] = m; lbuf[wave][n] = l; }
+    __syncthreads();
+
+    const long long ri = row_index(p, sq, wk.b, wk.h, rok ? r : row0);
+    float mall = -INFINITY, m0 = -INFINITY, l0 = 0.f;
+    if (a.flags & kEngLoadState) {
+        m0 = a.Min[ri] / p.sigma;
+        l0 = a.Lin[ri];
+        mall = m0;
+    }
+    float mw[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        mw[w] = mbuf[w][n];
+        mall = fmaxf(mall, mw[w]);
+    }
+    auto scale_of = [&](float x) -> float {          // a part that has seen no key counts for nothing
+        return x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((x - mall) * c2);
+    };
+    float lall = 0.f, res[4 * T];                    // res[T e + db]: column T (8 wave + 4 hf) + T e + db
+    const long long col0 = T * (8 * wave + 4 * hf);
+    if (a.flags & kEngLoadState) {
+        const float f0 = scale_of(m0);
+        lall = l0 * f0;
+#pragma unroll
+        for (int c = 0; c < 4 * T; c += 4) {
+            const floatx4 x = *(const floatx4*)(a.Accin + ri * D + col0 + c);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) res[c + e] = x[e] * f0;
         }
-        if (a.xa) {
-            __syncthreads();
-            if (hh == 0) smem[lr] = rok ? ms : 0.f;
-            __syncthreads();
-            if (tid == 0) {
-                const int nrows = rlast - row0 + 1;
-                float sum = 0.f;
-                for (int e = 0; e < nrows; ++e) sum += smem[e];
-                a.xa[blk_index(p, sq, wk.b, wk.h, wk.i)] = sum / (float)nrows;
-            }
+    } else {
+#pragma unroll
+        for (int c = 0; c < 4 * T; ++c) res[c] = 0.f;
+    }
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const float f = scale_of(mw[w]);
+        lall = fmaf(lbuf[w][n], f, lall);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int db = 0; db < T; ++db) res[T * e + db] = fmaf(obuf[w][db][4 * wave + e][lane], f, res[T * e + db]);
+    }
+
+    const float ms = mall * p.sigma;
+    if (!rok) return;
+    const bool first = wave == 0 && hf == 0;
+    if (a.flags & kEngStoreState) {
+        if (first) { a.Mout[ri] = ms; a.Lout[ri] = lall; }
+        if (a.Accout) {
+            float* dst = a.Accout + ri * D + col0;
+#pragma unroll
+            for (int c = 0; c < 4 * T; c += 4) *(floatx4*)(dst + c) = floatx4{res[c], res[c + 1], res[c + 2], res[c + 3]};
         }
     }
-    if ((a.flags & kEngStoreOut) && rok) {
-        const float inv = 1.f / l;
-        float* dst = (float*)a.out + tok_offset(p, p.os, sq, wk.b, wk.h, r) + hh * DH;
+    if (a.flags & kEngStoreOut) {
+        const float inv = 1.f / lall;
+        float* dst = (float*)a.out + tok_offset(p, p.os, sq, wk.b, wk.h, r) + col0;
 #pragma unroll
-        for (int c = 0; c < DH; c += 4)
-            *(float4*)(dst + c) = make_float4(acc[c] * inv, acc[c + 1] * inv, acc[c + 2] * inv, acc[c + 3] * inv);
-        if (a.lse && hh == 0) a.lse[ri] = ms + logf(l);
+        for (int c = 0; c < 4 * T; c += 4)
+            *(floatx4*)(dst + c) = floatx4{res[c] * inv, res[c + 1] * inv, res[c + 2] * inv, res[c + 3] * inv};
+        if (a.lse && first) a.lse[ri] = ms + logf(lall);
     }
 }
 }  // namespace
 
-__global__ __launch_bounds__(256) void engine_fp32_kernel(EngineArgs a) {
-    extern __shared__ __attribute__((aligned(16))) float smem_f[];
-    switch (a.p.d) {
-        case 32: engine_fp32_body<16>(a, smem_f); break;
-        case 64: engine_fp32_body<32>(a, smem_f); break;
-        case 128: engine_fp32_body<64>(a, smem_f); break;
-        default: break;
+int launch_engine_fp32(const EngineArgs& ea, hipStream_t st) {
+    const KParams& p = ea.p;
+    const unsigned grid = (unsigned)((long long)p.nblk_max * ((p.bq + RT - 1) / RT) * p.Hq * p.B);
+    switch (p.d) {
+        case 32: return (int)launch_kernel(engine_fp32_kernel<32>, dim3(grid), dim3(64 * NW), 0, st, ea);
+        case 64: return (int)launch_kernel(engine_fp32_kernel<64>, dim3(grid), dim3(64 * NW), 0, st, ea);
+        case 128: return (int)launch_kernel(engine_fp32_kernel<128>, dim3(grid), dim3(64 * NW), 0, st, ea);
+        default: return -1;
     }
-}
-
-size_t engine_fp32_lds_bytes(int d, int bq) {
-    size_t tiles = 2 * (size_t)TK * (d + 4) * sizeof(float);
-    size_t red = (size_t)bq * sizeof(float);
-    return tiles > red ? tiles : red;
 }
 
 }  // namespace aa

@@ -40,6 +40,8 @@ struct SelectArgs {
     const float* xa;          // pooled anchors, per block
     void *qp_hi, *qp_lo;      // bf16 path: pooled queries, hi / lo parts, rows of 128
     float* qp_f32;            // fp32 path: pooled queries, rows of d
+    const float* m_rows;      // fp32 path, nullable: stage 1's M; the pooling kernel then writes
+    float* xa_out;            //   the pooled anchors here
     float* kp_f32;            // block granularity: pooled keys per (KV head, key block), rows of d
     float* qlo_norm;          // bf16 path: Euclidean norm of the lo part of each pooled query row
     float* kmax_blk;          // bf16 stripe path: largest key norm per (KV head, key block)
@@ -61,9 +63,9 @@ struct SelectArgs {
 };
 
 __global__ void pool_q_bf16_kernel(SelectArgs a);
-__global__ void pool_q_fp32_kernel(SelectArgs a);
+__global__ void pool_fp32_kernel(SelectArgs a);
 __global__ void mask_bf16_kernel(SelectArgs a);
-__global__ void mask_fp32_kernel(SelectArgs a);
+int launch_mask_fp32(const SelectArgs& a, hipStream_t st);   // the launch's hipError_t, or -1 for another d
 __global__ void pool_k_kernel(SelectArgs a);
 __global__ void mask_block_kernel(SelectArgs a);
 size_t mask_block_lds_bytes(int N, int d, int bq, int step);

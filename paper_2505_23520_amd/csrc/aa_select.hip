@@ -35,7 +35,6 @@ __device__ __forceinline__ unsigned short f_to_bf16_rne(float f) {
 // more rows in y: those work-groups write the largest key norm of their key block (the mask kernel
 // bounds |<lo, k>| by |lo| |k| to decide whether the lo products are needed).  pool_skip_q: the
 // queries were pooled by stage 1 already, the grid holds the Hkv key rows only.
-// fp32: 128 threads, float rows of d.
 __global__ __launch_bounds__(256) void pool_q_bf16_kernel(SelectArgs a) {
     const KParams& p = a.p;
     const int i = blockIdx.x, b = blockIdx.z;
@@ -96,19 +95,41 @@ __global__ __launch_bounds__(256) void pool_q_bf16_kernel(SelectArgs a) {
                       a.qp_hi, a.qp_lo, a.qlo_norm);
 }
 
-__global__ __launch_bounds__(128) void pool_q_fp32_kernel(SelectArgs a) {
+// fp32: 256 threads per query block.  With qp_f32 set, the block mean of the queries (16 bytes of a row per
+// thread, 1024 / d rows side by side, then added up in LDS); with m_rows set, the pooled anchor (mean of
+// M over the block's rows): the fp32 engine's work-groups own 32 rows each, not a block.
+__global__ __launch_bounds__(256) void pool_fp32_kernel(SelectArgs a) {
     const KParams& p = a.p;
     const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const Seq sq = seq_of(p, b);
     const int r0 = i * p.bq;
     if (r0 >= sq.len) return;
-    const int r1 = min(r0 + p.bq, sq.len);
-    const float* src = (const float*)a.q + tok_offset(p, p.qs, sq, b, h, 0);
+    const int r1 = min(r0 + p.bq, sq.len), tid = threadIdx.x;
     const long long bi = blk_index(p, sq, b, h, i);
-    for (int c = threadIdx.x; c < p.d; c += blockDim.x) {
+    if (a.m_rows && tid < 64) {
+        const float* m = a.m_rows + row_index(p, sq, b, h, r0);
         float s = 0.f;
-        for (int r = r0; r < r1; ++r) s += src[(long long)r * p.qs[2] + c];
-        a.qp_f32[bi * p.d + c] = s / (float)(r1 - r0);
+        for (int r = tid; r < r1 - r0; r += 64) s += m[r];
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+        if (tid == 0) a.xa_out[bi] = s / (float)(r1 - r0);
+    }
+    if (!a.qp_f32) return;
+    __shared__ __attribute__((aligned(16))) float part[1024];
+    const int d4 = p.d / 4, c = tid % d4, rs = tid / d4, nrs = 256 / d4;
+    const float* src = (const float*)a.q + tok_offset(p, p.qs, sq, b, h, 0) + 4 * c;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+    for (int r = r0 + rs; r < r1; r += nrs) {
+        const float4 x = *(const float4*)(src + (long long)r * p.qs[2]);
+        s.x += x.x; s.y += x.y; s.z += x.z; s.w += x.w;
+    }
+    *(float4*)(part + rs * p.d + 4 * c) = s;
+    __syncthreads();
+    if (tid < p.d) {
+        float t = 0.f;
+        for (int k = 0; k < nrs; ++k) t += part[k * p.d + tid];
+        a.qp_f32[bi * p.d + tid] = t / (float)(r1 - r0);
     }
 }
 
@@ -400,40 +421,94 @@ __global__ __launch_bounds__(256, 3) void mask_bf16_kernel(SelectArgs a) {
     }
 }
 
-// ------------------------------------------------------------------ mask, fp32 vector FMA
-// grid (key chunks of 256, ngrp_max, B*Hq), 256 threads: one key per thread.
+// ------------------------------------------------------------------ mask, fp32 MFMA
+// grid (key blocks of 32 / 4, Hq, B), 256 threads = 4 waves, one 32-key block per wave.  The wave keeps
+// its keys in registers (B operand of v_mfma_f32_32x32x2_f32: lane (n, hf) holds the 16-byte pieces
+// 8 j + 4 hf of key n) and walks the pooled rows of the groups that have the block among their
+// candidates, 32 rows at a time; a lane then holds 16 rows' products with its key.  Its decisions
+// become one 32-bit word of rows, and a ballot per group gives the bit word of the 32 keys.
+// Latency-bound at the sizes of fp32 use; 4000 tokens, 8 / 2 heads, d = 128: 59 us with one key per thread and
+// vector FMAs (every thread streaming its own key row), 9 us so; the pooling kernel 32 -> 5 us.
+template <int D>
 __global__ __launch_bounds__(256) void mask_fp32_kernel(SelectArgs a) {
+    constexpr int NK = D / 8;
+    typedef float floatx4 __attribute__((ext_vector_type(4)));
     const KParams& p = a.p;
-    const int b = blockIdx.z / p.Hq, h = blockIdx.z % p.Hq, hk = h / p.grp;
-    const int g = blockIdx.y;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int n = lane & 31, hf = lane >> 5;
+    const int h = blockIdx.y, b = blockIdx.z, hk = h / p.grp;
     const Seq sq = seq_of(p, b);
     const int nblk = (sq.len + p.bq - 1) / p.bq;
-    const int i0 = g * p.step;
-    if (i0 >= nblk) return;
-    const int nb = min(p.step, nblk - i0);
-    const int Wg = window_start(p, g);
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if ((int)(blockIdx.x * 256) >= Wg) return;
-    extern __shared__ float qs[];                      // nb pooled rows of d floats
-    for (int e = threadIdx.x; e < nb * p.d; e += 256)
-        qs[e] = a.qp_f32[blk_index(p, sq, b, h, i0 + e / p.d) * p.d + e % p.d];
-    __syncthreads();
-    bool pred = false;
-    if (j >= p.n_init && j < Wg) {
-        const float* kr = (const float*)a.k + tok_offset(p, p.ks, sq, b, hk, j);
-        for (int s = 0; s < nb; ++s) {
-            float dot = 0.f;
-            for (int c = 0; c < p.d; ++c) dot = fmaf(qs[s * p.d + c], kr[c], dot);
-            const float xbar = p.use_anchor ? a.xa[blk_index(p, sq, b, h, i0 + s)] : 0.f;
-            pred = pred || ((xbar - p.sigma * dot) <= p.theta);
+    const int j0 = 32 * (4 * (int)blockIdx.x + wave);
+    if (j0 >= sq.len || j0 + 32 <= p.n_init) return;
+    // first group whose candidates reach into the block: W_g > max(j0, n_init)
+    const long long span = (long long)p.bq * p.step;
+    const long long g0 = ((long long)max(j0, p.n_init) + p.w) / span + 1;
+    if (g0 * p.step >= nblk) return;
+    floatx4 kf[NK];
+    {
+        const float* src = (const float*)a.k + tok_offset(p, p.ks, sq, b, hk, min(j0 + n, sq.len - 1)) + 4 * hf;
+#pragma unroll
+        for (int j = 0; j < NK; ++j) kf[j] = *(const floatx4*)(src + 8 * j);
+    }
+    const long long bi0 = blk_index(p, sq, b, h, 0), gi0 = grp_index(p, sq, b, h, 0);
+    unsigned carry = 0;                                  // bit word so far of a group that continues in the next tile
+    for (int i0 = (int)g0 * p.step; i0 < nblk; i0 += 32) {
+        const int rows = min(32, nblk - i0);
+        const float* qsrc = a.qp_f32 + (bi0 + i0 + min(n, rows - 1)) * D + 4 * hf;
+        floatx16 s = kZero16;
+#pragma unroll
+        for (int j = 0; j < NK; ++j) {
+            const floatx4 x = *(const floatx4*)(qsrc + 8 * j);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], kf[j][e], s, 0, 0, 0);
+        }
+        unsigned dec = 0;                                // bit v: decision of row 8 (v / 4) + 4 hf + v % 4
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int row = 8 * (v >> 2) + 4 * hf + (v & 3);
+            const float xbar = p.use_anchor ? a.xa[bi0 + i0 + min(row, rows - 1)] : 0.f;
+            dec |= (xbar - p.sigma * s[v] <= p.theta) ? 1u << v : 0u;
+        }
+        dec = (dec | (dec << 8)) & 0x00ff00ffu;          // nibble i of the 16 bits -> nibble 2 i of the word
+        dec = (dec | (dec << 4)) & 0x0f0f0f0fu;
+        dec <<= 4 * hf;
+        dec |= __shfl_xor(dec, 32, 64);                  // bit i: decision of row i of the tile
+        const int g_a = i0 / p.step, g_b = (i0 + rows - 1) / p.step;
+        unsigned mine = 0;
+        int done = 0;                                    // groups of this tile that end in it
+        for (int g = g_a; g <= g_b; ++g) {
+            const int lo = max(g * p.step - i0, 0), hi = min((g + 1) * p.step - i0, rows);   // rows lo .. hi - 1
+            const unsigned rowmask = (hi - lo >= 32) ? 0xffffffffu : ((1u << (hi - lo)) - 1u) << lo;
+            unsigned word = (unsigned)__ballot((dec & rowmask) != 0u);
+            if (g == g_a) word |= carry;
+            if ((g + 1) * p.step <= i0 + 32 || i0 + 32 >= nblk) {
+                if (lane == g - g_a) mine = word;
+                done = g - g_a + 1;
+            } else {
+                carry = word;
+            }
+        }
+        if ((g_b + 1) * p.step <= i0 + 32) carry = 0;
+        if (lane < done) {
+            const int g = g_a + lane, Wg = window_start(p, g);
+            const int lo = max(p.n_init - j0, 0), hi = min(Wg - j0, 32);   // keep n_init <= j0 + bit < Wg
+            unsigned keep = 0;
+            if (hi > lo) keep = (hi - lo >= 32) ? 0xffffffffu : (((1u << (hi - lo)) - 1u) << lo);
+            if (j0 / 32 < a.nwords) a.bits[(gi0 + g) * a.nwords + j0 / 32] = mine & keep;
         }
     }
-    const unsigned long long bal = __ballot(pred);
-    const int lane = threadIdx.x & 63;
-    const long long t = grp_index(p, sq, b, h, g);
-    const int w0 = (blockIdx.x * 256 + (threadIdx.x & ~63)) / 32;
-    if (lane == 0 && w0 < a.nwords) a.bits[t * a.nwords + w0] = (unsigned)bal;
-    if (lane == 32 && w0 + 1 < a.nwords) a.bits[t * a.nwords + w0 + 1] = (unsigned)(bal >> 32);
+}
+
+int launch_mask_fp32(const SelectArgs& a, hipStream_t st) {
+    const KParams& p = a.p;
+    const dim3 grid((unsigned)((p.N + 127) / 128), (unsigned)p.Hq, (unsigned)p.B);
+    switch (p.d) {
+        case 32: return (int)launch_kernel(mask_fp32_kernel<32>, grid, dim3(256), 0, st, a);
+        case 64: return (int)launch_kernel(mask_fp32_kernel<64>, grid, dim3(256), 0, st, a);
+        case 128: return (int)launch_kernel(mask_fp32_kernel<128>, grid, dim3(256), 0, st, a);
+        default: return -1;
+    }
 }
 
 // ------------------------------------------------------------------ block granularity

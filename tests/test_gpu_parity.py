@@ -98,6 +98,20 @@ def test_fp32_ragged_and_other_shapes(api):
     _run_and_check(api, wl, cfg)
 
 
+@pytest.mark.parametrize("d,block,lens,step,n_init,window,theta", [
+    (128, 16, [545], 5, 16, 16, 4.5),      # half-filled 32-row tiles; groups that straddle the mask's 32-row tiles
+    (64, 112, [1601], 1, 33, 7, 4.5),      # last tile of a block has 16 rows; unaligned key ranges
+    (32, 80, [1299], 2, 100, 300, 4.5),    # wide window and sink, d = 32
+    (64, 16, [1400], 40, 0, 16, 2.0),      # a group longer than the mask's row tile (its OR keeps every column at theta 4)
+    (128, 128, [33, 1, 900], 2, 40, 128, 4.5),   # packed: fewer key blocks than waves, a single row
+])
+def test_fp32_tiles(api, d, block, lens, step, n_init, window, theta):
+    wl = _wl("t", "fp32", lens, 2, 1, d, block, 60 + block, max(8, max(lens) // 40))
+    cfg = api.Config(block=block, n_init=n_init, window=window, step=step, theta=theta)
+    run, worst = _run_and_check(api, wl, cfg)
+    assert 0 < worst["selected"] < worst["candidates"]
+
+
 # ------------------------------------------------------------------ bf16 MFMA path
 @pytest.mark.parametrize("N,step,n_init,window,theta", [
     (2048, 1, 128, 128, 3.5),
