@@ -233,7 +233,10 @@ int launch_engine(const Plan& pl, const aa_params* prm, EngineArgs& ea, hipStrea
         int choice = prm->engine;                   // 0 auto, 1: 128 rows, 2: 256 rows
         if (!pair_ok) choice = AA_ENGINE_128;
         if (choice == AA_ENGINE_AUTO) {
-            if (ea.flags & kEngList) choice = 3;    // decided on the device from the list lengths
+            const long long pp_entries = 48ll * 64 * pl.sz.groups;   // mean list of 48 tiles
+            // stage 3: decided on the device from the list lengths, unless no outcome reaches the limit
+            // (a launch that finds itself not selected still takes 4 us, 15 us at 128k)
+            if (ea.flags & kEngList) choice = pl.sz.idx_capacity_max < pp_entries ? AA_ENGINE_128 : 3;
             else if (ea.flags & kEngDense) choice = k.N >= 8192 ? AA_ENGINE_256 : AA_ENGINE_128;
             else choice = AA_ENGINE_128;            // anchor region alone: at most step + 3 blocks of keys
         }
@@ -256,21 +259,33 @@ int launch_engine(const Plan& pl, const aa_params* prm, EngineArgs& ea, hipStrea
     return engine_status(launch_engine_fp32(ea, st), "engine_fp32_kernel");
 }
 
+// no group of the call has candidates (the last group of the longest sequence has the most)
+bool no_candidates(const KParams& k) {
+    return (long long)(k.ngrp_max - 1) * k.step * k.bq - k.w <= k.n_init;
+}
+
+// Stage 1 of the fused prefill may finish the rows of groups without candidates itself.  The stage-wise path
+// must give the same bits, so only where both take the same engine (the 256-row engine, when forced, does not).
+bool direct_ok(const aa_params* p) { return p->dtype != AA_BF16 || p->engine != AA_ENGINE_256 || p->step % 2; }
+
 // sel_ws (nullable): a stripe_select workspace; the bf16 engines then also leave the pooled queries of
-// stage 2 there, and the fp32 path leaves the pooled anchors to run_select (which is told so)
+// stage 2 there, and the fp32 path leaves the pooled anchors to run_select (which is told so).
+// out (nullable), lse, stats: see EngineArgs::direct
 int run_anchor(const Plan& pl, const aa_params* p, const void* q, const void* k, const void* v, float* M, float* L,
-               float* Acc, float* xa, char* sel_ws, hipStream_t st) {
+               float* Acc, float* xa, char* sel_ws, void* out, float* lse, int64_t* stats, hipStream_t st) {
     EngineArgs ea;
     memset(&ea, 0, sizeof(ea));
     ea.p = pl.kp;
     ea.flags = kEngAnchorRegion | kEngStoreState;
     ea.q = q; ea.k = k; ea.v = v;
     ea.Mout = M; ea.Lout = L; ea.Accout = Acc; ea.xa = xa;
+    ea.direct = out != nullptr;
+    ea.out = out; ea.lse = lse; ea.stats = (long long*)stats;
     if (sel_ws && p->dtype == AA_BF16) {
         ea.qp_hi = sel_ws + pl.sel_qhi; ea.qp_lo = sel_ws + pl.sel_qlo; ea.qlo_norm = (float*)(sel_ws + pl.sel_qln);
     }
     const int rc = launch_engine(pl, p, ea, st);
-    if (rc != AA_OK || p->dtype == AA_BF16 || sel_ws) return rc;
+    if (rc != AA_OK || p->dtype == AA_BF16 || sel_ws || !xa) return rc;
     SelectArgs sa;
     memset(&sa, 0, sizeof(sa));
     sa.p = pl.kp;
@@ -342,7 +357,7 @@ int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k,
 
 int run_sparse(const Plan& pl, const aa_params* p, const void* q, const void* k, const void* v, const float* M,
                const float* L, const float* Acc, const int32_t* counts, const int64_t* offsets, const int32_t* idx,
-               int64_t idx_capacity, void* out, float* lse, hipStream_t st) {
+               int64_t idx_capacity, void* out, float* lse, bool direct, hipStream_t st) {
     EngineArgs ea;
     memset(&ea, 0, sizeof(ea));
     ea.p = pl.kp;
@@ -352,6 +367,7 @@ int run_sparse(const Plan& pl, const aa_params* p, const void* q, const void* k,
     ea.counts = counts; ea.offsets = (const long long*)offsets; ea.idx = idx;
     ea.idx_capacity = idx_capacity;
     ea.out = out; ea.lse = lse;
+    ea.direct = direct;
     return launch_engine(pl, p, ea, st);
 }
 
@@ -387,7 +403,8 @@ int anchor_compute(const aa_params* params, const void* q, const void* k, const 
     if (rc != AA_OK) return rc;
     if (!q || !k || !v || !M || !L || !xa_pooled) return AA_EINVAL;
     if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(Acc)) return AA_EINVAL;
-    return run_anchor(pl, params, q, k, v, M, L, Acc, xa_pooled, nullptr, (hipStream_t)stream);
+    return run_anchor(pl, params, q, k, v, M, L, Acc, xa_pooled, nullptr, nullptr, nullptr, nullptr,
+                      (hipStream_t)stream);
 }
 
 int stripe_select(const aa_params* params, const void* q, const void* k, const float* xa_pooled, int32_t* counts,
@@ -430,7 +447,7 @@ int sparse_attn(const aa_params* params, const void* q, const void* k, const voi
     if (nstate != 0 && nstate != 3) return AA_EINVAL;
     if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(out) || misaligned(idx) || misaligned(Acc))
         return AA_EINVAL;
-    return run_sparse(pl, params, q, k, v, M, L, Acc, counts, offsets, idx, idx_capacity, out, lse,
+    return run_sparse(pl, params, q, k, v, M, L, Acc, counts, offsets, idx, idx_capacity, out, lse, false,
                       (hipStream_t)stream);
 }
 
@@ -454,12 +471,18 @@ int anchor_attention_prefill(const aa_params* params, const void* q, const void*
     int32_t* idx = (int32_t*)(w + pl.pf_idx);
     // bf16: the block means of Q (first step of stage 2) come out of stage 1, which holds the block's
     // queries in registers; the stage-wise entry points compute the same bits in a kernel of their own
-    rc = run_anchor(pl, params, q, k, v, M, L, Acc, xa, w + pl.pf_sel, st);
+    // Rows of groups without candidates are complete after stage 1, which writes their output; if that is every
+    // row (a prompt within its first group and window), it is the whole call: 53 -> 29 us at 1000 tokens, where
+    // the other kernels' launches alone took 25 us.  At 8k tokens and step 16 it is a quarter of the rows.
+    const bool direct = direct_ok(params);
+    if (direct && no_candidates(pl.kp))
+        return run_anchor(pl, params, q, k, v, M, L, Acc, nullptr, nullptr, out, lse, stats, st);
+    rc = run_anchor(pl, params, q, k, v, M, L, Acc, xa, w + pl.pf_sel, direct ? out : nullptr, lse, nullptr, st);
     if (rc != AA_OK) return rc;
     rc = run_select(pl, params, q, k, xa, counts, offsets, idx, pl.sz.idx_capacity_max, flag, w + pl.pf_sel, M, xa,
                     stats, st);
     if (rc != AA_OK) return rc;
-    rc = run_sparse(pl, params, q, k, v, M, L, Acc, counts, offsets, idx, pl.sz.idx_capacity_max, out, lse, st);
+    rc = run_sparse(pl, params, q, k, v, M, L, Acc, counts, offsets, idx, pl.sz.idx_capacity_max, out, lse, direct, st);
     if (rc != AA_OK) return rc;
     return AA_OK;
 }

@@ -28,6 +28,11 @@ struct EngineArgs {
     float* qlo_norm;
     void* out;
     float* lse;
+    // Fused prefill: rows of a group without candidates (W_g <= n_init) are finished by stage 1, which writes
+    // out and lse instead of the state, and left alone by stage 3.  stats (nullable, stage 1): set if no
+    // group has candidates, so that nothing else runs; receives the statistics of the call.
+    int direct;
+    long long* stats;
     // List-driven calls: offsets[groups_total] is the total (padded) list length.  Lists that do not
     // fit the caller's idx buffer (idx_capacity entries) are incomplete: the launch then does nothing.
     // Two engines can be launched for the same list-driven call; each decides on the device from that
@@ -37,6 +42,18 @@ struct EngineArgs {
     int sel;
     long long sel_entries;
 };
+
+// statistics of a call none of whose groups has candidates: every row attends all keys up to itself
+__device__ __forceinline__ void store_dense_stats(const EngineArgs& a) {
+    if (!a.stats || blockIdx.x != 0 || threadIdx.x != 0) return;
+    long long pairs = 0;
+    for (int b = 0; b < a.p.B; ++b) {
+        const long long len = a.p.packed ? a.p.cu[b + 1] - a.p.cu[b] : a.p.N;
+        pairs += len * (len + 1) / 2;
+    }
+    a.stats[0] = pairs * a.p.Hq;
+    a.stats[1] = 0; a.stats[2] = 0; a.stats[3] = 0;
+}
 
 // true iff this launch has work to do (uniform over the grid)
 __device__ __forceinline__ bool engine_selected(const EngineArgs& a) {

@@ -63,6 +63,7 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keep it scalar
     const int n = lane & 31, hf = lane >> 5;
 
+    if (flags & kEngStoreState) store_dense_stats(a);
     if (!engine_selected(a)) return;
     const Work wk = decode_work(p, p.nblk_max, blockIdx.x);
     const Seq sq = seq_of(p, wk.b);
@@ -74,6 +75,8 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     __builtin_amdgcn_s_setprio(2);
     const int hk = wk.h / p.grp;
     const int g = wk.i / p.step;
+    const bool direct = a.direct && window_start(p, g) <= p.n_init;   // no candidates: stage 1 finishes the rows
+    if ((flags & kEngLoadState) && direct) return;
     const int rw = row0 + 32 * wave;                 // first row of this wave
     const int r = rw + n;                            // this lane's query row
     const bool rok = r < sq.len;
@@ -307,9 +310,16 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     // of one wave execute in order, so no barrier separates its writes from its reads.
     char* const stg = wave == 0 ? Ks0 : wave == 1 ? Ks1 : Vs0 + (wave - 2) * kOutStageBytes;
     const int wave_rows = min(32, sq.len - rw);      // rows of this wave inside the sequence (<= 0: none)
-    const float lt = row_sum(l);                     // row sum relative to mref
+    float lt = row_sum(l);                           // row sum relative to mref
     if (flags & kEngStoreState) {
-        const float ms = store_state(a, ri, tile, rok, wave_rows > 0, lane, hf, c2, mref, mtrue, lt, o);
+        const float ms = rebase_state(a, c2, mref, mtrue, lt, o);
+        if (!direct) {
+            store_state(a, ri, tile, rok, wave_rows > 0, lane, hf, ms, lt, o);
+        } else if (wave_rows > 0) {
+            // what stage 3 makes of a cached state and an empty list, bit for bit
+            store_out(a, stg, tok_offset(p, p.os, sq, wk.b, wk.h, rw), wave_rows, lane, n, hf, lt, o);
+            if (rok && a.lse && hf == 0) a.lse[ri] = ms / p.sigma * p.sigma + __logf(lt);
+        }
         if (a.qp_hi) {
             // pooled query of the block (Algorithm 2, avgpool of Q) from the fragments in registers
             float s0, s1;

@@ -176,18 +176,29 @@ __device__ __forceinline__ float row_sum(float l) {
     return u + w;
 }
 
-// Stage 1's exports for this lane's row, relative to the true maximum (Algorithm 1's m, l, acc):
-// M and L at ri, the wave's Acc tile in fragment order (every store instruction writes 1 KB of
-// consecutive addresses; stage 3 reads the tile back the same way).  Returns M in scaled-logit units.
-__device__ __forceinline__ float store_state(const EngineArgs& a, long long ri, long long tile, bool rok,
-                                             bool wave_has_rows, int lane, int hf, float c2, float mref, float mtrue,
-                                             float lt, const floatx16 (&o)[4]) {
+// The row's state relative to its true maximum (Algorithm 1's m, l, acc): scales lt and o, returns M in
+// scaled-logit units.
+__device__ __forceinline__ float rebase_state(const EngineArgs& a, float c2, float mref, float mtrue, float& lt,
+                                              floatx16 (&o)[4]) {
     float ma, mb;
     both_halves(mtrue, ma, mb);
     mtrue = fmaxf(ma, mb);
     const float down = (mref == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f((mref - mtrue) * c2);
-    const float ms = mtrue * a.p.sigma;
-    if (rok && hf == 0) { a.Mout[ri] = ms; a.Lout[ri] = lt * down; }
+    lt *= down;
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[db][v] *= down;
+    return mtrue * a.p.sigma;
+}
+
+// Stage 1's exports for this lane's row, after rebase_state: M and L at ri, the wave's Acc tile in fragment
+// order (every store instruction writes 1 KB of consecutive addresses; stage 3 reads the tile back the
+// same way).
+__device__ __forceinline__ void store_state(const EngineArgs& a, long long ri, long long tile, bool rok,
+                                            bool wave_has_rows, int lane, int hf, float ms, float lt,
+                                            const floatx16 (&o)[4]) {
+    if (rok && hf == 0) { a.Mout[ri] = ms; a.Lout[ri] = lt; }
     if (a.Accout && wave_has_rows) {
         float* acc = a.Accout + tile;
 #pragma unroll
@@ -195,10 +206,8 @@ __device__ __forceinline__ float store_state(const EngineArgs& a, long long ri, 
 #pragma unroll
             for (int v4 = 0; v4 < 4; ++v4)
                 *(floatx4*)(acc + (4 * db + v4) * 256 + 4 * lane) =
-                    floatx4{o[db][4 * v4] * down, o[db][4 * v4 + 1] * down, o[db][4 * v4 + 2] * down,
-                            o[db][4 * v4 + 3] * down};
+                    floatx4{o[db][4 * v4], o[db][4 * v4 + 1], o[db][4 * v4 + 2], o[db][4 * v4 + 3]};
     }
-    return ms;
 }
 
 // out = acc / l for the wave's 32 rows (wave_rows of them exist), through a private staging area of

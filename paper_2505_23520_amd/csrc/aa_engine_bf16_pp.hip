@@ -65,6 +65,7 @@ __global__ __launch_bounds__(512, 1) void engine_bf16_pp_kernel(EngineArgs a) {
     if (row0 >= sq.len) return;
     const int hk = wk.h / p.grp;
     const int g = (2 * wk.i) / p.step;
+    if ((flags & kEngLoadState) && a.direct && window_start(p, g) <= p.n_init) return;   // stage 1 finished these rows
     const int rw = row0 + 32 * chunk;                // first row of this wave
     const int r = rw + n;                            // this lane's query row
     const bool rok = r < sq.len;
@@ -342,9 +343,10 @@ __global__ __launch_bounds__(512, 1) void engine_bf16_pp_kernel(EngineArgs a) {
     if (!grpB) slot_barrier();
 
     // ---- epilogue
-    const float lt = row_sum(l);                     // row sum relative to mref
+    float lt = row_sum(l);                           // row sum relative to mref
     if (flags & kEngStoreState) {
-        const float ms = store_state(a, ri, tile, rok, wave_on, lane, hf, c2, mref, mtrue, lt, o);
+        const float ms = rebase_state(a, c2, mref, mtrue, lt, o);
+        store_state(a, ri, tile, rok, wave_on, lane, hf, ms, lt, o);
         if (FLAGS < 0 && a.qp_hi) {
             // pooled query of each block (Algorithm 2, avgpool of Q) from the fragments in registers;
             // the four waves of a block are a team

@@ -57,6 +57,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void engine_fp32_kernel(
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int n = lane & 31, hf = lane >> 5;
 
+    if (a.flags & kEngStoreState) store_dense_stats(a);
     if (!engine_selected(a)) return;
     const int rts = (p.bq + RT - 1) / RT;            // row tiles of a query block
     const Work wk = decode_work(p, p.nblk_max * rts, blockIdx.x);
@@ -67,6 +68,8 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void engine_fp32_kernel(
     if (row0 >= rend) return;
     const int hk = wk.h / p.grp;
     const int g = blk / p.step;
+    const bool direct = a.direct && window_start(p, g) <= p.n_init;   // no candidates: stage 1 finishes the rows
+    if ((a.flags & kEngLoadState) && direct) return;
     const int r = row0 + n;
     const bool rok = r < rend;
     const int rlast = rend - 1;
@@ -256,10 +259,15 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void engine_fp32_kernel(
             for (int db = 0; db < T; ++db) res[T * e + db] = fmaf(obuf[w][db][4 * wave + e][lane], f, res[T * e + db]);
     }
 
-    const float ms = mall * p.sigma;
+    float ms = mall * p.sigma;
     if (!rok) return;
     const bool first = wave == 0 && hf == 0;
-    if (a.flags & kEngStoreState) {
+    bool store_out = (a.flags & kEngStoreOut) != 0;
+    if ((a.flags & kEngStoreState) && direct) {
+        // what stage 3 makes of a cached state and an empty list, bit for bit
+        ms = ms / p.sigma * p.sigma;
+        store_out = true;
+    } else if (a.flags & kEngStoreState) {
         if (first) { a.Mout[ri] = ms; a.Lout[ri] = lall; }
         if (a.Accout) {
             float* dst = a.Accout + ri * D + col0;
@@ -267,7 +275,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void engine_fp32_kernel(
             for (int c = 0; c < 4 * T; c += 4) *(floatx4*)(dst + c) = floatx4{res[c], res[c + 1], res[c + 2], res[c + 3]};
         }
     }
-    if (a.flags & kEngStoreOut) {
+    if (store_out) {
         const float inv = 1.f / lall;
         float* dst = (float*)a.out + tok_offset(p, p.os, sq, wk.b, wk.h, r) + col0;
 #pragma unroll

@@ -137,6 +137,23 @@ def test_bf16_short_sequences(api):
         _run_and_check(api, wl, cfg)
 
 
+@pytest.mark.parametrize("dtype,d,block,lens,n_init,window", [
+    ("bf16", 128, 128, [300, 0, 700, 1], 50, 128),       # every row is finished by stage 1 (one group per sequence)
+    ("bf16", 128, 128, [700, 2500], 300, 2000),          # second group's candidate range is empty: W_g = n_init
+    ("fp32", 64, 32, [33, 0, 500], 16, 32),
+    ("fp32", 128, 16, [250, 300], 5, 300),
+])
+def test_prefill_without_candidates(api, dtype, d, block, lens, n_init, window):
+    wl = _wl("t", dtype, lens, 2, 1, d, block, 80 + block, 8)
+    cfg = api.Config(block=block, n_init=n_init, window=window, step=16, theta=4.0)
+    run, worst = _run_and_check(api, wl, cfg, packed=True)      # output, lse and stats as the stages give them
+    assert worst["candidates"] == 0
+    out = torch.zeros_like(run.out)
+    ws = torch.full((run.sizes.prefill_ws_bytes,), 255, dtype=torch.uint8, device="cuda")
+    api.anchor_attention_prefill(run.p, run.q, run.k, run.v, out, None, None, ws)
+    assert torch.equal(out, run.out)
+
+
 @pytest.mark.parametrize("theta", [float("inf"), float("-inf")])
 def test_bf16_theta_extremes(api, theta):
     from parity_util import DeviceRun
