@@ -268,11 +268,14 @@ bool no_candidates(const KParams& k) {
 // must give the same bits, so only where both take the same engine (the 256-row engine, when forced, does not).
 bool direct_ok(const aa_params* p) { return p->dtype != AA_BF16 || p->engine != AA_ENGINE_256 || p->step % 2; }
 
-// sel_ws (nullable): a stripe_select workspace; the bf16 engines then also leave the pooled queries of
+// the 128-row engine's stage 1 also leaves the key norms of the stripe mask and its cleared counters
+bool pooled_keys(const aa_params* p) { return p->granularity == AA_STRIPE && direct_ok(p); }
+
+// sel_ws (nullable): a stripe_select workspace (with the call's counts); the bf16 engines then also leave the pooled queries of
 // stage 2 there, and the fp32 path leaves the pooled anchors to run_select (which is told so).
 // out (nullable), lse, stats: see EngineArgs::direct
 int run_anchor(const Plan& pl, const aa_params* p, const void* q, const void* k, const void* v, float* M, float* L,
-               float* Acc, float* xa, char* sel_ws, void* out, float* lse, int64_t* stats, hipStream_t st) {
+               float* Acc, float* xa, char* sel_ws, int32_t* counts, void* out, float* lse, int64_t* stats, hipStream_t st) {
     EngineArgs ea;
     memset(&ea, 0, sizeof(ea));
     ea.p = pl.kp;
@@ -283,6 +286,10 @@ int run_anchor(const Plan& pl, const aa_params* p, const void* q, const void* k,
     ea.out = out; ea.lse = lse; ea.stats = (long long*)stats;
     if (sel_ws && p->dtype == AA_BF16) {
         ea.qp_hi = sel_ws + pl.sel_qhi; ea.qp_lo = sel_ws + pl.sel_qlo; ea.qlo_norm = (float*)(sel_ws + pl.sel_qln);
+        if (pooled_keys(p)) {
+            ea.kmax_blk = (float*)(sel_ws + pl.sel_kmax);
+            ea.zero_counts = counts; ea.zero_seg = (int*)(sel_ws + pl.sel_segc); ea.nseg = (int)cdiv(pl.nwords, 64);
+        }
     }
     const int rc = launch_engine(pl, p, ea, st);
     if (rc != AA_OK || p->dtype == AA_BF16 || sel_ws || !xa) return rc;
@@ -321,7 +328,8 @@ int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k,
 
     const dim3 gblk(kp.nblk_max, kp.Hq, kp.B), ggrp(kp.ngrp_max, kp.Hq, kp.B);
     if (p->granularity == AA_BLOCK) AA_HIP(raise_lds_limits());   // before anything is enqueued
-    if (kp.packed)
+    const bool counted = p->dtype == AA_BF16 && p->granularity == AA_STRIPE;   // the mask kernel counts
+    if (kp.packed && !counted)
         AA_LAUNCH(zero_i32_kernel, dim3((unsigned)cdiv(pl.sz.groups, 256)), dim3(256), 0, st, counts,
                   (long long)pl.sz.groups);
     const bool q_pooled = fused_M && p->dtype == AA_BF16;
@@ -336,10 +344,18 @@ int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k,
         AA_LAUNCH(mask_block_kernel, ggrp, dim3(256), mask_block_lds_bytes(kp.N, kp.d, kp.bq, kp.step), st, sa);
     } else if (p->dtype == AA_BF16) {
         sa.kmax_blk = (float*)(ws + pl.sel_kmax);
-        AA_LAUNCH(pool_q_bf16_kernel, dim3(kp.nblk_max, (q_pooled ? 0 : kp.Hq) + kp.Hkv, kp.B), dim3(256), 0, st, sa);
-        // one work-group per (query head, row tile, key chunk with candidates); the longest
-        // sequence bounds every other
-        sa.mask_items = mask_pair_items(kp.nblk_max, kp.step, kp.bq, kp.w, kp.n_init);
+        if (!q_pooled || !pooled_keys(p))
+            AA_LAUNCH(pool_q_bf16_kernel, dim3(kp.nblk_max, (q_pooled ? 0 : kp.Hq) + kp.Hkv, kp.B), dim3(256), 0, st, sa);
+        // One work-group per (query head, row tile, key span with candidates); the longest sequence bounds
+        // every other.  Three work-groups fit a CU: the span is halved until there are that many (a span's fixed
+        // cost, loading the pooled rows, is about three of its 64-key tiles).  8k tokens: 96 work-groups of 2048
+        // keys took 32 us, 736 of 256 keys take 16; 16k tokens at step 1: 48 -> 32 us.
+        sa.mask_span = kSegKeys;
+        for (;;) {
+            sa.mask_items = mask_pair_items(kp.nblk_max, kp.step, kp.bq, kp.w, kp.n_init, sa.mask_span);
+            if ((long long)sa.mask_items * kp.Hq * (kp.packed ? 1 : kp.B) >= 768 || sa.mask_span == kMaskSpanMin) break;
+            sa.mask_span /= 2;
+        }
         const long long mask_per_xcd = cdiv((long long)sa.mask_items * kp.Hq * kp.B, 8);
         if (mask_per_xcd * 8 > 0x7fffffffll) return AA_EUNSUPPORTED;
         const dim3 gm((unsigned)(mask_per_xcd > 0 ? mask_per_xcd * 8 : 8));
@@ -349,7 +365,7 @@ int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k,
         const int rc = engine_status(launch_mask_fp32(sa, st), "mask_fp32_kernel");
         if (rc != AA_OK) return rc;
     }
-    AA_LAUNCH(count_kernel, ggrp, dim3(256), 0, st, sa);
+    if (!counted) AA_LAUNCH(count_kernel, ggrp, dim3(256), 0, st, sa);
     AA_LAUNCH(scan_kernel, dim3(1), dim3(1024), 0, st, sa);
     AA_LAUNCH(fill_kernel, dim3(kp.ngrp_max, (unsigned)cdiv(sa.nseg, 4), kp.Hq * kp.B), dim3(256), 0, st, sa);
     return AA_OK;
@@ -403,7 +419,7 @@ int anchor_compute(const aa_params* params, const void* q, const void* k, const 
     if (rc != AA_OK) return rc;
     if (!q || !k || !v || !M || !L || !xa_pooled) return AA_EINVAL;
     if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(Acc)) return AA_EINVAL;
-    return run_anchor(pl, params, q, k, v, M, L, Acc, xa_pooled, nullptr, nullptr, nullptr, nullptr,
+    return run_anchor(pl, params, q, k, v, M, L, Acc, xa_pooled, nullptr, nullptr, nullptr, nullptr, nullptr,
                       (hipStream_t)stream);
 }
 
@@ -476,8 +492,9 @@ int anchor_attention_prefill(const aa_params* params, const void* q, const void*
     // the other kernels' launches alone took 25 us.  At 8k tokens and step 16 it is a quarter of the rows.
     const bool direct = direct_ok(params);
     if (direct && no_candidates(pl.kp))
-        return run_anchor(pl, params, q, k, v, M, L, Acc, nullptr, nullptr, out, lse, stats, st);
-    rc = run_anchor(pl, params, q, k, v, M, L, Acc, xa, w + pl.pf_sel, direct ? out : nullptr, lse, nullptr, st);
+        return run_anchor(pl, params, q, k, v, M, L, Acc, nullptr, nullptr, nullptr, out, lse, stats, st);
+    rc = run_anchor(pl, params, q, k, v, M, L, Acc, xa, w + pl.pf_sel, counts, direct ? out : nullptr, lse, nullptr,
+                    st);
     if (rc != AA_OK) return rc;
     rc = run_select(pl, params, q, k, xa, counts, offsets, idx, pl.sz.idx_capacity_max, flag, w + pl.pf_sel, M, xa,
                     stats, st);

@@ -67,6 +67,10 @@ __device__ __forceinline__ long long row_index(const KParams& p, const Seq& s, i
 __device__ __forceinline__ long long blk_index(const KParams& p, const Seq& s, int b, int h, int i) {
     return p.packed ? (long long)h * p.blk_cap + s.blk0 + i : ((long long)b * p.Hq + h) * p.blk_cap + i;
 }
+// per (KV head, key block) arrays of stage 2
+__device__ __forceinline__ long long kblk_index(const KParams& p, const Seq& s, int b, int hk, int i) {
+    return (p.packed ? (long long)hk * p.blk_cap + s.blk0 : ((long long)b * p.Hkv + hk) * p.blk_cap) + i;
+}
 __device__ __forceinline__ long long grp_index(const KParams& p, const Seq& s, int b, int h, int g) {
     return p.packed ? (long long)h * p.grp_cap + s.grp0 + g : ((long long)b * p.Hq + h) * p.grp_cap + g;
 }

@@ -26,6 +26,10 @@ struct EngineArgs {
     // written from the Q fragments the block's work-group holds anyway (see aa_pool.h)
     void *qp_hi, *qp_lo;
     float* qlo_norm;
+    // stage 1 only, nullable: largest key norm per (KV head, key block) for stage 2, and the counters to clear for it
+    float* kmax_blk;
+    int *zero_counts, *zero_seg;
+    int nseg;
     void* out;
     float* lse;
     // Fused prefill: rows of a group without candidates (W_g <= n_init) are finished by stage 1, which writes

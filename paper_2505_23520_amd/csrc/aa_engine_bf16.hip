@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     // one LDS object per stage, so that the compiler can tell that the asynchronous loads into
     // one stage do not alias the operand reads from the others
     __shared__ __attribute__((aligned(16))) char Ks0[KBYTES], Ks1[KBYTES], Vs0[VBYTES];
-    __shared__ float red[NW];
+    __shared__ float red[NW], knorm[NW];
     __shared__ float qpart[(FLAGS & kEngStoreState) ? 4 : 1][128];   // pooled-query partial sums (stage 1)
     const KParams& p = a.p;
     const int tid = threadIdx.x;
@@ -63,7 +63,11 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keep it scalar
     const int n = lane & 31, hf = lane >> 5;
 
-    if (flags & kEngStoreState) store_dense_stats(a);
+    if (flags & kEngStoreState) {
+        store_dense_stats(a);
+        if (a.kmax_blk)
+            clear_counters(a.zero_counts, a.groups_total, a.zero_seg, a.nseg, blockIdx.x * 256ll + tid, gridDim.x * 256ll);
+    }
     if (!engine_selected(a)) return;
     const Work wk = decode_work(p, p.nblk_max, blockIdx.x);
     const Seq sq = seq_of(p, wk.b);
@@ -327,6 +331,11 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
             pool_block_finish(qpart, wave, n, hf, s0, s1, tid, rlast - row0 + 1,
                               blk_index(p, sq, wk.b, wk.h, wk.i), true, a.qp_hi, a.qp_lo, a.qlo_norm);
         }
+        // the key norms of block i of a KV head fall to one of the head's query heads, in turn (its rows were the
+        // last tiles of the loop)
+        if (a.kmax_blk && wk.h % p.grp == wk.i % p.grp)
+            key_block_norm((const unsigned short*)a.k + tok_offset(p, p.ks, sq, wk.b, hk, 0), p.ks[2], row0, rlast + 1, tid,
+                           knorm, a.kmax_blk + kblk_index(p, sq, wk.b, hk, wk.i));
         if (a.xa) {
             // pooled anchor of the block: mean of M over its rows (Algorithm 2, avgpool of the anchor)
             float red_m = (rok && hf == 0) ? ms : 0.f;

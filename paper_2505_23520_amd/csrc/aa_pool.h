@@ -77,4 +77,42 @@ __device__ __forceinline__ void pool_block_finish(float (*part)[128], int tile, 
     }
 }
 
+// Largest key norm of a key block (the mask kernel bounds |<lo, k>| by |lo| |k| to decide whether the lo
+// products are needed): rows r0 .. r1 - 1 (at most 128) of the head whose row r starts at k + r * stride, two
+// threads per row, so that a row's sum takes one exchange.  All 256 threads of the work-group must call this (it
+// holds a barrier); part: 4 floats of LDS.
+__device__ __forceinline__ void key_block_norm(const unsigned short* k, long long stride, int r0, int r1, int tid,
+                                               float* part, float* out) {
+    typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+    const unsigned short* src = k + (long long)min(r0 + (tid >> 1), r1 - 1) * stride + 8 * (tid & 1);
+    uintx4 x[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) x[c] = *(const uintx4*)(src + 16 * c);
+    float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float lo = __uint_as_float(x[c][e] << 16), hi = __uint_as_float(x[c][e] & 0xffff0000u);
+            s0 = fmaf(lo, lo, s0);
+            s1 = fmaf(hi, hi, s1);
+        }
+    float big = s0 + s1;
+    big += __shfl_xor(big, 1, 64);
+#pragma unroll
+    for (int off = 32; off >= 2; off >>= 1) big = fmaxf(big, __shfl_xor(big, off, 64));
+    if ((tid & 63) == 0) part[tid >> 6] = big;
+    __syncthreads();
+    if (tid == 0) *out = sqrtf(fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3])));
+}
+
+// Clears the counters that the bf16 mask kernel adds to; called by every thread of a kernel that runs before it.
+__device__ __forceinline__ void clear_counters(int* counts, long long groups, int* segcount, int nseg,
+                                               long long thread, long long nthreads) {
+    for (long long e = thread; e < groups * (nseg + 1); e += nthreads) {
+        if (e < groups) counts[e] = 0;
+        else segcount[e - groups] = 0;
+    }
+}
+
 }  // namespace aa

@@ -5,14 +5,19 @@
 namespace aa {
 
 constexpr int kMaskChunkKeys = 1024;   // keys per chunk of the bf16 mask kernel (its LDS holds one chunk's compare words)
-constexpr int kMaskChunksPerWG = 2;    // consecutive chunks walked by one work-group (2: -3 %, 4: no further gain)
+// Keys per work-group of the bf16 mask kernel (SelectArgs::mask_span): kSegKeys, or a half, a quarter or an
+// eighth of it where that many keys would leave the chip short of work-groups.
+constexpr int kSegKeys = 2048;         // keys per segment of a group's bit words
+constexpr int kMaskSpanMin = 256;
+// first word of a group's first segment
+__host__ __device__ inline int seg_word0(int n_init) { return n_init / 64 * 2; }
 
 // bf16 mask kernel: pooled rows per row tile, and the number of key chunks a row tile has
 // candidates in (all groups of the tile end their candidates before the last group's window).
 // Host and device use the same arithmetic: the host sizes the grid with it, the kernel decodes
 // its work-group index with it.
 __host__ __device__ inline int mask_row_tile(int step) { return 128 - 128 % step; }
-__host__ __device__ inline int mask_tile_chunks(int nblk, int rt, int step, int bq, int w, int n_init) {
+__host__ __device__ inline int mask_tile_chunks(int nblk, int rt, int step, int bq, int w, int n_init, int span) {
     const int RT = mask_row_tile(step);
     if (rt < 0 || rt * RT >= nblk) return 0;
     const int rows = nblk - rt * RT < RT ? nblk - rt * RT : RT;
@@ -20,17 +25,16 @@ __host__ __device__ inline int mask_tile_chunks(int nblk, int rt, int step, int 
     const long long W = (long long)g_last * step * bq - w;
     const int Wmax = W > n_init ? (int)W : n_init;
     const int key_lo = (n_init / 64) * 64;
-    const int span = kMaskChunkKeys * kMaskChunksPerWG;
     return Wmax > key_lo ? (Wmax - key_lo + span - 1) / span : 0;
 }
 // Work items of one (sequence, KV head) pair in the bf16 mask kernel: one per (row tile, key chunk
 // that holds candidates of the tile).  The count for the longest sequence sizes the grid; a
 // shorter sequence has fewer and its surplus work-groups return.
-__host__ __device__ inline int mask_pair_items(int nblk, int step, int bq, int w, int n_init) {
+__host__ __device__ inline int mask_pair_items(int nblk, int step, int bq, int w, int n_init, int span) {
     const int RT = mask_row_tile(step);
     const int ny = (nblk + RT - 1) / RT;
     int n = 0;
-    for (int y = 0; y < ny; ++y) n += mask_tile_chunks(nblk, y, step, bq, w, n_init);
+    for (int y = 0; y < ny; ++y) n += mask_tile_chunks(nblk, y, step, bq, w, n_init, span);
     return n;
 }
 
@@ -49,7 +53,7 @@ struct SelectArgs {
     int pool_skip_q;          // bf16: the pooled queries are there already (stage 1 wrote them)
     unsigned* bits;           // [groups][nwords] selection bit words, bit (j % 32) of word j / 32
     int nwords;               // ceil(N / 32)
-    int* segcount;            // [groups][nseg] selected columns per segment of 64 bit words (2048 keys)
+    int* segcount;            // [groups][nseg] selected columns per segment of 64 bit words (kSegKeys keys)
     int nseg;                 // ceil(nwords / 64)
     int* counts;
     long long* offsets;
@@ -60,6 +64,7 @@ struct SelectArgs {
     long long* stats;         // nullable, int64[4]: { attended pairs, selected entries, 0, 0 }
     // bf16 mask kernel: work items per (sequence, KV head) pair for the longest sequence (sizes the grid)
     int mask_items;
+    int mask_span;            // keys per work item
 };
 
 __global__ void pool_q_bf16_kernel(SelectArgs a);

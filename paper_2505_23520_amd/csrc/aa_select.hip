@@ -31,47 +31,28 @@ __device__ __forceinline__ unsigned short f_to_bf16_rne(float f) {
 
 // ------------------------------------------------------------------ pool_q
 // grid (nblk_max, Hq [+ Hkv], B).  bf16: 256 threads = the four waves of the tile engines; writes
-// hi/lo bf16 rows of 128 and the norm of the lo row (aa_pool.h).  With kmax_blk set the grid has Hkv
-// more rows in y: those work-groups write the largest key norm of their key block (the mask kernel
-// bounds |<lo, k>| by |lo| |k| to decide whether the lo products are needed).  pool_skip_q: the
-// queries were pooled by stage 1 already, the grid holds the Hkv key rows only.
+// hi/lo bf16 rows of 128 and the norm of the lo row (aa_pool.h).  With kmax_blk set (stripe granularity)
+// the grid has Hkv more rows in y, whose work-groups write the largest key norm of their key block, and the
+// mask kernel's counters are cleared.  pool_skip_q: the queries were pooled by stage 1 already, the
+// grid holds the Hkv key rows only.
 __global__ __launch_bounds__(256) void pool_q_bf16_kernel(SelectArgs a) {
     const KParams& p = a.p;
-    const int i = blockIdx.x, b = blockIdx.z;
+    const int i = blockIdx.x, b = blockIdx.z, tid = threadIdx.x;
+    if (a.kmax_blk) {
+        const long long wg = blockIdx.x + (long long)gridDim.x * (blockIdx.y + (long long)gridDim.y * blockIdx.z);
+        clear_counters(a.counts, a.groups_total, a.segcount, a.nseg, wg * 256 + tid,
+                       (long long)gridDim.x * gridDim.y * gridDim.z * 256);
+    }
     const Seq sq = seq_of(p, b);
     const int r0 = i * p.bq;
     if (r0 >= sq.len) return;
     const int r1 = min(r0 + p.bq, sq.len);
-    const int tid = threadIdx.x, c = tid & 15, rs = tid >> 4;
-    __shared__ float red[16][128];
+    __shared__ float red[4][128];
     const int y = blockIdx.y + (a.pool_skip_q ? p.Hq : 0);
     if (y >= p.Hq) {
-        // key block i of KV head hk: squared norm of every row (16 threads per row), largest
         const int hk = y - p.Hq;
-        const unsigned short* src = (const unsigned short*)a.k + tok_offset(p, p.ks, sq, b, hk, 0) + 8 * c;
-        float big = 0.f;
-        for (int r = r0 + rs; r < r1; r += 16) {
-            const uintx4 x = *(const uintx4*)(src + (long long)r * p.ks[2]);
-            float ss = 0.f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float lo = __uint_as_float(x[e] << 16), hi = __uint_as_float(x[e] & 0xffff0000u);
-                ss = fmaf(lo, lo, ss);
-                ss = fmaf(hi, hi, ss);
-            }
-#pragma unroll
-            for (int off = 8; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
-            big = fmaxf(big, ss);
-        }
-#pragma unroll
-        for (int off = 32; off >= 16; off >>= 1) big = fmaxf(big, __shfl_xor(big, off, 64));
-        if ((tid & 63) == 0) red[0][tid >> 6] = big;
-        __syncthreads();
-        if (tid == 0) {
-            const long long kb = (p.packed ? (long long)hk * p.blk_cap + sq.blk0
-                                           : ((long long)b * p.Hkv + hk) * p.blk_cap) + i;
-            a.kmax_blk[kb] = sqrtf(fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3])));
-        }
+        key_block_norm((const unsigned short*)a.k + tok_offset(p, p.ks, sq, b, hk, 0), p.ks[2], r0, r1, tid, red[0],
+                       a.kmax_blk + kblk_index(p, sq, b, hk, i));
         return;
     }
     // query block i of head h: the fragments of the tile engines (wave w: rows 32 w .. 32 w + 31, lane
@@ -91,7 +72,7 @@ __global__ __launch_bounds__(256) void pool_q_bf16_kernel(SelectArgs a) {
     }
     float s0, s1;
     pool_wave_columns(qf, n, s0, s1);
-    pool_block_finish((float(*)[128])red, wave, n, hf, s0, s1, tid, r1 - r0, blk_index(p, sq, b, h, i), true,
+    pool_block_finish(red, wave, n, hf, s0, s1, tid, r1 - r0, blk_index(p, sq, b, h, i), true,
                       a.qp_hi, a.qp_lo, a.qlo_norm);
 }
 
@@ -176,7 +157,7 @@ __global__ __launch_bounds__(256, 3) void mask_bf16_kernel(SelectArgs a) {
     long long real = 0;
     if (p.packed) {
         for (int s = 0; s < p.B; ++s)
-            real += mask_pair_items((p.cu[s + 1] - p.cu[s] + span_blk - 1) / span_blk, p.step, p.bq, p.w, p.n_init);
+            real += mask_pair_items((p.cu[s + 1] - p.cu[s] + span_blk - 1) / span_blk, p.step, p.bq, p.w, p.n_init, a.mask_span);
         real *= p.Hq;
     } else {
         real = (long long)a.mask_items * p.Hq * p.B;
@@ -189,7 +170,8 @@ __global__ __launch_bounds__(256, 3) void mask_bf16_kernel(SelectArgs a) {
     int b = 0, items_b = a.mask_items;
     if (p.packed) {
         for (;; ++b) {
-            items_b = mask_pair_items((p.cu[b + 1] - p.cu[b] + span_blk - 1) / span_blk, p.step, p.bq, p.w, p.n_init);
+            items_b = mask_pair_items((p.cu[b + 1] - p.cu[b] + span_blk - 1) / span_blk, p.step, p.bq, p.w, p.n_init,
+                                      a.mask_span);
             const long long n = (long long)items_b * p.Hq;
             if (L < n) break;
             L -= n;
@@ -212,7 +194,7 @@ __global__ __launch_bounds__(256, 3) void mask_bf16_kernel(SelectArgs a) {
     {
         int item = e / p.grp, prev = 0;
         for (int y = 0; y < ny; ++y) {
-            const int n = mask_tile_chunks(nblk, y, p.step, p.bq, p.w, p.n_init);
+            const int n = mask_tile_chunks(nblk, y, p.step, p.bq, p.w, p.n_init, a.mask_span);
             const int width = ny - y, items = (n - prev) * width;
             if (item < items) {
                 chunk = prev + item / width;
@@ -231,7 +213,7 @@ __global__ __launch_bounds__(256, 3) void mask_bf16_kernel(SelectArgs a) {
     const int g_last = (row_t0 + rows_here - 1) / p.step;
     const int Wmax = window_start(p, g_last);            // candidates of the tile end before Wmax
     const int key_lo = (p.n_init / kMaskTileKeys) * kMaskTileKeys;
-    if (key_lo + chunk * kMaskChunksPerWG * kMaskChunkKeys >= Wmax) return;
+    if (key_lo + chunk * a.mask_span >= Wmax) return;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -242,6 +224,7 @@ __global__ __launch_bounds__(256, 3) void mask_bf16_kernel(SelectArgs a) {
     __shared__ __attribute__((aligned(16))) char kt0[kKTile], kt1[kKTile];
     // compare words of the whole chunk: [tile][pooled row][word]
     __shared__ unsigned rowword[kMaskChunkTiles][128][2];
+    __shared__ int gcount[128];                          // selected columns of each group in this work-group's keys
 
     // B operand: this lane's pooled query row, hi and lo parts, columns 16 ks + 8 hf .. +8
     bf16x8 bhi[8], blo[8];
@@ -288,13 +271,14 @@ __global__ __launch_bounds__(256, 3) void mask_bf16_kernel(SelectArgs a) {
     const int ngrp = (nblk + p.step - 1) / p.step;
     const int ngt = g_last - g_first + 1;
     // OR the rows of each group, clip to the group's candidate range, write the bit words of a tile
-    // a work-group walks kMaskChunksPerWG chunks of kMaskChunkKeys keys: the pooled rows stay in
+    // a work-group walks its mask_span keys in chunks of at most kMaskChunkKeys: the pooled rows stay in
     // registers, the compare words of a chunk are combined and written before the next one starts
     const int koff = (n & 15) * kKGrp + (n >> 4) * 256 + 16 * hf;   // K row of key 32 kb + n
-    for (int cc = 0; cc < kMaskChunksPerWG; ++cc) {
-    const int chunk0 = key_lo + (chunk * kMaskChunksPerWG + cc) * kMaskChunkKeys;
-    if (chunk0 >= Wmax) break;
-    const int chunk1 = min(chunk0 + kMaskChunkKeys, ((Wmax + kMaskTileKeys - 1) / kMaskTileKeys) * kMaskTileKeys);
+    if (tid < 128) gcount[tid] = 0;                      // (the first tile's barrier publishes it)
+    const int span_end = min(key_lo + (chunk + 1) * a.mask_span,
+                             ((Wmax + kMaskTileKeys - 1) / kMaskTileKeys) * kMaskTileKeys);
+    for (int chunk0 = key_lo + chunk * a.mask_span; chunk0 < span_end; chunk0 += kMaskChunkKeys) {
+    const int chunk1 = min(chunk0 + kMaskChunkKeys, span_end);
     const int ntiles = (chunk1 - chunk0) / kMaskTileKeys;
     // |sigma <lo, k>| <= sigma |lo| max|k| over the chunk's keys: a score whose margin from the hi
     // products alone is farther from zero than that keeps its sign whatever the lo products add
@@ -329,8 +313,11 @@ __global__ __launch_bounds__(256, 3) void mask_bf16_kernel(SelectArgs a) {
             const int lo = max(p.n_init - j0, 0), hi = min(Wg - j0, 32);   // keep n_init <= j0 + bit < Wg
             unsigned keep = 0;
             if (hi > lo) keep = (hi - lo >= 32) ? 0xffffffffu : (((1u << (hi - lo)) - 1u) << lo);
-            if (g < ngrp && j0 / 32 < nwords)
-                a.bits[grp_index(p, sq, b, h, g) * nwords + j0 / 32] = wd & keep;
+            wd &= keep;
+            if (g < ngrp && j0 / 32 < nwords) {
+                a.bits[grp_index(p, sq, b, h, g) * nwords + j0 / 32] = wd;
+                if (wd) atomicAdd(&gcount[gi], __popc(wd));
+            }
         }
     };
 
@@ -418,6 +405,12 @@ __global__ __launch_bounds__(256, 3) void mask_bf16_kernel(SelectArgs a) {
     __builtin_amdgcn_s_waitcnt(0x0F70);              // the trailing loads have landed before LDS is reused
     combine_all();
     __syncthreads();                                 // rowword is reused by the next chunk
+    }
+    // A work-group's keys lie in one segment; the groups of a row tile have several work-groups
+    if (tid < ngt && gcount[tid]) {
+        const long long t = grp_index(p, sq, b, h, g_first + tid);
+        atomicAdd(&a.counts[t], gcount[tid]);
+        atomicAdd(&a.segcount[t * a.nseg + chunk * a.mask_span / kSegKeys], gcount[tid]);
     }
 }
 
@@ -656,7 +649,8 @@ __global__ void zero_i32_kernel(int* x, long long nelem) {
 }
 
 // grid (ngrp_max, Hq, B), 256 threads: selected columns of the group, in total and per segment of
-// 64 bit words (the segment counts let fill_kernel expand the segments independently)
+// 64 bit words = kSegKeys keys from seg_word0 on (the segment counts let fill_kernel expand the segments
+// independently).  fp32 and block granularity; the bf16 mask kernel counts what it writes itself.
 __global__ __launch_bounds__(256) void count_kernel(SelectArgs a) {
     const KParams& p = a.p;
     const int g = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
@@ -670,8 +664,9 @@ __global__ __launch_bounds__(256) void count_kernel(SelectArgs a) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int w_lo = p.n_init / 32, w_hi = Wg > p.n_init ? (Wg + 31) / 32 : w_lo;
     int total = 0;
-    for (int seg = wave; seg * 64 < w_hi; seg += 4) {
-        const int w = seg * 64 + lane;
+    const int w0 = seg_word0(p.n_init);
+    for (int seg = wave; w0 + seg * 64 < w_hi; seg += 4) {
+        const int w = w0 + seg * 64 + lane;
         int c = (w >= w_lo && w < w_hi) ? __popc(bits[w]) : 0;
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off, 64);
@@ -780,7 +775,8 @@ __global__ __launch_bounds__(256) void fill_kernel(SelectArgs a) {
     const int lane = threadIdx.x & 63;
     const int seg = __builtin_amdgcn_readfirstlane(4 * blockIdx.y + (threadIdx.x >> 6));
     const int w_lo = p.n_init / 32, w_hi = (Wg + 31) / 32;
-    if (seg * 64 >= w_hi) return;
+    const int w0 = seg_word0(p.n_init) + seg * 64;       // the segment's first word
+    if (w0 >= w_hi) return;
     const long long t = grp_index(p, sq, b, h, g);
     // every load is issued before the first decision, so the wave pays one memory round trip
     const int* segc = a.segcount + t * a.nseg;
@@ -789,7 +785,7 @@ __global__ __launch_bounds__(256) void fill_kernel(SelectArgs a) {
     const long long base = a.offsets[t];
     int pre = 0;                                         // selected columns in earlier segments
     for (int s = lane; s < seg; s += 64) pre += segc[s];
-    const int w = seg * 64 + lane;                       // this lane's word
+    const int w = w0 + lane;                             // this lane's word
     const unsigned wd = (w >= w_lo && w < w_hi) ? a.bits[t * a.nwords + w] : 0u;
     if (own == 0) return;                                // the group's last entry is never in such a segment
 #pragma unroll
@@ -807,7 +803,7 @@ __global__ __launch_bounds__(256) void fill_kernel(SelectArgs a) {
         const unsigned mine = half ? second : first;
         const bool on = (mine >> bit) & 1u;
         const long long dst = pos + __popc(mine & ((1u << bit) - 1u)) + (half ? __popc(first) : 0);
-        if (on && dst < a.idx_capacity) a.idx[dst] = (seg * 64 + 2 * i + half) * 32 + bit;
+        if (on && dst < a.idx_capacity) a.idx[dst] = (w0 + 2 * i + half) * 32 + bit;
         pos += __popc(first) + __popc(second);
     }
     // the wave that wrote the group's last entry pads the list to the next multiple of 64 with it
@@ -815,7 +811,7 @@ __global__ __launch_bounds__(256) void fill_kernel(SelectArgs a) {
         const unsigned long long nz = __ballot(wd != 0u);
         const int top = 63 - __builtin_clzll(nz);        // own > 0: some word is non-zero
         const unsigned lastw = __shfl(wd, top, 64);
-        const int last_key = (seg * 64 + top) * 32 + 31 - __clz(lastw);
+        const int last_key = (w0 + top) * 32 + 31 - __clz(lastw);
         const int padded = (cnt + kIdxPad - 1) / kIdxPad * kIdxPad;
         for (int e = cnt + lane; e < padded; e += 64)
             if (base + e < a.idx_capacity) a.idx[base + e] = last_key;
