@@ -328,10 +328,17 @@ int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k,
 
     const dim3 gblk(kp.nblk_max, kp.Hq, kp.B), ggrp(kp.ngrp_max, kp.Hq, kp.B);
     if (p->granularity == AA_BLOCK) AA_HIP(raise_lds_limits());   // before anything is enqueued
-    const bool counted = p->dtype == AA_BF16 && p->granularity == AA_STRIPE;   // the mask kernel counts
-    if (kp.packed && !counted)
-        AA_LAUNCH(zero_i32_kernel, dim3((unsigned)cdiv(pl.sz.groups, 256)), dim3(256), 0, st, counts,
-                  (long long)pl.sz.groups);
+    // A group's count is the sum of its segments'.  The scan takes it from there while that is little work for its one
+    // work-group (64k segments: 16k tokens at step 1 32k; adding to the counts from every mask work-group cost 9 us
+    // there); beyond, the mask kernels add to the counts as well.
+    const long long segs = (long long)pl.sz.groups * sa.nseg;
+    sa.sum_segs = segs <= 65536;
+    if (p->granularity == AA_BLOCK) {
+        AA_LAUNCH(zero_i32_kernel, dim3((unsigned)cdiv(segs, 256)), dim3(256), 0, st, sa.segcount, segs);
+        if (!sa.sum_segs)
+            AA_LAUNCH(zero_i32_kernel, dim3((unsigned)cdiv(pl.sz.groups, 256)), dim3(256), 0, st, counts,
+                      (long long)pl.sz.groups);
+    }
     const bool q_pooled = fused_M && p->dtype == AA_BF16;
     if (p->dtype != AA_BF16) { sa.m_rows = fused_M; sa.xa_out = xa_out; }
     sa.pool_skip_q = q_pooled;
@@ -347,13 +354,14 @@ int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k,
         if (!q_pooled || !pooled_keys(p))
             AA_LAUNCH(pool_q_bf16_kernel, dim3(kp.nblk_max, (q_pooled ? 0 : kp.Hq) + kp.Hkv, kp.B), dim3(256), 0, st, sa);
         // One work-group per (query head, row tile, key span with candidates); the longest sequence bounds
-        // every other.  Three work-groups fit a CU: the span is halved until there are that many (a span's fixed
-        // cost, loading the pooled rows, is about three of its 64-key tiles).  8k tokens: 96 work-groups of 2048
-        // keys took 32 us, 736 of 256 keys take 16; 16k tokens at step 1: 48 -> 32 us.
+        // every other.  The span is halved until there are more than 1.5 work-groups per CU (three fit, but a span's
+        // fixed cost, loading the pooled rows, is about three of its 64-key tiles).  All of stage 2 at 8k tokens: 54 us
+        // with 96 work-groups of 2048 keys, 36 with 736 of 256 keys, 37 with 384 of 512; at 16k: 66 us with 224 of 2048,
+        // 56 with 448 of 1024, 62 with 896 of 512.
         sa.mask_span = kSegKeys;
         for (;;) {
             sa.mask_items = mask_pair_items(kp.nblk_max, kp.step, kp.bq, kp.w, kp.n_init, sa.mask_span);
-            if ((long long)sa.mask_items * kp.Hq * (kp.packed ? 1 : kp.B) >= 768 || sa.mask_span == kMaskSpanMin) break;
+            if ((long long)sa.mask_items * kp.Hq * (kp.packed ? 1 : kp.B) > 384 || sa.mask_span == kMaskSpanMin) break;
             sa.mask_span /= 2;
         }
         const long long mask_per_xcd = cdiv((long long)sa.mask_items * kp.Hq * kp.B, 8);
@@ -365,10 +373,12 @@ int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k,
         const int rc = engine_status(launch_mask_fp32(sa, st), "mask_fp32_kernel");
         if (rc != AA_OK) return rc;
     }
-    if (!counted) AA_LAUNCH(count_kernel, ggrp, dim3(256), 0, st, sa);
-    AA_LAUNCH(scan_kernel, dim3(1), dim3(1024), 0, st, sa);
-    AA_LAUNCH(fill_kernel, dim3(kp.ngrp_max, (unsigned)cdiv(sa.nseg, 4), kp.Hq * kp.B), dim3(256), 0, st, sa);
-    return AA_OK;
+    if (p->granularity == AA_BLOCK) AA_LAUNCH(count_kernel, ggrp, dim3(256), 0, st, sa);
+    // few groups: the fill kernel does the scan's work (a launch less, 5 us); every one of its work-groups then
+    // reads up to all segments, 8 per thread at this limit
+    const bool fill_scans = segs <= 2048;
+    if (!fill_scans) AA_LAUNCH(scan_kernel, dim3(1), dim3(1024), 0, st, sa);
+    return engine_status(launch_fill(sa, fill_scans, st), "fill_kernel");
 }
 
 int run_sparse(const Plan& pl, const aa_params* p, const void* q, const void* k, const void* v, const float* M,

@@ -55,6 +55,7 @@ struct SelectArgs {
     int nwords;               // ceil(N / 32)
     int* segcount;            // [groups][nseg] selected columns per segment of 64 bit words (kSegKeys keys)
     int nseg;                 // ceil(nwords / 64)
+    int sum_segs;             // the groups' counts are still to be added up from segcount (by the scan)
     int* counts;
     long long* offsets;
     int* idx;
@@ -78,6 +79,7 @@ constexpr size_t kMaskBlockLdsMax = 128 * 1024;   // dynamic LDS limit set for m
 __global__ void zero_i32_kernel(int* x, long long nelem);
 __global__ void count_kernel(SelectArgs a);
 __global__ void scan_kernel(SelectArgs a);
-__global__ void fill_kernel(SelectArgs a);
+// scan: also does scan_kernel's work, which is then not launched
+int launch_fill(const SelectArgs& a, bool scan, hipStream_t st);
 
 }  // namespace aa

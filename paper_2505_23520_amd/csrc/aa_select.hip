@@ -29,6 +29,15 @@ __device__ __forceinline__ unsigned short f_to_bf16_rne(float f) {
 }
 }  // namespace
 
+namespace {
+// c more selected columns in segment seg of group t.  The group's total is added up here only if the scan does not
+// do it from the segments.
+__device__ __forceinline__ void add_counts(const SelectArgs& a, long long t, int seg, int c) {
+    atomicAdd(&a.segcount[t * a.nseg + seg], c);
+    if (!a.sum_segs) atomicAdd(&a.counts[t], c);
+}
+}  // namespace
+
 // ------------------------------------------------------------------ pool_q
 // grid (nblk_max, Hq [+ Hkv], B).  bf16: 256 threads = the four waves of the tile engines; writes
 // hi/lo bf16 rows of 128 and the norm of the lo row (aa_pool.h).  With kmax_blk set (stripe granularity)
@@ -78,14 +87,21 @@ __global__ __launch_bounds__(256) void pool_q_bf16_kernel(SelectArgs a) {
 
 // fp32: 256 threads per query block.  With qp_f32 set, the block mean of the queries (16 bytes of a row per
 // thread, 1024 / d rows side by side, then added up in LDS); with m_rows set, the pooled anchor (mean of
-// M over the block's rows): the fp32 engine's work-groups own 32 rows each, not a block.
+// M over the block's rows): the fp32 engine's work-groups own 32 rows each, not a block; with segcount set, the
+// counters of stage 2 are cleared.
 __global__ __launch_bounds__(256) void pool_fp32_kernel(SelectArgs a) {
     const KParams& p = a.p;
     const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const int tid = threadIdx.x;
+    if (a.segcount) {
+        const long long wg = blockIdx.x + (long long)gridDim.x * (blockIdx.y + (long long)gridDim.y * blockIdx.z);
+        clear_counters(a.counts, a.groups_total, a.segcount, a.nseg, wg * 256 + tid,
+                       (long long)gridDim.x * gridDim.y * gridDim.z * 256);
+    }
     const Seq sq = seq_of(p, b);
     const int r0 = i * p.bq;
     if (r0 >= sq.len) return;
-    const int r1 = min(r0 + p.bq, sq.len), tid = threadIdx.x;
+    const int r1 = min(r0 + p.bq, sq.len);
     const long long bi = blk_index(p, sq, b, h, i);
     if (a.m_rows && tid < 64) {
         const float* m = a.m_rows + row_index(p, sq, b, h, r0);
@@ -406,12 +422,9 @@ __global__ __launch_bounds__(256, 3) void mask_bf16_kernel(SelectArgs a) {
     combine_all();
     __syncthreads();                                 // rowword is reused by the next chunk
     }
-    // A work-group's keys lie in one segment; the groups of a row tile have several work-groups
-    if (tid < ngt && gcount[tid]) {
-        const long long t = grp_index(p, sq, b, h, g_first + tid);
-        atomicAdd(&a.counts[t], gcount[tid]);
-        atomicAdd(&a.segcount[t * a.nseg + chunk * a.mask_span / kSegKeys], gcount[tid]);
-    }
+    // a work-group's keys lie in one segment
+    if (tid < ngt && gcount[tid])
+        add_counts(a, grp_index(p, sq, b, h, g_first + tid), chunk * a.mask_span / kSegKeys, gcount[tid]);
 }
 
 // ------------------------------------------------------------------ mask, fp32 MFMA
@@ -488,7 +501,9 @@ __global__ __launch_bounds__(256) void mask_fp32_kernel(SelectArgs a) {
             const int lo = max(p.n_init - j0, 0), hi = min(Wg - j0, 32);   // keep n_init <= j0 + bit < Wg
             unsigned keep = 0;
             if (hi > lo) keep = (hi - lo >= 32) ? 0xffffffffu : (((1u << (hi - lo)) - 1u) << lo);
-            if (j0 / 32 < a.nwords) a.bits[(gi0 + g) * a.nwords + j0 / 32] = mine & keep;
+            mine &= keep;
+            if (j0 / 32 < a.nwords) a.bits[(gi0 + g) * a.nwords + j0 / 32] = mine;
+            if (mine) add_counts(a, gi0 + g, (j0 / 32 - seg_word0(p.n_init)) / (kSegKeys / 32), __popc(mine));
         }
     }
 }
@@ -648,9 +663,8 @@ __global__ void zero_i32_kernel(int* x, long long nelem) {
     if (i < nelem) x[i] = 0;
 }
 
-// grid (ngrp_max, Hq, B), 256 threads: selected columns of the group, in total and per segment of
-// 64 bit words = kSegKeys keys from seg_word0 on (the segment counts let fill_kernel expand the segments
-// independently).  fp32 and block granularity; the bf16 mask kernel counts what it writes itself.
+// grid (ngrp_max, Hq, B), 256 threads: selected columns of the group per segment of 64 bit words = kSegKeys
+// keys from seg_word0 on (block granularity; the stripe mask kernels count what they write themselves)
 __global__ __launch_bounds__(256) void count_kernel(SelectArgs a) {
     const KParams& p = a.p;
     const int g = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
@@ -660,28 +674,18 @@ __global__ __launch_bounds__(256) void count_kernel(SelectArgs a) {
     const int Wg = window_start(p, g);
     const long long t = grp_index(p, sq, b, h, g);
     const unsigned* bits = a.bits + t * a.nwords;
-    int* segc = a.segcount + t * a.nseg;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int w_lo = p.n_init / 32, w_hi = Wg > p.n_init ? (Wg + 31) / 32 : w_lo;
-    int total = 0;
     const int w0 = seg_word0(p.n_init);
     for (int seg = wave; w0 + seg * 64 < w_hi; seg += 4) {
         const int w = w0 + seg * 64 + lane;
         int c = (w >= w_lo && w < w_hi) ? __popc(bits[w]) : 0;
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off, 64);
-        if (lane == 0) segc[seg] = c;
-        total += c;
+        if (lane == 0 && c) add_counts(a, t, seg, c);
     }
-    __shared__ int wsum[4];
-    if (lane == 0) wsum[wave] = total;
-    __syncthreads();
-    if (threadIdx.x == 0) a.counts[t] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
 }
 
-// one work-group of 1024 threads: offsets[t] = sum_{t' < t} roundup64(counts[t']).  With a.stats set
-// it also adds up what the prefill reports: attended (row, key) pairs = every row's anchor region
-// (closed form per group) plus its group's list, and the selected entries.
 namespace {
 __device__ __forceinline__ long long tri(long long m) { return m > 0 ? m * (m + 1) / 2 : 0; }
 // pairs of the anchor regions of the rows r0 .. r1-1 of a group with window start W:
@@ -695,77 +699,109 @@ __device__ __forceinline__ long long anchor_pairs(long long n_init, long long W,
 }
 }  // namespace
 
-__global__ __launch_bounds__(1024) void scan_kernel(SelectArgs a) {
+namespace {
+__device__ __forceinline__ long long pad_list(int c) { return (c + kIdxPad - 1) / kIdxPad * (long long)kIdxPad; }
+
+// selected columns of group t
+__device__ __forceinline__ int group_count(const SelectArgs& a, long long t) {
+    if (!a.sum_segs) return a.counts[t];
+    const int* sc = a.segcount + t * a.nseg;
+    int c = 0;
+    if (a.nseg % 4 == 0) {                               // rows of whole 16-byte pieces (the array is aligned)
+        for (int s = 0; s < a.nseg; s += 4) {
+            const int4 x = *(const int4*)(sc + s);
+            c += (x.x + x.y) + (x.z + x.w);
+        }
+    } else {
+        for (int s = 0; s < a.nseg; ++s) c += sc[s];
+    }
+    return c;
+}
+
+// One work-group of NT threads: offsets[t] = sum_{t' < t} roundup64(counts[t']), the counts themselves where they
+// are still in segments, the overflow flag, and, with a.stats set, what the prefill reports:
+// attended (row, key) pairs = every row's anchor region (closed form per group) plus its group's list, and
+// the selected entries.
+template <int NT>
+__device__ __forceinline__ void scan_groups(const SelectArgs& a) {
+    constexpr int NWV = NT / 64;
+    __shared__ long long part[3][NWV];
     const KParams& p = a.p;
     const long long T = a.groups_total;
-    const int tid = threadIdx.x;
-    const long long per = (T + 1023) / 1024;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const long long per = (T + NT - 1) / NT;
     const long long lo = min(T, per * tid), hi = min(T, lo + per);
     long long s = 0, pairs = 0, entries = 0;
     for (long long t = lo; t < hi; ++t) {
-        const int cnt = a.counts[t];
-        s += (cnt + kIdxPad - 1) / kIdxPad * (long long)kIdxPad;
+        const int cnt = group_count(a, t);
+        if (a.sum_segs) a.counts[t] = cnt;
+        s += pad_list(cnt);
         if (a.stats) {
             // group t -> (sequence, group in the sequence); slots past a packed batch's groups hold 0
-            const long long slot = t % p.grp_cap;
-            const long long span = (long long)p.bq * p.step;
-            long long len = p.N, g = slot;
+            const int span = p.bq * p.step;
+            int len = p.N, g = (int)((unsigned)t % (unsigned)p.grp_cap);
             if (p.packed) {
                 len = 0;
                 for (int b = 0; b < p.B; ++b) {
-                    const long long n = p.cu[b + 1] - p.cu[b], ng = (n + span - 1) / span;
+                    const int n = p.cu[b + 1] - p.cu[b], ng = (n + span - 1) / span;
                     if (g < ng) { len = n; break; }
                     g -= ng;
                 }
             }
-            if (g * span < len) {
-                const long long r0 = g * span, r1 = min(r0 + span, len);
-                pairs += anchor_pairs(p.n_init, window_start(p, (int)g), r0, r1) + (r1 - r0) * cnt;
+            if ((long long)g * span < len) {
+                const long long r0 = (long long)g * span, r1 = min(r0 + span, (long long)len);
+                pairs += anchor_pairs(p.n_init, window_start(p, g), r0, r1) + (r1 - r0) * cnt;
                 entries += cnt;
             }
         }
     }
-    __shared__ long long part[1024];
-    part[tid] = s;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        long long x = tid >= off ? part[tid - off] : 0;
-        __syncthreads();
-        part[tid] += x;
-        __syncthreads();
+    long long x = s;                                     // inclusive scan over the wave
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const long long y = __shfl_up(x, off, 64);
+        if (lane >= off) x += y;
     }
-    long long run = part[tid] - s;
+    if (lane == 63) part[0][wave] = x;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        pairs += __shfl_xor(pairs, off, 64);
+        entries += __shfl_xor(entries, off, 64);
+    }
+    if (lane == 0) { part[1][wave] = pairs; part[2][wave] = entries; }
+    __syncthreads();
+    long long run = x - s;
+    for (int w = 0; w < wave; ++w) run += part[0][w];
     for (long long t = lo; t < hi; ++t) {
         a.offsets[t] = run;
-        run += (a.counts[t] + kIdxPad - 1) / kIdxPad * (long long)kIdxPad;
+        run += pad_list(a.counts[t]);                    // (written by this thread above, where it was)
     }
-    if (tid == 1023) {
-        a.offsets[T] = part[1023];
-        if (a.overflow) *a.overflow = part[1023] > a.idx_capacity ? 1 : 0;
+    if (tid == NT - 1) {
+        a.offsets[T] = run;
+        if (a.overflow) *a.overflow = run > a.idx_capacity ? 1 : 0;
     }
-    if (a.stats) {                                           // block sums of pairs and entries
-        __syncthreads();
-        for (int pass = 0; pass < 2; ++pass) {
-            long long x = pass ? entries : pairs;
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-            if ((tid & 63) == 0) part[pass * 16 + (tid >> 6)] = x;
-        }
-        __syncthreads();
-        if (tid < 4) {
-            long long x = 0;
-            if (tid < 2)
-                for (int w = 0; w < 16; ++w) x += part[tid * 16 + w];
-            a.stats[tid] = x;
-        }
+    if (a.stats && tid < 4) {
+        long long sum = 0;
+        if (tid < 2)
+            for (int w = 0; w < NWV; ++w) sum += part[1 + tid][w];
+        a.stats[tid] = sum;
     }
 }
+}  // namespace
 
-// grid (ngrp_max, ceil(nseg / 4), B*Hq), 256 threads: each wave expands one segment (64 bit words =
-// 2048 keys) of the group's bit words into its part of the ascending list; the segment counts give
-// its position.  No barriers: a wave without work returns.
+__global__ __launch_bounds__(1024) void scan_kernel(SelectArgs a) { scan_groups<1024>(a); }
+
+// grid (ngrp_max, ceil(nseg / 4), B*Hq [+ 1]), 256 threads: each wave expands one segment (64 bit words =
+// kSegKeys keys) of the group's bit words into its part of the ascending list; the segment counts give its
+// position.  SCAN: no scan_kernel ran; every work-group adds up the lists before its group's itself, and the first
+// work-group of one more grid layer does scan_kernel's work beside the others.  For few groups that is a fraction
+// of what the launch costs (5 us); it grows with groups x groups, so the host draws the line.
+template <bool SCAN>
 __global__ __launch_bounds__(256) void fill_kernel(SelectArgs a) {
     const KParams& p = a.p;
+    if (SCAN && blockIdx.z == (unsigned)(p.Hq * p.B)) {
+        if (blockIdx.x == 0 && blockIdx.y == 0) scan_groups<256>(a);
+        return;
+    }
     const int g = blockIdx.x, h = blockIdx.z % p.Hq, b = blockIdx.z / p.Hq;
     const Seq sq = seq_of(p, b);
     const int ngrp = (sq.len + p.bq * p.step - 1) / (p.bq * p.step);
@@ -776,20 +812,36 @@ __global__ __launch_bounds__(256) void fill_kernel(SelectArgs a) {
     const int seg = __builtin_amdgcn_readfirstlane(4 * blockIdx.y + (threadIdx.x >> 6));
     const int w_lo = p.n_init / 32, w_hi = (Wg + 31) / 32;
     const int w0 = seg_word0(p.n_init) + seg * 64;       // the segment's first word
-    if (w0 >= w_hi) return;
     const long long t = grp_index(p, sq, b, h, g);
-    // every load is issued before the first decision, so the wave pays one memory round trip
     const int* segc = a.segcount + t * a.nseg;
-    const int cnt = a.counts[t];
+    long long base = 0;
+    if (SCAN) {
+        __shared__ long long part[4];
+        for (long long u = threadIdx.x; u < t; u += 256) base += pad_list(group_count(a, u));
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) base += __shfl_xor(base, off, 64);
+        if (lane == 0) part[threadIdx.x >> 6] = base;
+        __syncthreads();
+        base = (part[0] + part[1]) + (part[2] + part[3]);
+    }
+    if (w0 >= w_hi) return;
+    // every load is issued before the first decision, so the wave pays one memory round trip
     const int own = segc[seg];
-    const long long base = a.offsets[t];
-    int pre = 0;                                         // selected columns in earlier segments
-    for (int s = lane; s < seg; s += 64) pre += segc[s];
+    int cnt = 0, pre = 0;                                // selected columns of the group, and in earlier segments
+    if (!SCAN) base = a.offsets[t];
+    for (int s = lane; s < a.nseg; s += 64) {
+        const int c = segc[s];
+        cnt += c;
+        pre += s < seg ? c : 0;
+    }
     const int w = w0 + lane;                             // this lane's word
     const unsigned wd = (w >= w_lo && w < w_hi) ? a.bits[t * a.nwords + w] : 0u;
     if (own == 0) return;                                // the group's last entry is never in such a segment
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) pre += __shfl_xor(pre, off, 64);
+    for (int off = 32; off >= 1; off >>= 1) {
+        pre += __shfl_xor(pre, off, 64);
+        cnt += __shfl_xor(cnt, off, 64);
+    }
     // two words per step: lanes 0..31 test word 2 i, lanes 32..63 word 2 i + 1 (coalesced stores)
     long long pos = base + pre;
     const int bit = lane & 31, half = lane >> 5;
@@ -808,14 +860,19 @@ __global__ __launch_bounds__(256) void fill_kernel(SelectArgs a) {
     }
     // the wave that wrote the group's last entry pads the list to the next multiple of 64 with it
     if (pre + own == cnt) {
-        const unsigned long long nz = __ballot(wd != 0u);
-        const int top = 63 - __builtin_clzll(nz);        // own > 0: some word is non-zero
+        const int top = 63 - __builtin_clzll(nzw);       // own > 0: some word is non-zero
         const unsigned lastw = __shfl(wd, top, 64);
         const int last_key = (w0 + top) * 32 + 31 - __clz(lastw);
         const int padded = (cnt + kIdxPad - 1) / kIdxPad * kIdxPad;
         for (int e = cnt + lane; e < padded; e += 64)
             if (base + e < a.idx_capacity) a.idx[base + e] = last_key;
     }
+}
+
+int launch_fill(const SelectArgs& a, bool scan, hipStream_t st) {
+    const dim3 grid((unsigned)a.p.ngrp_max, (unsigned)((a.nseg + 3) / 4), (unsigned)(a.p.Hq * a.p.B + (scan ? 1 : 0)));
+    return scan ? (int)launch_kernel(fill_kernel<true>, grid, dim3(256), 0, st, a)
+                : (int)launch_kernel(fill_kernel<false>, grid, dim3(256), 0, st, a);
 }
 
 }  // namespace aa

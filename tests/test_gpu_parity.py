@@ -154,6 +154,26 @@ def test_prefill_without_candidates(api, dtype, d, block, lens, n_init, window):
     assert torch.equal(out, run.out)
 
 
+@pytest.mark.parametrize("dtype,d,block,N,Hq,step,granularity", [
+    ("bf16", 128, 128, 35000, 16, 1, 0),     # groups x segments > 65536: the mask kernel adds up the counts itself
+    ("bf16", 128, 128, 35000, 16, 1, 1),     # the same for block granularity (count kernel)
+    ("fp32", 32, 16, 9000, 24, 1, 0),        # and for fp32
+    ("bf16", 128, 128, 9000, 4, 1, 0),       # 65536 >= groups x segments > 2048: the scan adds up the segments
+    ("bf16", 128, 128, 9000, 4, 16, 1),      # <= 2048: the fill kernel scans
+])
+def test_list_building_paths(api, dtype, d, block, N, Hq, step, granularity, engine_mode):
+    if engine_mode:
+        pytest.skip("the engine has no part in it")
+    wl = _wl("t", dtype, [N], Hq, 1, d, block, 90 + step, N // 100)
+    cfg = api.Config(block=block, n_init=block, window=block, step=step, theta=5.3 if granularity else 4.0,
+                     granularity=granularity)
+    last = (N - 1) // (block * step)
+    run, worst = _run_and_check(api, wl, cfg, samples=[(0, 0, 2), (0, Hq - 1, last), (0, Hq // 2, last // 2)])
+    offsets = run.buf["offsets"].cpu().numpy()
+    counts = run.buf["counts"].cpu().numpy().astype(np.int64)
+    assert (np.diff(offsets) == (counts + 63) // 64 * 64).all() and offsets[0] == 0 and counts.max() > 64
+
+
 @pytest.mark.parametrize("theta", [float("inf"), float("-inf")])
 def test_bf16_theta_extremes(api, theta):
     from parity_util import DeviceRun
