@@ -206,7 +206,10 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
         v_load(t, kcur);
         idx_prefetch(t + 2, kcur);
         __builtin_amdgcn_sched_barrier(0);           // the wait below counts on this issue order
-        k_load(min(t + 1, nT - 1), Knext, knext);    // past the end: the last tile again, into a stage nobody reads
+        // the next K tile (past the end the last one again, into a stage nobody reads): gathered rows go out now,
+        // contiguous ones, which L2 serves, after the softmax, out of the way of the V tile (-1 %; gathered rows
+        // issued there cost 29 %)
+        if (FLAGS & kEngList) k_load(min(t + 1, nT - 1), Knext, knext);
         const char* Kb = Kcur + koff;
         const char* Vb = Vs0 + voff;
 
@@ -274,6 +277,11 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
             softmax_tile(s, pf, c2, rescale_gap, mref, mtrue, l, o);
             __builtin_amdgcn_s_setprio(2);
         }
+        if (!(FLAGS & kEngList)) {
+            __builtin_amdgcn_sched_barrier(0);
+            k_load(min(t + 1, nT - 1), Knext, knext);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         // V tile t has landed (vmcnt(4): the four loads of the next K tile are younger)
         __builtin_amdgcn_s_waitcnt(0x0F74);
         bare_barrier();
@@ -317,13 +325,7 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     float lt = row_sum(l);                           // row sum relative to mref
     if (flags & kEngStoreState) {
         const float ms = rebase_state(a, c2, mref, mtrue, lt, o);
-        if (!direct) {
-            store_state(a, ri, tile, rok, wave_rows > 0, lane, hf, ms, lt, o);
-        } else if (wave_rows > 0) {
-            // what stage 3 makes of a cached state and an empty list, bit for bit
-            store_out(a, stg, tok_offset(p, p.os, sq, wk.b, wk.h, rw), wave_rows, lane, n, hf, lt, o);
-            if (rok && a.lse && hf == 0) a.lse[ri] = ms / p.sigma * p.sigma + __logf(lt);
-        }
+        // (the state goes out last: the barriers in between would wait for its stores to drain)
         if (a.qp_hi) {
             // pooled query of the block (Algorithm 2, avgpool of Q) from the fragments in registers
             float s0, s1;
@@ -347,6 +349,13 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
                 const int nrows = rlast - row0 + 1;
                 a.xa[blk_index(p, sq, wk.b, wk.h, wk.i)] = (red[0] + red[1] + red[2] + red[3]) / (float)nrows;
             }
+        }
+        if (!direct) {
+            store_state(a, ri, tile, rok, wave_rows > 0, lane, hf, ms, lt, o);
+        } else if (wave_rows > 0) {
+            // what stage 3 makes of a cached state and an empty list, bit for bit
+            store_out(a, stg, tok_offset(p, p.os, sq, wk.b, wk.h, rw), wave_rows, lane, n, hf, lt, o);
+            if (rok && a.lse && hf == 0) a.lse[ri] = ms / p.sigma * p.sigma + __logf(lt);
         }
     }
     if ((flags & kEngStoreOut) && wave_rows > 0) {
