@@ -154,6 +154,31 @@ def test_prefill_without_candidates(api, dtype, d, block, lens, n_init, window):
     assert torch.equal(out, run.out)
 
 
+@pytest.mark.parametrize("lens,n_init,window,step", [
+    ([767], 128, 128, 16),               # just below the tile count from which a work-group has two teams
+    ([768], 128, 128, 16),               # at it; an even number of tiles
+    ([835], 100, 128, 16),               # an odd number of tiles: the second team's last step is empty
+    ([1300, 100, 900], 64, 192, 5),      # packed, blocks of one tile up to the longest; with candidates
+    ([4096], 128, 128, 16),              # 32 blocks x 16 heads = the largest grid with two teams
+    ([4097], 128, 128, 16),              # one more
+])
+def test_bf16_two_teams(api, lens, n_init, window, step):
+    Hq = 16 if lens[0] > 4000 else 4
+    wl = _wl("t", "bf16", lens, Hq, Hq // 2, 128, 128, 100 + len(lens), max(8, max(lens) // 64))
+    cfg = api.Config(block=128, n_init=n_init, window=window, step=step, theta=4.0)
+    span = 128 * step
+    samples = [(b, h, g) for b, n in enumerate(lens) for h in (0, Hq - 1) for g in {0, (n - 1) // span}]
+    run, worst = _run_and_check(api, wl, cfg, samples=samples)
+    # the dense kernel splits in the same places: with every column selected both are the same attention
+    inf = api.Config(block=128, n_init=n_init, window=window, step=step, theta=math.inf)
+    from parity_util import DeviceRun
+    full = DeviceRun(api, run.seqs, inf, "bf16").stages()
+    dense, dlse = full.dense()
+    assert (dense.float() - full.out.float()).abs().max().item() <= 2e-2     # as in test_bf16_theta_extremes
+    rows = slice(0, min(lens))                   # (rows of head 0, sequence 0)
+    assert (dlse[rows] - full.buf["lse"][rows]).abs().max().item() <= 4e-3
+
+
 @pytest.mark.parametrize("dtype,d,block,N,Hq,step,granularity", [
     ("bf16", 128, 128, 35000, 16, 1, 0),     # groups x segments > 65536: the mask kernel adds up the counts itself
     ("bf16", 128, 128, 35000, 16, 1, 1),     # the same for block granularity (count kernel)
