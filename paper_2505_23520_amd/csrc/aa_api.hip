@@ -225,10 +225,12 @@ int launch_engine(const Plan& pl, const aa_params* prm, EngineArgs& ea, hipStrea
     ea.groups_total = pl.sz.groups;
     ea.sel = 0;
     if (prm->dtype == AA_BF16) {
-        // Two bf16 engines: 128 query rows per work-group (two work-groups per CU) and 256 rows
+        // Two bf16 engines: 128 query rows per work-group (three work-groups per CU) and 256 rows
         // per work-group with the MFMA / softmax phases of the two waves of a SIMD alternating.
         // The second is faster on long tile loops and slower on short ones (its prologue and
         // epilogue overlap with nothing); it needs both blocks of a pair to share window and list.
+        // Dense, 32 heads, 128 / 256 rows: 4096 tokens 130 / 133 us, 6000 273 / 280, 8192 481 / 474,
+        // 32768 7214 / 6956.
         const bool pair_ok = (ea.flags & kEngDense) || k.step % 2 == 0;
         int choice = prm->engine;                   // 0 auto, 1: 128 rows, 2: 256 rows
         if (!pair_ok) choice = AA_ENGINE_128;

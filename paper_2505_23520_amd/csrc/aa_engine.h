@@ -1,4 +1,4 @@
-// Arguments of the online-softmax tile engines (bf16 MFMA and fp32 vector-FMA).
+// Arguments of the online-softmax tile engines (bf16 and fp32 MFMA).
 #pragma once
 #include "aa_common.h"
 
