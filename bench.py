@@ -171,7 +171,7 @@ def stage_rooflines(wl, res, sustained):
     return dict(
         anchor=entry("engine_bf16_kernel<anchor region, store state>", f1, b1, t1,
                      "FLOP = 4 d x anchor-region pairs; bytes = Q + K + V + Acc + M + L + pooled anchor"),
-        select=entry("pool_q + mask_bf16 + count + scan + fill", f2, b2, t2,
+        select=entry("pool_q + mask_bf16 + scan + fill", f2, b2, t2,
                      "FLOP = 2 d x (pooled row, candidate key) pairs (the kernel issues up to twice that: "
                      "bf16 hi and lo parts of the pooled query); bytes = Q + K + pooled queries + bit words "
                      "(written, read) + index lists"),

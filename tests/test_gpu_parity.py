@@ -186,9 +186,7 @@ def test_bf16_two_teams(api, lens, n_init, window, step):
     ("bf16", 128, 128, 9000, 4, 1, 0),       # 65536 >= groups x segments > 2048: the scan adds up the segments
     ("bf16", 128, 128, 9000, 4, 16, 1),      # <= 2048: the fill kernel scans
 ])
-def test_list_building_paths(api, dtype, d, block, N, Hq, step, granularity, engine_mode):
-    if engine_mode:
-        pytest.skip("the engine has no part in it")
+def test_list_building_paths(api, dtype, d, block, N, Hq, step, granularity):
     wl = _wl("t", dtype, [N], Hq, 1, d, block, 90 + step, N // 100)
     cfg = api.Config(block=block, n_init=block, window=block, step=step, theta=5.3 if granularity else 4.0,
                      granularity=granularity)
