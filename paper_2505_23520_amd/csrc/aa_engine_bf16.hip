@@ -8,8 +8,7 @@
 //
 // Shape of the computation (d = 128, b_q = 128, bf16 in, fp32 accumulate):
 //   work-group = one query block = 4 waves x 32 query rows, three work-groups per CU
-//   (three waves per SIMD, so one wave's softmax and LDS latency overlap the others' MFMAs), or, on small
-//   grids, two teams of 4 waves that share the rows and take every other tile;
+//   (three waves per SIMD, so one wave's softmax and LDS latency overlap the others' MFMAs);
 //   K/V tile   = 64 keys, two K stages and one V stage in LDS, filled by 16-byte direct-to-LDS
 //   buffer loads (no staging registers; a gathered row and a contiguous row cost the same);
 //   S^T = K Q^T  with v_mfma_f32_32x32x16_bf16 (keys are the M dimension, query
@@ -50,24 +49,20 @@ using namespace eng;
 // FLAGS (a combination of kEng*) is a compile-time parameter: every mode gets its own code without
 // the other modes' branches, registers and, above all, merged control-flow paths (where paths with
 // different numbers of outstanding loads meet, the compiler's waits assume the shortest).
-// TEAMS = 2: a second team of four waves shares the block's rows and takes every other tile, with LDS stages of its own;
-// the two states are merged at the end.
-template <int FLAGS, int TEAMS>
-__global__ __launch_bounds__(256 * TEAMS, TEAMS == 1 ? 3 : 2) void engine_bf16_kernel(EngineArgs a) {
+template <int FLAGS>
+__global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     constexpr int flags = FLAGS;
-    constexpr int NW = 4;                            // waves per team
+    constexpr int NW = 4;                            // waves per work-group
     static_assert(NW == 4, "the loader deals four groups of a tile to every wave");
     // one LDS object per stage, so that the compiler can tell that the asynchronous loads into
     // one stage do not alias the operand reads from the others
     __shared__ __attribute__((aligned(16))) char Ks0[KBYTES], Ks1[KBYTES], Vs0[VBYTES];
-    __shared__ __attribute__((aligned(16))) char Kt0[TEAMS == 2 ? KBYTES : 16], Kt1[TEAMS == 2 ? KBYTES : 16], Vt0[TEAMS == 2 ? VBYTES : 16];
     __shared__ float red[NW], knorm[NW];
     __shared__ float qpart[(FLAGS & kEngStoreState) ? 4 : 1][128];   // pooled-query partial sums (stage 1)
     const KParams& p = a.p;
-    const int tid = threadIdx.x & 255;               // thread of its team
+    const int tid = threadIdx.x & 255;               // (256 threads; with the range stated, stage 1 spills no register)
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keep it scalar
-    const int team = TEAMS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
     const int n = lane & 31, hf = lane >> 5;
 
     if (flags & kEngStoreState) {
@@ -160,7 +155,7 @@ __global__ __launch_bounds__(256 * TEAMS, TEAMS == 1 ? 3 : 2) void engine_bf16_k
     auto k_load = [&](int t, char* Kb, const intx4& kidx) {
         rows_load(t, krs, kstb, klane, klast, Kb + GPW * wave * KGRP, KGRP, kidx);
     };
-    auto v_load = [&](int t, char* Vb, const intx4& kidx) { rows_load(t, vrs, vstb, vlane, vlast, Vb + GPW * wave * VGRP, VGRP, kidx); };
+    auto v_load = [&](int t, const intx4& kidx) { rows_load(t, vrs, vstb, vlane, vlast, Vs0 + GPW * wave * VGRP, VGRP, kidx); };
     // Work-group barrier that leaves vector-memory operations in flight.  LDS operand reads before it
     // have been consumed by their MFMAs and the tile loads it publishes were awaited; the fences only
     // keep the compiler from moving work across it.
@@ -175,7 +170,6 @@ __global__ __launch_bounds__(256 * TEAMS, TEAMS == 1 ? 3 : 2) void engine_bf16_k
     // The first list indices are requested before everything else: the first tile's loads need them,
     // and only them, so they go out while the Q fragments and the cached state are still on their way
     // (waits are in issue order: behind those loads the indices would arrive last).
-    static_assert(TEAMS == 1 || !(FLAGS & kEngList), "teams: contiguous tiles only");
     if (nT > 0) idx_prefetch(0, kidx0);
 
     // ---- Q fragments (B operand of S^T = K Q^T): lane (n, hf) holds Q[row][16 ks + 8 hf .. +8)
@@ -185,7 +179,7 @@ __global__ __launch_bounds__(256 * TEAMS, TEAMS == 1 ? 3 : 2) void engine_bf16_k
     // ---- pipeline prologue: the first K tile goes out ahead of the cached state, which is not needed
     // before the first P V block
     if (nT > 0) {
-        if (TEAMS == 1 || team == 0) k_load(0, Ks0, kidx0); else k_load(min(1, nT - 1), Kt0, kidx0);
+        k_load(0, Ks0, kidx0);
         idx_prefetch(1, kidx1);
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -210,16 +204,16 @@ __global__ __launch_bounds__(256 * TEAMS, TEAMS == 1 ? 3 : 2) void engine_bf16_k
     const int ls = lane & 15, lg = lane >> 4;
     const int voff = (4 * hf + (ls >> 2)) * VGRP + 32 * (lg & 1) + 8 * (ls & 3);
 
-    auto tile_step = [&](int t, const char* Kcur, char* Knext, char* Vst, intx4& kcur, intx4& knext) __attribute__((always_inline)) {
-        v_load(TEAMS == 1 ? t : min(t, nT - 1), Vst, kcur);
+    auto tile_step = [&](int t, const char* Kcur, char* Knext, intx4& kcur, intx4& knext) __attribute__((always_inline)) {
+        v_load(t, kcur);
         idx_prefetch(t + 2, kcur);
         __builtin_amdgcn_sched_barrier(0);           // the wait below counts on this issue order
         // the next K tile (past the end the last one again, into a stage nobody reads): gathered rows go out now,
         // contiguous ones, which L2 serves, after the softmax, out of the way of the V tile (-1 %; gathered rows
         // issued there cost 29 %)
-        if (FLAGS & kEngList) k_load(min(t + TEAMS, nT - 1), Knext, knext);
+        if (FLAGS & kEngList) k_load(min(t + 1, nT - 1), Knext, knext);
         const char* Kb = Kcur + koff;
-        const char* Vb = Vst + voff;
+        const char* Vb = Vs0 + voff;
 
         // S^T = K Q^T : s[kb], 32 keys x 32 rows each.  Masks (tiles that touch a region
         // boundary, the diagonal or a list tail) enter as the initial accumulator: 0 for a
@@ -234,7 +228,7 @@ __global__ __launch_bounds__(256 * TEAMS, TEAMS == 1 ? 3 : 2) void engine_bf16_k
         }
         // a contiguous tile that starts beyond this wave's last row is hidden from all its rows
         // (the work-group still needs it for its later rows): nothing to compute
-        const bool on = !(t < nA && t0 > rw + 31) && (TEAMS == 1 || t < nT);
+        const bool on = !(t < nA && t0 > rw + 31);
         bf16x8 pf[2][2];  // [kb][s16]
         if (on) {
             floatx16 s[2];
@@ -287,7 +281,7 @@ __global__ __launch_bounds__(256 * TEAMS, TEAMS == 1 ? 3 : 2) void engine_bf16_k
         }
         if (!(FLAGS & kEngList)) {
             __builtin_amdgcn_sched_barrier(0);
-            k_load(min(t + TEAMS, nT - 1), Knext, knext);
+            k_load(min(t + 1, nT - 1), Knext, knext);
             __builtin_amdgcn_sched_barrier(0);
         }
         // V tile t has landed (vmcnt(4): the four loads of the next K tile are younger)
@@ -319,43 +313,9 @@ __global__ __launch_bounds__(256 * TEAMS, TEAMS == 1 ? 3 : 2) void engine_bf16_k
         wait_vmem();                                 // next K tile has landed in LDS
         bare_barrier();
     };
-    auto tile_loop = [&](int first, char* K0, char* K1, char* V0) __attribute__((always_inline)) {
-        for (int t = 0; t < nT; t += 2 * TEAMS) {        // (both teams make the same number of steps)
-            tile_step(t + first, K0, K1, V0, kidx0, kidx1);
-            if (t + TEAMS < nT) tile_step(t + TEAMS + first, K1, K0, V0, kidx1, kidx0);
-        }
-    };
-    // a loop per team: the compiler must see which LDS object a load or read belongs to
-    if (TEAMS == 1 || team == 0) tile_loop(0, Ks0, Ks1, Vs0); else tile_loop(1, Kt0, Kt1, Vt0);
-    if constexpr (TEAMS == 2) {
-        // merge: the second team leaves its state in free stages (16 KB of accumulators per wave) and
-        // ends (a barrier counts only the waves that have not)
-        float* const ob = (float*)(wave == 0 ? Kt0 : wave == 1 ? Kt1 : wave == 2 ? Vt0 : Vs0) + lane;
-        float* const mb = (float*)Ks0 + wave * 192 + lane;
-        static_assert(KBYTES >= 16384 && VBYTES >= 16384, "accumulators of a wave");
-        if (team == 1) {
-#pragma unroll
-            for (int db = 0; db < 4; ++db)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) ob[(16 * db + v) * 64] = o[db][v];
-            mb[0] = mref; mb[64] = mtrue; mb[128] = l;
-        }
-        __syncthreads();
-        if (team == 1) return;
-        const float m1 = mb[0], mnew = fmaxf(mref, m1);
-        // (a team that has seen none of the row's keys has no reference and counts for nothing)
-        const float f0 = mref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mref - mnew) * c2);
-        const float f1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m1 - mnew) * c2);
-        mref = mnew;
-        mtrue = fmaxf(mtrue, mb[64]);
-        l = l * f0 + mb[128] * f1;
-#pragma unroll
-        for (int db = 0; db < 4; ++db)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) o[db][v] = o[db][v] * f0 + ob[(16 * db + v) * 64] * f1;
-        // the stages become the waves' staging areas below
-        __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0)
-        bare_barrier();
+    for (int t = 0; t < nT; t += 2) {
+        tile_step(t, Ks0, Ks1, kidx0, kidx1);
+        if (t + 1 < nT) tile_step(t + 1, Ks1, Ks0, kidx1, kidx0);
     }
 
     // ---- epilogue
@@ -407,35 +367,15 @@ __global__ __launch_bounds__(256 * TEAMS, TEAMS == 1 ? 3 : 2) void engine_bf16_k
 }
 
 
-// A work-group has two teams where the chip is short of waves and the chain of one block is long: up to kTeamBlocks
-// query blocks (of all heads and sequences, two per CU; counted from the tokens, so that empty sequences of a packed
-// batch change nothing), and at least kTeamTiles tiles in the longest block.  Dense causal attention, 32 heads, one
-// team / two: 1024 tokens (256 blocks) 22.6 / 21.8 us, 1500 (384) 33.2 / 30.1, 2048 (512) 46.5 / 45.1; with three
-// blocks per CU the chip is full (3001 tokens: 82 us with one).  Below 12 tiles the merge costs more than the halved
-// chain saves (512 tokens 13.6 / 14.0 us).  Prefill of 1000 tokens (one launch of stage 1): 23.3 / 20.8 us.
-constexpr long long kTeamBlocks = 512;
-constexpr int kTeamTiles = 12;
-
 int launch_engine_bf16(const EngineArgs& ea, unsigned grid, hipStream_t st) {
-    const KParams& p = ea.p;
-    long long keys = p.N;                                // of the longest block's contiguous tiles
-    if (!(ea.flags & kEngDense)) {
-        const long long region = (long long)p.n_init + p.w + (long long)p.step * BQ;
-        if (region < keys) keys = region;
-    }
-    const bool teams = (p.total + BQ - 1) / BQ * p.Hq <= kTeamBlocks && keys >= kTeamTiles * TK;
     switch (ea.flags) {
 #define AA_ENGINE_CASE(F) \
-    case (F): return (int)launch_kernel(engine_bf16_kernel<(F), 1>, dim3(grid), dim3(256), 0, st, ea);
-#define AA_ENGINE_CASE_TEAMS(F) \
-    case (F): return teams ? (int)launch_kernel(engine_bf16_kernel<(F), 2>, dim3(grid), dim3(512), 0, st, ea) \
-                           : (int)launch_kernel(engine_bf16_kernel<(F), 1>, dim3(grid), dim3(256), 0, st, ea);
-    AA_ENGINE_CASE_TEAMS(kEngAnchorRegion | kEngStoreState)           // stage 1
+    case (F): return (int)launch_kernel(engine_bf16_kernel<(F)>, dim3(grid), dim3(256), 0, st, ea);
+    AA_ENGINE_CASE(kEngAnchorRegion | kEngStoreState)                 // stage 1
     AA_ENGINE_CASE(kEngList | kEngLoadState | kEngStoreOut)           // stage 3 from the cached state
     AA_ENGINE_CASE(kEngList | kEngAnchorRegion | kEngStoreOut)        // stage 3 recomputing the anchor region
-    AA_ENGINE_CASE_TEAMS(kEngAnchorRegion | kEngDense | kEngStoreOut) // dense causal attention
+    AA_ENGINE_CASE(kEngAnchorRegion | kEngDense | kEngStoreOut)       // dense causal attention
 #undef AA_ENGINE_CASE
-#undef AA_ENGINE_CASE_TEAMS
     default: return -1;
     }
 }

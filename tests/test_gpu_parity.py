@@ -155,21 +155,21 @@ def test_prefill_without_candidates(api, dtype, d, block, lens, n_init, window):
 
 
 @pytest.mark.parametrize("lens,n_init,window,step", [
-    ([767], 128, 128, 16),               # just below the tile count from which a work-group has two teams
-    ([768], 128, 128, 16),               # at it; an even number of tiles
-    ([835], 100, 128, 16),               # an odd number of tiles: the second team's last step is empty
+    ([767], 128, 128, 16),               # few work-groups: odd, even numbers of tiles, last tile cut
+    ([768], 128, 128, 16),
+    ([835], 100, 128, 16),
     ([1300, 100, 900], 64, 192, 5),      # packed, blocks of one tile up to the longest; with candidates
-    ([4096], 128, 128, 16),              # 32 blocks x 16 heads = the largest grid with two teams
-    ([4097], 128, 128, 16),              # one more
+    ([4096], 128, 128, 16),              # 32 blocks x 16 heads: two work-groups per CU
+    ([4097], 128, 128, 16),              # one more block
 ])
-def test_bf16_two_teams(api, lens, n_init, window, step):
+def test_bf16_small_grids(api, lens, n_init, window, step):
     Hq = 16 if lens[0] > 4000 else 4
     wl = _wl("t", "bf16", lens, Hq, Hq // 2, 128, 128, 100 + len(lens), max(8, max(lens) // 64))
     cfg = api.Config(block=128, n_init=n_init, window=window, step=step, theta=4.0)
     span = 128 * step
     samples = [(b, h, g) for b, n in enumerate(lens) for h in (0, Hq - 1) for g in {0, (n - 1) // span}]
     run, worst = _run_and_check(api, wl, cfg, samples=samples)
-    # the dense kernel splits in the same places: with every column selected both are the same attention
+    # the dense kernel: with every column selected both are the same attention
     inf = api.Config(block=128, n_init=n_init, window=window, step=step, theta=math.inf)
     from parity_util import DeviceRun
     full = DeviceRun(api, run.seqs, inf, "bf16").stages()
@@ -177,6 +177,31 @@ def test_bf16_two_teams(api, lens, n_init, window, step):
     assert (dense.float() - full.out.float()).abs().max().item() <= 2e-2     # as in test_bf16_theta_extremes
     rows = slice(0, min(lens))                   # (rows of head 0, sequence 0)
     assert (dlse[rows] - full.buf["lse"][rows]).abs().max().item() <= 4e-3
+
+
+@pytest.mark.parametrize("lens", [[1000] * 3, [1000, 300, 700]])
+def test_bf16_rows_do_not_depend_on_the_batch(api, lens):
+    """A sequence has the same bits alone (256 work-groups) and in a batch or a packed batch (more than two work-groups
+    per CU): state, output and dense attention."""
+    from parity_util import DeviceRun
+    wl = _wl("t", "bf16", lens, 32, 8, 128, 128, 110, 16)
+    cfg = api.Config(block=128, n_init=128, window=128, step=4, theta=4.0)
+    seqs = [synth.make_sequence(wl, s, signal="logit") for s in range(len(lens))]
+    many = DeviceRun(api, seqs, cfg, "bf16").stages()
+    mout, mlse = many.dense()
+    for b, n in enumerate(lens):
+        one = DeviceRun(api, seqs[b:b + 1], cfg, "bf16").stages()
+        dout, dlse = one.dense()
+        for h in range(32):
+            ri, r1 = many.row_index(b, h, 0), one.row_index(0, h, 0)
+            for x, y in ((many.buf["M"], one.buf["M"]), (many.buf["L"], one.buf["L"]), (many.buf["lse"], one.buf["lse"]),
+                         (mlse, dlse)):
+                assert torch.equal(x[ri:ri + n], y[r1:r1 + n])
+            for x, y in ((many.out, one.out), (mout, dout)):
+                assert torch.equal(many.out_rows(x, b, h, 0, n), one.out_rows(y, 0, h, 0, n))
+        for g in range((n + 511) // 512):
+            rows = min(512, n - 512 * g)
+            assert (many.acc_rows(b, 31, g, rows) == one.acc_rows(0, 31, g, rows)).all()
 
 
 @pytest.mark.parametrize("dtype,d,block,N,Hq,step,granularity", [
