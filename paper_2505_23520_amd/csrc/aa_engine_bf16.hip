@@ -41,6 +41,7 @@
 // Several blocks per work-group in one loop, which saves the replacement, was 3 to 11 % slower.
 #include "aa_engine_bf16_common.h"
 #include "aa_pool.h"
+#include "aa_rows.h"
 
 namespace aa {
 
@@ -138,16 +139,15 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     };
     // asynchronous: completion is awaited by wait_vmem()
     // (no branch: the byte offsets of a contiguous tile are clamped to the sequence's last row)
-    const unsigned klane = (unsigned)kq0 * kstb + 16u * lch, vlane = (unsigned)kq0 * vstb + 16u * lch;
+    const unsigned klane = lane_row_offset(kq0, kstb, lch), vlane = lane_row_offset(kq0, vstb, lch);
     const unsigned klast = (unsigned)(sq.len - 1) * kstb + 16u * lch, vlast = (unsigned)(sq.len - 1) * vstb + 16u * lch;
     auto rows_load = [&](int t, const __amdgpu_buffer_rsrc_t& rs, unsigned stb, unsigned lane0, unsigned last, char* dst,
                          int pitch, const intx4& kidx) {
         const bool is_list = (FLAGS & kEngList) && t >= nA;
-        const unsigned base = (unsigned)tile_start(t) * stb;
 #pragma unroll
         for (int j = 0; j < GPW; ++j) {
             unsigned off = 0;
-            if (FLAGS & kEngAnchorRegion) off = min(lane0 + (base + j * stb), last);
+            if (FLAGS & kEngAnchorRegion) off = clamped_row_offset(lane0, tile_row_offset(tile_start(t), sq.len, j, stb), last);
             if (FLAGS & kEngList) off = is_list ? (unsigned)kidx[j] * stb + 16u * lch : off;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(dst + j * pitch), 16, (int)off, 0, 0, 0);
         }

@@ -17,6 +17,7 @@
 // launches this kernel for dense attention and for even `step`, the 128-row kernel otherwise.
 #include "aa_engine_bf16_common.h"
 #include "aa_pool.h"
+#include "aa_rows.h"
 
 namespace aa {
 
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(512, 1) void engine_bf16_pp_kernel(EngineArgs a) {
     // base + per-lane constants, clamped to the last row; list tile: index * stride).
     unsigned lpre[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) lpre[j] = (unsigned)(kq0 + j) * lstb + 16u * lch;
+    for (int j = 0; j < 4; ++j) lpre[j] = lane_row_offset(kq0 + j, lstb, lch);
     const unsigned lmax = (unsigned)(sq.len - 1) * lstb + 16u * lch;
 
     // ---- Q fragments (B operand of S^T = K Q^T): lane (n, hf) holds Q[row][16 ks + 8 hf .. +8)
@@ -201,10 +202,10 @@ __global__ __launch_bounds__(512, 1) void engine_bf16_pp_kernel(EngineArgs a) {
         {
             char* dst = (grpB ? Vld : Kld) + 4 * simd * lgrp;
             const bool is_list = u >= nA;
-            const unsigned sbase = (unsigned)tile_start(u) * lstb;
+            const unsigned sbase = tile_row_offset(tile_start(u), sq.len, 0, lstb);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const unsigned oc = min(sbase + lpre[j], lmax);
+                const unsigned oc = clamped_row_offset(lpre[j], sbase, lmax);
                 const unsigned ol = (unsigned)keys[j] * lstb + 16u * lch;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(lrs, (lds_void*)(dst + j * lgrp), 16,
                                                          (int)(is_list ? ol : oc), 0, 0, 0);

@@ -204,6 +204,34 @@ def test_bf16_rows_do_not_depend_on_the_batch(api, lens):
             assert (many.acc_rows(b, 31, g, rows) == one.acc_rows(0, 31, g, rows)).all()
 
 
+def test_bf16_rows_far_apart(api):
+    """16 tokens as far apart as the library accepts (N * stride * 2 just below 2^31), not-a-number in between: loads of
+    keys past the end go to the last row, so every result has the bits of the compact tensors'."""
+    from parity_util import DeviceRun
+    wl = _wl("t", "bf16", [16], 2, 1, 128, 128, 120, 0)
+    cfg = api.Config(block=128, n_init=8, window=128, step=2, theta=4.0)
+    run = DeviceRun(api, [synth.make_sequence(wl, 0, signal="logit")], cfg, "bf16").stages()
+    want = dict(M=run.buf["M"].clone(), L=run.buf["L"].clone(), out=run.out.clone(), lse=run.buf["lse"].clone())
+    fused, dense = run.fused(), run.dense()
+    stride = 67108800
+    for name in ("k", "v"):
+        far = torch.full((15 * stride + 128,), math.nan, dtype=torch.bfloat16, device="cuda")
+        far = far.as_strided((1, 1, 16, 128), (128, 128, stride, 1))
+        far.copy_(getattr(run, name))
+        setattr(run, name, far)
+    run.p = api.make_params(run.cfg, run.q, run.k, run.v, run.out)
+    run.out.zero_()
+    run.stages()
+    got = dict(M=run.buf["M"], L=run.buf["L"], out=run.out, lse=run.buf["lse"])
+    for key in want:
+        assert torch.equal(got[key], want[key]), key
+    for a, b in zip(run.fused()[:2] + run.dense(), fused[:2] + dense):
+        assert torch.equal(a, b)
+    out, lse, B = torch.zeros_like(run.out), torch.zeros_like(run.buf["lse"]), run.buf
+    api.sparse_attn(run.p, run.q, run.k, run.v, None, None, None, B["counts"], B["offsets"], B["idx"], out, lse)
+    assert not out.isnan().any() and not lse.isnan().any()
+
+
 @pytest.mark.parametrize("dtype,d,block,N,Hq,step,granularity", [
     ("bf16", 128, 128, 35000, 16, 1, 0),     # groups x segments > 65536: the mask kernel adds up the counts itself
     ("bf16", 128, 128, 35000, 16, 1, 1),     # the same for block granularity (count kernel)
