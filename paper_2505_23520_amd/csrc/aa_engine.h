@@ -49,7 +49,7 @@ struct EngineArgs {
 
 // statistics of a call none of whose groups has candidates: every row attends all keys up to itself
 __device__ __forceinline__ void store_dense_stats(const EngineArgs& a) {
-    if (!a.stats || blockIdx.x != 0 || threadIdx.x != 0) return;
+    if (!a.stats || blockIdx.x != 0 || blockIdx.y != 0 || threadIdx.x != 0) return;
     long long pairs = 0;
     for (int b = 0; b < a.p.B; ++b) {
         const long long len = a.p.packed ? a.p.cu[b + 1] - a.p.cu[b] : a.p.N;

@@ -60,7 +60,9 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void engine_fp32_kernel(
     if (a.flags & kEngStoreState) store_dense_stats(a);
     if (!engine_selected(a)) return;
     const int rts = (p.bq + RT - 1) / RT;            // row tiles of a query block
-    const Work wk = decode_work(p, p.nblk_max * rts, blockIdx.x);
+    const unsigned id = blockIdx.y * gridDim.x + blockIdx.x, tiles = (unsigned)(p.nblk_max * rts);
+    if (id >= tiles * (unsigned)p.Hq * (unsigned)p.B) return;
+    const Work wk = decode_work(p, (int)tiles, id);
     const Seq sq = seq_of(p, wk.b);
     const int blk = wk.i / rts;
     const int row0 = blk * p.bq + (wk.i % rts) * RT;             // first row of the tile
@@ -286,13 +288,18 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void engine_fp32_kernel(
 }
 }  // namespace
 
+// Work-groups per grid row: a launch takes fewer than 2^32 threads in x, and 256 threads per 32 rows (per 16 at a block of
+// 16) reach that with 5e8 (2.7e8) rows times heads.  A multiple of 8, so that decode_work's XCD of a work-group holds.
+constexpr long long kGridX = 1 << 23;
+
 int launch_engine_fp32(const EngineArgs& ea, hipStream_t st) {
     const KParams& p = ea.p;
-    const unsigned grid = (unsigned)((long long)p.nblk_max * ((p.bq + RT - 1) / RT) * p.Hq * p.B);
+    const long long total = (long long)p.nblk_max * ((p.bq + RT - 1) / RT) * p.Hq * p.B;
+    const dim3 grid((unsigned)(total < kGridX ? total : kGridX), (unsigned)((total + kGridX - 1) / kGridX));
     switch (p.d) {
-        case 32: return (int)launch_kernel(engine_fp32_kernel<32>, dim3(grid), dim3(64 * NW), 0, st, ea);
-        case 64: return (int)launch_kernel(engine_fp32_kernel<64>, dim3(grid), dim3(64 * NW), 0, st, ea);
-        case 128: return (int)launch_kernel(engine_fp32_kernel<128>, dim3(grid), dim3(64 * NW), 0, st, ea);
+        case 32: return (int)launch_kernel(engine_fp32_kernel<32>, grid, dim3(64 * NW), 0, st, ea);
+        case 64: return (int)launch_kernel(engine_fp32_kernel<64>, grid, dim3(64 * NW), 0, st, ea);
+        case 128: return (int)launch_kernel(engine_fp32_kernel<128>, grid, dim3(64 * NW), 0, st, ea);
         default: return -1;
     }
 }

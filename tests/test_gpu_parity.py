@@ -112,6 +112,29 @@ def test_fp32_tiles(api, d, block, lens, step, n_init, window, theta):
     assert 0 < worst["selected"] < worst["candidates"]
 
 
+def test_fp32_grid_beyond_32_bits_of_threads(api):
+    """65535 sequences of 4128 rows in blocks of 16: 16.9 million tiles, 4.3e9 threads.  Every sequence is the same one
+    (batch stride 0), its log-sum-exp has rows of its own."""
+    wl = _wl("t", "fp32", [4128], 1, 1, 32, 16, 21, 8)
+    s = synth.make_sequence(wl, 0, signal="logit")
+    q, k, v = (torch.from_numpy(s[x])[None].cuda() for x in ("q", "k", "v"))
+    cfg = api.Config(block=16, n_init=16, window=16, step=1, theta=4.0)
+    got = []
+    for B in (1, 65535):
+        qb, kb, vb = (x.expand(B, -1, -1, -1) for x in (q, k, v))
+        out = torch.zeros_like(q)
+        p = api.make_params(cfg, qb, kb, vb, out.expand(B, -1, -1, -1))
+        sizes = api.anchor_sizes(p)
+        lse = torch.full((sizes.rows,), math.nan, device="cuda")
+        counts = torch.zeros(sizes.groups, dtype=torch.int32, device="cuda")
+        offsets = torch.zeros(sizes.groups + 1, dtype=torch.int64, device="cuda")
+        idx = torch.zeros(64, dtype=torch.int32, device="cuda")
+        api.sparse_attn(p, qb, kb, vb, None, None, None, counts, offsets, idx, out, lse)
+        got.append((out, lse.view(B, -1)))
+    assert torch.equal(got[0][0], got[1][0])
+    assert not got[0][1].isnan().any() and bool((got[1][1] == got[0][1]).all())
+
+
 # ------------------------------------------------------------------ bf16 MFMA path
 @pytest.mark.parametrize("N,step,n_init,window,theta", [
     (2048, 1, 128, 128, 3.5),
