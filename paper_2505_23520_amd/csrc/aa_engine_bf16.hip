@@ -61,10 +61,10 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     __shared__ float red[NW], knorm[NW];
     __shared__ float qpart[(FLAGS & kEngStoreState) ? 4 : 1][128];   // pooled-query partial sums (stage 1)
     const KParams& p = a.p;
-    const int tid = threadIdx.x & 255;               // (256 threads; with the range stated, stage 1 spills no register)
-    const int lane = tid & 63;
+    int tid = threadIdx.x;
+    int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keep it scalar
-    const int n = lane & 31, hf = lane >> 5;
+    int n = lane & 31, hf = lane >> 5;
 
     if (flags & kEngStoreState) {
         store_dense_stats(a);
@@ -85,8 +85,8 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     const bool direct = a.direct && window_start(p, g) <= p.n_init;   // no candidates: stage 1 finishes the rows
     if ((flags & kEngLoadState) && direct) return;
     const int rw = row0 + 32 * wave;                 // first row of this wave
-    const int r = rw + n;                            // this lane's query row
-    const bool rok = r < sq.len;
+    int r = rw + n;                                  // this lane's query row
+    bool rok = r < sq.len;
     const int rlast = min(row0 + BQ, sq.len) - 1;    // last row of the block
 
     // ---- tile sequence: [range 1: initial tokens][range 2: window .. diagonal][list chunks]
@@ -139,8 +139,12 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     };
     // asynchronous: completion is awaited by wait_vmem()
     // (no branch: the byte offsets of a contiguous tile are clamped to the sequence's last row)
-    const unsigned klane = lane_row_offset(kq0, kstb, lch), vlane = lane_row_offset(kq0, vstb, lch);
-    const unsigned klast = (unsigned)(sq.len - 1) * kstb + 16u * lch, vlast = (unsigned)(sq.len - 1) * vstb + 16u * lch;
+    // (contiguous and list tiles in one loop: the lane's 16-byte piece is added after the choice between the two, which
+    // leaves the limits in scalar registers; the other modes need no such addition)
+    constexpr bool mixed = (FLAGS & kEngList) && (FLAGS & kEngAnchorRegion);
+    const unsigned piece = 16u * lch, cpiece = mixed ? 0 : piece;
+    const unsigned klane = lane_row_offset(kq0, kstb, mixed ? 0 : lch), vlane = lane_row_offset(kq0, vstb, mixed ? 0 : lch);
+    const unsigned klast = (unsigned)(sq.len - 1) * kstb + cpiece, vlast = (unsigned)(sq.len - 1) * vstb + cpiece;
     auto rows_load = [&](int t, const __amdgpu_buffer_rsrc_t& rs, unsigned stb, unsigned lane0, unsigned last, char* dst,
                          int pitch, const intx4& kidx) {
         const bool is_list = (FLAGS & kEngList) && t >= nA;
@@ -148,7 +152,8 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
         for (int j = 0; j < GPW; ++j) {
             unsigned off = 0;
             if (FLAGS & kEngAnchorRegion) off = clamped_row_offset(lane0, tile_row_offset(tile_start(t), sq.len, j, stb), last);
-            if (FLAGS & kEngList) off = is_list ? (unsigned)kidx[j] * stb + 16u * lch : off;
+            if (mixed) off = (is_list ? (unsigned)kidx[j] * stb : off) + piece;
+            else if (FLAGS & kEngList) off = is_list ? (unsigned)kidx[j] * stb + piece : off;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(dst + j * pitch), 16, (int)off, 0, 0, 0);
         }
     };
@@ -187,11 +192,10 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     // ---- running state (see load_state)
     const float c2 = p.sigma * 1.4426950408889634f;  // exp(sigma*x) = exp2(c2*x)
     const float rescale_gap = kRescaleLog2 / c2;
-    const long long ri = row_index(p, sq, wk.b, wk.h, rok ? r : row0);
     const long long tile = acc_tile(p, sq, wk.b, wk.h, wk.i, wave);
     float mref, mtrue, l;
     floatx16 o[4];
-    if (flags & kEngLoadState) load_state(a, ri, tile, lane, hf, mref, mtrue, l, o);
+    if (flags & kEngLoadState) load_state(a, row_index(p, sq, wk.b, wk.h, rok ? r : row0), tile, lane, hf, mref, mtrue, l, o);
     else init_state(mref, mtrue, l, o);
     __builtin_amdgcn_sched_barrier(0);
     // K tile 0 is there; the 16 loads of the cached accumulators are younger and may still be on their way
@@ -248,10 +252,11 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
                     // key j = t0 + jl is visible to row r iff j <= r and (j < ninit or j >= W);
                     // entry jl of the last list chunk is real iff jl < rem
                     // (jl = 32 kb + 8 (v / 4) + 4 hf + v % 4: the lane's part is taken off the limits instead)
-                    int jr = (mode == 1 ? r - t0 : cnt - (t - nA) * TK - 1) - 4 * hf;
-                    asm volatile("" : "+v"(jr));     // opaque: the 32 comparisons are not hoisted out of the loop
-                    const int jn = (mode == 1 ? ninit - t0 : TK) - 4 * hf;
-                    const int jw = W - t0 - 4 * hf;
+                    // (with the lane opaque, the 32 comparisons are not hoisted out of the loop either)
+                    const int ln = counted_lane(), h4 = 4 * (ln >> 5);
+                    const int jr = (mode == 1 ? rw - t0 + (ln & 31) : cnt - (t - nA) * TK - 1) - h4;
+                    const int jn = (mode == 1 ? ninit - t0 : TK) - h4;
+                    const int jw = W - t0 - h4;
 #pragma unroll
                     for (int kb = 0; kb < 2; ++kb) {
                         floatx16 bias;
@@ -325,6 +330,12 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     char* const stg = wave == 0 ? Ks0 : wave == 1 ? Ks1 : Vs0 + (wave - 2) * kOutStageBytes;
     const int wave_rows = min(32, sq.len - rw);      // rows of this wave inside the sequence (<= 0: none)
     float lt = row_sum(l);                           // row sum relative to mref
+    lane = counted_lane();                           // (no lane's value but addresses lives through the loop)
+    tid = 64 * wave + lane;
+    n = lane & 31; hf = lane >> 5;
+    r = rw + n;
+    rok = r < sq.len;
+    const long long ri = row_index(p, sq, wk.b, wk.h, rok ? r : row0);
     if (flags & kEngStoreState) {
         const float ms = rebase_state(a, c2, mref, mtrue, lt, o);
         // (the state goes out last: the barriers in between would wait for its stores to drain)
@@ -367,14 +378,24 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
 }
 
 
+// Stage 3 recomputing the anchor region: two work-groups per CU instead of three, by 8 KB of unused LDS, where the query blocks
+// of the call fill two slots per CU once to twice and a group is long (its blocks then have chains of uneven length, and the
+// last third of a full chip waits for the longest).  32 heads, three / two per CU: step 16, 3000 tokens (750 blocks)
+// 64.6 / 59.6 us, 4096 (1024) 90.9 / 85.2, 5000 (1250) 105.2 / 102.9, 8192 (2048) 171.6 / 175.2; step 8, 3000 tokens
+// 50.8 / 49.4; step 4 41.6 / 43.7; up to 512 blocks there is no third either way.
+static size_t recompute_extra_lds(const KParams& p) {
+    const long long blocks = (p.total + BQ - 1) / BQ * p.Hq;
+    return p.step >= 8 && blocks > 512 && blocks <= 1024 ? 8192 : 0;
+}
+
 int launch_engine_bf16(const EngineArgs& ea, unsigned grid, hipStream_t st) {
     switch (ea.flags) {
-#define AA_ENGINE_CASE(F) \
-    case (F): return (int)launch_kernel(engine_bf16_kernel<(F)>, dim3(grid), dim3(256), 0, st, ea);
-    AA_ENGINE_CASE(kEngAnchorRegion | kEngStoreState)                 // stage 1
-    AA_ENGINE_CASE(kEngList | kEngLoadState | kEngStoreOut)           // stage 3 from the cached state
-    AA_ENGINE_CASE(kEngList | kEngAnchorRegion | kEngStoreOut)        // stage 3 recomputing the anchor region
-    AA_ENGINE_CASE(kEngAnchorRegion | kEngDense | kEngStoreOut)       // dense causal attention
+#define AA_ENGINE_CASE(F, lds) \
+    case (F): return (int)launch_kernel(engine_bf16_kernel<(F)>, dim3(grid), dim3(256), lds, st, ea);
+    AA_ENGINE_CASE(kEngAnchorRegion | kEngStoreState, 0)              // stage 1
+    AA_ENGINE_CASE(kEngList | kEngLoadState | kEngStoreOut, 0)         // stage 3 from the cached state
+    AA_ENGINE_CASE(kEngList | kEngAnchorRegion | kEngStoreOut, recompute_extra_lds(ea.p))   // stage 3 recomputing the anchor region
+    AA_ENGINE_CASE(kEngAnchorRegion | kEngDense | kEngStoreOut, 0)     // dense causal attention
 #undef AA_ENGINE_CASE
     default: return -1;
     }

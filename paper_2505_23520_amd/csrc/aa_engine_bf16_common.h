@@ -38,6 +38,14 @@ constexpr floatx16 kZero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 
 constexpr int kOutPitch = 136;       // bf16 per row of the output staging area in LDS
 constexpr int kOutStageBytes = 32 * kOutPitch * 2;   // one wave's 32 rows
 
+// The lane's number, counted anew from an opaque zero: what is derived from it after the tile loop, or in a rare branch
+// of it, is not kept in registers through the loop.
+__device__ __forceinline__ int counted_lane() {
+    unsigned zero = 0;
+    asm volatile("" : "+v"(zero));
+    return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+}
+
 // s_waitcnt vmcnt(0) only (gfx9 encoding: expcnt and lgkmcnt fields left at their maxima)
 __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 

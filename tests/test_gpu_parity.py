@@ -320,6 +320,27 @@ def test_bf16_recompute_anchor_in_stage3(api):
     assert worst["selected"] > 0
 
 
+@pytest.mark.parametrize("N,n_init,window,step", [(2560, 100, 150, 16), (2500, 0, 0, 8), (1700, 64, 300, 3)])
+def test_bf16_recompute_odd_regions(api, N, n_init, window, step):
+    """The same over contiguous and list tiles with unaligned limits, against the cached-state path; alone (513 to 1024
+    query blocks: two work-groups per CU from step 8 on) and in a batch of two (three) with the same bits."""
+    from parity_util import DeviceRun
+    wl = _wl("t", "bf16", [N], 32, 8, 128, 128, 71 + step, N // 40)
+    cfg = api.Config(block=128, n_init=n_init, window=window, step=step, theta=4.0)
+    seqs = [synth.make_sequence(wl, 0, signal="logit")]
+    got = []
+    for B in (1, 2):
+        run = DeviceRun(api, seqs * B, cfg, "bf16").stages()
+        out, lse, b = torch.zeros_like(run.out), torch.empty_like(run.buf["lse"]), run.buf
+        api.sparse_attn(run.p, run.q, run.k, run.v, None, None, None, b["counts"], b["offsets"], b["idx"], out, lse)
+        assert 0 < int(b["counts"].sum()) and (out.float() - run.out.float()).abs().max().item() <= 2e-2
+        assert (lse - b["lse"]).abs().max().item() <= 4e-3
+        got.append((out, lse))
+    for i in range(2):
+        assert torch.equal(got[1][0][i], got[0][0][0])
+        assert torch.equal(got[1][1].view(2, -1)[i], got[0][1])
+
+
 def _plant_columns(wl, cols, mag):
     """Input edit: every query gets d^(1/4) u and the key columns `cols` get mag d^(1/4) u along a
     fixed unit direction u, so that these columns' logits sit about mag above the background's."""
