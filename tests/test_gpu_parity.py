@@ -177,6 +177,23 @@ def test_prefill_without_candidates(api, dtype, d, block, lens, n_init, window):
     assert torch.equal(out, run.out)
 
 
+@pytest.mark.parametrize("dtype,d,block,granularity", [("bf16", 128, 128, 0), ("bf16", 128, 128, 1), ("fp32", 64, 32, 0),
+                                                       ("fp32", 64, 32, 1)])
+def test_prefill_reads_nothing_it_has_not_written(api, dtype, d, block, granularity):
+    """The fused call on a workspace of not-a-number bytes: groups with candidates beside ones without, whose state
+    stage 1 does not write."""
+    wl = _wl("t", dtype, [11 * block + 5, 4 * block, 20], 4, 2, d, block, 85, 24)
+    cfg = api.Config(block=block, n_init=block, window=block, step=3, theta=5.3 if granularity else 4.0, granularity=granularity)
+    run, worst = _run_and_check(api, wl, cfg, packed=True)
+    assert worst["candidates"] > 0
+    for byte in (255, 0x7f):
+        out, lse, stats = torch.zeros_like(run.out), torch.zeros_like(run.buf["lse"]), torch.zeros(4, dtype=torch.int64, device="cuda")
+        ws = torch.full((run.sizes.prefill_ws_bytes,), byte, dtype=torch.uint8, device="cuda")
+        api.anchor_attention_prefill(run.p, run.q, run.k, run.v, out, lse, stats, ws)
+        assert torch.equal(out, run.out) and torch.equal(lse, run.buf["lse"])
+        assert int(stats[1]) == int(run.buf["counts"].sum())
+
+
 @pytest.mark.parametrize("lens,n_init,window,step", [
     ([767], 128, 128, 16),               # few work-groups: odd, even numbers of tiles, last tile cut
     ([768], 128, 128, 16),
