@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
 
     // ---- running state (see load_state)
     const float c2 = p.sigma * 1.4426950408889634f;  // exp(sigma*x) = exp2(c2*x)
-    const float rescale_gap = kRescaleLog2 / c2;
+    const float rescale_gap = rescale_limit(c2);
     const long long tile = acc_tile(p, sq, wk.b, wk.h, wk.i, wave);
     float mref, mtrue, l;
     floatx16 o[4];

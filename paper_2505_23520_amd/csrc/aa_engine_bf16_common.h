@@ -72,6 +72,10 @@ __device__ __forceinline__ void load_q_fragments(bf16x8 (&qf)[8], const EngineAr
     }
 }
 
+// How far a row's maximum may exceed the reference, in raw dot-product units.  Finite for the smallest scales too, so that
+// a first maximum always raises the reference from -inf.
+__device__ __forceinline__ float rescale_limit(float c2) { return fminf(kRescaleLog2 / c2, 3.402823466e38f); }
+
 // Running state of a lane's query row, raw dot-product units: reference mref of the exponentials,
 // true maximum mtrue (the anchor that stage 1 exports), per-lane partial row sum l (the two halves
 // of a row are added at the end), O^T accumulators.

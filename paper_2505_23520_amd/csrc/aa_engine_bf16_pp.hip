@@ -158,7 +158,7 @@ __global__ __launch_bounds__(512, 1) void engine_bf16_pp_kernel(EngineArgs a) {
     // 2 i + chunk / 4; a wave whose rows lie past the end of the sequence reads the pair's first
     // block (in bounds, unused).
     const float c2 = p.sigma * 1.4426950408889634f;  // exp(sigma*x) = exp2(c2*x)
-    const float rescale_gap = kRescaleLog2 / c2;
+    const float rescale_gap = rescale_limit(c2);
     const long long ri = row_index(p, sq, wk.b, wk.h, rok ? r : row0);
     const long long tile = acc_tile(p, sq, wk.b, wk.h, 2 * wk.i + (wave_on ? chunk >> 2 : 0), chunk & 3);
     float mref, mtrue, l;

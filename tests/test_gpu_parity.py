@@ -337,6 +337,22 @@ def test_bf16_recompute_anchor_in_stage3(api):
     assert worst["selected"] > 0
 
 
+def test_smallest_softmax_scale(api):
+    """A scale so small that every score is 0: plain means, log-sum-exp = log(number of keys)."""
+    from parity_util import DeviceRun
+    wl = _wl("t", "bf16", [300], 2, 1, 128, 128, 130, 0)
+    cfg = api.Config(block=128, n_init=128, window=128, step=2, theta=4.0, softmax_scale=1e-39)
+    run = DeviceRun(api, [synth.make_sequence(wl, 0, signal="logit")], cfg, "bf16").stages()
+    r = torch.arange(1, 301, device="cuda")
+    mean = run.v[0, 0].double().cumsum(0) / r[:, None]
+    out2, lse2, B = torch.zeros_like(run.out), torch.zeros_like(run.buf["lse"]), run.buf
+    api.sparse_attn(run.p, run.q, run.k, run.v, None, None, None, B["counts"], B["offsets"], B["idx"], out2, lse2)
+    for out, lse in (run.dense(), run.fused()[:2], (run.out, B["lse"]), (out2, lse2)):
+        for h in range(2):
+            assert (out[0, h].double() - mean).abs().max().item() <= 2e-2
+            assert (lse[h * 300:(h + 1) * 300] - r.float().log()).abs().max().item() <= 1e-5
+
+
 @pytest.mark.parametrize("N,n_init,window,step", [(2560, 100, 150, 16), (2500, 0, 0, 8), (1700, 64, 300, 3)])
 def test_bf16_recompute_odd_regions(api, N, n_init, window, step):
     """The same over contiguous and list tiles with unaligned limits, against the cached-state path; alone (513 to 1024
