@@ -1,4 +1,4 @@
-"""What the compiler reports for the engines' kernels: no vector register spilled (a reload is a vector-memory load, and the
+"""What the compiler makes of the engines' kernels: no vector register spilled (a reload is a vector-memory load, and the
 wait for it waits for the tile loads in flight), and as many waves per SIMD as each kernel is written for."""
 import os
 import re
@@ -20,3 +20,18 @@ def test_engines_do_not_spill(tmp_path, source, waves):
     assert len(names) >= 3 and len(spills) == len(occupancy) == len(names)
     assert not any(spills), dict(zip(names, spills))
     assert min(occupancy) >= waves, dict(zip(names, occupancy))
+
+
+def test_list_loop_address(tmp_path):
+    """The tile loop of the 256-row engine's list mode stands where it fetches least from memory: its first barrier at 12
+    modulo 64 (the figures are beside the directive that puts it there; after a change inside the loop they are to be
+    measured again)."""
+    obj = str(tmp_path / "x.o")
+    source = "aa_engine_bf16_pp.hip"
+    subprocess.check_call(["hipcc", *build.FLAGS, *build.EXTRA[source], "--cuda-device-only", "--no-gpu-bundle-output", "-c",
+                           os.path.join(build.CSRC, source), "-o", obj])
+    code = subprocess.check_output(["/opt/rocm/llvm/bin/llvm-objdump", "-d", obj], text=True)
+    kernel = code[code.index("engine_bf16_pp_kernelILi44E"):]
+    loop = re.search(r"(?:\ts_nop 0[^\n]*\n){13,}", kernel)
+    barrier = re.search(r"\ts_barrier[^\n]*// ([0-9A-F]+):", kernel[loop.end():])
+    assert int(barrier.group(1), 16) % 64 == 12
