@@ -111,8 +111,10 @@ int make_plan(const aa_params* p, Plan* pl) {
     const long long span = (long long)p->block_q * p->step;
     k.nblk_max = (int)cdiv(p->N, p->block_q);
     k.ngrp_max = (int)cdiv(p->N, span);
-    // launch grids put heads (times sequences) on y / z, and the fp32 mask kernel puts groups on y
+    // launch grids put heads (times sequences) on y / z
     if ((long long)p->Hq * p->B > 65535 || p->Hq + p->Hkv > 65535) return AA_EUNSUPPORTED;
+    // no grid of the fp32 path limits the groups; such calls are refused because nothing has run them (from 1048561 tokens on,
+    // with 8 GB of bit words per head)
     if (p->dtype == AA_FP32 && k.ngrp_max > 65535) return AA_EUNSUPPORTED;
 
     aa_sizes& s = pl->sz;
@@ -231,11 +233,15 @@ int launch_engine(const Plan& pl, const aa_params* prm, EngineArgs& ea, hipStrea
         // epilogue overlap with nothing); it needs both blocks of a pair to share window and list.
         // Dense, 32 heads, 128 / 256 rows: 4096 tokens 130 / 133 us, 6000 273 / 280, 8192 481 / 474,
         // 32768 7214 / 6956.
+        // Stage 3, where the line lies depends on heads, step and the spread of the lists; time of the 256-row engine over
+        // the 128-row one: 32 / 8 heads, step 16, every column selected, mean list 14 tiles 1.09, 29 0.98, 45 1.02, 61 1.00,
+        // 108 0.98; a part selected, 16 tiles 1.09, 25 1.00, 35 1.03, 50 (131072 tokens) 1.05; 8 / 8 heads 45 tiles 1.06, 61
+        // 1.04, 108 0.93; 16 / 2 heads, step 4, 24 tiles 0.89, 56 0.83, 72 0.99.  48 tiles lie in the middle.
+        const long long pp_entries = 48ll * kIdxPad * pl.sz.groups;
         const bool pair_ok = (ea.flags & kEngDense) || k.step % 2 == 0;
         int choice = prm->engine;                   // 0 auto, 1: 128 rows, 2: 256 rows
         if (!pair_ok) choice = AA_ENGINE_128;
         if (choice == AA_ENGINE_AUTO) {
-            const long long pp_entries = 48ll * 64 * pl.sz.groups;   // mean list of 48 tiles
             // stage 3: decided on the device from the list lengths, unless no outcome reaches the limit
             // (a launch that finds itself not selected still takes 4 us, 15 us at 128k)
             if (ea.flags & kEngList) choice = pl.sz.idx_capacity_max < pp_entries ? AA_ENGINE_128 : 3;
@@ -245,7 +251,7 @@ int launch_engine(const Plan& pl, const aa_params* prm, EngineArgs& ea, hipStrea
         const unsigned gridp = (unsigned)((long long)((k.nblk_max + 1) / 2) * k.Hq * k.B);
         int rc = AA_OK;
         if (choice == 3) {
-            ea.sel_entries = 48ll * 64 * pl.sz.groups;   // mean list of 48 tiles
+            ea.sel_entries = pp_entries;
             ea.sel = 1;
             rc = engine_status(launch_engine_bf16(ea, grid, st), "engine_bf16_kernel");
             if (rc != AA_OK) return rc;
@@ -318,7 +324,6 @@ int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k,
     sa.bits = (unsigned*)(ws + pl.sel_bits);
     sa.kp_f32 = (float*)(ws + pl.sel_kp);
     sa.qlo_norm = (float*)(ws + pl.sel_qln);
-    sa.kmax_blk = nullptr;
     sa.segcount = (int*)(ws + pl.sel_segc);
     sa.nseg = (int)cdiv(pl.nwords, 64);
     sa.is_bf16 = p->dtype == AA_BF16;
@@ -500,7 +505,7 @@ int anchor_attention_prefill(const aa_params* params, const void* q, const void*
     // bf16: the block means of Q (first step of stage 2) come out of stage 1, which holds the block's
     // queries in registers; the stage-wise entry points compute the same bits in a kernel of their own
     // Rows of groups without candidates are complete after stage 1, which writes their output; if that is every
-    // row (a prompt within its first group and window), it is the whole call: 53 -> 29 us at 1000 tokens, where
+    // row (a prompt within its first group and window), it is the whole call: 53 -> 25 us at 1000 tokens, where
     // the other kernels' launches alone took 25 us.  At 8k tokens and step 16 it is a quarter of the rows.
     const bool direct = direct_ok(params);
     if (direct && no_candidates(pl.kp))

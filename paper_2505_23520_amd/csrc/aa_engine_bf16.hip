@@ -25,16 +25,16 @@
 // alone.  The true row maximum, which is the anchor that stage 1 exports, is tracked separately.
 //
 // What bounds it: a wave's own chain per tile (load issue, 16 score MFMAs, softmax, 16 P V MFMAs,
-// two barriers) is about 2.7 times as long as its 1024 MFMA cycles, so the matrix pipe needs three
-// waves per SIMD to stay busy.  Three fit if a wave takes at most 168 registers and a work-group a
+// two barriers) is about four times as long as its 1024 MFMA cycles, so the matrix pipe needs as many waves per
+// SIMD as fit to stay busy.  Three fit if a wave takes at most 168 registers and a work-group a
 // third of the LDS.  V therefore has one stage: V tile t is issued when tile t - 1 has been
 // consumed and is awaited after the scores and softmax of tile t, behind which its latency hides
 // (K tile t + 1 has the whole of tile t).  At 168 registers the compiler left alone issues every LDS operand
 // read right before its MFMA, so the read-ahead is written out and pinned with scheduling fences,
 // and no load or wait stands under a condition (a path on which fewer loads are outstanding would
-// turn the waits into vmcnt(0)).
+// turn the waits into vmcnt(0)).  Nothing may be spilled: a reload is a vector-memory load, too.
 // Measured, 131072 tokens x 32 heads, step 16: anchor computation 3.10 -> 2.71 ms (the two-per-CU form
-// with two V stages before), matrix pipe 50 -> 61 % busy; the engine clock falls from 1.70 to 1.62 GHz
+// with two V stages before), matrix pipe 50 -> 65 % busy; the engine clock falls from 1.70 to 1.57 GHz
 // at the same time (the card's power limit), which is why the time gains less than the cycles.  Of this the third
 // wave alone gave 5 %, the pinned order 4 %.  Inside the tile loop the pipe is 77 % busy (3980 cycles per
 // tile and three waves); the rest is a work-group's prologue (6400 cycles), epilogue (4000) and replacement.

@@ -128,7 +128,7 @@ __device__ __forceinline__ float probabilities(const floatx16 (&s)[2], bf16x8 (&
 // lanes away).  s: the tile's scores, hidden pairs already at -inf.  The reference is raised only
 // when some row's maximum exceeds it by more than rescale_gap (2^8; wave-uniform branch, rare after
 // the first tiles); the accumulators are then rescaled, otherwise untouched.  mtrue is the maximum
-// over the keys of this lane alone (the two halves meet in store_state).
+// over the keys of this lane alone (the two halves meet in rebase_state).
 __device__ __forceinline__ void softmax_tile(const floatx16 (&s)[2], bf16x8 (&pf)[2][2], float c2, float rescale_gap,
                                              float& mref, float& mtrue, float& l, floatx16 (&o)[4]) {
     float mx = fmaxf(s[0][0], s[1][0]);
@@ -150,8 +150,8 @@ __device__ __forceinline__ void softmax_tile(const floatx16 (&s)[2], bf16x8 (&pf
     l += probabilities(s, pf, c2, mref);
 }
 
-// The same for the modes that do not export the true row maximum (stage 3, dense attention): the
-// maximum is only looked for when it is needed.  The probabilities are computed against the
+// The same for the 256-row engine's modes that do not export the true row maximum (stage 3, dense attention; in the
+// 128-row engine this form spills): the maximum is only looked for when it is needed.  The probabilities are computed against the
 // current reference straight away; only if some lane's partial row sum shows a probability above
 // 2^8 (or infinite), or some row has no reference yet (the first tiles), the wave
 // finds the row maxima, raises the references, rescales the accumulators and computes the tile's

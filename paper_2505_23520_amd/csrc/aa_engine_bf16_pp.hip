@@ -337,8 +337,8 @@ __global__ __launch_bounds__(512, 1) void engine_bf16_pp_kernel(EngineArgs a) {
     };
     // The instruction addresses of the list mode's loop, modulo 64, are fixed: they set the pace at which work-groups that share
     // an L2 run apart, and with it what each of them fetches again.  131072 tokens, 32 heads, every column selected, the same
-    // loop with its first barrier at another address modulo 64: 9.6 GiB fetched per launch at 12 (here) and 44, 14 to 18 at
-    // 20, 24, 28, 56 and 60, 50 to 72 at 0, 8, 16, 32, 40 and 48; the time stays within 0.5 %.  Without the directive any
+    // loop with its first barrier at another address modulo 64: 19 GiB fetched per launch at 12 (here) and 44, 27 to 37 at
+    // 20, 24, 28, 56 and 60, 99 to 145 at 0, 8, 16, 32, 40 and 48; the time stays within 0.5 %.  Without the directive any
     // change ahead of the loop picks one of them.
     if (FLAGS == (kEngList | kEngLoadState | kEngStoreOut)) asm volatile(".p2align 6\n.rept 13\n s_nop 0\n.endr");
     // whole rounds of three tiles (one per LDS stage); tiles past the end only keep the barriers

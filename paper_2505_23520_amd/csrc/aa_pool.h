@@ -106,7 +106,7 @@ __device__ __forceinline__ void key_block_norm(const unsigned short* k, long lon
     if (tid == 0) *out = sqrtf(fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3])));
 }
 
-// Clears the counters that the bf16 mask kernel adds to; called by every thread of a kernel that runs before it.
+// Clears the counters that the mask kernels of both types (and count_kernel) add to; called by every thread of a kernel that runs before it.
 __device__ __forceinline__ void clear_counters(int* counts, long long groups, int* segcount, int nseg,
                                                long long thread, long long nthreads) {
     for (long long e = thread; e < groups * (nseg + 1); e += nthreads) {

@@ -2,7 +2,8 @@
 // (arXiv 2505.23520 Sec. 3.2 mask, Algorithm 2, and the step rule of Sec. 3.4):
 //   pool_q   : qbar_i = mean of query block i's rows               (Alg. 2, avgpool(Q))
 //   mask     : bit (g, j) = OR_{i in g} [ xbar_i - sigma <qbar_i, k_j> <= theta ],  j in C_g
-//   count    : |I_g| = popcount of the group's bits
+//   count    : |I_g| = popcount of the group's bits (added up by the stripe mask kernels as they write them; a kernel of its
+//              own for block granularity only)
 //   scan     : offsets = exclusive prefix sum of the counts rounded up to 64
 //   fill     : ballot / prefix-popcount stream compaction of the bits into ascending lists
 // The bf16 mask kernel is a skinny MFMA GEMM (pooled rows x keys); the pooled
@@ -510,7 +511,7 @@ __global__ __launch_bounds__(256) void mask_fp32_kernel(SelectArgs a) {
             unsigned keep = 0;
             if (hi > lo) keep = (hi - lo >= 32) ? 0xffffffffu : (((1u << (hi - lo)) - 1u) << lo);
             mine &= keep;
-            if (j0 / 32 < a.nwords) a.bits[(gi0 + g) * a.nwords + j0 / 32] = mine;
+            a.bits[(gi0 + g) * a.nwords + j0 / 32] = mine;
             if (mine) add_counts(a, gi0 + g, (j0 / 32 - seg_word0(p.n_init)) / (kSegKeys / 32), __popc(mine));
         }
     }

@@ -22,7 +22,7 @@ int main() {
         for (u64 st : strides) {
             if (st > most || st < 256) continue;
             for (int len : {N, (N + 1) / 2, 1}) {                      // a packed batch has shorter sequences
-                for (int start = 0; start < len + 4 * 64; start += 64)  // the 256-row engine loads ahead of the end
+                for (int start = 0; start < len + 4 * 64; start += 64)  // (starts past the end too)
                     for (int row = 0; row < 64; ++row)
                         for (int piece = 0; piece < 16; ++piece) {
                             const u64 want = (u64)std::min(start + row, len - 1) * st + 16 * piece;
