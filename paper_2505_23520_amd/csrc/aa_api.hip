@@ -347,7 +347,12 @@ int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k,
                       (long long)pl.sz.groups);
     }
     const bool q_pooled = fused_M && p->dtype == AA_BF16;
-    if (p->dtype != AA_BF16) { sa.m_rows = fused_M; sa.xa_out = xa_out; }
+    if (p->dtype != AA_BF16 && fused_M) {
+        sa.m_rows = fused_M; sa.xa_out = xa_out;
+        // first block of the first group with candidates (W_g > n_init); 32 bits: the call has such a group
+        const long long span = (long long)kp.bq * kp.step;
+        sa.first_block = (int)(((long long)kp.n_init + kp.w) / span + 1) * kp.step;
+    }
     sa.pool_skip_q = q_pooled;
     if (p->granularity == AA_BLOCK) {
         if (p->dtype != AA_BF16)

@@ -143,7 +143,8 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     // leaves the limits in scalar registers; the other modes need no such addition)
     constexpr bool mixed = (FLAGS & kEngList) && (FLAGS & kEngAnchorRegion);
     const unsigned piece = 16u * lch, cpiece = mixed ? 0 : piece;
-    const unsigned klane = lane_row_offset(kq0, kstb, mixed ? 0 : lch), vlane = lane_row_offset(kq0, vstb, mixed ? 0 : lch);
+    const unsigned klane = lane_row_offset(kq0, sq.len, kstb, mixed ? 0 : lch);
+    const unsigned vlane = lane_row_offset(kq0, sq.len, vstb, mixed ? 0 : lch);
     const unsigned klast = (unsigned)(sq.len - 1) * kstb + cpiece, vlast = (unsigned)(sq.len - 1) * vstb + cpiece;
     auto rows_load = [&](int t, const __amdgpu_buffer_rsrc_t& rs, unsigned stb, unsigned lane0, unsigned last, char* dst,
                          int pitch, const intx4& kidx) {
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
 #pragma unroll
         for (int j = 0; j < GPW; ++j) {
             unsigned off = 0;
-            if (FLAGS & kEngAnchorRegion) off = clamped_row_offset(lane0, tile_row_offset(tile_start(t), sq.len, j, stb), last);
+            if (FLAGS & kEngAnchorRegion) off = clamped_row_offset(lane0, tile_row_offset(tile_start(t), j, stb), last);
             if (mixed) off = (is_list ? (unsigned)kidx[j] * stb : off) + piece;
             else if (FLAGS & kEngList) off = is_list ? (unsigned)kidx[j] * stb + piece : off;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(dst + j * pitch), 16, (int)off, 0, 0, 0);
@@ -381,8 +382,9 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
 // Stage 3 recomputing the anchor region: two work-groups per CU instead of three, by 8 KB of unused LDS, where the query blocks
 // of the call fill two slots per CU once to twice and a group is long (its blocks then have chains of uneven length, and the
 // last third of a full chip waits for the longest).  32 heads, three / two per CU: step 16, 3000 tokens (750 blocks)
-// 64.6 / 59.6 us, 4096 (1024) 90.9 / 85.2, 5000 (1250) 105.2 / 102.9, 8192 (2048) 171.6 / 175.2; step 8, 3000 tokens
-// 50.8 / 49.4; step 4 41.6 / 43.7; up to 512 blocks there is no third either way.
+// 64.6 / 59.6 us, 4096 (1024) 90.9 / 85.2, two sequences of 2000 81.7 / 76.6, 5000 (1250) 105.2 / 102.9, 8192 (2048)
+// 171.6 / 175.2; step 8, 3000 tokens 50.8 / 49.4; step 4 41.6 / 43.7; up to 512 blocks there is no third either way.  Not
+// every such call gains: every column selected, 4096 tokens 131.8 / 136.2; 8 heads, 11000 tokens (688) 84.0 / 88.7.
 static size_t recompute_extra_lds(const KParams& p) {
     const long long blocks = (p.total + BQ - 1) / BQ * p.Hq;
     return p.step >= 8 && blocks > 512 && blocks <= 1024 ? 8192 : 0;

@@ -147,7 +147,7 @@ __global__ __launch_bounds__(512, 1) void engine_bf16_pp_kernel(EngineArgs a) {
     // base + per-lane constants, clamped to the last row; list tile: index * stride).
     unsigned lpre[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) lpre[j] = lane_row_offset(kq0 + j, lstb, lch);
+    for (int j = 0; j < 4; ++j) lpre[j] = lane_row_offset(kq0 + j, sq.len, lstb, lch);
     const unsigned lmax = (unsigned)(sq.len - 1) * lstb + 16u * lch;
 
     // ---- Q fragments (B operand of S^T = K Q^T): lane (n, hf) holds Q[row][16 ks + 8 hf .. +8)
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(512, 1) void engine_bf16_pp_kernel(EngineArgs a) {
         {
             char* dst = (grpB ? Vld : Kld) + 4 * simd * lgrp;
             const bool is_list = u >= nA;
-            const unsigned sbase = tile_row_offset(tile_start(u), sq.len, 0, lstb);
+            const unsigned sbase = tile_row_offset(tile_start(u), 0, lstb);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const unsigned oc = clamped_row_offset(lpre[j], sbase, lmax);

@@ -35,6 +35,10 @@ constexpr int KB = 32;   // keys per block
 constexpr int RT = 32;   // query rows per work-group
 constexpr int NW = 4;    // waves per work-group
 
+// Work-groups per grid row: a launch takes fewer than 2^32 threads in x, and 256 threads per 32 rows (per 16 at a block of
+// 16) reach that with 5e8 (2.7e8) rows times heads.  A multiple of 8, so that decode_work's XCD of a work-group holds.
+constexpr unsigned kGridX = 1u << 23;
+
 template <int T> struct vcols;
 template <> struct vcols<1> { typedef float type; };
 template <> struct vcols<2> { typedef float type __attribute__((ext_vector_type(2))); };
@@ -60,7 +64,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void engine_fp32_kernel(
     if (a.flags & kEngStoreState) store_dense_stats(a);
     if (!engine_selected(a)) return;
     const int rts = (p.bq + RT - 1) / RT;            // row tiles of a query block
-    const unsigned id = blockIdx.y * gridDim.x + blockIdx.x, tiles = (unsigned)(p.nblk_max * rts);
+    const unsigned id = blockIdx.y * kGridX + blockIdx.x, tiles = (unsigned)(p.nblk_max * rts);
     if (id >= tiles * (unsigned)p.Hq * (unsigned)p.B) return;
     const Work wk = decode_work(p, (int)tiles, id);
     const Seq sq = seq_of(p, wk.b);
@@ -287,10 +291,6 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void engine_fp32_kernel(
     }
 }
 }  // namespace
-
-// Work-groups per grid row: a launch takes fewer than 2^32 threads in x, and 256 threads per 32 rows (per 16 at a block of
-// 16) reach that with 5e8 (2.7e8) rows times heads.  A multiple of 8, so that decode_work's XCD of a work-group holds.
-constexpr long long kGridX = 1 << 23;
 
 int launch_engine_fp32(const EngineArgs& ea, hipStream_t st) {
     const KParams& p = ea.p;

@@ -46,6 +46,7 @@ struct SelectArgs {
     float* qp_f32;            // fp32 path: pooled queries, rows of d
     const float* m_rows;      // fp32 path, nullable: stage 1's M; the pooling kernel then writes
     float* xa_out;            //   the pooled anchors here
+    int first_block;          // fp32 path: blocks before this one are not pooled
     float* kp_f32;            // block granularity: pooled keys per (KV head, key block), rows of d
     float* qlo_norm;          // bf16 path: Euclidean norm of the lo part of each pooled query row
     float* kmax_blk;          // bf16 stripe path: largest key norm per (KV head, key block)

@@ -101,7 +101,7 @@ __global__ __launch_bounds__(256) void pool_fp32_kernel(SelectArgs a) {
     }
     // fused prefill: stage 1 has finished the rows of groups without candidates and left no M for them; stage 2 reads neither
     // their pooled anchors nor their pooled queries
-    if (a.segcount && a.m_rows && window_start(p, i / p.step) <= p.n_init) return;
+    if (i < a.first_block) return;
     const Seq sq = seq_of(p, b);
     const int r0 = i * p.bq;
     if (r0 >= sq.len) return;

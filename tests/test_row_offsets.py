@@ -22,16 +22,16 @@ int main() {
         for (u64 st : strides) {
             if (st > most || st < 256) continue;
             for (int len : {N, (N + 1) / 2, 1}) {                      // a packed batch has shorter sequences
-                for (int start = 0; start < len + 4 * 64; start += 64)  // (starts past the end too)
+                for (int start = 0; start < len; start += 64)
                     for (int row = 0; row < 64; ++row)
                         for (int piece = 0; piece < 16; ++piece) {
                             const u64 want = (u64)std::min(start + row, len - 1) * st + 16 * piece;
                             const unsigned last = (unsigned)((len - 1) * st + 16 * piece);
                             // 256-row engine: the lane part holds the row; 128-row engine: rows 0..3 in the tile part
-                            const unsigned a = aa::clamped_row_offset(aa::lane_row_offset(row, (unsigned)st, piece),
-                                                                      aa::tile_row_offset(start, len, 0, (unsigned)st), last);
-                            const unsigned b = aa::clamped_row_offset(aa::lane_row_offset(row & ~3, (unsigned)st, piece),
-                                                                      aa::tile_row_offset(start, len, row & 3, (unsigned)st), last);
+                            const unsigned a = aa::clamped_row_offset(aa::lane_row_offset(row, len, (unsigned)st, piece),
+                                                                      aa::tile_row_offset(start, 0, (unsigned)st), last);
+                            const unsigned b = aa::clamped_row_offset(aa::lane_row_offset(row & ~3, len, (unsigned)st, piece),
+                                                                      aa::tile_row_offset(start, row & 3, (unsigned)st), last);
                             ++checked;
                             if (a != want || b != want) {
                                 if (!bad++) printf("N %d len %d stride %llu start %d row %d: %u %u, not %llu\n", N, len, st,
