@@ -1,30 +1,37 @@
 // fp32 tile engine: the same online-softmax walk as the bf16 engines (stage 1
 // anchor computation, Algorithm 1; stage 3 gathered sparse attention, Algorithm 3;
 // dense causal comparator -- arXiv 2505.23520) with fp32 inputs, fp32 products and
-// fp32 probabilities, on the fp32 matrix instruction v_mfma_f32_32x32x2_f32.
+// fp32 probabilities, on the bf16 matrix instruction.
 //
-// Fragments (the layout of the bf16 engines with k = 2 per instruction): lane (n, hf) = (lane % 32,
-// lane / 32).  S^T = K Q^T: keys = M, query rows = N; k slot hf of step (j, e) is column
-// 8 j + 4 hf + e, so one 16-byte piece of a K row feeds four instructions.  Score register v of lane
-// (n, hf) belongs to query row n and key 8 (v / 4) + 4 hf + v % 4 -- which is exactly the B operand
-// of O^T = V^T P^T if k slot hf of step v is that key: the probabilities never move between lanes.
+// Products: every fp32 value is the exact sum of three bf16 parts (h, m, l: 3 x 8 bits), and a product of two values
+// is six products of parts, hh + hm + mh + mm + hl + lh; the other three are below 2^-24 of it.  Six instructions of
+// 32 matrix cycles for 16 columns take 192 cycles where v_mfma_f32_32x32x2_f32 takes 512.  Scores: the hh products have an
+// accumulator of their own, which sees 8 roundings at d = 128 (64 with the fp32 instruction); relative error of the output
+// against 64 bits, 4000 tokens, d = 128: 8.8e-7 with the fp32 instruction, 5.9e-7 so, and smaller by a third on every size tried.
+//
+// Fragments (the layout of the bf16 engines): lane (n, hf) = (lane % 32, lane / 32).  S^T = K Q^T: keys = M, query
+// rows = N; lane (n, hf) holds columns 16 j + 8 hf .. + 8 of row n.  Score register v of lane (n, hf) belongs to query
+// row n and key 8 (v / 4) + 4 hf + v % 4 -- which is exactly the B operand of O^T = V^T P^T if those are the keys of
+// the k slots: the probabilities never move between lanes.
 // V^T rows are columns of V in any order: row c of column block db is column T c + db (T = d / 32),
 // so a lane's T columns are one wide load and a wave reads two whole V rows at once.
 //
 // Shape: work-group = one tile of 32 query rows = 4 waves that share the rows and split the 32-key
 // blocks among them (block b belongs to wave b % 4); each keeps its own (m, l, O) and they are merged
-// once, through LDS, at the end.  At 64 matrix cycles per instruction 32 keys of K and V (32 KB at
-// d = 128) feed 8192 cycles of a wave, 16 B/clk for a CU: K and V come straight from L2 into
-// registers, the loop has no LDS stage and no barrier, and a gathered row costs what a contiguous one
-// does.  32 rows per work-group keep the chip filled at small sizes, and splitting the keys
+// once, through LDS, at the end.  The loop has no barrier: K goes to LDS of the wave's own, a block ahead, V straight to
+// registers.  32 rows per work-group keep the chip filled at small sizes, and splitting the keys
 // shortens the chain of a short sequence.
-// Bound: the fp32 matrix pipe (157 TFLOP/s nominal; the vector ALU without packed instructions
-// reaches half of that), and on short sequences the chain of one wave's blocks.
-// Measured against vector FMAs over LDS tiles (one work-group per query block, two lanes per row):
-// prefill of 4000 tokens, 8 / 2 heads, d = 128, block 128: 918 -> 155 us; 1024 tokens, 1 head, d = 64: 201 -> 42 us
-// (both with the matching stage-2 kernels); dense causal, 2313 tokens, 2 heads, d = 64: 858 -> 61 us.
+// Bound: the split is 11 vector instructions for two values and nothing shares it between work-groups, 700 of the 1000
+// vector instructions of a block at d = 128 (5.5 cycles each for a lone wave); they run beside the 3072 matrix cycles
+// (8192 with the fp32 instruction).  On short sequences the chain of one wave's blocks, and 15000 cycles of prologue and merge.
+// Measured against the fp32 instruction with K and V straight to registers, kernel times: prefill of 4000 tokens, 8 / 2 heads,
+// d = 128: stage 1 112 -> 68 us (the products 112 -> 84, the order of the tiles 84 -> 75, K through LDS 75 -> 68),
+// stage 3 29 -> 26; 1024 tokens, 1 head, d = 64: 15.1 -> 11.6 and 8.4 -> 7.5; dense causal, 2313 tokens, 2 heads, d = 64:
+// 60 -> 37 us.
 #include "aa_common.h"
 #include "aa_engine.h"
+
+#include <type_traits>
 
 namespace aa {
 
@@ -36,7 +43,7 @@ constexpr int RT = 32;   // query rows per work-group
 constexpr int NW = 4;    // waves per work-group
 
 // Work-groups per grid row: a launch takes fewer than 2^32 threads in x, and 256 threads per 32 rows (per 16 at a block of
-// 16) reach that with 5e8 (2.7e8) rows times heads.  A multiple of 8, so that decode_work's XCD of a work-group holds.
+// 16) reach that with 5e8 (2.7e8) rows times heads.  A multiple of 8, so that decode_tile's XCD of a work-group holds.
 constexpr unsigned kGridX = 1u << 23;
 
 template <int T> struct vcols;
@@ -44,29 +51,118 @@ template <> struct vcols<1> { typedef float type; };
 template <> struct vcols<2> { typedef float type __attribute__((ext_vector_type(2))); };
 template <> struct vcols<4> { typedef float type __attribute__((ext_vector_type(4))); };
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float comp(float x, int) { return x; }
 template <class V> __device__ __forceinline__ float comp(const V& x, int i) { return x[i]; }
 
-template <int D>
-__global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void engine_fp32_kernel(EngineArgs a) {
-    constexpr int T = D / 32;                        // column blocks of O
-    constexpr int NK = D / 8;                        // 16-byte pieces of a K / Q row per lane
-    constexpr int VK = 16 / NK;                      // V rows per K piece
-    constexpr int LAG = D == 128 ? NK / 2 : NK / 4;                      // K pieces (and their share of V rows) not yet in flight
+// Eight fp32 values as three bf16 parts, x = h + m + l exactly (8 + 8 + 8 bits, each rounded to nearest, so the
+// subtractions are exact); finite x below 3.39e38 and parts above the smallest bf16.
+struct Split {
+    uintx4 h, m, l;
+    __device__ __forceinline__ void pair(int i, float x0, float x1) {        // elements 2 i, 2 i + 1
+        auto pack = [](float a, float b) {
+            return __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{a, b}, bf16x2));
+        };
+        const unsigned ph = pack(x0, x1);
+        x0 -= __uint_as_float(ph << 16);
+        x1 -= __uint_as_float(ph & 0xffff0000u);
+        const unsigned pm = pack(x0, x1);
+        x0 -= __uint_as_float(pm << 16);
+        x1 -= __uint_as_float(pm & 0xffff0000u);
+        h[i] = ph; m[i] = pm; l[i] = pack(x0, x1);
+    }
+};
+__device__ __forceinline__ floatx16 mfma_bf16(const uintx4& a, const uintx4& b, const floatx16& c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// Work-group id -> (batch, query head, row tile), the tiles with the longest key ranges first.  Dense attention and lists: the
+// later the tile, the longer.  Anchor region alone: the later in its group, the longer, and the groups side by side.
+// A wave has the chip's matrix and vector pipes nearly to itself at these sizes, so the last round of work-groups lasts as
+// long as its longest tile.  All query heads of a KV head stay on one XCD (its L2) where the heads divide among the XCDs.
+__device__ __forceinline__ Work decode_tile(const KParams& p, unsigned tiles, int rts, bool anchor_only, unsigned id) {
+    const unsigned heads = (unsigned)p.B * p.Hq, pairs = (unsigned)p.B * p.Hkv, grp = (unsigned)p.grp;
+    unsigned x, hb;
+    if (pairs % 8 == 0) {
+        const unsigned slot = id >> 3, per_pair = tiles * grp, within = slot % per_pair;
+        hb = ((id & 7) + 8 * (slot / per_pair)) * grp + within % grp;
+        x = within / grp;
+    } else if (heads % 8 == 0) {
+        const unsigned slot = id >> 3, c = heads / 8;
+        hb = (id & 7) * c + slot % c;
+        x = slot / c;
+    } else {
+        hb = id % heads;
+        x = id / heads;
+    }
+    Work wk;
+    wk.b = (int)(hb / (unsigned)p.Hq);
+    wk.h = (int)(hb % (unsigned)p.Hq);
+    wk.i = (int)(tiles - 1 - x);
+    if (anchor_only) {
+        const unsigned per = (unsigned)p.step * rts, groups = (tiles + per - 1) / per;
+        const unsigned rem = tiles - (groups - 1) * per;             // tiles of the last group
+        const unsigned head = (per - rem) * (groups - 1);            // tiles at positions that it does not have
+        unsigned pos, gr;
+        if (x < head) {
+            pos = per - 1 - x / (groups - 1);
+            gr = x % (groups - 1);
+        } else {
+            pos = rem - 1 - (x - head) / groups;
+            gr = (x - head) % groups;
+        }
+        wk.i = (int)(gr * per + pos);
+    }
+    return wk;
+}
+
+// FLAGS (a combination of kEng*) as in engine_bf16_kernel
+template <int T> __device__ __forceinline__ typename vcols<T>::type buffer_load(__amdgpu_buffer_rsrc_t rs, unsigned off) {
     typedef typename vcols<T>::type vec;
-    __shared__ float obuf[NW][T][16][64];            // every wave's O^T registers
-    __shared__ float mbuf[NW][RT], lbuf[NW][RT];
+    if constexpr (T == 1) return __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 0));
+    else if constexpr (T == 2) return __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, 0));
+    else return __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0));
+}
+
+typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(1))) void global_void;
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }     // vmcnt(0)
+
+// WIDE: a head's rows of K or V span 4 GiB or more (64-bit addresses instead of buffer offsets).  The compiler waits for
+// every load in flight wherever it needs one of them then (its rule for loads of the flat encoding that write to LDS).
+template <int D, int FLAGS, bool WIDE>
+__global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void engine_fp32_kernel(EngineArgs a) {
+    constexpr int flags = FLAGS;
+    constexpr int T = D / 32;                        // column blocks of O
+    constexpr int KS = D / 16;                       // 16-column pieces of a K / Q row
+    constexpr int VK = 8 / KS;                       // V rows requested per piece of K consumed
+    typedef typename vcols<T>::type vec;
+    // Slot j holds piece j of every wave's K block (2 KB a wave) and, after the loop, 8 of every wave's O^T registers.  One
+    // object per slot, so that the compiler can tell that the asynchronous loads into one do not alias the reads from another.
+    __shared__ __attribute__((aligned(16))) floatx4 K0[NW][128], K1[NW][128], K2[NW][128], K3[NW][128], K4[NW][128],
+        K5[NW][128], K6[NW][128], K7[NW][128];
+    auto slot = [&](int j) -> floatx4(*)[128] {      // (j is a constant everywhere: slots beyond KS - 1 do not exist)
+        return j == 0 ? K0 : j == 1 ? K1 : j == 2 ? K2 : j == 3 ? K3 : j == 4 ? K4 : j == 5 ? K5 : j == 6 ? K6 : K7;
+    };
+    constexpr bool QREG = D == 128;                  // the queries' first parts in registers: two work-groups fill the LDS
+    __shared__ union {
+        uintx4 q[QREG ? 2 : 3][KS][64];              // the other parts (m, l) of the query rows
+        struct { float m[NW][RT], l[NW][RT]; } st;   // after the loop
+    } sm;
     const KParams& p = a.p;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int n = lane & 31, hf = lane >> 5;
 
-    if (a.flags & kEngStoreState) store_dense_stats(a);
+    if (flags & kEngStoreState) store_dense_stats(a);
     if (!engine_selected(a)) return;
     const int rts = (p.bq + RT - 1) / RT;            // row tiles of a query block
     const unsigned id = blockIdx.y * kGridX + blockIdx.x, tiles = (unsigned)(p.nblk_max * rts);
     if (id >= tiles * (unsigned)p.Hq * (unsigned)p.B) return;
-    const Work wk = decode_work(p, (int)tiles, id);
+    const Work wk = decode_tile(p, tiles, rts, !(flags & (kEngDense | kEngList)), id);
     const Seq sq = seq_of(p, wk.b);
     const int blk = wk.i / rts;
     const int row0 = blk * p.bq + (wk.i % rts) * RT;             // first row of the tile
@@ -75,15 +171,15 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void engine_fp32_kernel(
     const int hk = wk.h / p.grp;
     const int g = blk / p.step;
     const bool direct = a.direct && window_start(p, g) <= p.n_init;   // no candidates: stage 1 finishes the rows
-    if ((a.flags & kEngLoadState) && direct) return;
+    if ((flags & kEngLoadState) && direct) return;
     const int r = row0 + n;
     const bool rok = r < rend;
     const int rlast = rend - 1;
 
     // ---- block sequence: [initial tokens][window .. diagonal][list]
     int W = 0, ninit = 0, T1 = 0, t2s = 0, nA = 0;
-    if (a.flags & kEngAnchorRegion) {
-        if (!(a.flags & kEngDense)) { W = window_start(p, g); ninit = p.n_init; }
+    if (flags & kEngAnchorRegion) {
+        if (!(flags & kEngDense)) { W = window_start(p, g); ninit = p.n_init; }
         const int e1 = min(ninit, rlast + 1);
         T1 = (e1 + KB - 1) / KB;
         t2s = max(T1, W / KB);
@@ -91,7 +187,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void engine_fp32_kernel(
     }
     int cnt = 0;
     long long lbase = 0;
-    if (a.flags & kEngList) {
+    if (flags & kEngList) {
         const long long t = grp_index(p, sq, wk.b, wk.h, g);
         cnt = a.counts[t];
         lbase = a.offsets[t];
@@ -104,55 +200,119 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void engine_fp32_kernel(
         return t < nA ? min(block_start(t) + n, sq.len - 1) : a.idx[lbase + (long long)(t - nA) * KB + n];
     };
 
-    const float* kb_ = (const float*)a.k + tok_offset(p, p.ks, sq, wk.b, hk, 0) + 4 * hf;
-    const float* vb_ = (const float*)a.v + tok_offset(p, p.vs, sq, wk.b, hk, 0) + T * n;
+    const float* kb_ = (const float*)a.k + tok_offset(p, p.ks, sq, wk.b, hk, 0);
+    const float* vb_ = (const float*)a.v + tok_offset(p, p.vs, sq, wk.b, hk, 0);
+    const float* qsrc = (const float*)a.q + tok_offset(p, p.qs, sq, wk.b, wk.h, rok ? r : row0) + 8 * hf;
 
     int key = key_of(wave), key_next = key_of(wave + NW);
-    floatx4 q[NK], kf[NK];
+    // K: piece j of a block (16 columns of its 32 keys) is two direct-to-LDS loads, in each of which four lanes fetch 64
+    // bytes of a row together: lane 4 i + s the 16 bytes s ^ (i / 2 % 4) of row i, or 16 + i.  (Every lane fetching its own row's
+    // bytes into registers is 64 accesses to the L1 an instruction instead of 16.)  The fragments, lane (n, hf) columns
+    // 8 hf .. + 8 of key n, are read from the slot that only this wave uses; the exchange of the 16-byte places spreads
+    // the reads of eight consecutive rows over the banks.
+    floatx4 frag[2][2];
     vec vf[16];
-    auto load_k = [&](int j, int kk) { kf[j] = *(const floatx4*)(kb_ + (long long)kk * p.ks[2] + 8 * j); };
-    auto load_v = [&](int v, int kk) {
+    const unsigned kstb = (unsigned)p.ks[2] * 4u, vstb = (unsigned)p.vs[2] * 4u;   // token strides in bytes (not WIDE)
+    const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)kb_, 0, (int)((unsigned)(sq.len - 1) * kstb + 4u * D), 0x00020000);
+    const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)vb_, 0, (int)((unsigned)(sq.len - 1) * vstb + 4u * D), 0x00020000);
+    const float *krow0 = nullptr, *krow1 = nullptr;  // of the block whose pieces are being requested (WIDE)
+    unsigned koff0 = 0, koff1 = 0;
+    auto k_rows = [&](int kk) {
+        int src = lane & ~3;                         // byte address of lane (lane / 4)
+        asm volatile("" : "+v"(src));
+        const int k0 = __builtin_amdgcn_ds_bpermute(src, kk), k1 = __builtin_amdgcn_ds_bpermute(src + 64, kk);
+        const int c = 4 * ((lane & 3) ^ (lane >> 3 & 3));
+        if (WIDE) {
+            krow0 = kb_ + (long long)k0 * p.ks[2] + c;
+            krow1 = kb_ + (long long)k1 * p.ks[2] + c;
+        } else {
+            koff0 = (unsigned)k0 * kstb + 4u * c;
+            koff1 = (unsigned)k1 * kstb + 4u * c;
+        }
+    };
+    auto load_k = [&](int j) {                       // asynchronous
+        lds_void *d0 = (lds_void*)&slot(j)[wave][0], *d1 = (lds_void*)&slot(j)[wave][64];
+        if (WIDE) {
+            __builtin_amdgcn_global_load_lds((const global_void*)(krow0 + 16 * j), d0, 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((const global_void*)(krow1 + 16 * j), d1, 16, 0, 0);
+        } else {
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, d0, 16, (int)koff0, 64 * j, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, d1, 16, (int)koff1, 64 * j, 0, 0);
+        }
+    };
+    const int kr0 = 4 * n + (2 * hf ^ (n >> 1 & 3)), kr1 = 4 * n + ((2 * hf + 1) ^ (n >> 1 & 3));
+    auto read_k = [&](int j) {
+        frag[j & 1][0] = slot(j)[wave][kr0];
+        frag[j & 1][1] = slot(j)[wave][kr1];
+    };
+    // The lane's row of V, as a byte offset; it goes to the lanes that read it (a product per row and lane instead would be
+    // 64 bits wide in the WIDE form).  A lane's T columns are one load, a wave reads two whole rows with each.
+    int vlo = 0, vhi = 0;
+    auto v_rows = [&](int kk) {
+        if (WIDE) {
+            const long long off = (long long)kk * p.vs[2] * 4;
+            vlo = (int)off; vhi = (int)(off >> 32);
+        } else {
+            vlo = (int)((unsigned)kk * vstb);
+        }
+    };
+    // rows of loads v .. v + N - 1: every exchange is issued before the first result is waited for
+    auto load_v = [&](int v, auto count) {
+        constexpr int N = decltype(count)::value;
+        unsigned lo[N], hi[N];
         int src = 16 * hf;                           // byte address of lane 4 hf, opaque: 16 sums are not kept in registers
         asm volatile("" : "+v"(src));
-        const int row = __builtin_amdgcn_ds_bpermute(src + 4 * (8 * (v >> 2) + (v & 3)), kk);
-        vf[v] = *(const vec*)(vb_ + (long long)row * p.vs[2]);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int from = src + 4 * (8 * ((v + i) >> 2) + ((v + i) & 3));
+            lo[i] = (unsigned)__builtin_amdgcn_ds_bpermute(from, vlo);
+            if (WIDE) hi[i] = (unsigned)__builtin_amdgcn_ds_bpermute(from, vhi);
+        }
+        return [=, &vf](int i) {                     // the load itself
+            if (WIDE) vf[v + i] = *(const vec*)((const char*)(vb_ + T * n) + (long long)((unsigned long long)hi[i] << 32 | lo[i]));
+            else vf[v + i] = buffer_load<T>(vrs, lo[i] + 4u * T * n);
+        };
     };
-    {
-        const float* src = (const float*)a.q + tok_offset(p, p.qs, sq, wk.b, wk.h, rok ? r : row0) + 4 * hf;
+    k_rows(key);
 #pragma unroll
-        for (int j = 0; j < NK; ++j) q[j] = *(const floatx4*)(src + 8 * j);
+    for (int j = 0; j < KS; ++j) load_k(j);
+    // the waves share the rows: each splits its part of them
+    uintx4 qreg[QREG ? KS : 1];
+    Split own[(KS + NW - 1) / NW];
+#pragma unroll
+    for (int i = 0; i < (KS + NW - 1) / NW; ++i) {
+        const int j = i * NW + wave;
+        if (j >= KS) break;
+        const floatx4 x = *(const floatx4*)(qsrc + 16 * j), y = *(const floatx4*)(qsrc + 16 * j + 4);
+        own[i].pair(0, x[0], x[1]); own[i].pair(1, x[2], x[3]); own[i].pair(2, y[0], y[1]); own[i].pair(3, y[2], y[3]);
+        sm.q[0][j][lane] = own[i].h;
+        sm.q[1][j][lane] = own[i].l;
+        if (!QREG) sm.q[QREG ? 0 : 2][j][lane] = own[i].m;
     }
+    if (QREG) {                                      // the first parts go on to every wave's registers, the second in their place
+        __syncthreads();
 #pragma unroll
-    for (int j = 0; j < NK - LAG; ++j) load_k(j, key);
+        for (int j = 0; j < KS; ++j) qreg[QREG ? j : 0] = sm.q[0][j][lane];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < (KS + NW - 1) / NW; ++i) sm.q[0][i * NW + wave][lane] = own[i].m;
+    }
 
     const float c2 = p.sigma * 1.4426950408889634f;  // exp(sigma*x) = exp2(c2*x)
     float m = -INFINITY, l = 0.f;                    // l: this lane's keys only
     floatx16 o[T];
+    auto reset = [&]() {
+        m = -INFINITY; l = 0.f;
 #pragma unroll
-    for (int db = 0; db < T; ++db)
+        for (int db = 0; db < T; ++db)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
-
-    // K pieces and V rows go through the registers in one stream: K pieces of a block, its V rows, K pieces
-    // of the wave's next block.  Each is requested NK - LAG pieces (half to three quarters of K's share) ahead of its use,
-    // into registers whose contents the products have just used; the order is pinned with scheduling fences.
-#pragma unroll 1
-    for (int t = wave; t < nT; t += NW) {
-        // two accumulation chains: half the rounding error of one (measured against 64 bits: d = 128 outputs
-        // 1.5e-6 off with one chain), and no product waits for the one before it
-        floatx16 s2[2] = {kZero16, kZero16};
-#pragma unroll
-        for (int j = 0; j < NK; ++j) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                s2[e & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][e], q[j][e], s2[e & 1], 0, 0, 0);
-#pragma unroll
-            for (int u = 0; u < VK; ++u)
-                if (j >= LAG) load_v((j - LAG) * VK + u, key);
-            if (j < LAG) load_k(j + NK - LAG, key);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        floatx16 s = s2[0] + s2[1];
+            for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
+    };
+    reset();
+    // scores of block t -> probabilities; updates m and l, rescales o
+    auto softmax = [&](int t, floatx16& s) {
         if (t < nA) {
             // key j is visible to row r iff j <= r and (j < ninit or j >= W); the lane's part of j,
             // 4 hf, is taken off the limits instead
@@ -198,59 +358,189 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void engine_fp32_kernel(
             rs += s[v];
         }
         l += rs;
-        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // K pieces are requested a block ahead, into the slot whose contents have just been split, V rows half during the scores of
+    // their block, half before its softmax.  The split of a piece is spread between the products of the one before; the order is pinned with
+    // scheduling fences.
+    Split sp[2];
+    auto split_k = [&](Split& d, int j, int i) {     // elements 2 i, 2 i + 1 of piece j
+        const floatx4& x = frag[j & 1][i >> 1];
+        d.pair(i, x[2 * (i & 1)], x[2 * (i & 1) + 1]);
+    };
+    auto split_v = [&](Split& d, int u, int i) {     // piece u: 16-key half u / T, column block u % T
+        const int v = 8 * (u / T) + 2 * i;
+        d.pair(i, comp(vf[v], u % T), comp(vf[v + 1], u % T));
+    };
+    __syncthreads();                                 // the query parts are there
+    read_k(0);
+    read_k(1);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
+    for (int i = 0; i < 4; ++i) split_k(sp[0], 0, i);
+#pragma unroll 1
+    for (int t = wave; t < nT; t += NW) {
+        // Two accumulation chains.  Of the nine products of the parts the three below 2^-24 of the largest are left out.
+        floatx16 s2[2] = {kZero16, kZero16};
+        v_rows(key);
+        key = key_next;
+        key_next = key_of(t + 2 * NW);
+        k_rows(key);
 #pragma unroll
-            for (int db = 0; db < T; ++db)
-                o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(comp(vf[v], db), s[v], o[db], 0, 0, 0);
-            if (v + VK * (NK - LAG) < 16) load_v(v + VK * (NK - LAG), key);
-            if (v == VK * LAG - 1) {
-                key = key_next;
-                key_next = key_of(t + 2 * NW);
-            }
-            if (v >= VK * LAG && v % VK == 0) load_k(v / VK - LAG, key);
+        for (int j = 0; j < KS; ++j) {
+            const Split& k = sp[j & 1];
+            Split& nx = sp[(j + 1) & 1];
+            const uintx4 qh = QREG ? qreg[QREG ? j : 0] : sm.q[0][j][lane];
+            const uintx4 qm = sm.q[QREG ? 0 : 2][j][lane], ql = sm.q[1][j][lane];
+            const auto next_v = load_v(j * VK, std::integral_constant<int, VK>());
+            const bool more = j + 1 < KS;
             __builtin_amdgcn_sched_barrier(0);
+            load_k(j);                               // of the next block: piece j of this one has been split
+            if (j + 2 < KS) read_k(j + 2);
+            __builtin_amdgcn_sched_barrier(0);
+            s2[1] = mfma_bf16(k.l, qh, s2[1]);
+            if (more) split_k(nx, j + 1, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            s2[1] = mfma_bf16(k.h, ql, s2[1]);
+            if (more) split_k(nx, j + 1, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            s2[1] = mfma_bf16(k.m, qm, s2[1]);
+            if (more) split_k(nx, j + 1, 2);
+            __builtin_amdgcn_sched_barrier(0);
+            s2[1] = mfma_bf16(k.m, qh, s2[1]);
+            if (more) split_k(nx, j + 1, 3);
+            __builtin_amdgcn_sched_barrier(0);
+            s2[0] = mfma_bf16(k.h, qh, s2[0]);
+            s2[1] = mfma_bf16(k.h, qm, s2[1]);
+#pragma unroll
+            for (int u = 0; u < VK; ++u) next_v(u);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        floatx16 s = s2[0] + s2[1];
+        {
+            const auto next_v = load_v(8, std::integral_constant<int, 8>());
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int v = 0; v < 8; ++v) next_v(v);   // (requested with the others they spill)
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        softmax(t, s);
+        Split pr[2];                                 // probabilities of the block's 16-key halves
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) pr[c].pair(i, s[8 * c + 2 * i], s[8 * c + 2 * i + 1]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) split_v(sp[0], 0, i);
+#pragma unroll
+        for (int u = 0; u < 2 * T; ++u) {
+            const Split& v = sp[u & 1];
+            Split& nx = sp[(u + 1) & 1];
+            const Split& x = pr[u / T];
+            floatx16& acc = o[u % T];
+            auto next = [&](int i) {
+                if (u + 1 < 2 * T) split_v(nx, u + 1, i);
+                else split_k(nx, 0, i);              // of the next block
+            };
+            __builtin_amdgcn_sched_barrier(0);
+            if (u == 2 * T - 1) { read_k(0); read_k(1); }        // of the next block
+            __builtin_amdgcn_sched_barrier(0);
+            acc = mfma_bf16(v.l, x.h, acc);
+            next(0);
+            __builtin_amdgcn_sched_barrier(0);
+            acc = mfma_bf16(v.h, x.l, acc);
+            next(1);
+            __builtin_amdgcn_sched_barrier(0);
+            acc = mfma_bf16(v.m, x.m, acc);
+            next(2);
+            __builtin_amdgcn_sched_barrier(0);
+            acc = mfma_bf16(v.m, x.h, acc);
+            next(3);
+            __builtin_amdgcn_sched_barrier(0);
+            acc = mfma_bf16(v.h, x.m, acc);
+            acc = mfma_bf16(v.h, x.h, acc);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+
+    wait_loads();                                    // (of a block that does not exist; the slots are about to be written)
+    // the cached state that this lane merges, requested before the waves wait for each other (before the loop: 16 more registers)
+    const long long ri = row_index(p, sq, wk.b, wk.h, rok ? r : row0);
+    const long long col0 = T * (8 * wave + 4 * hf);
+    floatx4 acc0[T];
+    float m0 = -INFINITY, l0 = 0.f;
+    if (flags & kEngLoadState) {
+        m0 = a.Min[ri];
+        l0 = a.Lin[ri];
+#pragma unroll
+        for (int c = 0; c < T; ++c) acc0[c] = *(const floatx4*)(a.Accin + ri * D + col0 + 4 * c);
+    }
+    // An infinite input, or one that its first part rounds to infinity, has no such parts (inf - inf): a wave whose
+    // results are not all finite takes its blocks again with the fp32 instruction, which gives what infinities give.
+    {
+        float z = 0.f * l;
+#pragma unroll
+        for (int db = 0; db < T; ++db)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) z = fmaf(0.f, o[db][v], z);
+        if (__builtin_expect(__any(!(z == 0.f)), 0)) {
+            reset();
+#pragma unroll 1
+            for (int t = wave; t < nT; t += NW) {
+                const int kk = key_of(t);
+                const float* ksrc = kb_ + 4 * hf + (long long)kk * p.ks[2];
+                floatx16 s2[2] = {kZero16, kZero16};
+#pragma unroll 1
+                for (int c = 0; c < D; c += 8) {     // k slot hf of step e is column c + 4 hf + e
+                    const floatx4 x = *(const floatx4*)(ksrc + c), y = *(const floatx4*)(qsrc - 4 * hf + c);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        s2[e & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], s2[e & 1], 0, 0, 0);
+                }
+                floatx16 s = s2[0] + s2[1];
+                softmax(t, s);
+                v_rows(kk);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {       // k slot hf of step v is key 8 (v / 4) + 4 hf + v % 4
+                    load_v(v, std::integral_constant<int, 1>())(0);
+#pragma unroll
+                    for (int db = 0; db < T; ++db)
+                        o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(comp(vf[v], db), s[v], o[db], 0, 0, 0);
+                }
+            }
         }
     }
 
     // ---- merge the four waves' states.  Wave w finishes O^T registers 4 w .. 4 w + 3 of every column
     // block: of row n the columns T (8 w + 4 hf) .. + 4 T - 1.
     l += __shfl_xor(l, 32, 64);
+    __syncthreads();                                 // the query parts are no longer read
 #pragma unroll
     for (int db = 0; db < T; ++db)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) obuf[wave][db][v][lane] = o[db][v];
-    if (hf == 0) { mbuf[wave][n] = m; lbuf[wave][n] = l; }
+        for (int v = 0; v < 16; ++v) ((float*)slot(2 * db + (v >> 3))[wave])[64 * (v & 7) + lane] = o[db][v];
+    if (hf == 0) { sm.st.m[wave][n] = m; sm.st.l[wave][n] = l; }
     __syncthreads();
 
-    const long long ri = row_index(p, sq, wk.b, wk.h, rok ? r : row0);
-    float mall = -INFINITY, m0 = -INFINITY, l0 = 0.f;
-    if (a.flags & kEngLoadState) {
-        m0 = a.Min[ri] / p.sigma;
-        l0 = a.Lin[ri];
+    float mall = -INFINITY;
+    if (flags & kEngLoadState) {
+        m0 = m0 / p.sigma;
         mall = m0;
     }
     float mw[NW];
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-        mw[w] = mbuf[w][n];
+        mw[w] = sm.st.m[w][n];
         mall = fmaxf(mall, mw[w]);
     }
     auto scale_of = [&](float x) -> float {          // a part that has seen no key counts for nothing
         return x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((x - mall) * c2);
     };
     float lall = 0.f, res[4 * T];                    // res[T e + db]: column T (8 wave + 4 hf) + T e + db
-    const long long col0 = T * (8 * wave + 4 * hf);
-    if (a.flags & kEngLoadState) {
+    if (flags & kEngLoadState) {
         const float f0 = scale_of(m0);
         lall = l0 * f0;
 #pragma unroll
-        for (int c = 0; c < 4 * T; c += 4) {
-            const floatx4 x = *(const floatx4*)(a.Accin + ri * D + col0 + c);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) res[c + e] = x[e] * f0;
-        }
+        for (int c = 0; c < 4 * T; ++c) res[c] = acc0[c / 4][c % 4] * f0;
     } else {
 #pragma unroll
         for (int c = 0; c < 4 * T; ++c) res[c] = 0.f;
@@ -258,22 +548,25 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void engine_fp32_kernel(
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
         const float f = scale_of(mw[w]);
-        lall = fmaf(lbuf[w][n], f, lall);
+        lall = fmaf(sm.st.l[w][n], f, lall);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int db = 0; db < T; ++db) res[T * e + db] = fmaf(obuf[w][db][4 * wave + e][lane], f, res[T * e + db]);
+            for (int db = 0; db < T; ++db) {
+                const float* ow = (const float*)(wave < 2 ? slot(2 * db)[w] : slot(2 * db + 1)[w]);      // registers 4 wave + e
+                res[T * e + db] = fmaf(ow[64 * ((4 * wave + e) & 7) + lane], f, res[T * e + db]);
+            }
     }
 
     float ms = mall * p.sigma;
     if (!rok) return;
     const bool first = wave == 0 && hf == 0;
-    bool store_out = (a.flags & kEngStoreOut) != 0;
-    if ((a.flags & kEngStoreState) && direct) {
+    bool store_out = (flags & kEngStoreOut) != 0;
+    if ((flags & kEngStoreState) && direct) {
         // what stage 3 makes of a cached state and an empty list, bit for bit
         ms = ms / p.sigma * p.sigma;
         store_out = true;
-    } else if (a.flags & kEngStoreState) {
+    } else if (flags & kEngStoreState) {
         if (first) { a.Mout[ri] = ms; a.Lout[ri] = lall; }
         if (a.Accout) {
             float* dst = a.Accout + ri * D + col0;
@@ -296,11 +589,25 @@ int launch_engine_fp32(const EngineArgs& ea, hipStream_t st) {
     const KParams& p = ea.p;
     const long long total = (long long)p.nblk_max * ((p.bq + RT - 1) / RT) * p.Hq * p.B;
     const dim3 grid((unsigned)(total < kGridX ? total : kGridX), (unsigned)((total + kGridX - 1) / kGridX));
-    switch (p.d) {
-        case 32: return (int)launch_kernel(engine_fp32_kernel<32>, grid, dim3(64 * NW), 0, st, ea);
-        case 64: return (int)launch_kernel(engine_fp32_kernel<64>, grid, dim3(64 * NW), 0, st, ea);
-        case 128: return (int)launch_kernel(engine_fp32_kernel<128>, grid, dim3(64 * NW), 0, st, ea);
-        default: return -1;
+    const long long stride = p.ks[2] > p.vs[2] ? p.ks[2] : p.vs[2];
+    const bool wide = stride >= (1ll << 30) || (long long)p.N * stride >= (1ll << 30);
+    switch ((p.d * 64 + ea.flags) * 2 + wide) {
+#define AA_ENGINE_CASE(d, F, w) \
+    case (((d) * 64 + (F)) * 2 + w): return (int)launch_kernel(engine_fp32_kernel<(d), (F), w>, grid, dim3(64 * NW), 0, st, ea);
+#define AA_ENGINE_CASES(d, w)                                            \
+    AA_ENGINE_CASE(d, kEngAnchorRegion | kEngStoreState, w)              \
+    AA_ENGINE_CASE(d, kEngList | kEngLoadState | kEngStoreOut, w)        \
+    AA_ENGINE_CASE(d, kEngList | kEngAnchorRegion | kEngStoreOut, w)     \
+    AA_ENGINE_CASE(d, kEngAnchorRegion | kEngDense | kEngStoreOut, w)
+    AA_ENGINE_CASES(32, false)
+    AA_ENGINE_CASES(64, false)
+    AA_ENGINE_CASES(128, false)
+    AA_ENGINE_CASES(32, true)
+    AA_ENGINE_CASES(64, true)
+    AA_ENGINE_CASES(128, true)
+#undef AA_ENGINE_CASES
+#undef AA_ENGINE_CASE
+    default: return -1;
     }
 }
 

@@ -135,6 +135,62 @@ def test_fp32_grid_beyond_32_bits_of_threads(api):
     assert not got[0][1].isnan().any() and bool((got[1][1] == got[0][1]).all())
 
 
+def _dense(api, q, k, v):
+    out = torch.empty(q.shape, dtype=q.dtype, device="cuda")
+    p = api.make_params(api.Config(block=32), q, k, v, out)
+    lse = torch.empty(api.anchor_sizes(p).rows, device="cuda")
+    api.dense_causal_flash(p, q, k, v, out, lse)
+    return out, lse
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_fp32_infinities(api, d):
+    """What has no bf16 parts: infinite keys (score -inf) and values, and a key entry that bf16 rounds to infinity."""
+    N, gen = 300, torch.Generator().manual_seed(d)
+    q, k, v = (torch.randn(1, 1, N, d, generator=gen) for _ in range(3))
+    q[..., 0] = q[..., 0].abs() + 0.1
+    k[0, 0, 7, 0] = -math.inf                        # no row attends key 7
+    q[..., 1] = 1e-38
+    k[0, 0, 40, 1] = 3.4e38
+    v[0, 0, 128, 3] = math.inf                       # (seen by every row of its 32-row tile: hidden, it would give 0 x inf)
+    out, lse = _dense(api, q.cuda(), k.cuda(), v.cuda())
+    s = (q[0, 0].double() @ k[0, 0].double().T) / math.sqrt(d)
+    s.masked_fill_(torch.ones(N, N, dtype=torch.bool).triu(1), -math.inf)
+    want = torch.softmax(s, dim=1)
+    want[:, 7] = 0
+    inf_col = v[0, 0].clone()
+    inf_col[128, 3] = 0
+    ref = want @ inf_col.double()
+    ref[128:, 3] = math.inf
+    got = out[0, 0].cpu().double()
+    assert torch.equal(got.isinf(), ref.isinf())
+    fin = ref.isfinite()
+    assert (got[fin] - ref[fin]).abs().max() < 1e-5   # (the file's bound for fp32 outputs)
+    assert (lse.cpu().double() - torch.logsumexp(s, dim=1)).abs().max() < 1e-5
+
+
+def test_fp32_rows_beyond_32_bit_offsets(api):
+    """Keys 16 MiB apart: 300 of them span 4.7 GiB and are addressed with 64 bits, to the same bits."""
+    N, d, gen = 300, 64, torch.Generator(device="cuda").manual_seed(1)
+    q, k, v = (torch.randn(1, 2, N, d, generator=gen, device="cuda") for _ in range(3))
+    far = torch.empty(N * (1 << 22), device="cuda")
+    kf = torch.as_strided(far, (1, 2, N, d), (0, d, 1 << 22, 1))
+    vf = torch.as_strided(far, (1, 2, N, d), (0, d, 1 << 22, 1), 2 * d)
+    kf.copy_(k)
+    vf.copy_(v)
+    a, b = _dense(api, q, k, v), _dense(api, q, kf, vf)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    cfg = api.Config(block=32, n_init=16, window=32, step=2, theta=3.0)
+    outs = []
+    for kk, vv in ((k, v), (kf, vf)):
+        out = torch.empty_like(q)
+        p = api.make_params(cfg, q, kk, vv, out)
+        ws = torch.empty(api.anchor_sizes(p).prefill_ws_bytes, dtype=torch.uint8, device="cuda")
+        api.anchor_attention_prefill(p, q, kk, vv, out, None, None, ws)
+        outs.append(out)
+    assert torch.equal(outs[0], outs[1])
+
+
 # ------------------------------------------------------------------ bf16 MFMA path
 @pytest.mark.parametrize("N,step,n_init,window,theta", [
     (2048, 1, 128, 128, 3.5),
