@@ -135,7 +135,7 @@ __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70
 // WIDE: a head's rows of K or V span 4 GiB or more (64-bit addresses instead of buffer offsets).  The compiler waits for
 // every load in flight wherever it needs one of them then (its rule for loads of the flat encoding that write to LDS).
 template <int D, int FLAGS, bool WIDE>
-__global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void engine_fp32_kernel(EngineArgs a) {
+__global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32_kernel(EngineArgs a) {
     constexpr int flags = FLAGS;
     constexpr int T = D / 32;                        // column blocks of O
     constexpr int KS = D / 16;                       // 16-column pieces of a K / Q row
