@@ -279,6 +279,19 @@ bool direct_ok(const aa_params* p) { return p->dtype != AA_BF16 || p->engine != 
 // the 128-row engine's stage 1 also leaves the key norms of the stripe mask and its cleared counters
 bool pooled_keys(const aa_params* p) { return p->granularity == AA_STRIPE && direct_ok(p); }
 
+// Fused prefill without the cached state: stage 1 leaves the row maxima's means only, stage 3 attends the anchor region again, to
+// the same bits.  At step 1 the region is (n_init + window) / 64 + 2 tiles of keys; finding its maxima costs half of
+// attending it, the state's way through memory (128 KB per block and direction with M, L and Acc) three to four tiles.
+// 32 / 8 heads, n_init = window = 128, cached / again: 4096 tokens (1024 blocks) 80.5 / 81.4 us, 8192 150 / 142, 16384
+// 324 / 281, 30011 592 / 552, two sequences of 5000 198 / 171, every column selected 16384 1995 / 1990; with 8 / 8 heads,
+// 9000 tokens (568 blocks) 67.7 / 68.3; 1000 tokens 36.0 / 37.3 (a chip that is not full pays for the longer chain of a block).
+// 16384 tokens with n_init + window = 512: 367 / 348, 640: 393 / 392.  An even step could take the 256-row engine, a step of 3
+// has two tiles more.
+bool recompute_anchor(const Plan& pl, const aa_params* p) {
+    const long long blocks = (pl.kp.total + p->block_q - 1) / p->block_q * p->Hq;
+    return p->dtype == AA_BF16 && p->step == 1 && (long long)p->n_init + p->window <= 512 && blocks >= 1536 && direct_ok(p);
+}
+
 // sel_ws (nullable): a stripe_select workspace (with the call's counts); the bf16 engines then also leave the pooled queries of
 // stage 2 there, and the fp32 path leaves the pooled anchors to run_select (which is told so).
 // out (nullable), lse, stats: see EngineArgs::direct
@@ -298,6 +311,12 @@ int run_anchor(const Plan& pl, const aa_params* p, const void* q, const void* k,
             ea.kmax_blk = (float*)(sel_ws + pl.sel_kmax);
             ea.zero_counts = counts; ea.zero_seg = (int*)(sel_ws + pl.sel_segc); ea.nseg = (int)cdiv(pl.nwords, 64);
         }
+    }
+    if (!M) {                                        // fused prefill that keeps no state (see recompute_anchor)
+        ea.groups_total = pl.sz.groups;
+        if (!pl.kp.use_anchor) ea.xa = nullptr;
+        return engine_status(launch_anchor_max_bf16(ea, (unsigned)((long long)pl.kp.nblk_max * pl.kp.Hq * pl.kp.B), st),
+                             "anchor_max_bf16_kernel");
     }
     const int rc = launch_engine(pl, p, ea, st);
     if (rc != AA_OK || p->dtype == AA_BF16 || sel_ws || !xa) return rc;
@@ -515,13 +534,15 @@ int anchor_attention_prefill(const aa_params* params, const void* q, const void*
     const bool direct = direct_ok(params);
     if (direct && no_candidates(pl.kp))
         return run_anchor(pl, params, q, k, v, M, L, Acc, nullptr, nullptr, nullptr, out, lse, stats, st);
-    rc = run_anchor(pl, params, q, k, v, M, L, Acc, xa, w + pl.pf_sel, counts, direct ? out : nullptr, lse, nullptr,
-                    st);
+    const bool again = recompute_anchor(pl, params);
+    rc = run_anchor(pl, params, q, k, v, again ? nullptr : M, L, Acc, xa, w + pl.pf_sel, counts,
+                    direct && !again ? out : nullptr, lse, nullptr, st);
     if (rc != AA_OK) return rc;
     rc = run_select(pl, params, q, k, xa, counts, offsets, idx, pl.sz.idx_capacity_max, flag, w + pl.pf_sel, M, xa,
                     stats, st);
     if (rc != AA_OK) return rc;
-    rc = run_sparse(pl, params, q, k, v, M, L, Acc, counts, offsets, idx, pl.sz.idx_capacity_max, out, lse, direct, st);
+    rc = run_sparse(pl, params, q, k, v, again ? nullptr : M, L, Acc, counts, offsets, idx, pl.sz.idx_capacity_max, out, lse,
+                    direct && !again, st);
     if (rc != AA_OK) return rc;
     return AA_OK;
 }

@@ -71,6 +71,8 @@ __device__ __forceinline__ bool engine_selected(const EngineArgs& a) {
 // Launchers: the launch's hipError_t, or -1 if there is no instantiation for ea.flags.
 // 128 query rows per work-group, one instantiation per mode
 int launch_engine_bf16(const EngineArgs& ea, unsigned grid, hipStream_t st);
+// stage 1 without M, L and Acc: pooled anchors (ea.xa nullable) and what else stage 2 needs, 128 rows per work-group
+int launch_anchor_max_bf16(const EngineArgs& ea, unsigned grid, hipStream_t st);
 // 256 query rows (two consecutive blocks) per work-group; needs dense mode or an even step
 int launch_engine_bf16_pp(const EngineArgs& ea, unsigned grid, hipStream_t st);
 

@@ -43,9 +43,56 @@
 #include "aa_pool.h"
 #include "aa_rows.h"
 
+#include <type_traits>
+
 namespace aa {
 
 using namespace eng;
+
+namespace {
+// Work-group barrier that leaves vector-memory operations in flight.  LDS operand reads before it
+// have been consumed by their MFMAs and the tile loads it publishes were awaited; the fences only
+// keep the compiler from moving work across it.
+__device__ __forceinline__ void bare_barrier() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// What stage 2 needs of a query block, from the work-group that holds it: the pooled query (Algorithm 2, avgpool of Q) from the
+// fragments in registers, the key norms of the block, the pooled anchor (mean of M over its rows).  ms: M of the
+// lane's row.
+__device__ __forceinline__ void stage2_exports(const EngineArgs& a, const Seq& sq, const Work& wk, int hk, const bf16x8 (&qf)[8],
+                                               float (*qpart)[128], float* red, float* knorm, int row0, int rlast, int wave,
+                                               int lane, bool rok, float ms) {
+    const KParams& p = a.p;
+    const int tid = 64 * wave + lane, n = lane & 31, hf = lane >> 5;
+    if (a.qp_hi) {
+        float s0, s1;
+        pool_wave_columns(qf, n, s0, s1);
+        pool_block_finish(qpart, wave, n, hf, s0, s1, tid, rlast - row0 + 1,
+                          blk_index(p, sq, wk.b, wk.h, wk.i), true, a.qp_hi, a.qp_lo, a.qlo_norm);
+    }
+    // the key norms of block i of a KV head fall to one of the head's query heads, in turn (its rows were the
+    // last tiles of the loop)
+    if (a.kmax_blk && wk.h % p.grp == wk.i % p.grp)
+        key_block_norm((const unsigned short*)a.k + tok_offset(p, p.ks, sq, wk.b, hk, 0), p.ks[2], row0, rlast + 1, tid,
+                       knorm, a.kmax_blk + kblk_index(p, sq, wk.b, hk, wk.i));
+    if (a.xa) {
+        float red_m = (rok && hf == 0) ? ms : 0.f;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) red_m += __shfl_xor(red_m, off, 64);
+        if (lane == 0) red[wave] = red_m;
+        __syncthreads();
+        if (tid == 0) {
+            const int nrows = rlast - row0 + 1;
+            a.xa[blk_index(p, sq, wk.b, wk.h, wk.i)] = (red[0] + red[1] + red[2] + red[3]) / (float)nrows;
+        }
+    }
+}
+}  // namespace
 
 // FLAGS (a combination of kEng*) is a compile-time parameter: every mode gets its own code without
 // the other modes' branches, registers and, above all, merged control-flow paths (where paths with
@@ -107,7 +154,6 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
         lbase = a.offsets[t];
     }
     const int nL = (cnt + TK - 1) / TK;
-    const int nT = nA + nL;
 
     // K / V rows of this KV head are fetched with raw buffer loads: scalar base, 32-bit byte offsets
     const unsigned short* kb_ = (const unsigned short*)a.k + tok_offset(p, p.ks, sq, wk.b, hk, 0);
@@ -128,66 +174,58 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     auto tile_start = [&](int t) -> int {            // first key of contiguous tile t (t < nA)
         return TK * (t < T1 ? t : t2s + (t - T1));
     };
-    // Keys of a list tile come from the index list.  Tile t's are fetched into kidx0 / kidx1 (by the
-    // parity of t) two steps ahead: its K rows are loaded in step t - 1, its V rows in step t.
+    // Keys of a list tile come from the index list.  Tile c's are fetched into kidx0 / kidx1 (by the
+    // parity of c) two steps ahead: its K rows are loaded in step c - 1, its V rows in step c.
     // Nothing else ever writes these registers: a vector-ALU write to registers that may still
     // be the target of an outstanding load makes the compiler wait for every outstanding load,
     // the asynchronous tile loads included.  Keys of a contiguous tile are plain arithmetic.
     intx4 kidx0 = {0, 0, 0, 0}, kidx1 = {0, 0, 0, 0};
-    auto idx_prefetch = [&](int t, intx4& kidx) {
-        if (t >= nA && t < nT) kidx = *(const intx4*)(a.idx + lbase + (long long)(t - nA) * TK + kq0);
+    auto idx_prefetch = [&](int c, intx4& kidx) {
+        if (c < nL) kidx = *(const intx4*)(a.idx + lbase + (long long)c * TK + kq0);
     };
     // asynchronous: completion is awaited by wait_vmem()
     // (no branch: the byte offsets of a contiguous tile are clamped to the sequence's last row)
-    // (contiguous and list tiles in one loop: the lane's 16-byte piece is added after the choice between the two, which
-    // leaves the limits in scalar registers; the other modes need no such addition)
+    // LIST (here and below): tile t of the list, else contiguous tile t
+    // (contiguous and list tiles in one kernel: the lane's 16-byte piece is added after the clamp, which leaves the limits in
+    // scalar registers; the other modes need no such addition)
     constexpr bool mixed = (FLAGS & kEngList) && (FLAGS & kEngAnchorRegion);
     const unsigned piece = 16u * lch, cpiece = mixed ? 0 : piece;
     const unsigned klane = lane_row_offset(kq0, sq.len, kstb, mixed ? 0 : lch);
     const unsigned vlane = lane_row_offset(kq0, sq.len, vstb, mixed ? 0 : lch);
     const unsigned klast = (unsigned)(sq.len - 1) * kstb + cpiece, vlast = (unsigned)(sq.len - 1) * vstb + cpiece;
-    auto rows_load = [&](int t, const __amdgpu_buffer_rsrc_t& rs, unsigned stb, unsigned lane0, unsigned last, char* dst,
-                         int pitch, const intx4& kidx) {
-        const bool is_list = (FLAGS & kEngList) && t >= nA;
+    auto rows_load = [&](auto list, int t, const __amdgpu_buffer_rsrc_t& rs, unsigned stb, unsigned lane0, unsigned last,
+                         char* dst, int pitch, const intx4& kidx) {
 #pragma unroll
         for (int j = 0; j < GPW; ++j) {
-            unsigned off = 0;
-            if (FLAGS & kEngAnchorRegion) off = clamped_row_offset(lane0, tile_row_offset(tile_start(t), j, stb), last);
-            if (mixed) off = (is_list ? (unsigned)kidx[j] * stb : off) + piece;
-            else if (FLAGS & kEngList) off = is_list ? (unsigned)kidx[j] * stb + piece : off;
+            unsigned off;
+            if (decltype(list)::value) off = (unsigned)kidx[j] * stb + piece;
+            else off = clamped_row_offset(lane0, tile_row_offset(tile_start(t), j, stb), last) + (mixed ? piece : 0);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(dst + j * pitch), 16, (int)off, 0, 0, 0);
         }
     };
-    auto k_load = [&](int t, char* Kb, const intx4& kidx) {
-        rows_load(t, krs, kstb, klane, klast, Kb + GPW * wave * KGRP, KGRP, kidx);
+    auto k_load = [&](auto list, int t, char* Kb, const intx4& kidx) {
+        rows_load(list, t, krs, kstb, klane, klast, Kb + GPW * wave * KGRP, KGRP, kidx);
     };
-    auto v_load = [&](int t, const intx4& kidx) { rows_load(t, vrs, vstb, vlane, vlast, Vs0 + GPW * wave * VGRP, VGRP, kidx); };
-    // Work-group barrier that leaves vector-memory operations in flight.  LDS operand reads before it
-    // have been consumed by their MFMAs and the tile loads it publishes were awaited; the fences only
-    // keep the compiler from moving work across it.
-    auto bare_barrier = [&]() {
-        __builtin_amdgcn_sched_barrier(0);
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
+    auto v_load = [&](auto list, int t, const intx4& kidx) {
+        rows_load(list, t, vrs, vstb, vlane, vlast, Vs0 + GPW * wave * VGRP, VGRP, kidx);
     };
 
     // The first list indices are requested before everything else: the first tile's loads need them,
     // and only them, so they go out while the Q fragments and the cached state are still on their way
     // (waits are in issue order: behind those loads the indices would arrive last).
-    if (nT > 0) idx_prefetch(0, kidx0);
+    idx_prefetch(0, kidx0);
 
+    constexpr std::integral_constant<bool, false> contiguous{};
+    constexpr std::integral_constant<bool, true> listed{};
     // ---- Q fragments (B operand of S^T = K Q^T): lane (n, hf) holds Q[row][16 ks + 8 hf .. +8)
     bf16x8 qf[8];
     load_q_fragments(qf, a, sq, wk.b, wk.h, r, rok, 0, hf);
 
     // ---- pipeline prologue: the first K tile goes out ahead of the cached state, which is not needed
     // before the first P V block
-    if (nT > 0) {
-        k_load(0, Ks0, kidx0);
-        idx_prefetch(1, kidx1);
-    }
+    if (flags & kEngAnchorRegion) k_load(contiguous, 0, Ks0, kidx0);     // (a block has its diagonal tile)
+    else if (nL > 0) k_load(listed, 0, Ks0, kidx0);
+    if (!(flags & kEngAnchorRegion)) idx_prefetch(1, kidx1);
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- running state (see load_state)
@@ -209,31 +247,28 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     const int ls = lane & 15, lg = lane >> 4;
     const int voff = (4 * hf + (ls >> 2)) * VGRP + 32 * (lg & 1) + 8 * (ls & 3);
 
-    auto tile_step = [&](int t, const char* Kcur, char* Knext, intx4& kcur, intx4& knext) __attribute__((always_inline)) {
-        v_load(t, kcur);
-        idx_prefetch(t + 2, kcur);
+    auto tile_step = [&](auto list, int t, int nT, const char* Kcur, char* Knext, intx4& kcur, intx4& knext)
+                         __attribute__((always_inline)) {
+        constexpr bool LIST = decltype(list)::value;
+        v_load(list, t, kcur);
+        if (LIST) idx_prefetch(t + 2, kcur);
         __builtin_amdgcn_sched_barrier(0);           // the wait below counts on this issue order
         // the next K tile (past the end the last one again, into a stage nobody reads): gathered rows go out now,
         // contiguous ones, which L2 serves, after the softmax, out of the way of the V tile (-1 %; gathered rows
         // issued there cost 29 %)
-        if (FLAGS & kEngList) k_load(min(t + 1, nT - 1), Knext, knext);
+        if (LIST) k_load(list, min(t + 1, nT - 1), Knext, knext);
         const char* Kb = Kcur + koff;
         const char* Vb = Vs0 + voff;
 
         // S^T = K Q^T : s[kb], 32 keys x 32 rows each.  Masks (tiles that touch a region
         // boundary, the diagonal or a list tail) enter as the initial accumulator: 0 for a
         // visible (key, row) pair, -inf otherwise; the common unmasked tile starts from literal 0.
-        int mode = 0, t0 = 0;
-        if (t < nA) {
-            t0 = tile_start(t);
-            const bool interior = (t0 + TK - 1 <= rw) && (t0 + TK <= ninit || t0 >= W);
-            mode = interior ? 0 : 1;
-        } else if (t == nT - 1 && (cnt & (TK - 1))) {
-            mode = 2;
-        }
+        const int t0 = LIST ? 0 : tile_start(t);
+        const bool masked = LIST ? t == nT - 1 && (cnt & (TK - 1))
+                                 : !((t0 + TK - 1 <= rw) && (t0 + TK <= ninit || t0 >= W));
         // a contiguous tile that starts beyond this wave's last row is hidden from all its rows
         // (the work-group still needs it for its later rows): nothing to compute
-        const bool on = !(t < nA && t0 > rw + 31);
+        const bool on = LIST || t0 <= rw + 31;
         bf16x8 pf[2][2];  // [kb][s16]
         if (on) {
             floatx16 s[2];
@@ -245,7 +280,7 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) read_k(i);
                 __builtin_amdgcn_sched_barrier(0);
-                if (__builtin_expect(mode == 0, 1)) {
+                if (__builtin_expect(!masked, 1)) {
 #pragma unroll
                     for (int kb = 0; kb < 2; ++kb)
                         s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb], qf[0], kZero16, 0, 0, 0);
@@ -255,9 +290,8 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
                     // (jl = 32 kb + 8 (v / 4) + 4 hf + v % 4: the lane's part is taken off the limits instead)
                     // (with the lane opaque, the 32 comparisons are not hoisted out of the loop either)
                     const int ln = counted_lane(), h4 = 4 * (ln >> 5);
-                    const int jr = (mode == 1 ? rw - t0 + (ln & 31) : cnt - (t - nA) * TK - 1) - h4;
-                    const int jn = (mode == 1 ? ninit - t0 : TK) - h4;
-                    const int jw = W - t0 - h4;
+                    const int jr = (LIST ? cnt - t * TK - 1 : rw - t0 + (ln & 31)) - h4;
+                    const int jn = ninit - t0 - h4, jw = W - t0 - h4;
 #pragma unroll
                     for (int kb = 0; kb < 2; ++kb) {
                         floatx16 bias;
@@ -265,7 +299,7 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
                         for (int v = 0; v < 16; ++v) {
                             const int jc = 32 * kb + 8 * (v >> 2) + (v & 3);
                             bool ok = jc <= jr;
-                            if (FLAGS & kEngAnchorRegion) ok = ok & ((jc < jn) | (jc >= jw));
+                            if (!LIST) ok = ok & ((jc < jn) | (jc >= jw));
                             bias[v] = ok ? 0.f : -INFINITY;
                         }
                         s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb], qf[0], bias, 0, 0, 0);
@@ -285,9 +319,9 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
             softmax_tile(s, pf, c2, rescale_gap, mref, mtrue, l, o);
             __builtin_amdgcn_s_setprio(2);
         }
-        if (!(FLAGS & kEngList)) {
+        if (!LIST) {
             __builtin_amdgcn_sched_barrier(0);
-            k_load(min(t + 1, nT - 1), Knext, knext);
+            k_load(list, min(t + 1, nT - 1), Knext, knext);
             __builtin_amdgcn_sched_barrier(0);
         }
         // V tile t has landed (vmcnt(4): the four loads of the next K tile are younger)
@@ -319,10 +353,27 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
         wait_vmem();                                 // next K tile has landed in LDS
         bare_barrier();
     };
-    for (int t = 0; t < nT; t += 2) {
-        tile_step(t, Ks0, Ks1, kidx0, kidx1);
-        if (t + 1 < nT) tile_step(t + 1, Ks1, Ks0, kidx1, kidx0);
+    auto tile_loop = [&](auto list, int nT) __attribute__((always_inline)) {
+        for (int t = 0; t < nT; t += 2) {
+            tile_step(list, t, nT, Ks0, Ks1, kidx0, kidx1);
+            if (t + 1 < nT) tile_step(list, t + 1, nT, Ks1, Ks0, kidx1, kidx0);
+        }
+    };
+    if (flags & kEngAnchorRegion) tile_loop(contiguous, nA);
+    if (mixed) {
+        // Anchor region, then list: a loop for each (in one loop for both every list tile pays for the choice between the two).
+        // In between the state is put in the form in which stage 1 caches it, so the result is the same with and
+        // without a cached state, bit for bit.
+        if (nL > 0) k_load(listed, 0, Ks0, kidx0);
+        idx_prefetch(1, kidx1);                      // (its registers are needed in the first loop)
+        float lt = row_sum(l);
+        const float ms = rebase_state(a, c2, mref, mtrue, lt, o);
+        mref = mtrue = ms / p.sigma;
+        l = hf == 0 ? lt : 0.f;
+        wait_vmem();
+        bare_barrier();
     }
+    if (flags & kEngList) tile_loop(listed, nL);
 
     // ---- epilogue
     // The tile stages are free now (every wave has passed the barrier that ends the last tile):
@@ -340,30 +391,7 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     if (flags & kEngStoreState) {
         const float ms = rebase_state(a, c2, mref, mtrue, lt, o);
         // (the state goes out last: the barriers in between would wait for its stores to drain)
-        if (a.qp_hi) {
-            // pooled query of the block (Algorithm 2, avgpool of Q) from the fragments in registers
-            float s0, s1;
-            pool_wave_columns(qf, n, s0, s1);
-            pool_block_finish(qpart, wave, n, hf, s0, s1, tid, rlast - row0 + 1,
-                              blk_index(p, sq, wk.b, wk.h, wk.i), true, a.qp_hi, a.qp_lo, a.qlo_norm);
-        }
-        // the key norms of block i of a KV head fall to one of the head's query heads, in turn (its rows were the
-        // last tiles of the loop)
-        if (a.kmax_blk && wk.h % p.grp == wk.i % p.grp)
-            key_block_norm((const unsigned short*)a.k + tok_offset(p, p.ks, sq, wk.b, hk, 0), p.ks[2], row0, rlast + 1, tid,
-                           knorm, a.kmax_blk + kblk_index(p, sq, wk.b, hk, wk.i));
-        if (a.xa) {
-            // pooled anchor of the block: mean of M over its rows (Algorithm 2, avgpool of the anchor)
-            float red_m = (rok && hf == 0) ? ms : 0.f;
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) red_m += __shfl_xor(red_m, off, 64);
-            if (lane == 0) red[wave] = red_m;
-            __syncthreads();
-            if (tid == 0) {
-                const int nrows = rlast - row0 + 1;
-                a.xa[blk_index(p, sq, wk.b, wk.h, wk.i)] = (red[0] + red[1] + red[2] + red[3]) / (float)nrows;
-            }
-        }
+        stage2_exports(a, sq, wk, hk, qf, qpart, red, knorm, row0, rlast, wave, lane, rok, ms);
         if (!direct) {
             store_state(a, ri, tile, rok, wave_rows > 0, lane, hf, ms, lt, o);
         } else if (wave_rows > 0) {
@@ -378,6 +406,101 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     }
 }
 
+// Stage 1 for a stage 3 that attends the anchor region itself: the row maxima, of which only the pooled anchor is kept, and
+// the other things that stage 2 needs.  The scores are those of engine_bf16_kernel, instruction by instruction, so the maxima
+// are the same bits.  One barrier per tile.
+__global__ __launch_bounds__(256, 4) void anchor_max_bf16_kernel(EngineArgs a) {
+    __shared__ __attribute__((aligned(16))) char Ks0[KBYTES], Ks1[KBYTES];
+    __shared__ float red[4], knorm[4], qpart[4][128];
+    const KParams& p = a.p;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 31, hf = lane >> 5;
+    if (a.kmax_blk)
+        clear_counters(a.zero_counts, a.groups_total, a.zero_seg, a.nseg, blockIdx.x * 256ll + tid, gridDim.x * 256ll);
+    const Work wk = decode_work(p, p.nblk_max, blockIdx.x);
+    const Seq sq = seq_of(p, wk.b);
+    const int row0 = wk.i * BQ;
+    if (row0 >= sq.len) return;
+    const int hk = wk.h / p.grp;
+    const int rw = row0 + 32 * wave, r = rw + n;
+    const bool rok = r < sq.len;
+    const int rlast = min(row0 + BQ, sq.len) - 1;
+    const int W = window_start(p, wk.i / p.step), ninit = p.n_init;
+    const int T1 = (min(ninit, rlast + 1) + TK - 1) / TK, t2s = max(T1, W / TK);
+    const int nA = a.xa ? T1 + max(0, rlast / TK + 1 - t2s) : 0;     // (xa null: the anchors are not compared with)
+    auto tile_start = [&](int t) -> int { return TK * (t < T1 ? t : t2s + (t - T1)); };
+
+    const unsigned kstb = (unsigned)p.ks[2] * 2u;
+    const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)((const unsigned short*)a.k + tok_offset(p, p.ks, sq, wk.b, hk, 0)), 0,
+        (int)((unsigned)(sq.len - 1) * kstb + 2u * D), 0x00020000);
+    const int lch = lane & 15, kq0 = 16 * (lane >> 4) + 4 * wave;
+    const unsigned klane = lane_row_offset(kq0, sq.len, kstb, lch), klast = (unsigned)(sq.len - 1) * kstb + 16u * lch;
+    auto k_load = [&](int t, char* Kb) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, (lds_void*)(Kb + (4 * wave + j) * KGRP), 16,
+                                                     (int)clamped_row_offset(klane, tile_row_offset(tile_start(t), j, kstb), klast),
+                                                     0, 0, 0);
+    };
+    bf16x8 qf[8];
+    load_q_fragments(qf, a, sq, wk.b, wk.h, r, rok, 0, hf);
+    __builtin_amdgcn_sched_barrier(0);               // the waits below count on this order
+    if (nA > 0) k_load(0, Ks0);
+    const int koff = (n & 15) * KGRP + (n >> 4) * 256 + 16 * hf;
+    float mtrue = -INFINITY;
+    auto tile_step = [&](int t, const char* Kcur, char* Kld) __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+        wait_vmem();                                 // tile t is there
+        bare_barrier();                              // everywhere, and the stage of tile t - 1 has been read
+        k_load(min(t + 1, nA - 1), Kld);
+        __builtin_amdgcn_sched_barrier(0);
+        const char* Kb = Kcur + koff;
+        const int t0 = tile_start(t);
+        if (t0 > rw + 31) return;                    // hidden from all rows of the wave
+        floatx16 s[2];
+        bf16x8 kf[16];
+        auto read_k = [&](int i) { kf[i] = *(const bf16x8*)(Kb + 512 * (i & 1) + 32 * (i >> 1)); };
+#pragma unroll
+        for (int i = 0; i < 6; ++i) read_k(i);
+        if (__builtin_expect((t0 + TK - 1 <= rw) && (t0 + TK <= ninit || t0 >= W), 1)) {
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+                s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb], qf[0], kZero16, 0, 0, 0);
+        } else {
+            const int ln = counted_lane(), h4 = 4 * (ln >> 5);
+            const int jr = rw - t0 + (ln & 31) - h4, jn = ninit - t0 - h4, jw = W - t0 - h4;
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                floatx16 bias;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int jc = 32 * kb + 8 * (v >> 2) + (v & 3);
+                    bias[v] = ((jc <= jr) & ((jc < jn) | (jc >= jw))) ? 0.f : -INFINITY;
+                }
+                s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb], qf[0], bias, 0, 0, 0);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 2; i < 16; ++i) {
+            s[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i], qf[i >> 1], s[i & 1], 0, 0, 0);
+            if (i + 4 < 16) read_k(i + 4);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) mtrue = fmaxf(fmaxf(mtrue, s[0][v]), s[1][v]);
+    };
+#pragma unroll 1
+    for (int t = 0; t < nA; t += 2) {
+        tile_step(t, Ks0, Ks1);
+        if (t + 1 < nA) tile_step(t + 1, Ks1, Ks0);
+    }
+    wait_vmem();
+    float ma, mb;
+    both_halves(mtrue, ma, mb);
+    stage2_exports(a, sq, wk, hk, qf, qpart, red, knorm, row0, rlast, wave, lane, rok, fmaxf(ma, mb) * p.sigma);
+}
 
 // Stage 3 recomputing the anchor region: two work-groups per CU instead of three, by 8 KB of unused LDS, where the query blocks
 // of the call fill two slots per CU once to twice and a group is long (its blocks then have chains of uneven length, and the
@@ -401,6 +524,10 @@ int launch_engine_bf16(const EngineArgs& ea, unsigned grid, hipStream_t st) {
 #undef AA_ENGINE_CASE
     default: return -1;
     }
+}
+
+int launch_anchor_max_bf16(const EngineArgs& ea, unsigned grid, hipStream_t st) {
+    return (int)launch_kernel(anchor_max_bf16_kernel, dim3(grid), dim3(256), 0, st, ea);
 }
 
 }  // namespace aa

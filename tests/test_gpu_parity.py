@@ -209,6 +209,44 @@ def test_bf16_pipeline(api, N, step, n_init, window, theta):
         assert 0 < worst["selected"] < worst["candidates"]
 
 
+@pytest.mark.parametrize("lens,Hq,Hkv,n_init,window,theta,use_anchor,granularity", [
+    ([6145], 32, 8, 128, 128, 2.8, True, 0),          # last block of one row
+    ([900, 0, 3333, 129], 64, 8, 100, 60, 2.7, True, 0),     # packed, an empty sequence, region bounds inside tiles
+    ([1500], 128, 128, 0, 0, 2.2, True, 0),           # no sink, no window
+    ([1900, 1700], 64, 32, 512, 0, 3.0, True, 0),     # the first blocks without candidates
+    ([3100], 64, 16, 128, 256, 0.3, False, 0),        # anchors not compared with: no scores in stage 1
+    ([3100], 64, 16, 128, 256, 3.0, True, 1),         # one decision per key block
+    ([6200], 32, 8, 128, 128, -1e30, True, 0),        # empty lists
+])
+def test_step1_prefill_keeps_no_state(api, engine_mode, lens, Hq, Hkv, n_init, window, theta, use_anchor, granularity):
+    """The fused call at step 1 attends the anchor region in stage 3: the same bits as the stages with the cached state."""
+    gen = torch.Generator(device="cuda").manual_seed(Hq + lens[0])
+    packed = len(lens) > 1
+    total = sum(lens)
+    assert Hq * ((total + 127) // 128) >= 1536       # (where the call takes this path)
+    q, k, v = (torch.randn(h, total, 128, generator=gen, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv))
+    k[:, :4] += 2 * q[::Hq // Hkv, :1]
+    cu = torch.tensor([0] + list(np.cumsum(lens)), dtype=torch.int32, device="cuda") if packed else None
+    if not packed:
+        q, k, v = q[None], k[None], v[None]
+    cfg = api.Config(block=128, n_init=n_init, window=window, step=1, theta=theta, use_anchor=use_anchor,
+                     granularity=granularity, engine=engine_mode)
+    out, want = torch.zeros_like(q), torch.zeros_like(q)
+    p = api.make_params(cfg, q, k, v, out, cu_seqlens=cu, max_seqlen=max(lens))
+    b = api.alloc_stage_buffers(p)
+    api.anchor_compute(p, q, k, v, b["M"], b["L"], b["Acc"], b["xa"])
+    api.stripe_select(p, q, k, b["xa"], b["counts"], b["offsets"], b["idx"], b["flag"], b["ws"])
+    api.sparse_attn(p, q, k, v, b["M"], b["L"], b["Acc"], b["counts"], b["offsets"], b["idx"], want, b["lse"])
+    lse, stats = torch.empty_like(b["lse"]), torch.zeros(4, dtype=torch.int64, device="cuda")
+    ws = torch.full((b["sizes"].prefill_ws_bytes,), 255, dtype=torch.uint8, device="cuda")
+    api.anchor_attention_prefill(p, q, k, v, out, lse, stats, ws)
+    assert torch.equal(out, want) and torch.equal(lse, b["lse"])
+    groups = Hq * sum((n + 127) // 128 for n in lens)
+    slots = b["counts"].view(Hq, -1)[:, :groups // Hq]
+    assert int(stats[1]) == int(slots.sum())
+    assert (int(stats[1]) > 0) == (theta > -1e29)
+
+
 def test_bf16_short_sequences(api):
     for N in (1, 50, 128, 129):
         wl = _wl("t", "bf16", [N], 2, 1, 128, 128, 40 + N, 0)
