@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "aa_div.h"
+
 namespace aa {
 
 constexpr int kLane = 64;          // wavefront width on CDNA4
@@ -33,6 +35,9 @@ struct KParams {
     long long total;        // packed: total tokens
     long long blk_cap, grp_cap;
     int nblk_max, ngrp_max; // blocks / groups of the longest sequence
+    // divisors of the work-group maps: Hq / Hkv, Hkv, step, bq, and the blocks (pairs of blocks) of the longest sequence times
+    // Hq / Hkv
+    FastDiv by_grp, by_hkv, by_step, by_bq, by_pair, by_pair2;
 };
 
 // Where sequence b lives.
@@ -49,11 +54,10 @@ __device__ __forceinline__ Seq seq_of(const KParams& p, int b) {
         return s;
     }
     long long blk = 0, grp = 0;
-    const int span = p.bq * p.step;
     for (int i = 0; i < b; ++i) {
-        int len = p.cu[i + 1] - p.cu[i];
-        blk += (len + p.bq - 1) / p.bq;
-        grp += (len + span - 1) / span;
+        const unsigned nb = p.by_bq.div((unsigned)(p.cu[i + 1] - p.cu[i] + p.bq - 1));
+        blk += nb;
+        grp += p.by_step.div(nb + p.step - 1);
     }
     s.len = p.cu[b + 1] - p.cu[b];
     s.tok0 = p.cu[b];
@@ -98,23 +102,22 @@ __device__ __forceinline__ int window_start(const KParams& p, int g) {
 // heads of one KV head on one XCD (its K/V stay in that XCD's L2) and hands out
 // the longest query blocks first (causal work grows with the block index).
 struct Work { int b, h, i; };
-__device__ __forceinline__ Work decode_work(const KParams& p, int nblk, unsigned id) {
+// per_pair: nblk * Hq / Hkv
+__device__ __forceinline__ Work decode_work(const KParams& p, int nblk, const FastDiv& per_pair, unsigned id) {
     Work wk;
-    const unsigned pairs = (unsigned)p.B * p.Hkv;
-    const unsigned per_pair = (unsigned)nblk * p.grp;
     unsigned pr, within;
-    if (pairs % 8 == 0) {
-        unsigned xcd = id & 7, slot = id >> 3;
-        pr = xcd + 8 * (slot / per_pair);
-        within = slot % per_pair;
+    if ((unsigned)p.B * p.Hkv % 8 == 0) {
+        const unsigned xcd = id & 7, slot = id >> 3, q = per_pair.div(slot);
+        pr = xcd + 8 * q;
+        within = slot - q * per_pair.d;
     } else {
-        pr = id / per_pair;
-        within = id % per_pair;
+        pr = per_pair.div(id);
+        within = id - pr * per_pair.d;
     }
-    wk.b = pr / p.Hkv;
-    int hk = pr % p.Hkv;
-    wk.h = hk * p.grp + (within % p.grp);
-    wk.i = nblk - 1 - (int)(within / p.grp);
+    wk.b = (int)p.by_hkv.div(pr);
+    const unsigned i = p.by_grp.div(within);
+    wk.h = (int)(pr * p.grp - (unsigned)wk.b * p.Hq + (within - i * p.grp));
+    wk.i = nblk - 1 - (int)i;
     return wk;
 }
 

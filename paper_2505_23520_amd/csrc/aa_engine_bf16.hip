@@ -63,34 +63,42 @@ __device__ __forceinline__ void bare_barrier() {
 
 // What stage 2 needs of a query block, from the work-group that holds it: the pooled query (Algorithm 2, avgpool of Q) from the
 // fragments in registers, the key norms of the block, the pooled anchor (mean of M over its rows).  ms: M of the
-// lane's row.
+// lane's row.  EARLY: the keys are requested ahead of the pooling (32 registers more at its peak).
+template <bool EARLY>
 __device__ __forceinline__ void stage2_exports(const EngineArgs& a, const Seq& sq, const Work& wk, int hk, const bf16x8 (&qf)[8],
                                                float (*qpart)[128], float* red, float* knorm, int row0, int rlast, int wave,
                                                int lane, bool rok, float ms) {
     const KParams& p = a.p;
     const int tid = 64 * wave + lane, n = lane & 31, hf = lane >> 5;
+    // the key norms of block i of a KV head fall to one of the head's query heads, in turn (its rows were the
+    // last tiles of the loop)
+    const bool norms = a.kmax_blk && wk.h - hk * p.grp == wk.i - (int)p.by_grp.div(wk.i) * p.grp;
+    KeyNorm kn;
+    auto load_keys = [&]() {
+        if (norms)
+            kn.load((const unsigned short*)a.k + tok_offset(p, p.ks, sq, wk.b, hk, 0), p.ks[2], row0, rlast + 1, tid);
+    };
+    if (EARLY) load_keys();
     if (a.qp_hi) {
         float s0, s1;
         pool_wave_columns(qf, n, s0, s1);
-        pool_block_finish(qpart, wave, n, hf, s0, s1, tid, rlast - row0 + 1,
-                          blk_index(p, sq, wk.b, wk.h, wk.i), true, a.qp_hi, a.qp_lo, a.qlo_norm);
+        pool_block_put(qpart, wave, n, hf, s0, s1);
     }
-    // the key norms of block i of a KV head fall to one of the head's query heads, in turn (its rows were the
-    // last tiles of the loop)
-    if (a.kmax_blk && wk.h % p.grp == wk.i % p.grp)
-        key_block_norm((const unsigned short*)a.k + tok_offset(p, p.ks, sq, wk.b, hk, 0), p.ks[2], row0, rlast + 1, tid,
-                       knorm, a.kmax_blk + kblk_index(p, sq, wk.b, hk, wk.i));
+    if (!EARLY) load_keys();
     if (a.xa) {
-        float red_m = (rok && hf == 0) ? ms : 0.f;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) red_m += __shfl_xor(red_m, off, 64);
+        const float red_m = wave_reduce<1>((rok && hf == 0) ? ms : 0.f, [](float x, float y) { return x + y; });
         if (lane == 0) red[wave] = red_m;
-        __syncthreads();
-        if (tid == 0) {
-            const int nrows = rlast - row0 + 1;
-            a.xa[blk_index(p, sq, wk.b, wk.h, wk.i)] = (red[0] + red[1] + red[2] + red[3]) / (float)nrows;
-        }
     }
+    if (norms) {
+        const float big = kn.wave_max();
+        if (lane == 0) knorm[wave] = big;
+    }
+    __syncthreads();                                 // one barrier, then a wave for each of the three
+    const int nrows = rlast - row0 + 1;
+    const long long bi = blk_index(p, sq, wk.b, wk.h, wk.i);
+    if (wave == 0 && a.qp_hi) pool_block_write(qpart, lane, nrows, bi, a.qp_hi, a.qp_lo, a.qlo_norm);
+    if (wave == 1 && lane == 0 && a.xa) a.xa[bi] = (red[0] + red[1] + red[2] + red[3]) / (float)nrows;
+    if (wave == 2 && lane == 0 && norms) a.kmax_blk[kblk_index(p, sq, wk.b, hk, wk.i)] = KeyNorm::block(knorm);
 }
 }  // namespace
 
@@ -119,7 +127,7 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
             clear_counters(a.zero_counts, a.groups_total, a.zero_seg, a.nseg, blockIdx.x * 256ll + tid, gridDim.x * 256ll);
     }
     if (!engine_selected(a)) return;
-    const Work wk = decode_work(p, p.nblk_max, blockIdx.x);
+    const Work wk = decode_work(p, p.nblk_max, p.by_pair, blockIdx.x);
     const Seq sq = seq_of(p, wk.b);
     const int row0 = wk.i * BQ;
     if (row0 >= sq.len) return;
@@ -127,8 +135,8 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     // for its MFMA blocks and drops it for its softmax, so a wave with matrix work wins over
     // siblings that are in their vector-ALU part, and they do not settle into lockstep.
     __builtin_amdgcn_s_setprio(2);
-    const int hk = wk.h / p.grp;
-    const int g = wk.i / p.step;
+    const int hk = (int)p.by_grp.div(wk.h);
+    const int g = (int)p.by_step.div(wk.i);
     const bool direct = a.direct && window_start(p, g) <= p.n_init;   // no candidates: stage 1 finishes the rows
     if ((flags & kEngLoadState) && direct) return;
     const int rw = row0 + 32 * wave;                 // first row of this wave
@@ -391,7 +399,7 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     if (flags & kEngStoreState) {
         const float ms = rebase_state(a, c2, mref, mtrue, lt, o);
         // (the state goes out last: the barriers in between would wait for its stores to drain)
-        stage2_exports(a, sq, wk, hk, qf, qpart, red, knorm, row0, rlast, wave, lane, rok, ms);
+        if (a.xa) stage2_exports<false>(a, sq, wk, hk, qf, qpart, red, knorm, row0, rlast, wave, lane, rok, ms);
         if (!direct) {
             store_state(a, ri, tile, rok, wave_rows > 0, lane, hf, ms, lt, o);
         } else if (wave_rows > 0) {
@@ -408,8 +416,11 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
 
 // Stage 1 for a stage 3 that attends the anchor region itself: the row maxima, of which only the pooled anchor is kept, and
 // the other things that stage 2 needs.  The scores are those of engine_bf16_kernel, instruction by instruction, so the maxima
-// are the same bits.  One barrier per tile.
-__global__ __launch_bounds__(256, 4) void anchor_max_bf16_kernel(EngineArgs a) {
+// are the same bits.  Bound: a block is six tiles at step 1, 3000 matrix cycles a wave, between the latencies of its query rows
+// and of its exports; so a work-group walks every gridDim.x-th block (all blocks cost the same) and requests the next block's
+// query rows ahead of the exports of this one.  16384 tokens, 32 heads: about 60 us with a work-group per block, 50 so (the whole call
+// 2 % faster); its compulsory bytes take 34 us.
+__global__ __launch_bounds__(256, 3) void anchor_max_bf16_kernel(EngineArgs a, unsigned total) {
     __shared__ __attribute__((aligned(16))) char Ks0[KBYTES], Ks1[KBYTES];
     __shared__ float red[4], knorm[4], qpart[4][128];
     const KParams& p = a.p;
@@ -417,89 +428,122 @@ __global__ __launch_bounds__(256, 4) void anchor_max_bf16_kernel(EngineArgs a) {
     const int n = lane & 31, hf = lane >> 5;
     if (a.kmax_blk)
         clear_counters(a.zero_counts, a.groups_total, a.zero_seg, a.nseg, blockIdx.x * 256ll + tid, gridDim.x * 256ll);
-    const Work wk = decode_work(p, p.nblk_max, blockIdx.x);
-    const Seq sq = seq_of(p, wk.b);
-    const int row0 = wk.i * BQ;
-    if (row0 >= sq.len) return;
-    const int hk = wk.h / p.grp;
-    const int rw = row0 + 32 * wave, r = rw + n;
-    const bool rok = r < sq.len;
-    const int rlast = min(row0 + BQ, sq.len) - 1;
-    const int W = window_start(p, wk.i / p.step), ninit = p.n_init;
-    const int T1 = (min(ninit, rlast + 1) + TK - 1) / TK, t2s = max(T1, W / TK);
-    const int nA = a.xa ? T1 + max(0, rlast / TK + 1 - t2s) : 0;     // (xa null: the anchors are not compared with)
-    auto tile_start = [&](int t) -> int { return TK * (t < T1 ? t : t2s + (t - T1)); };
-
-    const unsigned kstb = (unsigned)p.ks[2] * 2u;
-    const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)((const unsigned short*)a.k + tok_offset(p, p.ks, sq, wk.b, hk, 0)), 0,
-        (int)((unsigned)(sq.len - 1) * kstb + 2u * D), 0x00020000);
-    const int lch = lane & 15, kq0 = 16 * (lane >> 4) + 4 * wave;
-    const unsigned klane = lane_row_offset(kq0, sq.len, kstb, lch), klast = (unsigned)(sq.len - 1) * kstb + 16u * lch;
-    auto k_load = [&](int t, char* Kb) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, (lds_void*)(Kb + (4 * wave + j) * KGRP), 16,
-                                                     (int)clamped_row_offset(klane, tile_row_offset(tile_start(t), j, kstb), klast),
-                                                     0, 0, 0);
-    };
-    bf16x8 qf[8];
-    load_q_fragments(qf, a, sq, wk.b, wk.h, r, rok, 0, hf);
-    __builtin_amdgcn_sched_barrier(0);               // the waits below count on this order
-    if (nA > 0) k_load(0, Ks0);
     const int koff = (n & 15) * KGRP + (n >> 4) * 256 + 16 * hf;
-    float mtrue = -INFINITY;
-    auto tile_step = [&](int t, const char* Kcur, char* Kld) __attribute__((always_inline)) {
-        __builtin_amdgcn_sched_barrier(0);
-        wait_vmem();                                 // tile t is there
-        bare_barrier();                              // everywhere, and the stage of tile t - 1 has been read
-        k_load(min(t + 1, nA - 1), Kld);
-        __builtin_amdgcn_sched_barrier(0);
-        const char* Kb = Kcur + koff;
-        const int t0 = tile_start(t);
-        if (t0 > rw + 31) return;                    // hidden from all rows of the wave
-        floatx16 s[2];
-        bf16x8 kf[16];
-        auto read_k = [&](int i) { kf[i] = *(const bf16x8*)(Kb + 512 * (i & 1) + 32 * (i >> 1)); };
-#pragma unroll
-        for (int i = 0; i < 6; ++i) read_k(i);
-        if (__builtin_expect((t0 + TK - 1 <= rw) && (t0 + TK <= ninit || t0 >= W), 1)) {
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-                s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb], qf[0], kZero16, 0, 0, 0);
-        } else {
-            const int ln = counted_lane(), h4 = 4 * (ln >> 5);
-            const int jr = rw - t0 + (ln & 31) - h4, jn = ninit - t0 - h4, jw = W - t0 - h4;
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                floatx16 bias;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int jc = 32 * kb + 8 * (v >> 2) + (v & 3);
-                    bias[v] = ((jc <= jr) & ((jc < jn) | (jc >= jw))) ? 0.f : -INFINITY;
-                }
-                s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb], qf[0], bias, 0, 0, 0);
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 2; i < 16; ++i) {
-            s[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i], qf[i >> 1], s[i & 1], 0, 0, 0);
-            if (i + 4 < 16) read_k(i + 4);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) mtrue = fmaxf(fmaxf(mtrue, s[0][v]), s[1][v]);
+    const int lch = lane & 15, kq0 = 16 * (lane >> 4) + 4 * wave;
+    const unsigned kstb = (unsigned)p.ks[2] * 2u;
+    const int ninit = p.n_init;
+
+    // the block that work item `id` stands for, if it exists
+    struct Block { Work wk; Seq sq; int row0, hk; };
+    auto block_of = [&](unsigned id) -> Block {
+        Block x;
+        x.wk = decode_work(p, p.nblk_max, p.by_pair, id);
+        x.sq = seq_of(p, x.wk.b);
+        x.row0 = x.wk.i * BQ;
+        x.hk = (int)p.by_grp.div(x.wk.h);
+        return x;
     };
+    auto next_block = [&](unsigned& id) -> Block {   // from id on; id >= total: none left
+        Block x = block_of(min(id, total - 1));
+        while (id < total && x.row0 >= x.sq.len) {
+            id += gridDim.x;
+            x = block_of(min(id, total - 1));
+        }
+        return x;
+    };
+    auto load_q = [&](bf16x8 (&qf)[8], const Block& x) {
+        const int r = x.row0 + 32 * wave + n;
+        load_q_fragments(qf, a, x.sq, x.wk.b, x.wk.h, r, r < x.sq.len, 0, hf);
+    };
+
+    unsigned id = blockIdx.x;
+    Block cur = next_block(id);
+    if (id >= total) return;
+    bf16x8 qf[8];
+    load_q(qf, cur);
+    for (;;) {
+        const Seq& sq = cur.sq;
+        const int row0 = cur.row0, rw = row0 + 32 * wave;
+        const int rlast = min(row0 + BQ, sq.len) - 1;
+        const int W = window_start(p, (int)p.by_step.div(cur.wk.i));
+        const int T1 = (min(ninit, rlast + 1) + TK - 1) / TK, t2s = max(T1, W / TK);
+        const int nA = a.xa ? T1 + max(0, rlast / TK + 1 - t2s) : 0;     // (xa null: the anchors are not compared with)
+        auto tile_start = [&](int t) -> int { return TK * (t < T1 ? t : t2s + (t - T1)); };
+        const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)((const unsigned short*)a.k + tok_offset(p, p.ks, sq, cur.wk.b, cur.hk, 0)), 0,
+            (int)((unsigned)(sq.len - 1) * kstb + 2u * D), 0x00020000);
+        const unsigned klane = lane_row_offset(kq0, sq.len, kstb, lch), klast = (unsigned)(sq.len - 1) * kstb + 16u * lch;
+        auto k_load = [&](int t, char* Kb) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, (lds_void*)(Kb + (4 * wave + j) * KGRP), 16,
+                                                         (int)clamped_row_offset(klane, tile_row_offset(tile_start(t), j, kstb), klast),
+                                                         0, 0, 0);
+        };
+        if (nA > 0) k_load(0, Ks0);                  // (every wave has passed a barrier since the last read of this stage)
+        float mtrue = -INFINITY;
+        auto tile_step = [&](int t, const char* Kcur, char* Kld) __attribute__((always_inline)) {
+            __builtin_amdgcn_sched_barrier(0);
+            wait_vmem();                             // tile t is there
+            bare_barrier();                          // everywhere, and the stage of tile t - 1 has been read
+            k_load(min(t + 1, nA - 1), Kld);
+            __builtin_amdgcn_sched_barrier(0);
+            const char* Kb = Kcur + koff;
+            const int t0 = tile_start(t);
+            if (t0 > rw + 31) return;                // hidden from all rows of the wave
+            floatx16 s[2];
+            bf16x8 kf[16];
+            auto read_k = [&](int i) { kf[i] = *(const bf16x8*)(Kb + 512 * (i & 1) + 32 * (i >> 1)); };
+#pragma unroll
+            for (int i = 0; i < 6; ++i) read_k(i);
+            if (__builtin_expect((t0 + TK - 1 <= rw) && (t0 + TK <= ninit || t0 >= W), 1)) {
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+                    s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb], qf[0], kZero16, 0, 0, 0);
+            } else {
+                const int ln = counted_lane(), h4 = 4 * (ln >> 5);
+                const int jr = rw - t0 + (ln & 31) - h4, jn = ninit - t0 - h4, jw = W - t0 - h4;
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) {
+                    floatx16 bias;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int jc = 32 * kb + 8 * (v >> 2) + (v & 3);
+                        bias[v] = ((jc <= jr) & ((jc < jn) | (jc >= jw))) ? 0.f : -INFINITY;
+                    }
+                    s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb], qf[0], bias, 0, 0, 0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 2; i < 16; ++i) {
+                s[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i], qf[i >> 1], s[i & 1], 0, 0, 0);
+                if (i + 4 < 16) read_k(i + 4);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) mtrue = fmaxf(fmaxf(mtrue, s[0][v]), s[1][v]);
+        };
 #pragma unroll 1
-    for (int t = 0; t < nA; t += 2) {
-        tile_step(t, Ks0, Ks1);
-        if (t + 1 < nA) tile_step(t + 1, Ks1, Ks0);
+        for (int t = 0; t < nA; t += 2) {
+            tile_step(t, Ks0, Ks1);
+            if (t + 1 < nA) tile_step(t + 1, Ks1, Ks0);
+        }
+        wait_vmem();
+        id += gridDim.x;
+        const Block nx = next_block(id);
+        bf16x8 qn[8];
+        load_q(qn, nx);                              // (none left: the last item's rows again)
+        float ma, mb;
+        both_halves(mtrue, ma, mb);
+        stage2_exports<false>(a, sq, cur.wk, cur.hk, qf, qpart, red, knorm, row0, rlast, wave, lane, rw + n < sq.len,
+                             fmaxf(ma, mb) * p.sigma);
+        if (id >= total) return;
+        cur = nx;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) qf[ks] = qn[ks];
+        __syncthreads();                             // red, knorm and qpart have been read
     }
-    wait_vmem();
-    float ma, mb;
-    both_halves(mtrue, ma, mb);
-    stage2_exports(a, sq, wk, hk, qf, qpart, red, knorm, row0, rlast, wave, lane, rok, fmaxf(ma, mb) * p.sigma);
 }
 
 // Stage 3 recomputing the anchor region: two work-groups per CU instead of three, by 8 KB of unused LDS, where the query blocks
@@ -527,7 +571,8 @@ int launch_engine_bf16(const EngineArgs& ea, unsigned grid, hipStream_t st) {
 }
 
 int launch_anchor_max_bf16(const EngineArgs& ea, unsigned grid, hipStream_t st) {
-    return (int)launch_kernel(anchor_max_bf16_kernel, dim3(grid), dim3(256), 0, st, ea);
+    // three work-groups per CU, a multiple of 8 (decode_work's XCD of a work item)
+    return (int)launch_kernel(anchor_max_bf16_kernel, dim3(grid < 768 ? grid : 768), dim3(256), 0, st, ea, grid);
 }
 
 }  // namespace aa

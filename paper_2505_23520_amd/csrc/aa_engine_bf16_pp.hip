@@ -60,12 +60,12 @@ __global__ __launch_bounds__(512, 1) void engine_bf16_pp_kernel(EngineArgs a) {
 
     if (!engine_selected(a)) return;
     const int npair = (p.nblk_max + 1) >> 1;
-    const Work wk = decode_work(p, npair, blockIdx.x);   // wk.i = pair index
+    const Work wk = decode_work(p, npair, p.by_pair2, blockIdx.x);   // wk.i = pair index
     const Seq sq = seq_of(p, wk.b);
     const int row0 = wk.i * PAIR;
     if (row0 >= sq.len) return;
-    const int hk = wk.h / p.grp;
-    const int g = (2 * wk.i) / p.step;
+    const int hk = (int)p.by_grp.div(wk.h);
+    const int g = (int)p.by_step.div(2 * wk.i);
     if ((flags & kEngLoadState) && a.direct && window_start(p, g) <= p.n_init) return;   // stage 1 finished these rows
     const int rw = row0 + 32 * chunk;                // first row of this wave
     const int r = rw + n;                            // this lane's query row
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(512, 1) void engine_bf16_pp_kernel(EngineArgs a) {
     // loop with its first barrier at another address modulo 64: 19 GiB fetched per launch at 12 (here) and 44, 27 to 37 at
     // 20, 24, 28, 56 and 60, 99 to 145 at 0, 8, 16, 32, 40 and 48; the time stays within 0.5 %.  Without the directive any
     // change ahead of the loop picks one of them.
-    if (FLAGS == (kEngList | kEngLoadState | kEngStoreOut)) asm volatile(".p2align 6\n.rept 13\n s_nop 0\n.endr");
+    if (FLAGS == (kEngList | kEngLoadState | kEngStoreOut)) asm volatile(".p2align 6\n.rept 14\n s_nop 0\n.endr");
     // whole rounds of three tiles (one per LDS stage); tiles past the end only keep the barriers
     for (int t = 0; t < nT; t += 3) {
         tile_iter(t, Ks0, Vs2, Vs0, Ks1, kidx[0], kidx[1]);
@@ -360,8 +360,11 @@ __global__ __launch_bounds__(512, 1) void engine_bf16_pp_kernel(EngineArgs a) {
             const int blk = (FLAGS < 0) ? chunk >> 2 : 0, b0 = row0 + BQ * blk;
             float s0, s1;
             pool_wave_columns(qf, n, s0, s1);
-            pool_block_finish(qpart[blk], chunk & 3, n, hf, s0, s1, 64 * (chunk & 3) + lane, min(b0 + BQ, sq.len) - b0,
-                              blk_index(p, sq, wk.b, wk.h, 2 * wk.i + blk), b0 < sq.len, a.qp_hi, a.qp_lo, a.qlo_norm);
+            pool_block_put(qpart[blk], chunk & 3, n, hf, s0, s1);
+            __syncthreads();
+            if ((chunk & 3) == 0 && b0 < sq.len)
+                pool_block_write(qpart[blk], lane, min(b0 + BQ, sq.len) - b0, blk_index(p, sq, wk.b, wk.h, 2 * wk.i + blk),
+                                 a.qp_hi, a.qp_lo, a.qlo_norm);
         }
         if (a.xa) {
             // pooled anchor of each block: mean of M over its rows (Algorithm 2, avgpool of the anchor)

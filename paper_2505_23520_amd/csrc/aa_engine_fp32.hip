@@ -84,38 +84,59 @@ __device__ __forceinline__ floatx16 mfma_bf16(const uintx4& a, const uintx4& b, 
 // later the tile, the longer.  Anchor region alone: the later in its group, the longer, and the groups side by side.
 // A wave has the chip's matrix and vector pipes nearly to itself at these sizes, so the last round of work-groups lasts as
 // long as its longest tile.  All query heads of a KV head stay on one XCD (its L2) where the heads divide among the XCDs.
-__device__ __forceinline__ Work decode_tile(const KParams& p, unsigned tiles, int rts, bool anchor_only, unsigned id) {
-    const unsigned heads = (unsigned)p.B * p.Hq, pairs = (unsigned)p.B * p.Hkv, grp = (unsigned)p.grp;
+struct TileMap {
+    unsigned tiles;                                  // of the longest sequence
+    FastDiv rts, pair, heads, heads8;                // row tiles of a block; tiles x Hq / Hkv; B x Hq, and an eighth of it
+    FastDiv hq;
+    // anchor region alone: tiles of a group; the groups, and the groups but the last; tiles at positions in a group that the
+    // last group does not have, over all groups
+    FastDiv per, groups, groups1;
+    unsigned head, rem;
+    void set(const KParams& p) {
+        const unsigned r = (unsigned)((p.bq + RT - 1) / RT);
+        tiles = (unsigned)p.nblk_max * r;
+        rts.set(r);
+        pair.set(tiles * (unsigned)p.grp);
+        heads.set((unsigned)(p.B * p.Hq));
+        heads8.set(heads.d >= 8 ? heads.d / 8 : 1);
+        hq.set((unsigned)p.Hq);
+        per.set((unsigned)p.step * r);
+        groups.set((tiles + per.d - 1) / per.d);
+        groups1.set(groups.d > 1 ? groups.d - 1 : 1);
+        rem = tiles - (groups.d - 1) * per.d;
+        head = (per.d - rem) * (groups.d - 1);
+    }
+};
+__device__ __forceinline__ Work decode_tile(const KParams& p, const TileMap& m, bool anchor_only, unsigned id) {
     unsigned x, hb;
-    if (pairs % 8 == 0) {
-        const unsigned slot = id >> 3, per_pair = tiles * grp, within = slot % per_pair;
-        hb = ((id & 7) + 8 * (slot / per_pair)) * grp + within % grp;
-        x = within / grp;
-    } else if (heads % 8 == 0) {
-        const unsigned slot = id >> 3, c = heads / 8;
-        hb = (id & 7) * c + slot % c;
-        x = slot / c;
+    if ((unsigned)(p.B * p.Hkv) % 8 == 0) {
+        const unsigned slot = id >> 3, q = m.pair.div(slot), within = slot - q * m.pair.d;
+        x = p.by_grp.div(within);
+        hb = ((id & 7) + 8 * q) * p.grp + within - x * p.grp;
+    } else if (m.heads.d % 8 == 0) {
+        const unsigned slot = id >> 3;
+        x = m.heads8.div(slot);
+        hb = (id & 7) * m.heads8.d + slot - x * m.heads8.d;
     } else {
-        hb = id % heads;
-        x = id / heads;
+        x = m.heads.div(id);
+        hb = id - x * m.heads.d;
     }
     Work wk;
-    wk.b = (int)(hb / (unsigned)p.Hq);
-    wk.h = (int)(hb % (unsigned)p.Hq);
-    wk.i = (int)(tiles - 1 - x);
+    wk.b = (int)m.hq.div(hb);
+    wk.h = (int)hb - wk.b * p.Hq;
+    wk.i = (int)(m.tiles - 1 - x);
     if (anchor_only) {
-        const unsigned per = (unsigned)p.step * rts, groups = (tiles + per - 1) / per;
-        const unsigned rem = tiles - (groups - 1) * per;             // tiles of the last group
-        const unsigned head = (per - rem) * (groups - 1);            // tiles at positions that it does not have
         unsigned pos, gr;
-        if (x < head) {
-            pos = per - 1 - x / (groups - 1);
-            gr = x % (groups - 1);
+        if (x < m.head) {
+            const unsigned q = m.groups1.div(x);
+            pos = m.per.d - 1 - q;
+            gr = x - q * m.groups1.d;
         } else {
-            pos = rem - 1 - (x - head) / groups;
-            gr = (x - head) % groups;
+            const unsigned q = m.groups.div(x - m.head);
+            pos = m.rem - 1 - q;
+            gr = x - m.head - q * m.groups.d;
         }
-        wk.i = (int)(gr * per + pos);
+        wk.i = (int)(gr * m.per.d + pos);
     }
     return wk;
 }
@@ -135,7 +156,7 @@ __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70
 // WIDE: a head's rows of K or V span 4 GiB or more (64-bit addresses instead of buffer offsets).  The compiler waits for
 // every load in flight wherever it needs one of them then (its rule for loads of the flat encoding that write to LDS).
 template <int D, int FLAGS, bool WIDE>
-__global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32_kernel(EngineArgs a) {
+__global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32_kernel(EngineArgs a, TileMap map) {
     constexpr int flags = FLAGS;
     constexpr int T = D / 32;                        // column blocks of O
     constexpr int KS = D / 16;                       // 16-column pieces of a K / Q row
@@ -159,17 +180,16 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
 
     if (flags & kEngStoreState) store_dense_stats(a);
     if (!engine_selected(a)) return;
-    const int rts = (p.bq + RT - 1) / RT;            // row tiles of a query block
-    const unsigned id = blockIdx.y * kGridX + blockIdx.x, tiles = (unsigned)(p.nblk_max * rts);
-    if (id >= tiles * (unsigned)p.Hq * (unsigned)p.B) return;
-    const Work wk = decode_tile(p, tiles, rts, !(flags & (kEngDense | kEngList)), id);
+    const unsigned id = blockIdx.y * kGridX + blockIdx.x;
+    if (id >= map.tiles * map.heads.d) return;
+    const Work wk = decode_tile(p, map, !(flags & (kEngDense | kEngList)), id);
     const Seq sq = seq_of(p, wk.b);
-    const int blk = wk.i / rts;
-    const int row0 = blk * p.bq + (wk.i % rts) * RT;             // first row of the tile
+    const int blk = (int)map.rts.div(wk.i);
+    const int row0 = blk * p.bq + (wk.i - blk * (int)map.rts.d) * RT;        // first row of the tile
     const int rend = min(min(blk * p.bq + p.bq, row0 + RT), sq.len);
     if (row0 >= rend) return;
-    const int hk = wk.h / p.grp;
-    const int g = blk / p.step;
+    const int hk = (int)p.by_grp.div(wk.h);
+    const int g = (int)p.by_step.div(blk);
     const bool direct = a.direct && window_start(p, g) <= p.n_init;   // no candidates: stage 1 finishes the rows
     if ((flags & kEngLoadState) && direct) return;
     const int r = row0 + n;
@@ -589,11 +609,13 @@ int launch_engine_fp32(const EngineArgs& ea, hipStream_t st) {
     const KParams& p = ea.p;
     const long long total = (long long)p.nblk_max * ((p.bq + RT - 1) / RT) * p.Hq * p.B;
     const dim3 grid((unsigned)(total < kGridX ? total : kGridX), (unsigned)((total + kGridX - 1) / kGridX));
+    TileMap map;
+    map.set(p);
     const long long stride = p.ks[2] > p.vs[2] ? p.ks[2] : p.vs[2];
     const bool wide = stride >= (1ll << 30) || (long long)p.N * stride >= (1ll << 30);
     switch ((p.d * 64 + ea.flags) * 2 + wide) {
 #define AA_ENGINE_CASE(d, F, w) \
-    case (((d) * 64 + (F)) * 2 + w): return (int)launch_kernel(engine_fp32_kernel<(d), (F), w>, grid, dim3(64 * NW), 0, st, ea);
+    case (((d) * 64 + (F)) * 2 + w): return (int)launch_kernel(engine_fp32_kernel<(d), (F), w>, grid, dim3(64 * NW), 0, st, ea, map);
 #define AA_ENGINE_CASES(d, w)                                            \
     AA_ENGINE_CASE(d, kEngAnchorRegion | kEngStoreState, w)              \
     AA_ENGINE_CASE(d, kEngList | kEngLoadState | kEngStoreOut, w)        \

@@ -61,8 +61,12 @@ __global__ __launch_bounds__(256) void pool_q_bf16_kernel(SelectArgs a) {
     const int y = blockIdx.y + (a.pool_skip_q ? p.Hq : 0);
     if (y >= p.Hq) {
         const int hk = y - p.Hq;
-        key_block_norm((const unsigned short*)a.k + tok_offset(p, p.ks, sq, b, hk, 0), p.ks[2], r0, r1, tid, red[0],
-                       a.kmax_blk + kblk_index(p, sq, b, hk, i));
+        KeyNorm kn;
+        kn.load((const unsigned short*)a.k + tok_offset(p, p.ks, sq, b, hk, 0), p.ks[2], r0, r1, tid);
+        const float big = kn.wave_max();
+        if ((tid & 63) == 0) red[0][tid >> 6] = big;
+        __syncthreads();
+        if (tid == 0) a.kmax_blk[kblk_index(p, sq, b, hk, i)] = KeyNorm::block(red[0]);
         return;
     }
     // query block i of head h: the fragments of the tile engines (wave w: rows 32 w .. 32 w + 31, lane
@@ -82,8 +86,9 @@ __global__ __launch_bounds__(256) void pool_q_bf16_kernel(SelectArgs a) {
     }
     float s0, s1;
     pool_wave_columns(qf, n, s0, s1);
-    pool_block_finish(red, wave, n, hf, s0, s1, tid, r1 - r0, blk_index(p, sq, b, h, i), true,
-                      a.qp_hi, a.qp_lo, a.qlo_norm);
+    pool_block_put(red, wave, n, hf, s0, s1);
+    __syncthreads();
+    if (tid < 64) pool_block_write(red, lane, r1 - r0, blk_index(p, sq, b, h, i), a.qp_hi, a.qp_lo, a.qlo_norm);
 }
 
 // fp32: 256 threads per query block.  With qp_f32 set, the block mean of the queries (16 bytes of a row per

@@ -47,6 +47,42 @@ int main() {
 """
 
 
+DIVISIONS = r"""
+#include <cstdio>
+#include "aa_div.h"
+
+int main() {
+    long long bad = 0;
+    unsigned long long x = 88172645463325252ull;
+    for (unsigned k = 0; k < 4000; ++k) {
+        x ^= x << 13; x ^= x >> 7; x ^= x << 17;
+        // small divisors, powers of two and their neighbours, and any up to 2^31
+        const unsigned d = k < 1500 ? k + 1 : k < 1593 ? (1u << ((k - 1500) / 3)) - 1 + (k - 1500) % 3 : (unsigned)(x >> 33) + 1;
+        if (!d || d > (1u << 31)) continue;
+        aa::FastDiv f{};
+        f.set(d);
+        for (unsigned e = 0; e < 400; ++e) {
+            x ^= x << 13; x ^= x >> 7; x ^= x << 17;
+            const unsigned q = (unsigned)(x >> 33) / d;
+            const unsigned ns[] = {(unsigned)(x >> 33), e, 0x7fffffffu - e, q * d, q * d + d - 1, q * d - 1};
+            for (unsigned n : ns)
+                if (n < (1u << 31) && f.div(n) != n / d && !bad++) printf("%u / %u: %u\n", n, d, f.div(n));
+        }
+    }
+    return bad != 0;
+}
+"""
+
+
+def test_divisions_by_known_divisors(tmp_path):
+    src, exe = tmp_path / "div.cpp", tmp_path / "div"
+    src.write_text(DIVISIONS)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I",
+                           os.path.join(ROOT, "paper_2505_23520_amd", "csrc"), str(src), "-o", str(exe)])
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
 def test_row_offsets_match_64_bit_arithmetic(tmp_path):
     src, exe = tmp_path / "rows.cpp", tmp_path / "rows"
     src.write_text(PROGRAM)
