@@ -300,9 +300,10 @@ bool recompute_anchor(const Plan& pl, const aa_params* p) {
 
 // sel_ws (nullable): a stripe_select workspace (with the call's counts); the bf16 engines then also leave the pooled queries of
 // stage 2 there, and the fp32 path leaves the pooled anchors to run_select (which is told so).
-// out (nullable), lse, stats: see EngineArgs::direct
+// out (nullable), lse, stats: see EngineArgs::direct; total, call_stats: the sums that the fill kernel adds to, cleared here
 int run_anchor(const Plan& pl, const aa_params* p, const void* q, const void* k, const void* v, float* M, float* L,
-               float* Acc, float* xa, char* sel_ws, int32_t* counts, void* out, float* lse, int64_t* stats, hipStream_t st) {
+               float* Acc, float* xa, char* sel_ws, int32_t* counts, long long* total, int64_t* call_stats, void* out,
+               float* lse, int64_t* stats, hipStream_t st) {
     EngineArgs ea;
     memset(&ea, 0, sizeof(ea));
     ea.p = pl.kp;
@@ -316,6 +317,7 @@ int run_anchor(const Plan& pl, const aa_params* p, const void* q, const void* k,
         if (pooled_keys(p)) {
             ea.kmax_blk = (float*)(sel_ws + pl.sel_kmax);
             ea.zero_counts = counts; ea.zero_seg = (int*)(sel_ws + pl.sel_segc); ea.nseg = (int)cdiv(pl.nwords, 64);
+            if (total) { ea.zero_total = total; ea.zero_stats = (long long*)call_stats; }
         }
     }
     if (!M) {                                        // fused prefill that keeps no state (see recompute_anchor)
@@ -336,10 +338,11 @@ int run_anchor(const Plan& pl, const aa_params* p, const void* q, const void* k,
 
 // fused_M (nullable): the call follows run_anchor with this workspace, M is stage 1's; bf16: the pooled queries
 // are in ws already; fp32: the pooled anchors are still to be computed, into xa
-// stats (nullable): the scan kernel also reports attended pairs and selected entries there
+// total (nullable): the lists stand at places of their own (fused call), and their padded entries are summed up there
+// stats (nullable): receives attended pairs and selected entries
 int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k, const float* xa, int32_t* counts,
                int64_t* offsets, int32_t* idx, int64_t cap, int32_t* flag, char* ws, const float* fused_M, float* xa_out,
-               int64_t* stats, hipStream_t st) {
+               long long* total, int64_t* stats, hipStream_t st) {
     const KParams& kp = pl.kp;
     SelectArgs sa;
     memset(&sa, 0, sizeof(sa));
@@ -357,6 +360,8 @@ int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k,
     sa.idx_capacity = cap; sa.overflow = flag;
     sa.groups_total = pl.sz.groups;
     sa.stats = (long long*)stats;
+    sa.total = total;
+    if (total) sa.list_room = cap / ((long long)kp.Hq * (kp.packed ? 1 : kp.B));
 
     const dim3 gblk(kp.nblk_max, kp.Hq, kp.B), ggrp(kp.ngrp_max, kp.Hq, kp.B);
     if (p->granularity == AA_BLOCK) AA_HIP(raise_lds_limits());   // before anything is enqueued
@@ -364,12 +369,13 @@ int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k,
     // work-group (64k segments: 16k tokens at step 1 32k; adding to the counts from every mask work-group cost 9 us
     // there); beyond, the mask kernels add to the counts as well.
     const long long segs = (long long)pl.sz.groups * sa.nseg;
-    sa.sum_segs = segs <= 65536;
+    sa.sum_segs = sa.list_room || segs <= 65536;
     if (p->granularity == AA_BLOCK) {
-        AA_LAUNCH(zero_i32_kernel, dim3((unsigned)cdiv(segs, 256)), dim3(256), 0, st, sa.segcount, segs);
+        AA_LAUNCH(zero_i32_kernel, dim3((unsigned)cdiv(segs, 256)), dim3(256), 0, st, sa.segcount, segs, sa.total,
+                  sa.total ? sa.stats : nullptr);
         if (!sa.sum_segs)
             AA_LAUNCH(zero_i32_kernel, dim3((unsigned)cdiv(pl.sz.groups, 256)), dim3(256), 0, st, counts,
-                      (long long)pl.sz.groups);
+                      (long long)pl.sz.groups, nullptr, nullptr);
     }
     const bool q_pooled = fused_M && p->dtype == AA_BF16;
     if (p->dtype != AA_BF16 && fused_M) {
@@ -413,9 +419,10 @@ int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k,
     if (p->granularity == AA_BLOCK) AA_LAUNCH(count_kernel, ggrp, dim3(256), 0, st, sa);
     // few groups: the fill kernel does the scan's work (a launch less, 5 us); every one of its work-groups then
     // reads up to all segments, 8 per thread at this limit
+    if (sa.list_room) return engine_status(launch_fill(sa, kFillPlaces, st), "fill_kernel");
     const bool fill_scans = segs <= 2048;
     if (!fill_scans) AA_LAUNCH(scan_kernel, dim3(1), dim3(1024), 0, st, sa);
-    return engine_status(launch_fill(sa, fill_scans, st), "fill_kernel");
+    return engine_status(launch_fill(sa, fill_scans ? kFillScan : kFillOffsets, st), "fill_kernel");
 }
 
 int run_sparse(const Plan& pl, const aa_params* p, const void* q, const void* k, const void* v, const float* M,
@@ -467,7 +474,7 @@ int anchor_compute(const aa_params* params, const void* q, const void* k, const 
     if (!q || !k || !v || !M || !L || !xa_pooled) return AA_EINVAL;
     if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(Acc)) return AA_EINVAL;
     return run_anchor(pl, params, q, k, v, M, L, Acc, xa_pooled, nullptr, nullptr, nullptr, nullptr, nullptr,
-                      (hipStream_t)stream);
+                      nullptr, nullptr, (hipStream_t)stream);
 }
 
 int stripe_select(const aa_params* params, const void* q, const void* k, const float* xa_pooled, int32_t* counts,
@@ -480,7 +487,7 @@ int stripe_select(const aa_params* params, const void* q, const void* k, const f
     if (idx_capacity < 0 || misaligned(q) || misaligned(k) || misaligned(idx) || misaligned(ws)) return AA_EINVAL;
     if (ws_bytes < pl.sz.select_ws_bytes) return AA_EWORKSPACE;
     return run_select(pl, params, q, k, xa_pooled, counts, offsets, idx, idx_capacity, overflow_flag, (char*)ws,
-                      nullptr, nullptr, nullptr, (hipStream_t)stream);
+                      nullptr, nullptr, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int stripe_select_noalloc(const aa_params* params, const void* q, const void* k, const float* xa_pooled,
@@ -496,7 +503,7 @@ int stripe_select_noalloc(const aa_params* params, const void* q, const void* k,
     rc = scratch_of_current_device(&ws);
     if (rc != AA_OK) return rc;
     return run_select(pl, params, q, k, xa_pooled, counts, offsets, idx, idx_capacity, overflow_flag, (char*)ws,
-                      nullptr, nullptr, nullptr, (hipStream_t)stream);
+                      nullptr, nullptr, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int sparse_attn(const aa_params* params, const void* q, const void* k, const void* v, const float* M, const float* L,
@@ -539,13 +546,16 @@ int anchor_attention_prefill(const aa_params* params, const void* q, const void*
     // the other kernels' launches alone took 25 us.  At 8k tokens and step 16 it is a quarter of the rows.
     const bool direct = direct_ok(params);
     if (direct && no_candidates(pl.kp))
-        return run_anchor(pl, params, q, k, v, M, L, Acc, nullptr, nullptr, nullptr, out, lse, stats, st);
+        return run_anchor(pl, params, q, k, v, M, L, Acc, nullptr, nullptr, nullptr, nullptr, nullptr, out, lse, stats, st);
+    // every list at a place of its own where the places can be computed (the index region holds every candidate)
+    const bool places = (long long)params->block_q * params->step % kIdxPad == 0;
+    long long* total = places ? (long long*)offsets + pl.sz.groups : nullptr;
     const bool again = recompute_anchor(pl, params);
     rc = run_anchor(pl, params, q, k, v, again ? nullptr : M, L, Acc, xa, w + pl.pf_sel, counts,
-                    direct && !again ? out : nullptr, lse, nullptr, st);
+                    total, places ? stats : nullptr, direct && !again ? out : nullptr, lse, nullptr, st);
     if (rc != AA_OK) return rc;
     rc = run_select(pl, params, q, k, xa, counts, offsets, idx, pl.sz.idx_capacity_max, flag, w + pl.pf_sel, M, xa,
-                    stats, st);
+                    total, stats, st);
     if (rc != AA_OK) return rc;
     rc = run_sparse(pl, params, q, k, v, again ? nullptr : M, L, Acc, counts, offsets, idx, pl.sz.idx_capacity_max, out, lse,
                     direct && !again, st);

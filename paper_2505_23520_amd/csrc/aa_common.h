@@ -6,11 +6,11 @@
 #include <stdint.h>
 
 #include "aa_div.h"
+#include "aa_lists.h"
 
 namespace aa {
 
 constexpr int kLane = 64;          // wavefront width on CDNA4
-constexpr int kIdxPad = 64;        // list chunks are 64 entries (one K/V tile)
 
 // Launch with the launch's own status as return value (hipGetLastError() after a <<<>>> launch
 // would also report, and clear, an error some earlier and unrelated call left behind).

@@ -29,6 +29,7 @@ struct EngineArgs {
     // stage 1 only, nullable: largest key norm per (KV head, key block) for stage 2, and the counters to clear for it
     float* kmax_blk;
     int *zero_counts, *zero_seg;
+    long long *zero_total, *zero_stats;
     int nseg;
     void* out;
     float* lse;

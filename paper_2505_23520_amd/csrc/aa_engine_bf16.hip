@@ -124,7 +124,7 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     if (flags & kEngStoreState) {
         store_dense_stats(a);
         if (a.kmax_blk)
-            clear_counters(a.zero_counts, a.groups_total, a.zero_seg, a.nseg, blockIdx.x * 256ll + tid, gridDim.x * 256ll);
+            clear_counters(a.zero_counts, a.groups_total, a.zero_seg, a.nseg, a.zero_total, a.zero_stats, blockIdx.x * 256ll + tid, gridDim.x * 256ll);
     }
     if (!engine_selected(a)) return;
     const Work wk = decode_work(p, p.nblk_max, p.by_pair, blockIdx.x);
@@ -427,7 +427,7 @@ __global__ __launch_bounds__(256, 3) void anchor_max_bf16_kernel(EngineArgs a, u
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, hf = lane >> 5;
     if (a.kmax_blk)
-        clear_counters(a.zero_counts, a.groups_total, a.zero_seg, a.nseg, blockIdx.x * 256ll + tid, gridDim.x * 256ll);
+        clear_counters(a.zero_counts, a.groups_total, a.zero_seg, a.nseg, a.zero_total, a.zero_stats, blockIdx.x * 256ll + tid, gridDim.x * 256ll);
     const int koff = (n & 15) * KGRP + (n >> 4) * 256 + 16 * hf;
     const int lch = lane & 15, kq0 = 16 * (lane >> 4) + 4 * wave;
     const unsigned kstb = (unsigned)p.ks[2] * 2u;

@@ -14,10 +14,13 @@ typedef __bf16 pool_bf16x8 __attribute__((ext_vector_type(8)));
 // The value of the lane whose number differs in one bit, without a trip through LDS (as __shfl_xor takes it): data-parallel
 // primitives inside a row of 16 lanes.  Exchanging 62 values of a wave so, and by row swaps, instead of through LDS took the
 // pooling of a block from 2500 to 1100 cycles.
+template <int CTRL> __device__ __forceinline__ int dpp_mov(int x) {
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, false);
+}
 template <int CTRL> __device__ __forceinline__ float dpp_mov(float x) {
     return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xf, 0xf, false));
 }
-template <int DIST> __device__ __forceinline__ float lane_xor(float x) {
+template <int DIST, class T> __device__ __forceinline__ T lane_xor(T x) {
     static_assert(DIST == 1 || DIST == 2 || DIST == 4 || DIST == 8, "inside a row of 16 lanes");
     if constexpr (DIST == 1) return dpp_mov<0xB1>(x);        // quad_perm [1, 0, 3, 2]
     if constexpr (DIST == 2) return dpp_mov<0x4E>(x);        // quad_perm [2, 3, 0, 1]
@@ -25,11 +28,11 @@ template <int DIST> __device__ __forceinline__ float lane_xor(float x) {
     if constexpr (DIST == 8) return dpp_mov<0x128>(x);       // row rotated by 8
 }
 // x combined over the wave by a commutative op, the distances in the order 32, 16, 8, 4, 2, 1 (down to LAST)
-template <int LAST, class Op> __device__ __forceinline__ float wave_reduce(float x, Op op) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
-    const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = op(__uint_as_float(q[0]), __uint_as_float(q[1]));
+template <int LAST, class T, class Op> __device__ __forceinline__ T wave_reduce(T x, Op op) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+    x = op(__builtin_bit_cast(T, (unsigned)r[0]), __builtin_bit_cast(T, (unsigned)r[1]));
+    const auto q = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+    x = op(__builtin_bit_cast(T, (unsigned)q[0]), __builtin_bit_cast(T, (unsigned)q[1]));
     x = op(x, lane_xor<8>(x));
     x = op(x, lane_xor<4>(x));
     x = op(x, lane_xor<2>(x));
@@ -135,12 +138,18 @@ struct KeyNorm {
     }
 };
 
-// Clears the counters that the mask kernels of both types (and count_kernel) add to; called by every thread of a kernel that runs before it.
-__device__ __forceinline__ void clear_counters(int* counts, long long groups, int* segcount, int nseg,
-                                               long long thread, long long nthreads) {
+// Clears the counters that the mask kernels of both types (and count_kernel) add to, and, where they are given, the sums
+// that the fused call's fill kernel adds to (the padded lists' total, the caller's statistics); called by every thread of a
+// kernel that runs before them.
+__device__ __forceinline__ void clear_counters(int* counts, long long groups, int* segcount, int nseg, long long* total,
+                                               long long* stats, long long thread, long long nthreads) {
     for (long long e = thread; e < groups * (nseg + 1); e += nthreads) {
         if (e < groups) counts[e] = 0;
         else segcount[e - groups] = 0;
+    }
+    if (thread < 4) {
+        if (total && thread == 0) *total = 0;
+        if (stats) stats[thread] = 0;
     }
 }
 

@@ -63,6 +63,10 @@ struct SelectArgs {
     long long idx_capacity;
     int* overflow;
     long long groups_total;
+    // Fused call whose groups have a multiple of 64 rows: every list has a place of its own, as long as its candidates (see
+    // padded_places); entries per head (and sequence, if they have one length).  0: lists one after the other.
+    long long list_room;
+    long long* total;         // list_room > 0: entries of all padded lists (cleared by the kernel that clears the counters)
     long long* stats;         // nullable, int64[4]: { attended pairs, selected entries, 0, 0 }
     // bf16 mask kernel: work items per (sequence, KV head) pair for the longest sequence (sizes the grid)
     int mask_items;
@@ -77,10 +81,10 @@ __global__ void pool_k_kernel(SelectArgs a);
 __global__ void mask_block_kernel(SelectArgs a);
 size_t mask_block_lds_bytes(int N, int d, int bq, int step);
 constexpr size_t kMaskBlockLdsMax = 128 * 1024;   // dynamic LDS limit set for mask_block_kernel
-__global__ void zero_i32_kernel(int* x, long long nelem);
+__global__ void zero_i32_kernel(int* x, long long nelem, long long* total, long long* stats);
 __global__ void count_kernel(SelectArgs a);
 __global__ void scan_kernel(SelectArgs a);
-// scan: also does scan_kernel's work, which is then not launched
-int launch_fill(const SelectArgs& a, bool scan, hipStream_t st);
+enum FillMode { kFillOffsets = 0, kFillScan = 1, kFillPlaces = 2 };   // see fill_kernel
+int launch_fill(const SelectArgs& a, FillMode mode, hipStream_t st);
 
 }  // namespace aa

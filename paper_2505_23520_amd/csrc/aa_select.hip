@@ -50,7 +50,7 @@ __global__ __launch_bounds__(256) void pool_q_bf16_kernel(SelectArgs a) {
     const int i = blockIdx.x, b = blockIdx.z, tid = threadIdx.x;
     if (a.kmax_blk) {
         const long long wg = blockIdx.x + (long long)gridDim.x * (blockIdx.y + (long long)gridDim.y * blockIdx.z);
-        clear_counters(a.counts, a.groups_total, a.segcount, a.nseg, wg * 256 + tid,
+        clear_counters(a.counts, a.groups_total, a.segcount, a.nseg, a.total, a.total ? a.stats : nullptr, wg * 256 + tid,
                        (long long)gridDim.x * gridDim.y * gridDim.z * 256);
     }
     const Seq sq = seq_of(p, b);
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(256) void pool_fp32_kernel(SelectArgs a) {
     const int tid = threadIdx.x;
     if (a.segcount) {
         const long long wg = blockIdx.x + (long long)gridDim.x * (blockIdx.y + (long long)gridDim.y * blockIdx.z);
-        clear_counters(a.counts, a.groups_total, a.segcount, a.nseg, wg * 256 + tid,
+        clear_counters(a.counts, a.groups_total, a.segcount, a.nseg, a.total, a.total ? a.stats : nullptr, wg * 256 + tid,
                        (long long)gridDim.x * gridDim.y * gridDim.z * 256);
     }
     // fused prefill: stage 1 has finished the rows of groups without candidates and left no M for them; stage 2 reads neither
@@ -672,8 +672,11 @@ __global__ __launch_bounds__(256) void mask_block_kernel(SelectArgs a) {
 }
 
 // ------------------------------------------------------------------ count / scan / fill
-__global__ void zero_i32_kernel(int* x, long long nelem) {
+// total, stats (nullable): see clear_counters
+__global__ void zero_i32_kernel(int* x, long long nelem, long long* total, long long* stats) {
     long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0 && total) *total = 0;
+    if (i < 4 && stats) stats[i] = 0;
     if (i < nelem) x[i] = 0;
 }
 
@@ -732,6 +735,27 @@ __device__ __forceinline__ int group_count(const SelectArgs& a, long long t) {
     return c;
 }
 
+// Attended (row, key) pairs of group t with a list of cnt columns: every row's anchor region (closed form) plus the list;
+// 0 for a slot past a packed batch's groups.
+__device__ __forceinline__ long long group_pairs(const KParams& p, long long t, int cnt) {
+    const int span = p.bq * p.step;
+    int len = p.N, g = (int)((unsigned)t % (unsigned)p.grp_cap);
+    if (p.packed) {
+        len = 0;
+        for (int b = 0; b < p.B; ++b) {
+            const int n = p.cu[b + 1] - p.cu[b], ng = (n + span - 1) / span;
+            if (g < ng) { len = n; break; }
+            g -= ng;
+        }
+    }
+    if ((long long)g * span >= len) return 0;
+    const long long r0 = (long long)g * span, r1 = min(r0 + span, (long long)len);
+    return anchor_pairs(p.n_init, window_start(p, g), r0, r1) + (r1 - r0) * cnt;
+}
+
+// At most this many selected columns in any word of a segment: a store per column and lane (else a step per pair of words)
+constexpr int kFillLaneBits = 12;
+
 // One work-group of NT threads: offsets[t] = sum_{t' < t} roundup64(counts[t']), the counts themselves where they
 // are still in segments, the overflow flag, and, with a.stats set, what the prefill reports:
 // attended (row, key) pairs = every row's anchor region (closed form per group) plus its group's list, and
@@ -751,22 +775,9 @@ __device__ __forceinline__ void scan_groups(const SelectArgs& a) {
         if (a.sum_segs) a.counts[t] = cnt;
         s += pad_list(cnt);
         if (a.stats) {
-            // group t -> (sequence, group in the sequence); slots past a packed batch's groups hold 0
-            const int span = p.bq * p.step;
-            int len = p.N, g = (int)((unsigned)t % (unsigned)p.grp_cap);
-            if (p.packed) {
-                len = 0;
-                for (int b = 0; b < p.B; ++b) {
-                    const int n = p.cu[b + 1] - p.cu[b], ng = (n + span - 1) / span;
-                    if (g < ng) { len = n; break; }
-                    g -= ng;
-                }
-            }
-            if ((long long)g * span < len) {
-                const long long r0 = (long long)g * span, r1 = min(r0 + span, (long long)len);
-                pairs += anchor_pairs(p.n_init, window_start(p, g), r0, r1) + (r1 - r0) * cnt;
-                entries += cnt;
-            }
+            const long long x = group_pairs(p, t, cnt);
+            pairs += x;
+            if (x) entries += cnt;
         }
     }
     long long x = s;                                     // inclusive scan over the wave
@@ -804,16 +815,56 @@ __device__ __forceinline__ void scan_groups(const SelectArgs& a) {
 
 __global__ __launch_bounds__(1024) void scan_kernel(SelectArgs a) { scan_groups<1024>(a); }
 
+// Places: group t's part of the sums that scan_groups takes, one group per thread of the work-groups of the last grid layer.
+namespace {
+__device__ __forceinline__ void add_sums(const SelectArgs& a) {
+    const long long wg = blockIdx.x + (long long)gridDim.x * blockIdx.y, nwg = (long long)gridDim.x * gridDim.y;
+    if (wg * 256 >= a.groups_total) return;
+    __shared__ long long part[3][4];
+    long long pad = 0, pairs = 0, entries = 0;
+    for (long long t = wg * 256 + threadIdx.x; t < a.groups_total; t += nwg * 256) {
+        const int cnt = group_count(a, t);
+        pad += pad_list(cnt);
+        if (a.stats) {
+            const long long x = group_pairs(a.p, t, cnt);
+            pairs += x;
+            if (x) entries += cnt;
+        }
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        pad += __shfl_xor(pad, off, 64);
+        pairs += __shfl_xor(pairs, off, 64);
+        entries += __shfl_xor(entries, off, 64);
+    }
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) { part[0][wave] = pad; part[1][wave] = pairs; part[2][wave] = entries; }
+    __syncthreads();
+    if (threadIdx.x < (a.stats ? 3 : 1)) {
+        const long long* x = part[threadIdx.x];
+        long long* dst = threadIdx.x == 0 ? a.total : a.stats + (threadIdx.x - 1);
+        atomicAdd((unsigned long long*)dst, (unsigned long long)(x[0] + x[1] + x[2] + x[3]));
+    }
+}
+}  // namespace
+
 // grid (ngrp_max, ceil(nseg / 4), B*Hq [+ 1]), 256 threads: each wave expands one segment (64 bit words =
 // kSegKeys keys) of the group's bit words into its part of the ascending list; the segment counts give its
-// position.  SCAN: no scan_kernel ran; every work-group adds up the lists before its group's itself, and the first
-// work-group of one more grid layer does scan_kernel's work beside the others.  For few groups that is a fraction
-// of what the launch costs (5 us); it grows with groups x groups, so the host draws the line.
-template <bool SCAN>
+// position inside the list.  Where the list begins:
+//   kFillOffsets  offsets[t], from scan_kernel;
+//   kFillScan     no scan_kernel ran; every work-group adds up the lists before its group's itself, and the first
+//                 work-group of one more grid layer does scan_kernel's work beside the others.  For few groups that is a
+//                 fraction of what the launch costs (5 us); it grows with groups x groups, so the host draws the line;
+//   kFillPlaces   the fused call, where nobody reads the lists but stage 3: at the group's own place.  No scan at all; counts
+//                 and offsets are written here, the sums (padded entries, statistics) by one more grid layer beside the others.
+//                 16384 tokens at step 1 (4096 groups x 8 segments): scan 12.6 us and its launch.
+template <int MODE>
 __global__ __launch_bounds__(256) void fill_kernel(SelectArgs a) {
+    constexpr bool SCAN = MODE == kFillScan, PLACES = MODE == kFillPlaces;
     const KParams& p = a.p;
-    if (SCAN && blockIdx.z == (unsigned)(p.Hq * p.B)) {
-        if (blockIdx.x == 0 && blockIdx.y == 0) scan_groups<256>(a);
+    if (MODE != kFillOffsets && blockIdx.z == (unsigned)(p.Hq * p.B)) {
+        if (PLACES) add_sums(a);
+        else if (blockIdx.x == 0 && blockIdx.y == 0) scan_groups<256>(a);
         return;
     }
     const int g = blockIdx.x, h = blockIdx.z % p.Hq, b = blockIdx.z / p.Hq;
@@ -821,12 +872,15 @@ __global__ __launch_bounds__(256) void fill_kernel(SelectArgs a) {
     const int ngrp = (sq.len + p.bq * p.step - 1) / (p.bq * p.step);
     if (g >= ngrp) return;
     const int Wg = window_start(p, g);
-    if (Wg <= p.n_init) return;
     const int lane = threadIdx.x & 63;
     const int seg = __builtin_amdgcn_readfirstlane(4 * blockIdx.y + (threadIdx.x >> 6));
+    const long long t = grp_index(p, sq, b, h, g);
+    if (Wg <= p.n_init) {
+        if (PLACES && seg == 0 && lane == 0) { a.counts[t] = 0; a.offsets[t] = 0; }
+        return;
+    }
     const int w_lo = p.n_init / 32, w_hi = (Wg + 31) / 32;
     const int w0 = seg_word0(p.n_init) + seg * 64;       // the segment's first word
-    const long long t = grp_index(p, sq, b, h, g);
     const int* segc = a.segcount + t * a.nseg;
     long long base = 0;
     if (SCAN) {
@@ -838,11 +892,11 @@ __global__ __launch_bounds__(256) void fill_kernel(SelectArgs a) {
         __syncthreads();
         base = (part[0] + part[1]) + (part[2] + part[3]);
     }
-    if (w0 >= w_hi) return;
+    if (w0 >= w_hi) return;                              // (never the first segment)
     // every load is issued before the first decision, so the wave pays one memory round trip
     const int own = segc[seg];
     int cnt = 0, pre = 0;                                // selected columns of the group, and in earlier segments
-    if (!SCAN) base = a.offsets[t];
+    if (MODE == kFillOffsets) base = a.offsets[t];
     for (int s = lane; s < a.nseg; s += 64) {
         const int c = segc[s];
         cnt += c;
@@ -850,32 +904,59 @@ __global__ __launch_bounds__(256) void fill_kernel(SelectArgs a) {
     }
     const int w = w0 + lane;                             // this lane's word
     const unsigned wd = (w >= w_lo && w < w_hi) ? a.bits[t * a.nwords + w] : 0u;
-    if (own == 0) return;                                // the group's last entry is never in such a segment
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        pre += __shfl_xor(pre, off, 64);
-        cnt += __shfl_xor(cnt, off, 64);
+    if (PLACES) {
+        const long long span = (long long)p.bq * p.step, c = (long long)p.n_init + p.w;
+        base = (p.packed ? (long long)h : (long long)b * p.Hq + h) * a.list_room + padded_places(g, span, c);
+        if (p.packed)
+            for (int e = 0; e < b; ++e) base += padded_places((p.cu[e + 1] - p.cu[e] + span - 1) / span, span, c);
     }
-    // two words per step: lanes 0..31 test word 2 i, lanes 32..63 word 2 i + 1 (coalesced stores)
+    const auto add = [](int x, int y) { return x + y; };
+    cnt = wave_reduce<1>(cnt, add);
+    if (PLACES && seg == 0 && lane == 0) { a.counts[t] = cnt; a.offsets[t] = base; }
+    if (own == 0) return;                                // the group's last entry is never in such a segment
+    pre = wave_reduce<1>(pre, add);
     long long pos = base + pre;
-    const int bit = lane & 31, half = lane >> 5;
-    // only the word pairs that hold a selected column are visited (scalar loop over a bit mask)
     const unsigned long long nzw = __ballot(wd != 0u);
-    unsigned long long pairs = (nzw | (nzw >> 1)) & 0x5555555555555555ull;
-    while (pairs) {
-        const int i = __builtin_ctzll(pairs) >> 1;
-        pairs &= pairs - 1;
-        const unsigned first = __builtin_amdgcn_readlane(wd, 2 * i), second = __builtin_amdgcn_readlane(wd, 2 * i + 1);
-        const unsigned mine = half ? second : first;
-        const bool on = (mine >> bit) & 1u;
-        const long long dst = pos + __popc(mine & ((1u << bit) - 1u)) + (half ? __popc(first) : 0);
-        if (on && dst < a.idx_capacity) a.idx[dst] = (w0 + 2 * i + half) * 32 + bit;
-        pos += __popc(first) + __popc(second);
+    const int most = wave_reduce<1>((int)__popc(wd), [](int x, int y) { return max(x, y); });
+    if (most <= kFillLaneBits) {
+        // few columns per word: every lane stores its own word's, one after the other.  Its first entry comes after the
+        // columns of the lower lanes, whose numbers are added up bit by bit.
+        const unsigned pc = __popc(wd);
+        unsigned mine = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {                    // pc <= kFillLaneBits < 16
+            const unsigned long long m = __ballot((pc >> k) & 1u);
+            mine += __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0)) << k;
+        }
+        unsigned rest = wd;
+        long long dst = pos + mine;
+        for (int k = 0; k < most; ++k) {
+            if (rest) {
+                if (dst < a.idx_capacity) a.idx[dst] = w * 32 + __builtin_ctz(rest);
+                rest &= rest - 1;
+                ++dst;
+            }
+        }
+    } else {
+        // two words per step: lanes 0..31 test word 2 i, lanes 32..63 word 2 i + 1 (coalesced stores); only the word
+        // pairs that hold a selected column are visited (scalar loop over a bit mask)
+        const int bit = lane & 31, half = lane >> 5;
+        unsigned long long pairs = (nzw | (nzw >> 1)) & 0x5555555555555555ull;
+        while (pairs) {
+            const int i = __builtin_ctzll(pairs) >> 1;
+            pairs &= pairs - 1;
+            const unsigned first = __builtin_amdgcn_readlane(wd, 2 * i), second = __builtin_amdgcn_readlane(wd, 2 * i + 1);
+            const unsigned mine = half ? second : first;
+            const bool on = (mine >> bit) & 1u;
+            const long long dst = pos + __popc(mine & ((1u << bit) - 1u)) + (half ? __popc(first) : 0);
+            if (on && dst < a.idx_capacity) a.idx[dst] = (w0 + 2 * i + half) * 32 + bit;
+            pos += __popc(first) + __popc(second);
+        }
     }
     // the wave that wrote the group's last entry pads the list to the next multiple of 64 with it
     if (pre + own == cnt) {
         const int top = 63 - __builtin_clzll(nzw);       // own > 0: some word is non-zero
-        const unsigned lastw = __shfl(wd, top, 64);
+        const unsigned lastw = __builtin_amdgcn_readlane(wd, top);
         const int last_key = (w0 + top) * 32 + 31 - __clz(lastw);
         const int padded = (cnt + kIdxPad - 1) / kIdxPad * kIdxPad;
         for (int e = cnt + lane; e < padded; e += 64)
@@ -883,10 +964,14 @@ __global__ __launch_bounds__(256) void fill_kernel(SelectArgs a) {
     }
 }
 
-int launch_fill(const SelectArgs& a, bool scan, hipStream_t st) {
-    const dim3 grid((unsigned)a.p.ngrp_max, (unsigned)((a.nseg + 3) / 4), (unsigned)(a.p.Hq * a.p.B + (scan ? 1 : 0)));
-    return scan ? (int)launch_kernel(fill_kernel<true>, grid, dim3(256), 0, st, a)
-                : (int)launch_kernel(fill_kernel<false>, grid, dim3(256), 0, st, a);
+int launch_fill(const SelectArgs& a, FillMode mode, hipStream_t st) {
+    const dim3 grid((unsigned)a.p.ngrp_max, (unsigned)((a.nseg + 3) / 4),
+                    (unsigned)(a.p.Hq * a.p.B + (mode == kFillOffsets ? 0 : 1)));
+    switch (mode) {
+        case kFillScan: return (int)launch_kernel(fill_kernel<kFillScan>, grid, dim3(256), 0, st, a);
+        case kFillPlaces: return (int)launch_kernel(fill_kernel<kFillPlaces>, grid, dim3(256), 0, st, a);
+        default: return (int)launch_kernel(fill_kernel<kFillOffsets>, grid, dim3(256), 0, st, a);
+    }
 }
 
 }  // namespace aa

@@ -247,6 +247,39 @@ def test_step1_prefill_keeps_no_state(api, engine_mode, lens, Hq, Hkv, n_init, w
     assert (int(stats[1]) > 0) == (theta > -1e29)
 
 
+@pytest.mark.parametrize("N,step,Hq", [(5000, 4, 4), (16500, 1, 32)])     # the scan inside the fill kernel, and before it
+@pytest.mark.parametrize("sel", [0.02, 0.3, 0.5, 0.97])                  # columns per word: below, about and above 12
+def test_lists_of_every_density(api, N, step, Hq, sel):
+    """Lists ascend, are padded with their last entry and hold what the counts say, whichever way their words are expanded; the
+    fused call, whose lists have places of their own, gives the bits that it gives with compact ones."""
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v = (torch.randn(1, h, N, 128, generator=gen, device="cuda").bfloat16() for h in (Hq, 1, 1))
+    cfg = api.Config(block=128, n_init=100, window=150, step=step, theta=0.0)
+    out, want = torch.empty_like(q), torch.empty_like(q)
+    p = api.make_params(cfg, q, k, v, out)
+    b = api.alloc_stage_buffers(p)
+    api.anchor_compute(p, q, k, v, b["M"], b["L"], b["Acc"], b["xa"])
+    # the threshold that lets about that share of columns pass: a normal distribution of pooled scores around the anchors
+    sigma = 1 / math.sqrt(128)
+    one = 1 - (1 - sel) ** (1 / step)                 # a column passes if it passes for one of the step's blocks
+    p.theta = float(b["xa"].mean()) - sigma * math.sqrt(2) * float(torch.erfinv(torch.tensor(1 - 2 * one)))
+    api.stripe_select(p, q, k, b["xa"], b["counts"], b["offsets"], b["idx"], b["flag"], b["ws"])
+    api.sparse_attn(p, q, k, v, b["M"], b["L"], b["Acc"], b["counts"], b["offsets"], b["idx"], want, b["lse"])
+    lse, stats = torch.empty_like(b["lse"]), torch.zeros(4, dtype=torch.int64, device="cuda")
+    ws = torch.full((b["sizes"].prefill_ws_bytes,), 255, dtype=torch.uint8, device="cuda")
+    api.anchor_attention_prefill(p, q, k, v, out, lse, stats, ws)
+    assert torch.equal(out, want) and torch.equal(lse, b["lse"])
+    counts, offs, idx = b["counts"].cpu().numpy(), b["offsets"].cpu().numpy(), b["idx"].cpu().numpy()
+    assert int(stats[1]) == counts.sum() > 0
+    per = len(counts) // Hq
+    for t in range(0, len(counts), 1 + len(counts) // 50):
+        c, W = int(counts[t]), max(100, (t % per) * 128 * step - 150)
+        pad = (c + 63) // 64 * 64
+        lst = idx[offs[t]:offs[t] + pad]
+        assert offs[t + 1] - offs[t] == pad
+        assert (np.diff(lst[:c]) > 0).all() and (c == 0 or (lst[0] >= 100 and lst[c - 1] < W and (lst[c:] == lst[c - 1]).all()))
+
+
 def test_bf16_short_sequences(api):
     for N in (1, 50, 128, 129):
         wl = _wl("t", "bf16", [N], 2, 1, 128, 128, 40 + N, 0)

@@ -74,6 +74,38 @@ int main() {
 """
 
 
+PLACES = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "aa_lists.h"
+
+int main() {
+    long long bad = 0;
+    for (long long span : {64, 128, 192, 256, 512, 1152, 2048, 16384})
+        for (long long n_init : {0, 1, 16, 63, 64, 100, 128, 1000, 5000})
+            for (long long window : {0, 1, 30, 64, 65, 128, 300, 2047, 2048, 40000}) {
+                long long sum = 0;
+                for (long long n = 0; n < 300; ++n) {
+                    if (aa::padded_places(n, span, n_init + window) != sum && !bad++)
+                        printf("span %lld n_init %lld window %lld n %lld\n", span, n_init, window, n);
+                    const long long W = n * span - window > n_init ? n * span - window : n_init;
+                    sum += (W - n_init + 63) / 64 * 64;
+                }
+            }
+    return bad != 0;
+}
+"""
+
+
+def test_places_of_the_lists(tmp_path):
+    src, exe = tmp_path / "places.cpp", tmp_path / "places"
+    src.write_text(PLACES)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I",
+                           os.path.join(ROOT, "paper_2505_23520_amd", "csrc"), str(src), "-o", str(exe)])
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
 def test_divisions_by_known_divisors(tmp_path):
     src, exe = tmp_path / "div.cpp", tmp_path / "div"
     src.write_text(DIVISIONS)
