@@ -226,8 +226,12 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     constexpr std::integral_constant<bool, false> contiguous{};
     constexpr std::integral_constant<bool, true> listed{};
     // ---- Q fragments (B operand of S^T = K Q^T): lane (n, hf) holds Q[row][16 ks + 8 hf .. +8)
+    // (through the stages that the first tiles do not use: Ks1 and Vs0)
+    static_assert(KBYTES >= 2 * kQStageBytes && VBYTES >= 2 * kQStageBytes, "two waves' query rows per stage");
+    char* const qstg = (wave < 2 ? Ks1 : Vs0) + (wave & 1) * kQStageBytes;
     bf16x8 qf[8];
-    load_q_fragments(qf, a, sq, wk.b, wk.h, r, rok, 0, hf);
+    if (a.q_lds) request_q(a, sq, wk.b, wk.h, rw, lane, qstg);
+    else load_q_fragments(qf, a, sq, wk.b, wk.h, r, rok, 0, hf);
 
     // ---- pipeline prologue: the first K tile goes out ahead of the cached state, which is not needed
     // before the first P V block
@@ -247,6 +251,10 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     __builtin_amdgcn_sched_barrier(0);
     // K tile 0 is there; the 16 loads of the cached accumulators are younger and may still be on their way
     if (flags & kEngLoadState) __builtin_amdgcn_s_waitcnt(0x4F70); else wait_vmem();
+    if (a.q_lds) {
+        read_q(qf, qstg, rok, n, hf);
+        __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0): read before the barrier, behind which V tile 0 takes the place
+    }
     bare_barrier();
 
     // operand addresses inside a stage (bytes): K row of key 32 kb + n; V chunk read by this lane
@@ -557,7 +565,9 @@ static size_t recompute_extra_lds(const KParams& p) {
     return p.step >= 8 && blocks > 512 && blocks <= 1024 ? 8192 : 0;
 }
 
-int launch_engine_bf16(const EngineArgs& ea, unsigned grid, hipStream_t st) {
+int launch_engine_bf16(const EngineArgs& args, unsigned grid, hipStream_t st) {
+    EngineArgs ea = args;
+    ea.q_lds = q_through_lds(ea.p);
     switch (ea.flags) {
 #define AA_ENGINE_CASE(F, lds) \
     case (F): return (int)launch_kernel(engine_bf16_kernel<(F)>, dim3(grid), dim3(256), lds, st, ea);

@@ -72,6 +72,39 @@ __device__ __forceinline__ void load_q_fragments(bf16x8 (&qf)[8], const EngineAr
     }
 }
 
+// The same through 8 KB of LDS that belong to the wave, in two steps.  A lane that fetches its own row's pieces makes every load
+// instruction 64 accesses to the L1; here 16 lanes fetch a 256-byte row together, and the fragments are read back.  Piece c of row
+// i is stored in place c ^ (i % 8), so that the reads of eight consecutive rows fall into different banks.
+// 128-row engine, 32 / 8 heads: 30011 tokens 876 -> 863 us, 131072 4677 -> 4642, two dense prompts of 3001 149.2 -> 148.5.  Up to two
+// work-groups per CU (512 blocks) share the L1 anyway and the second step only lengthens the way to the first tile (1000
+// tokens with inputs in memory 24.9 -> 25.1): such calls load fragments directly.
+// request_q: 8 asynchronous loads (rows past the end of the sequence: its last row); rows must lie less than 2^27 bytes apart.
+constexpr int kQStageBytes = 32 * 256;
+inline bool q_through_lds(const KParams& p) {
+    return p.qs[2] < (1ll << 26) && (p.total + BQ - 1) / BQ * p.Hq > 512;
+}
+__device__ __forceinline__ void request_q(const EngineArgs& a, const Seq& sq, int b, int h, int rw, int lane, char* stg) {
+    const KParams& p = a.p;
+    const int first = min(rw, sq.len - 1), last = sq.len - 1 - first;
+    const unsigned stb = (unsigned)p.qs[2] * 2u;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)((const unsigned short*)a.q + tok_offset(p, p.qs, sq, b, h, first)), 0, (int)(31u * stb + 2u * D), 0x00020000);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int row = 4 * i + (lane >> 4);
+        const unsigned off = (unsigned)min(row, last) * stb + 16u * ((lane & 15) ^ (row & 7));
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(stg + 1024 * i), 16, (int)off, 0, 0, 0);
+    }
+}
+__device__ __forceinline__ void read_q(bf16x8 (&qf)[8], const char* stg, bool rok, int n, int hf) {
+    const bf16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+        const bf16x8 x = *(const bf16x8*)(stg + 256 * n + 16 * ((2 * ks + hf) ^ (n & 7)));
+        qf[ks] = rok ? x : zero8;
+    }
+}
+
 // How far a row's maximum may exceed the reference, in raw dot-product units.  Finite for the smallest scales too, so that
 // a first maximum always raises the reference from -inf.
 __device__ __forceinline__ float rescale_limit(float c2) { return fminf(kRescaleLog2 / c2, 3.402823466e38f); }

@@ -280,6 +280,25 @@ def test_lists_of_every_density(api, N, step, Hq, sel):
         assert (np.diff(lst[:c]) > 0).all() and (c == 0 or (lst[0] >= 100 and lst[c - 1] < W and (lst[c:] == lst[c - 1]).all()))
 
 
+def test_query_rows_far_apart(api):
+    """Query rows 2^27 bytes apart, beyond the offsets of the loads through LDS: the same bits as from contiguous ones, which
+    come through LDS in a call of this many blocks."""
+    N, H, gen = 140, 300, torch.Generator(device="cuda").manual_seed(2)
+    q, k, v = (torch.randn(1, H, N, 128, generator=gen, device="cuda").bfloat16() for _ in range(3))
+    far = torch.as_strided(torch.empty(N << 26, dtype=torch.bfloat16, device="cuda"), (1, H, N, 128), (0, 128, 1 << 26, 1))
+    far.copy_(q)
+    got = []
+    for x in (q, far):
+        out = torch.empty_like(q)
+        p = api.make_params(api.Config(step=1), x, k, v, out)
+        ws = torch.empty(api.anchor_sizes(p).prefill_ws_bytes, dtype=torch.uint8, device="cuda")
+        api.anchor_attention_prefill(p, x, k, v, out, None, None, ws)
+        dense = torch.empty_like(q)
+        api.dense_causal_flash(p, x, k, v, dense, None)
+        got += [out, dense]
+    assert torch.equal(got[0], got[2]) and torch.equal(got[1], got[3])
+
+
 def test_bf16_short_sequences(api):
     for N in (1, 50, 128, 129):
         wl = _wl("t", "bf16", [N], 2, 1, 128, 128, 40 + N, 0)
