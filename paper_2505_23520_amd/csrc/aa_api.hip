@@ -44,6 +44,7 @@ struct Plan {
     // byte offsets inside the workspaces
     size_t sel_qhi, sel_qlo, sel_qln, sel_kmax, sel_bits, sel_segc, sel_kp;   // stripe_select workspace
     size_t pf_M, pf_L, pf_Acc, pf_xa, pf_counts, pf_offsets, pf_flag, pf_idx, pf_sel;  // prefill workspace
+    size_t pf_partq, pf_partm;                                                                  // fp32 only
 };
 
 // candidates of the first `ngroups` groups of a sequence, each group's count rounded up to a list
@@ -181,6 +182,12 @@ int make_plan(const aa_params* p, Plan* pl) {
     pl->pf_flag = off; off += 256;
     pl->pf_idx = off; off += align256((size_t)s.idx_capacity_max * 4);
     pl->pf_sel = off; off += s.select_ws_bytes;
+    pl->pf_partq = pl->pf_partm = off;
+    if (p->dtype == AA_FP32 && p->granularity == AA_STRIPE) {
+        const size_t tiles = (size_t)s.blocks * (size_t)cdiv(p->block_q, 32);
+        off += align256(tiles * p->d * 4);
+        pl->pf_partm = off; off += align256(tiles * 4);
+    }
     s.prefill_ws_bytes = off;
     return AA_OK;
 }
@@ -300,10 +307,11 @@ bool recompute_anchor(const Plan& pl, const aa_params* p) {
 
 // sel_ws (nullable): a stripe_select workspace (with the call's counts); the bf16 engines then also leave the pooled queries of
 // stage 2 there, and the fp32 path leaves the pooled anchors to run_select (which is told so).
-// out (nullable), lse, stats: see EngineArgs::direct; total, call_stats: the sums that the fill kernel adds to, cleared here
+// out (nullable), lse, stats: see EngineArgs::direct; total, call_stats: the sums that the fill kernel adds to, cleared here;
+// parts (nullable): the prefill workspace, where the fp32 path then leaves its sums per 32-row tile
 int run_anchor(const Plan& pl, const aa_params* p, const void* q, const void* k, const void* v, float* M, float* L,
-               float* Acc, float* xa, char* sel_ws, int32_t* counts, long long* total, int64_t* call_stats, void* out,
-               float* lse, int64_t* stats, hipStream_t st) {
+               float* Acc, float* xa, char* sel_ws, int32_t* counts, char* parts, long long* total, int64_t* call_stats,
+               void* out, float* lse, int64_t* stats, hipStream_t st) {
     EngineArgs ea;
     memset(&ea, 0, sizeof(ea));
     ea.p = pl.kp;
@@ -326,6 +334,12 @@ int run_anchor(const Plan& pl, const aa_params* p, const void* q, const void* k,
         return engine_status(launch_anchor_max_bf16(ea, (unsigned)((long long)pl.kp.nblk_max * pl.kp.Hq * pl.kp.B), st),
                              "anchor_max_bf16_kernel");
     }
+    if (parts) {                            // fp32 stripes in the fused call
+        ea.flags |= kEngParts;
+        ea.qp_hi = parts + pl.pf_partq; ea.qlo_norm = (float*)(parts + pl.pf_partm);
+        ea.zero_counts = counts; ea.zero_seg = (int*)(sel_ws + pl.sel_segc); ea.nseg = (int)cdiv(pl.nwords, 64);
+        ea.zero_total = total; ea.zero_stats = (long long*)call_stats;
+    }
     const int rc = launch_engine(pl, p, ea, st);
     if (rc != AA_OK || p->dtype == AA_BF16 || sel_ws || !xa) return rc;
     SelectArgs sa;
@@ -342,7 +356,7 @@ int run_anchor(const Plan& pl, const aa_params* p, const void* q, const void* k,
 // stats (nullable): receives attended pairs and selected entries
 int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k, const float* xa, int32_t* counts,
                int64_t* offsets, int32_t* idx, int64_t cap, int32_t* flag, char* ws, const float* fused_M, float* xa_out,
-               long long* total, int64_t* stats, hipStream_t st) {
+               const char* parts, long long* total, int64_t* stats, hipStream_t st) {
     const KParams& kp = pl.kp;
     SelectArgs sa;
     memset(&sa, 0, sizeof(sa));
@@ -412,7 +426,11 @@ int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k,
         const dim3 gm((unsigned)(mask_per_xcd > 0 ? mask_per_xcd * 8 : 8));
         AA_LAUNCH(mask_bf16_kernel, gm, dim3(256), 0, st, sa);
     } else {
-        AA_LAUNCH(pool_fp32_kernel, gblk, dim3(256), 0, st, sa);
+        if (parts) {
+            sa.part_q = (const float*)(parts + pl.pf_partq); sa.part_m = (const float*)(parts + pl.pf_partm);
+        } else {
+            AA_LAUNCH(pool_fp32_kernel, gblk, dim3(256), 0, st, sa);
+        }
         const int rc = engine_status(launch_mask_fp32(sa, st), "mask_fp32_kernel");
         if (rc != AA_OK) return rc;
     }
@@ -474,7 +492,7 @@ int anchor_compute(const aa_params* params, const void* q, const void* k, const 
     if (!q || !k || !v || !M || !L || !xa_pooled) return AA_EINVAL;
     if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(Acc)) return AA_EINVAL;
     return run_anchor(pl, params, q, k, v, M, L, Acc, xa_pooled, nullptr, nullptr, nullptr, nullptr, nullptr,
-                      nullptr, nullptr, (hipStream_t)stream);
+                      nullptr, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int stripe_select(const aa_params* params, const void* q, const void* k, const float* xa_pooled, int32_t* counts,
@@ -487,7 +505,7 @@ int stripe_select(const aa_params* params, const void* q, const void* k, const f
     if (idx_capacity < 0 || misaligned(q) || misaligned(k) || misaligned(idx) || misaligned(ws)) return AA_EINVAL;
     if (ws_bytes < pl.sz.select_ws_bytes) return AA_EWORKSPACE;
     return run_select(pl, params, q, k, xa_pooled, counts, offsets, idx, idx_capacity, overflow_flag, (char*)ws,
-                      nullptr, nullptr, nullptr, nullptr, (hipStream_t)stream);
+                      nullptr, nullptr, nullptr, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int stripe_select_noalloc(const aa_params* params, const void* q, const void* k, const float* xa_pooled,
@@ -503,7 +521,7 @@ int stripe_select_noalloc(const aa_params* params, const void* q, const void* k,
     rc = scratch_of_current_device(&ws);
     if (rc != AA_OK) return rc;
     return run_select(pl, params, q, k, xa_pooled, counts, offsets, idx, idx_capacity, overflow_flag, (char*)ws,
-                      nullptr, nullptr, nullptr, nullptr, (hipStream_t)stream);
+                      nullptr, nullptr, nullptr, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int sparse_attn(const aa_params* params, const void* q, const void* k, const void* v, const float* M, const float* L,
@@ -546,16 +564,22 @@ int anchor_attention_prefill(const aa_params* params, const void* q, const void*
     // the other kernels' launches alone took 25 us.  At 8k tokens and step 16 it is a quarter of the rows.
     const bool direct = direct_ok(params);
     if (direct && no_candidates(pl.kp))
-        return run_anchor(pl, params, q, k, v, M, L, Acc, nullptr, nullptr, nullptr, nullptr, nullptr, out, lse, stats, st);
+        return run_anchor(pl, params, q, k, v, M, L, Acc, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, out, lse, stats, st);
     // every list at a place of its own where the places can be computed (the index region holds every candidate)
     const bool places = (long long)params->block_q * params->step % kIdxPad == 0;
     long long* total = places ? (long long*)offsets + pl.sz.groups : nullptr;
+    // fp32: stage 1 leaves sums of every 32 rows, which the mask kernel turns into the pooled rows; a launch less (4 us), but
+    // every mask wave adds up the tiles of every block again.  Whole call, pooling kernel / sums: blocks of 64 (two tiles) 1024 tokens, 1
+    // head 31.0 / 28.2 us, 5098 tokens, 2 heads 37.6 / 35.7; blocks of 128 (four) 800 tokens, 8 heads 41.6 / 38.6, 4000
+    // tokens 95.4 / 96.8, 6000 226 / 230.
+    const bool few = params->block_q <= 64 || pl.kp.total * params->Hq <= 16384;
+    char* parts = few && params->dtype == AA_FP32 && params->granularity == AA_STRIPE ? w : nullptr;
     const bool again = recompute_anchor(pl, params);
     rc = run_anchor(pl, params, q, k, v, again ? nullptr : M, L, Acc, xa, w + pl.pf_sel, counts,
-                    total, places ? stats : nullptr, direct && !again ? out : nullptr, lse, nullptr, st);
+                    parts, total, places ? stats : nullptr, direct && !again ? out : nullptr, lse, nullptr, st);
     if (rc != AA_OK) return rc;
     rc = run_select(pl, params, q, k, xa, counts, offsets, idx, pl.sz.idx_capacity_max, flag, w + pl.pf_sel, M, xa,
-                    total, stats, st);
+                    parts, total, stats, st);
     if (rc != AA_OK) return rc;
     rc = run_sparse(pl, params, q, k, v, again ? nullptr : M, L, Acc, counts, offsets, idx, pl.sz.idx_capacity_max, out, lse,
                     direct && !again, st);

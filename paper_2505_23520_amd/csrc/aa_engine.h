@@ -10,7 +10,8 @@ enum : int {
     kEngList = 4,           // walk the chunks of the group's selected-column list
     kEngLoadState = 8,      // start from (M, L, Acc) instead of (-inf, 0, 0)
     kEngStoreState = 16,    // write M, L, (Acc), pooled anchor
-    kEngStoreOut = 32       // write out = acc / l and lse
+    kEngStoreOut = 32,      // write out = acc / l and lse
+    kEngParts = 64          // fp32, with kEngStoreState: write sums per 32-row tile, clear stage 2's counters
 };
 
 struct EngineArgs {
@@ -23,7 +24,9 @@ struct EngineArgs {
     const int* idx;
     float *Mout, *Lout, *Accout, *xa;
     // stage 1 only, nullable: pooled queries of stage 2 (bf16 hi / lo rows of 128, norm of lo),
-    // written from the Q fragments the block's work-group holds anyway (see aa_pool.h)
+    // written from the Q fragments the block's work-group holds anyway (see aa_pool.h).  fp32 with kEngParts: qp_hi and
+    // qlo_norm receive the sums of every 32-row tile's queries (rows of d floats) and maxima, of which mask_fp32_kernel makes the
+    // block means; tile t of block i at (block index) * ceil(bq / 32) + t
     void *qp_hi, *qp_lo;
     float* qlo_norm;
     // stage 1 only, nullable: largest key norm per (KV head, key block) for stage 2, and the counters to clear for it

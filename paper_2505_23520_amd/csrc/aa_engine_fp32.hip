@@ -30,6 +30,7 @@
 // 60 -> 37 us.
 #include "aa_common.h"
 #include "aa_engine.h"
+#include "aa_pool.h"
 
 #include <type_traits>
 
@@ -178,7 +179,14 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int n = lane & 31, hf = lane >> 5;
 
-    if (flags & kEngStoreState) store_dense_stats(a);
+    if (flags & kEngStoreState) {
+        store_dense_stats(a);
+        if (flags & kEngParts) {
+            const long long wg = blockIdx.x + (long long)gridDim.x * blockIdx.y;
+            clear_counters(a.zero_counts, a.groups_total, a.zero_seg, a.nseg, a.zero_total, a.zero_stats,
+                           wg * (64 * NW) + threadIdx.x, (long long)gridDim.x * gridDim.y * (64 * NW));
+        }
+    }
     if (!engine_selected(a)) return;
     const unsigned id = blockIdx.y * kGridX + blockIdx.x;
     if (id >= map.tiles * map.heads.d) return;
@@ -298,6 +306,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
     k_rows(key);
 #pragma unroll
     for (int j = 0; j < KS; ++j) load_k(j);
+    auto part_index = [&]() -> long long { return blk_index(p, sq, wk.b, wk.h, blk) * map.rts.d + (row0 - blk * p.bq) / RT; };
     // the waves share the rows: each splits its part of them
     uintx4 qreg[QREG ? KS : 1];
     Split own[(KS + NW - 1) / NW];
@@ -306,6 +315,13 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
         const int j = i * NW + wave;
         if (j >= KS) break;
         const floatx4 x = *(const floatx4*)(qsrc + 16 * j), y = *(const floatx4*)(qsrc + 16 * j + 4);
+        if ((flags & kEngParts) && !direct) {
+            float f[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) f[e] = rok ? (e < 4 ? x[e & 3] : y[e & 3]) : 0.f;
+            const float sum = half_sums8(f, n);
+            if (n % 4 == 0) ((float*)a.qp_hi)[part_index() * D + 16 * j + 8 * hf + n / 4] = sum;
+        }
         own[i].pair(0, x[0], x[1]); own[i].pair(1, x[2], x[3]); own[i].pair(2, y[0], y[1]); own[i].pair(3, y[2], y[3]);
         sm.q[0][j][lane] = own[i].h;
         sm.q[1][j][lane] = own[i].l;
@@ -579,6 +595,10 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
     }
 
     float ms = mall * p.sigma;
+    if ((flags & kEngParts) && !direct && wave == 0) {
+        const float sum = half_sum(rok ? ms : 0.f);
+        if (lane == 0) a.qlo_norm[part_index()] = sum;
+    }
     if (!rok) return;
     const bool first = wave == 0 && hf == 0;
     bool store_out = (flags & kEngStoreOut) != 0;
@@ -613,11 +633,12 @@ int launch_engine_fp32(const EngineArgs& ea, hipStream_t st) {
     map.set(p);
     const long long stride = p.ks[2] > p.vs[2] ? p.ks[2] : p.vs[2];
     const bool wide = stride >= (1ll << 30) || (long long)p.N * stride >= (1ll << 30);
-    switch ((p.d * 64 + ea.flags) * 2 + wide) {
+    switch ((p.d * 128 + ea.flags) * 2 + wide) {
 #define AA_ENGINE_CASE(d, F, w) \
-    case (((d) * 64 + (F)) * 2 + w): return (int)launch_kernel(engine_fp32_kernel<(d), (F), w>, grid, dim3(64 * NW), 0, st, ea, map);
+    case (((d) * 128 + (F)) * 2 + w): return (int)launch_kernel(engine_fp32_kernel<(d), (F), w>, grid, dim3(64 * NW), 0, st, ea, map);
 #define AA_ENGINE_CASES(d, w)                                            \
     AA_ENGINE_CASE(d, kEngAnchorRegion | kEngStoreState, w)              \
+    AA_ENGINE_CASE(d, kEngAnchorRegion | kEngStoreState | kEngParts, w)  \
     AA_ENGINE_CASE(d, kEngList | kEngLoadState | kEngStoreOut, w)        \
     AA_ENGINE_CASE(d, kEngList | kEngAnchorRegion | kEngStoreOut, w)     \
     AA_ENGINE_CASE(d, kEngAnchorRegion | kEngDense | kEngStoreOut, w)

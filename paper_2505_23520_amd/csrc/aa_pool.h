@@ -40,6 +40,35 @@ template <int LAST, class T, class Op> __device__ __forceinline__ T wave_reduce(
     return x;
 }
 
+// fp32 path.  Sum over the 32 lanes of a wave's half, and, for eight values per lane, a reduce-scatter of their sums: lane n
+// of the half returns that of value n / 4 (n % 4 = 0: the others hold the same).  The order of the additions is fixed here:
+// stage 1 and the pooling kernel give the same bits.
+__device__ __forceinline__ float half_sum(float x) {
+    const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+    x += lane_xor<8>(x);
+    x += lane_xor<4>(x);
+    x += lane_xor<2>(x);
+    return x + lane_xor<1>(x);
+}
+__device__ __forceinline__ float half_sums8(float (&f)[8], int n) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(f[i]), __float_as_uint(f[4 + i]), false, false);
+        f[i] = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+    }
+    const bool b8 = n & 8, b4 = n & 4;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const float keep = b8 ? f[2 + i] : f[i], send = b8 ? f[i] : f[2 + i];
+        f[i] = keep + lane_xor<8>(send);
+    }
+    const float keep = b4 ? f[1] : f[0], send = b4 ? f[0] : f[1];
+    float x = keep + lane_xor<4>(send);
+    x += lane_xor<2>(x);
+    return x + lane_xor<1>(x);
+}
+
 // Column sums over the 32 rows of a wave's half (lanes with the same hf): a reduce-scatter over
 // the lane bits 16, 8, 4, 2, 1 -- at every level a lane keeps one half of its values and receives
 // its partner's partial sums for that half.  On return lane (n, hf) holds the sums of columns

@@ -44,6 +44,7 @@ struct SelectArgs {
     const float* xa;          // pooled anchors, per block
     void *qp_hi, *qp_lo;      // bf16 path: pooled queries, hi / lo parts, rows of 128
     float* qp_f32;            // fp32 path: pooled queries, rows of d
+    const float *part_q, *part_m;   // fp32 path, nullable: stage 1's sums per 32-row tile (see EngineArgs::qp_hi), no pooling kernel runs
     const float* m_rows;      // fp32 path, nullable: stage 1's M; the pooling kernel then writes
     float* xa_out;            //   the pooled anchors here
     int first_block;          // fp32 path: blocks before this one are not pooled

@@ -91,14 +91,17 @@ __global__ __launch_bounds__(256) void pool_q_bf16_kernel(SelectArgs a) {
     if (tid < 64) pool_block_write(red, lane, r1 - r0, blk_index(p, sq, b, h, i), a.qp_hi, a.qp_lo, a.qlo_norm);
 }
 
-// fp32: 256 threads per query block.  With qp_f32 set, the block mean of the queries (16 bytes of a row per
-// thread, 1024 / d rows side by side, then added up in LDS); with m_rows set, the pooled anchor (mean of
+// fp32: 256 threads per query block.  With qp_f32 set, the block mean of the queries; with m_rows set, the pooled anchor (mean of
 // M over the block's rows): the fp32 engine's work-groups own 32 rows each, not a block; with segcount set, the
-// counters of stage 2 are cleared.
+// counters of stage 2 are cleared.  Sums per 32-row tile and their order are those of stage 1, which adds rows 16, 8, 4, 2 and 1
+// apart (half_sum): a thread holds 16 bytes of every other row of a tile, a row's threads fetch it together.
+__device__ __forceinline__ float block_sum(float t0, float t1, float t2, float t3) { return (t0 + t1) + (t2 + t3); }
+
 __global__ __launch_bounds__(256) void pool_fp32_kernel(SelectArgs a) {
+    typedef float floatx4 __attribute__((ext_vector_type(4)));
     const KParams& p = a.p;
     const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (a.segcount) {
         const long long wg = blockIdx.x + (long long)gridDim.x * (blockIdx.y + (long long)gridDim.y * blockIdx.z);
         clear_counters(a.counts, a.groups_total, a.segcount, a.nseg, a.total, a.total ? a.stats : nullptr, wg * 256 + tid,
@@ -110,32 +113,41 @@ __global__ __launch_bounds__(256) void pool_fp32_kernel(SelectArgs a) {
     const Seq sq = seq_of(p, b);
     const int r0 = i * p.bq;
     if (r0 >= sq.len) return;
-    const int r1 = min(r0 + p.bq, sq.len);
+    const int nrows = min(p.bq, sq.len - r0);
     const long long bi = blk_index(p, sq, b, h, i);
-    if (a.m_rows && tid < 64) {
-        const float* m = a.m_rows + row_index(p, sq, b, h, r0);
-        float s = 0.f;
-        for (int r = tid; r < r1 - r0; r += 64) s += m[r];
+    const float inv = 1.f / (float)nrows;
+    __shared__ __attribute__((aligned(16))) float part[4][2][128];
+    __shared__ float mpart[4];
+    if (a.m_rows) {                                      // a wave per tile; rows that do not exist count 0
+        const int r = 32 * wave + (lane & 31);
+        const float sum = half_sum(r < nrows ? a.m_rows[row_index(p, sq, b, h, r0 + r)] : 0.f);
+        if (lane == 0) mpart[wave] = sum;
+    }
+    if (a.qp_f32) {
+        const int d4 = p.d / 4, c = tid % d4, odd = tid / d4 & 1, tile = tid / d4 >> 1;
+        if (tile < 4) {
+            const float* src = (const float*)a.q + tok_offset(p, p.qs, sq, b, h, r0) + 4 * c;
+            floatx4 x[16];
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-        if (tid == 0) a.xa_out[bi] = s / (float)(r1 - r0);
+            for (int k = 0; k < 16; ++k) {
+                const int r = 32 * tile + 2 * k + odd;
+                x[k] = *(const floatx4*)(src + (long long)min(r, nrows - 1) * p.qs[2]);
+                if (r >= nrows) x[k] = floatx4{0.f, 0.f, 0.f, 0.f};
+            }
+#pragma unroll
+            for (int w = 8; w >= 1; w /= 2)
+#pragma unroll
+                for (int k = 0; k < w; ++k) x[k] += x[k + w];
+            *(floatx4*)&part[tile][odd][4 * c] = x[0];
+        }
     }
-    if (!a.qp_f32) return;
-    __shared__ __attribute__((aligned(16))) float part[1024];
-    const int d4 = p.d / 4, c = tid % d4, rs = tid / d4, nrs = 256 / d4;
-    const float* src = (const float*)a.q + tok_offset(p, p.qs, sq, b, h, 0) + 4 * c;
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 4
-    for (int r = r0 + rs; r < r1; r += nrs) {
-        const float4 x = *(const float4*)(src + (long long)r * p.qs[2]);
-        s.x += x.x; s.y += x.y; s.z += x.z; s.w += x.w;
-    }
-    *(float4*)(part + rs * p.d + 4 * c) = s;
     __syncthreads();
-    if (tid < p.d) {
-        float t = 0.f;
-        for (int k = 0; k < nrs; ++k) t += part[k * p.d + tid];
-        a.qp_f32[bi * p.d + tid] = t / (float)(r1 - r0);
+    if (a.m_rows && tid == 0) a.xa_out[bi] = block_sum(mpart[0], mpart[1], mpart[2], mpart[3]) * inv;
+    if (a.qp_f32 && tid < p.d) {
+        float t[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = part[e][0][tid] + part[e][1][tid];
+        a.qp_f32[bi * p.d + tid] = block_sum(t[0], t[1], t[2], t[3]) * inv;
     }
 }
 
@@ -449,7 +461,10 @@ __global__ __launch_bounds__(256, 3) void mask_bf16_kernel(SelectArgs a) {
 // become one 32-bit word of rows, and a ballot per group gives the bit word of the 32 keys.
 // Latency-bound at the sizes of fp32 use; 4000 tokens, 8 / 2 heads, d = 128: 59 us with one key per thread and
 // vector FMAs (every thread streaming its own key row), 9 us so; the pooling kernel 32 -> 5 us.
-template <int D>
+// PARTS > 0: the pooled rows are made here from stage 1's sums per 32-row tile (fused call: a launch less, 4 us; 1024 tokens, 1 head,
+// d = 64: 31.0 -> 28.4 us for the whole call).
+// At most PARTS tiles a block.
+template <int D, int PARTS>
 __global__ __launch_bounds__(256) void mask_fp32_kernel(SelectArgs a) {
     constexpr int NK = D / 8;
     typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -475,11 +490,38 @@ __global__ __launch_bounds__(256) void mask_fp32_kernel(SelectArgs a) {
     unsigned carry = 0;                                  // bit word so far of a group that continues in the next tile
     for (int i0 = (int)g0 * p.step; i0 < nblk; i0 += 32) {
         const int rows = min(32, nblk - i0);
-        const float* qsrc = a.qp_f32 + (bi0 + i0 + min(n, rows - 1)) * D + 4 * hf;
+        const int blk = i0 + min(n, rows - 1);           // this lane's pooled row
+        float xrow = 0.f, inv = 1.f;
+        const float* qsrc;
+        int nt = 1;                                      // tiles of the block
+        if (PARTS > 0) {
+            const int rts = (p.bq + 31) / 32, nrows = min(p.bq, sq.len - blk * p.bq);
+            const long long t = (bi0 + blk) * rts;
+            inv = 1.f / (float)nrows;
+            nt = (nrows + 31) / 32;
+            float m[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < PARTS; ++i) m[i] = i < nt ? a.part_m[t + min(i, nt - 1)] : 0.f;
+            xrow = block_sum(m[0], m[1], m[2], m[3]) * inv;
+            qsrc = a.part_q + t * D + 4 * hf;
+        } else {
+            qsrc = a.qp_f32 + (bi0 + blk) * D + 4 * hf;
+        }
         floatx16 s = kZero16;
 #pragma unroll
         for (int j = 0; j < NK; ++j) {
-            const floatx4 x = *(const floatx4*)(qsrc + 8 * j);
+            floatx4 x = *(const floatx4*)(qsrc + 8 * j);
+            if (PARTS > 0) {
+                floatx4 y[4] = {x, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+                for (int i = 1; i < PARTS; ++i) {
+                    const floatx4 z = *(const floatx4*)(qsrc + min(i, nt - 1) * D + 8 * j);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) y[i][e] = i < nt ? z[e] : 0.f;
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = block_sum(y[0][e], y[1][e], y[2][e], y[3][e]) * inv;
+            }
 #pragma unroll
             for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], kf[j][e], s, 0, 0, 0);
         }
@@ -487,7 +529,7 @@ __global__ __launch_bounds__(256) void mask_fp32_kernel(SelectArgs a) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int row = 8 * (v >> 2) + 4 * hf + (v & 3);
-            const float xbar = p.use_anchor ? a.xa[bi0 + i0 + min(row, rows - 1)] : 0.f;
+            const float xbar = !p.use_anchor ? 0.f : PARTS > 0 ? __shfl(xrow, row, 64) : a.xa[bi0 + i0 + min(row, rows - 1)];
             dec |= (xbar - p.sigma * s[v] <= p.theta) ? 1u << v : 0u;
         }
         dec = (dec | (dec << 8)) & 0x00ff00ffu;          // nibble i of the 16 bits -> nibble 2 i of the word
@@ -525,10 +567,16 @@ __global__ __launch_bounds__(256) void mask_fp32_kernel(SelectArgs a) {
 int launch_mask_fp32(const SelectArgs& a, hipStream_t st) {
     const KParams& p = a.p;
     const dim3 grid((unsigned)((p.N + 127) / 128), (unsigned)p.Hq, (unsigned)p.B);
-    switch (p.d) {
-        case 32: return (int)launch_kernel(mask_fp32_kernel<32>, grid, dim3(256), 0, st, a);
-        case 64: return (int)launch_kernel(mask_fp32_kernel<64>, grid, dim3(256), 0, st, a);
-        case 128: return (int)launch_kernel(mask_fp32_kernel<128>, grid, dim3(256), 0, st, a);
+    const int parts = !a.part_q ? 0 : p.bq <= 32 ? 1 : p.bq <= 64 ? 2 : 4;
+    switch (p.d * 8 + parts) {
+#define AA_MASK_CASE(d, n) \
+    case (d) * 8 + (n): return (int)launch_kernel(mask_fp32_kernel<d, n>, grid, dim3(256), 0, st, a);
+#define AA_MASK_CASES(d) AA_MASK_CASE(d, 0) AA_MASK_CASE(d, 1) AA_MASK_CASE(d, 2) AA_MASK_CASE(d, 4)
+        AA_MASK_CASES(32)
+        AA_MASK_CASES(64)
+        AA_MASK_CASES(128)
+#undef AA_MASK_CASES
+#undef AA_MASK_CASE
         default: return -1;
     }
 }
