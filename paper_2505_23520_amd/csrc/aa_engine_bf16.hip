@@ -36,8 +36,9 @@
 // Measured, 131072 tokens x 32 heads, step 16: anchor computation 3.10 -> 2.71 ms (the two-per-CU form
 // with two V stages before), matrix pipe 50 -> 65 % busy; the engine clock falls from 1.70 to 1.57 GHz
 // at the same time (the card's power limit), which is why the time gains less than the cycles.  Of this the third
-// wave alone gave 5 %, the pinned order 4 %.  Inside the tile loop the pipe is 77 % busy (3980 cycles per
-// tile and three waves); the rest is a work-group's prologue (6400 cycles), epilogue (4000) and replacement.
+// wave alone gave 5 %, the pinned order 4 %.  Inside the tile loop the pipe is 77 % busy (3970 cycles per
+// tile and three waves); the rest is a work-group's prologue (5700 cycles), epilogue (6000, of which what stage 2 needs takes 3800)
+// and replacement.
 // Several blocks per work-group in one loop, which saves the replacement, was 3 to 11 % slower.
 #include "aa_engine_bf16_common.h"
 #include "aa_pool.h"
@@ -558,7 +559,7 @@ __global__ __launch_bounds__(256, 3) void anchor_max_bf16_kernel(EngineArgs a, u
 // of the call fill two slots per CU once to twice and a group is long (its blocks then have chains of uneven length, and the
 // last third of a full chip waits for the longest).  32 heads, three / two per CU: step 16, 3000 tokens (750 blocks)
 // 64.6 / 59.6 us, 4096 (1024) 90.9 / 85.2, two sequences of 2000 81.7 / 76.6, 5000 (1250) 105.2 / 102.9, 8192 (2048)
-// 171.6 / 175.2; step 8, 3000 tokens 50.8 / 49.4; step 4 41.6 / 43.7; up to 512 blocks there is no third either way.  Not
+// 171.6 / 175.2 (before the two regions had a loop each); step 8, 3000 tokens 50.8 / 49.4; step 4 41.6 / 43.7; up to 512 blocks there is no third either way.  Not
 // every such call gains: every column selected, 4096 tokens 131.8 / 136.2; 8 heads, 11000 tokens (688) 84.0 / 88.7.
 static size_t recompute_extra_lds(const KParams& p) {
     const long long blocks = (p.total + BQ - 1) / BQ * p.Hq;

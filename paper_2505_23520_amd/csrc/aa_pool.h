@@ -12,8 +12,8 @@ namespace aa {
 typedef __bf16 pool_bf16x8 __attribute__((ext_vector_type(8)));
 
 // The value of the lane whose number differs in one bit, without a trip through LDS (as __shfl_xor takes it): data-parallel
-// primitives inside a row of 16 lanes.  Exchanging 62 values of a wave so, and by row swaps, instead of through LDS took the
-// pooling of a block from 2500 to 1100 cycles.
+// primitives inside a row of 16 lanes.  With these and row swaps instead of 62 exchanges through LDS, and one barrier instead of three,
+// what stage 2 needs of a block takes the step-1 maximum kernel 4450 cycles instead of 8100, stage 1 3800.
 template <int CTRL> __device__ __forceinline__ int dpp_mov(int x) {
     return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, false);
 }

@@ -4,7 +4,7 @@
 //   mask     : bit (g, j) = OR_{i in g} [ xbar_i - sigma <qbar_i, k_j> <= theta ],  j in C_g
 //   count    : |I_g| = popcount of the group's bits (added up by the stripe mask kernels as they write them; a kernel of its
 //              own for block granularity only)
-//   scan     : offsets = exclusive prefix sum of the counts rounded up to 64
+//   scan     : offsets = exclusive prefix sum of the counts rounded up to 64 (not in the fused call, see fill_kernel)
 //   fill     : ballot / prefix-popcount stream compaction of the bits into ascending lists
 // The bf16 mask kernel is a skinny MFMA GEMM (pooled rows x keys); the pooled
 // query, an fp32 mean, is split into bf16 hi + lo parts so that the products with
