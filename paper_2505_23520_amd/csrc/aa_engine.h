@@ -34,7 +34,6 @@ struct EngineArgs {
     int *zero_counts, *zero_seg;
     long long *zero_total, *zero_stats;
     int nseg;
-    int q_lds;               // bf16, 128 rows: query rows come through LDS (see request_q; set by the launcher)
     void* out;
     float* lse;
     // Fused prefill: rows of a group without candidates (W_g <= n_init) are finished by stage 1, which writes

@@ -106,7 +106,8 @@ __device__ __forceinline__ void stage2_exports(const EngineArgs& a, const Seq& s
 // FLAGS (a combination of kEng*) is a compile-time parameter: every mode gets its own code without
 // the other modes' branches, registers and, above all, merged control-flow paths (where paths with
 // different numbers of outstanding loads meet, the compiler's waits assume the shortest).
-template <int FLAGS>
+// QLDS: the query rows come through LDS (see request_q).
+template <int FLAGS, bool QLDS>
 __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     constexpr int flags = FLAGS;
     constexpr int NW = 4;                            // waves per work-group
@@ -231,7 +232,7 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     static_assert(KBYTES >= 2 * kQStageBytes && VBYTES >= 2 * kQStageBytes, "two waves' query rows per stage");
     char* const qstg = (wave < 2 ? Ks1 : Vs0) + (wave & 1) * kQStageBytes;
     bf16x8 qf[8];
-    if (a.q_lds) request_q(a, sq, wk.b, wk.h, rw, lane, qstg);
+    if (QLDS) request_q(a, sq, wk.b, wk.h, rw, lane, qstg);
     else load_q_fragments(qf, a, sq, wk.b, wk.h, r, rok, 0, hf);
 
     // ---- pipeline prologue: the first K tile goes out ahead of the cached state, which is not needed
@@ -252,7 +253,7 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
     __builtin_amdgcn_sched_barrier(0);
     // K tile 0 is there; the 16 loads of the cached accumulators are younger and may still be on their way
     if (flags & kEngLoadState) __builtin_amdgcn_s_waitcnt(0x4F70); else wait_vmem();
-    if (a.q_lds) {
+    if (QLDS) {
         read_q(qf, qstg, rok, n, hf);
         __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0): read before the barrier, behind which V tile 0 takes the place
     }
@@ -566,12 +567,11 @@ static size_t recompute_extra_lds(const KParams& p) {
     return p.step >= 8 && blocks > 512 && blocks <= 1024 ? 8192 : 0;
 }
 
-int launch_engine_bf16(const EngineArgs& args, unsigned grid, hipStream_t st) {
-    EngineArgs ea = args;
-    ea.q_lds = q_through_lds(ea.p);
-    switch (ea.flags) {
-#define AA_ENGINE_CASE(F, lds) \
-    case (F): return (int)launch_kernel(engine_bf16_kernel<(F)>, dim3(grid), dim3(256), lds, st, ea);
+int launch_engine_bf16(const EngineArgs& ea, unsigned grid, hipStream_t st) {
+    switch (ea.flags * 2 + q_through_lds(ea.p)) {
+#define AA_ENGINE_CASE(F, lds)                                                                                                 \
+    case (F) * 2: return (int)launch_kernel(engine_bf16_kernel<(F), false>, dim3(grid), dim3(256), lds, st, ea);               \
+    case (F) * 2 + 1: return (int)launch_kernel(engine_bf16_kernel<(F), true>, dim3(grid), dim3(256), lds, st, ea);
     AA_ENGINE_CASE(kEngAnchorRegion | kEngStoreState, 0)              // stage 1
     AA_ENGINE_CASE(kEngList | kEngLoadState | kEngStoreOut, 0)         // stage 3 from the cached state
     AA_ENGINE_CASE(kEngList | kEngAnchorRegion | kEngStoreOut, recompute_extra_lds(ea.p))   // stage 3 recomputing the anchor region
