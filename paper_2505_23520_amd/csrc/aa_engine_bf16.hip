@@ -41,6 +41,7 @@
 // and replacement.
 // Several blocks per work-group in one loop, which saves the replacement, was 3 to 11 % slower.
 #include "aa_engine_bf16_common.h"
+#include "aa_items.h"
 #include "aa_pool.h"
 #include "aa_rows.h"
 
@@ -453,13 +454,8 @@ __global__ __launch_bounds__(256, 3) void anchor_max_bf16_kernel(EngineArgs a, u
         x.hk = (int)p.by_grp.div(x.wk.h);
         return x;
     };
-    auto next_block = [&](unsigned& id) -> Block {   // from id on; id >= total: none left
-        Block x = block_of(min(id, total - 1));
-        while (id < total && x.row0 >= x.sq.len) {
-            id += gridDim.x;
-            x = block_of(min(id, total - 1));
-        }
-        return x;
+    auto next_block = [&](unsigned& id, Block& x) -> bool {
+        return next_item(id, gridDim.x, total, x, block_of, [](const Block& y) { return y.row0 < y.sq.len; });
     };
     auto load_q = [&](bf16x8 (&qf)[8], const Block& x) {
         const int r = x.row0 + 32 * wave + n;
@@ -467,8 +463,8 @@ __global__ __launch_bounds__(256, 3) void anchor_max_bf16_kernel(EngineArgs a, u
     };
 
     unsigned id = blockIdx.x;
-    Block cur = next_block(id);
-    if (id >= total) return;
+    Block cur;
+    if (!next_block(id, cur)) return;
     bf16x8 qf[8];
     load_q(qf, cur);
     for (;;) {
@@ -541,14 +537,15 @@ __global__ __launch_bounds__(256, 3) void anchor_max_bf16_kernel(EngineArgs a, u
         }
         wait_vmem();
         id += gridDim.x;
-        const Block nx = next_block(id);
+        Block nx = cur;                              // (none left: this block's rows again)
+        const bool more = next_block(id, nx);
         bf16x8 qn[8];
-        load_q(qn, nx);                              // (none left: the last item's rows again)
+        load_q(qn, nx);
         float ma, mb;
         both_halves(mtrue, ma, mb);
         stage2_exports<false>(a, sq, cur.wk, cur.hk, qf, qpart, red, knorm, row0, rlast, wave, lane, rw + n < sq.len,
                              fmaxf(ma, mb) * p.sigma);
-        if (id >= total) return;
+        if (!more) return;
         cur = nx;
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) qf[ks] = qn[ks];

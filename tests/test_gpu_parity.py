@@ -247,6 +247,25 @@ def test_step1_prefill_keeps_no_state(api, engine_mode, lens, Hq, Hkv, n_init, w
     assert (int(stats[1]) > 0) == (theta > -1e29)
 
 
+def test_step1_prefill_empty_last_sequence(api):
+    """Empty sequences at the ends of a packed batch: the bits of the batch without them (q a view, with room behind it)."""
+    lens, Hq, Hkv, gen = [900, 3333], 64, 8, torch.Generator(device="cuda").manual_seed(5)
+    total = sum(lens)
+    q, k, v = (torch.randn(h, total + 256, 128, generator=gen, device="cuda").bfloat16()[:, :total] for h in (Hq, Hkv, Hkv))
+    outs = []
+    for full in (lens, [0] + lens + [0, 0]):
+        cu = torch.tensor([0] + list(np.cumsum(full)), dtype=torch.int32, device="cuda")
+        out = torch.zeros(Hq, total, 128, dtype=torch.bfloat16, device="cuda")
+        p = api.make_params(api.Config(step=1, theta=2.7), q, k, v, out, cu_seqlens=cu, max_seqlen=max(full))
+        s = api.anchor_sizes(p)
+        assert Hq * ((total + 127) // 128) >= 1536       # (where no state is kept)
+        lse, stats = torch.zeros(s.rows, device="cuda"), torch.zeros(4, dtype=torch.int64, device="cuda")
+        ws = torch.full((s.prefill_ws_bytes,), 255, dtype=torch.uint8, device="cuda")
+        api.anchor_attention_prefill(p, q, k, v, out, lse, stats, ws)
+        outs.append((out, lse, stats))
+    assert all(torch.equal(x, y) for x, y in zip(*outs)) and int(outs[0][2][1]) > 0
+
+
 @pytest.mark.parametrize("N,step,Hq", [(5000, 4, 4), (16500, 1, 32)])     # the scan inside the fill kernel, and before it
 @pytest.mark.parametrize("sel", [0.02, 0.3, 0.5, 0.97])                  # columns per word: below, about and above 12
 def test_lists_of_every_density(api, N, step, Hq, sel):

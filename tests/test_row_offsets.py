@@ -1,5 +1,6 @@
-"""Host test of the byte offsets of K / V rows that the bf16 engines' tile loads use (csrc/aa_rows.h): every lane's
-offset, for token strides up to the largest the library accepts (N * stride * 2 < 2^31), against 64-bit arithmetic."""
+"""Host tests of the index arithmetic that the kernels share with the host.  csrc/aa_rows.h: byte offsets of K / V rows that the
+bf16 engines' tile loads use, every lane's, for token strides up to the largest the library accepts (N * stride * 2 < 2^31),
+against 64-bit arithmetic; csrc/aa_items.h: the blocks a persistent work-group walks; csrc/aa_lists.h; csrc/aa_div.h."""
 import os
 import subprocess
 
@@ -95,6 +96,66 @@ int main() {
     return bad != 0;
 }
 """
+
+
+ITEMS = r"""
+#include <cstdio>
+#include <vector>
+#include "aa_items.h"
+
+// packed batches of query blocks, numbered as if every sequence were as long as the longest
+struct Block { int seq, i, len; };
+
+int main() {
+    long long bad = 0, walked = 0;
+    const std::vector<std::vector<int>> batches = {{5}, {1, 0}, {0, 3}, {7, 26, 0}, {0, 0, 4, 0, 0}, {8, 0, 27, 2}, {0, 1, 0, 1}};
+    for (const auto& blocks : batches)                   // blocks of every sequence
+        for (int heads : {1, 3, 8})
+            for (unsigned stride : {1u, 3u, 8u, 64u, 768u}) {
+                int most = 0, all = 0;
+                for (int n : blocks) { most = n > most ? n : most; all += n * heads; }
+                const unsigned total = (unsigned)(most * heads * (int)blocks.size());
+                auto block_of = [&](unsigned id) {
+                    const int seq = (int)(id / (unsigned)(most * heads));
+                    return Block{seq, most - 1 - (int)(id % (unsigned)(most * heads)) / heads, blocks[seq]};
+                };
+                auto exists = [](const Block& x) { return x.i < x.len; };
+                std::vector<int> seen(total, 0);
+                for (unsigned wg = 0; wg < stride; ++wg) {       // as a work-group walks: requests ahead, then takes
+                    unsigned id = wg;
+                    Block cur{0, 0, 0};
+                    if (!aa::next_item(id, stride, total, cur, block_of, exists)) continue;
+                    for (;;) {
+                        ++seen[id];
+                        id += stride;
+                        Block nx = cur;
+                        const bool more = aa::next_item(id, stride, total, nx, block_of, exists);
+                        if (!exists(nx)) ++bad;                  // its rows are loaded
+                        if (more != (id < total)) ++bad;
+                        if (!more) break;
+                        cur = nx;
+                    }
+                }
+                for (unsigned id = 0; id < total; ++id) {
+                    if (seen[id] != (exists(block_of(id)) ? 1 : 0)) ++bad;
+                    walked += seen[id];
+                }
+                for (unsigned id = 0; id < total; ++id) all -= seen[id];
+                if (all) ++bad;
+            }
+    printf("%lld walked, %lld wrong\n", walked, bad);
+    return bad != 0 || walked < 1000;
+}
+"""
+
+
+def test_walk_over_blocks_requests_only_blocks_that_exist(tmp_path):
+    src, exe = tmp_path / "items.cpp", tmp_path / "items"
+    src.write_text(ITEMS)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I",
+                           os.path.join(ROOT, "paper_2505_23520_amd", "csrc"), str(src), "-o", str(exe)])
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
 
 
 def test_places_of_the_lists(tmp_path):
