@@ -112,17 +112,17 @@ int make_plan(const aa_params* p, Plan* pl) {
     const long long span = (long long)p->block_q * p->step;
     k.nblk_max = (int)cdiv(p->N, p->block_q);
     k.ngrp_max = (int)cdiv(p->N, span);
-    k.by_grp.set(k.grp);
-    k.by_hkv.set(k.Hkv);
-    k.by_step.set(k.step);
-    k.by_bq.set(k.bq);
-    k.by_pair.set((unsigned)k.nblk_max * k.grp);
-    k.by_pair2.set((unsigned)((k.nblk_max + 1) / 2) * k.grp);
     // launch grids put heads (times sequences) on y / z
     if ((long long)p->Hq * p->B > 65535 || p->Hq + p->Hkv > 65535) return AA_EUNSUPPORTED;
     // no grid of the fp32 path limits the groups; such calls are refused because nothing has run them (from 1048561 tokens on,
     // with 8 GB of bit words per head)
     if (p->dtype == AA_FP32 && k.ngrp_max > 65535) return AA_EUNSUPPORTED;
+    k.by_grp.set(k.grp);
+    k.by_hkv.set(k.Hkv);
+    k.by_step.set(k.step);
+    k.by_bq.set(k.bq);
+    k.by_pair.set((unsigned long long)k.nblk_max * k.grp);
+    k.by_pair2.set((unsigned long long)((k.nblk_max + 1) / 2) * k.grp);
 
     aa_sizes& s = pl->sz;
     memset(&s, 0, sizeof(s));

@@ -97,7 +97,7 @@ struct TileMap {
         const unsigned r = (unsigned)((p.bq + RT - 1) / RT);
         tiles = (unsigned)p.nblk_max * r;
         rts.set(r);
-        pair.set(tiles * (unsigned)p.grp);
+        pair.set((unsigned long long)tiles * p.grp);
         heads.set((unsigned)(p.B * p.Hq));
         heads8.set(heads.d >= 8 ? heads.d / 8 : 1);
         hq.set((unsigned)p.Hq);

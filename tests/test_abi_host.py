@@ -94,6 +94,31 @@ def test_rejects_bad_params(api, kw, code):
     assert e.value.code == code
 
 
+def _rows_apart(p, stride):
+    for name in ("q_stride", "k_stride", "v_stride", "o_stride"):
+        setattr(p, name, (ctypes.c_int64 * 3)(0, stride, stride))
+    return p
+
+
+@pytest.mark.parametrize("kw", [
+    dict(dtype=0, N=2**31 - 1, block_q=16, block_kv=16, step=1, Hq=32, Hkv=1),      # blocks x heads: 2^32
+    dict(N=512, Hq=2**30, Hkv=1),                                                      # 4 x 2^30
+    dict(N=2**23 - 1, Hq=65536, Hkv=1),
+    dict(B=2**30, Hq=4, Hkv=4),
+])
+def test_refuses_sizes_whose_products_leave_32_bits(api, kw):
+    """Refused with a code, whatever 32-bit products of the sizes come to."""
+    with pytest.raises(api.AnchorError) as e:
+        api.anchor_sizes(_rows_apart(_params(api, **kw), 128))
+    assert e.value.code == -2
+
+
+def test_accepts_the_largest_head_ratio(api):
+    """8388607 tokens and 65534 query heads of one KV head: 65536 blocks x 65534, just below 2^32."""
+    s = api.anchor_sizes(_rows_apart(_params(api, N=2**23 - 1, Hq=65534, Hkv=1), 128))
+    assert s.blk_cap == 65536 and s.rows == 65534 * (2**23 - 1)
+
+
 def test_engine_field_accepts_only_known_modes(api):
     for mode in (api.AA_ENGINE_AUTO, api.AA_ENGINE_128, api.AA_ENGINE_256):
         api.anchor_sizes(_params(api, engine=mode))

@@ -50,6 +50,7 @@ int main() {
 
 DIVISIONS = r"""
 #include <cstdio>
+#include <initializer_list>
 #include "aa_div.h"
 
 int main() {
@@ -69,6 +70,12 @@ int main() {
             for (unsigned n : ns)
                 if (n < (1u << 31) && f.div(n) != n / d && !bad++) printf("%u / %u: %u\n", n, d, f.div(n));
         }
+    }
+    for (unsigned long long d : {1ull << 31, (1ull << 31) + 1, 1ull << 32, (1ull << 32) + 5, 65536ull * 65534, 1ull << 44}) {
+        aa::FastDiv f{};
+        f.set(d);
+        for (unsigned n : {0u, 1u, 12345u, 0x7ffffffeu, 0x7fffffffu})
+            if (f.div(n) != 0 && !bad++) printf("%u / %llu: %u\n", n, d, f.div(n));
     }
     return bad != 0;
 }
