@@ -53,7 +53,7 @@ struct EngineArgs {
 
 // statistics of a call none of whose groups has candidates: every row attends all keys up to itself
 __device__ __forceinline__ void store_dense_stats(const EngineArgs& a) {
-    if (!a.stats || blockIdx.x != 0 || blockIdx.y != 0 || threadIdx.x != 0) return;
+    if (blockIdx.x != 0 || blockIdx.y != 0 || threadIdx.x != 0 || !a.stats) return;
     long long pairs = 0;
     for (int b = 0; b < a.p.B; ++b) {
         const long long len = a.p.packed ? a.p.cu[b + 1] - a.p.cu[b] : a.p.N;
@@ -61,6 +61,14 @@ __device__ __forceinline__ void store_dense_stats(const EngineArgs& a) {
     }
     a.stats[0] = pairs * a.p.Hq;
     a.stats[1] = 0; a.stats[2] = 0; a.stats[3] = 0;
+}
+
+// Requests all cache lines of the kernel arguments at once.  They are in no cache when a launch begins, and where the code
+// comes upon them one by one, each is a round trip of its own ahead of the first tile.
+__device__ __forceinline__ void touch_args(const EngineArgs& a) {
+    static_assert(sizeof(EngineArgs) == 8 * 64, "members of every line are named below");
+    asm volatile("" ::"s"(a.p.B), "s"(a.p.qs[2]), "s"(a.p.vs[2]), "s"(a.p.blk_cap), "s"(a.p.by_bq.d), "s"(a.q), "s"(a.idx),
+                 "s"(a.kmax_blk), "s"(a.out), "s"(a.sel));
 }
 
 // true iff this launch has work to do (uniform over the grid)

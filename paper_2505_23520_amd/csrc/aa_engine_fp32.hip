@@ -187,7 +187,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
                            wg * (64 * NW) + threadIdx.x, (long long)gridDim.x * gridDim.y * (64 * NW));
         }
     }
-    if (!engine_selected(a)) return;
+    if ((flags & kEngList) && !engine_selected(a)) return;
     const unsigned id = blockIdx.y * kGridX + blockIdx.x;
     if (id >= map.tiles * map.heads.d) return;
     const Work wk = decode_tile(p, map, !(flags & (kEngDense | kEngList)), id);
