@@ -305,6 +305,21 @@ bool recompute_anchor(const Plan& pl, const aa_params* p) {
     return p->dtype == AA_BF16 && p->step == 1 && (long long)p->n_init + p->window <= 512 && blocks >= 1536 && direct_ok(p);
 }
 
+// Fused fp32 prefill: stage 1 leaves sums of every 32 rows, which the mask kernel turns into the pooled rows, instead of a pooling
+// kernel.  That saves a launch and the kernel (4 us and more with the rows), but a mask wave, which meets every block of
+// its keys' future, has d / 8 loads for each of the block's T tiles (1, 2 or 4 as compiled) in its chain: N d T / block is the
+// measure.  Whole call, pooling kernel / sums, us (heads): 8192 (d = 64: 4096 tokens, block 64) 35.4 / 33.4 (1); 8000 (d = 64: 4000,
+// block 128) 41.5 / 40.3 (4); 12000 (d = 128: 3000, block 128) 79.1 / 78.3 (8), (3000, block 32) 44.9 / 44.8 (1); 16000 (d =
+// 128: 4000, block 128) 48.2 / 49.0 (1), (d = 64: 8000, block 64) 89.9 / 90.4 (8), (d = 32: 16000, block 64) 82.2 / 82.8 (2);
+// 32000 (d = 128: 16000, block 64) 339 / 350 (8).  Blocks of at most 32 rows need no addition, and many heads
+// make their pooling kernel long (d = 128, block 32, 8000 tokens: 100 / 103 (4), 167 / 164 (8), 297 / 275 (16)).
+bool pools_from_parts(const KParams& k, const aa_params* p) {
+    if (p->dtype != AA_FP32 || p->granularity != AA_STRIPE) return false;
+    if (p->block_q <= 32 && k.total * p->Hq >= 8ll * p->N) return true;
+    const long long tiles = p->block_q <= 32 ? 1 : p->block_q <= 64 ? 2 : 4;
+    return (long long)p->N * p->d * tiles <= 12288ll * p->block_q;
+}
+
 // sel_ws (nullable): a stripe_select workspace (with the call's counts); the bf16 engines then also leave the pooled queries of
 // stage 2 there, and the fp32 path leaves the pooled anchors to run_select (which is told so).
 // out (nullable), lse, stats: see EngineArgs::direct; total, call_stats: the sums that the fill kernel adds to, cleared here;
@@ -435,9 +450,9 @@ int run_select(const Plan& pl, const aa_params* p, const void* q, const void* k,
         if (rc != AA_OK) return rc;
     }
     if (p->granularity == AA_BLOCK) AA_LAUNCH(count_kernel, ggrp, dim3(256), 0, st, sa);
+    if (sa.list_room) return engine_status(launch_fill(sa, kFillPlaces, st), "fill_kernel");
     // few groups: the fill kernel does the scan's work (a launch less, 5 us); every one of its work-groups then
     // reads up to all segments, 8 per thread at this limit
-    if (sa.list_room) return engine_status(launch_fill(sa, kFillPlaces, st), "fill_kernel");
     const bool fill_scans = segs <= 2048;
     if (!fill_scans) AA_LAUNCH(scan_kernel, dim3(1), dim3(1024), 0, st, sa);
     return engine_status(launch_fill(sa, fill_scans ? kFillScan : kFillOffsets, st), "fill_kernel");
@@ -568,12 +583,7 @@ int anchor_attention_prefill(const aa_params* params, const void* q, const void*
     // every list at a place of its own where the places can be computed (the index region holds every candidate)
     const bool places = (long long)params->block_q * params->step % kIdxPad == 0;
     long long* total = places ? (long long*)offsets + pl.sz.groups : nullptr;
-    // fp32: stage 1 leaves sums of every 32 rows, which the mask kernel turns into the pooled rows; a launch less (4 us), but
-    // every mask wave adds up the tiles of every block again.  Whole call, pooling kernel / sums: blocks of 64 (two tiles) 1024 tokens, 1
-    // head 31.0 / 28.2 us, 5098 tokens, 2 heads 37.6 / 35.7; blocks of 128 (four) 800 tokens, 8 heads 41.6 / 38.6, 4000
-    // tokens 95.4 / 96.8, 6000 226 / 230.
-    const bool few = params->block_q <= 64 || pl.kp.total * params->Hq <= 16384;
-    char* parts = few && params->dtype == AA_FP32 && params->granularity == AA_STRIPE ? w : nullptr;
+    char* parts = pools_from_parts(pl.kp, params) ? w : nullptr;
     const bool again = recompute_anchor(pl, params);
     rc = run_anchor(pl, params, q, k, v, again ? nullptr : M, L, Acc, xa, w + pl.pf_sel, counts,
                     parts, total, places ? stats : nullptr, direct && !again ? out : nullptr, lse, nullptr, st);

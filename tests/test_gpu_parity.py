@@ -112,6 +112,28 @@ def test_fp32_tiles(api, d, block, lens, step, n_init, window, theta):
     assert 0 < worst["selected"] < worst["candidates"]
 
 
+@pytest.mark.parametrize("d,block,N,Hq", [                 # N d T / block below, at and above 12288 (T tiles of a block)
+    (128, 16, 1530, 2), (128, 16, 1544, 2), (128, 16, 1600, 8), (64, 32, 6144, 1), (64, 32, 6145, 1), (32, 48, 9200, 1),
+    (32, 48, 9230, 1), (128, 64, 3072, 1), (128, 64, 3073, 1), (128, 96, 2304, 2), (128, 128, 3072, 2), (128, 128, 3080, 2)])
+def test_fp32_pooled_rows_either_way(api, d, block, N, Hq):
+    """The fused call makes its pooled rows from stage 1's sums or in a kernel of their own: the bits of the stages, which have
+    the kernel."""
+    gen = torch.Generator(device="cuda").manual_seed(N + block)
+    q, k, v = (torch.randn(1, h, N, d, generator=gen, device="cuda") for h in (Hq, 1, 1))
+    out, want = torch.zeros_like(q), torch.zeros_like(q)
+    p = api.make_params(api.Config(block=block, n_init=20, window=block, step=3, theta=0.0), q, k, v, out)
+    b = api.alloc_stage_buffers(p)
+    api.anchor_compute(p, q, k, v, b["M"], b["L"], b["Acc"], b["xa"])
+    p.theta = float(b["xa"].mean())                   # about half of the columns
+    api.stripe_select(p, q, k, b["xa"], b["counts"], b["offsets"], b["idx"], b["flag"], b["ws"])
+    api.sparse_attn(p, q, k, v, b["M"], b["L"], b["Acc"], b["counts"], b["offsets"], b["idx"], want, b["lse"])
+    lse, stats = torch.empty_like(b["lse"]), torch.zeros(4, dtype=torch.int64, device="cuda")
+    ws = torch.full((b["sizes"].prefill_ws_bytes,), 255, dtype=torch.uint8, device="cuda")
+    api.anchor_attention_prefill(p, q, k, v, out, lse, stats, ws)
+    assert torch.equal(out, want) and torch.equal(lse, b["lse"])
+    assert 0 < int(stats[1]) == int(b["counts"].sum())
+
+
 def test_fp32_grid_beyond_32_bits_of_threads(api):
     """65535 sequences of 4128 rows in blocks of 16: 16.9 million tiles, 4.3e9 threads.  Every sequence is the same one
     (batch stride 0), its log-sum-exp has rows of its own."""
