@@ -557,14 +557,16 @@ __global__ __launch_bounds__(256, 3) void anchor_max_bf16_kernel(EngineArgs a, u
 }
 
 // Stage 3 recomputing the anchor region: two work-groups per CU instead of three, by 8 KB of unused LDS, where the query blocks
-// of the call fill two slots per CU once to twice and a group is long (its blocks then have chains of uneven length, and the
-// last third of a full chip waits for the longest).  32 heads, three / two per CU: step 16, 3000 tokens (750 blocks)
-// 64.6 / 59.6 us, 4096 (1024) 90.9 / 85.2, two sequences of 2000 81.7 / 76.6, 5000 (1250) 105.2 / 102.9, 8192 (2048)
-// 171.6 / 175.2 (before the two regions had a loop each); step 8, 3000 tokens 50.8 / 49.4; step 4 41.6 / 43.7; up to 512 blocks there is no third either way.  Not
-// every such call gains: every column selected, 4096 tokens 131.8 / 136.2; 8 heads, 11000 tokens (688) 84.0 / 88.7.
+// of the call fill two slots per CU once to one and three quarters times and a group is long (its blocks then have chains of
+// uneven length, and the last third of a full chip waits for the longest).  32 heads, three / two per CU, us: step 16, 2500 tokens
+// (640 blocks) 51.3 / 51.2, 3000 (768) 63.4 / 60.3, 3500 (896) 70.9 / 69.8, 5000 (1280) 103.2 / 106.0, 8192 (2048) 171.9 /
+// 182.3; step 8, 3000 tokens 51.1 / 48.8, 3500 54.4 / 54.0; step 4, 2500 34.4 / 33.3, 4096 48.6 / 50.7; step 2, 2500 29.5 / 32.7;
+// every column selected, 2500 64.7 / 62.7; 8 heads, 11000 tokens (688) 85.3 / 78.7.  Towards 1024 blocks it depends on the call:
+// 4096 tokens 90.5 / 90.0, every column selected 133.7 / 145.9, two sequences of 2000 82.1 / 79.7, 8 heads, 16000 tokens 106.3 /
+// 114.0.  (16 / 2 heads, 5000 tokens (640) 65.6 / 69.5.)  Up to 512 blocks there is no third either way.
 static size_t recompute_extra_lds(const KParams& p) {
     const long long blocks = (p.total + BQ - 1) / BQ * p.Hq;
-    return p.step >= 8 && blocks > 512 && blocks <= 1024 ? 8192 : 0;
+    return p.step >= 8 && blocks > 512 && blocks <= 896 ? 8192 : 0;
 }
 
 int launch_engine_bf16(const EngineArgs& ea, unsigned grid, hipStream_t st) {
