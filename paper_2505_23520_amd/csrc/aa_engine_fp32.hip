@@ -347,6 +347,11 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
             for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
     };
     reset();
+    // The sum of a block's scores is made before the branches of its masks.  Left alone, the compiler moves it behind them and then
+    // counts the wait states between the last matrix instruction and the first addition along the longer arm only: on
+    // the other, 12 instead of 18 in the fp32 form below, where a row's keys 27 and 31 had the score of earlier instructions, and 9
+    // instead of 12 in the loop.
+    auto keep_here = [](floatx16& s) __attribute__((always_inline)) { asm volatile("" : "+v"(s)); };
     // scores of block t -> probabilities; updates m and l, rescales o
     auto softmax = [&](int t, floatx16& s) {
         if (t < nA) {
@@ -458,6 +463,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
 #pragma unroll
             for (int v = 0; v < 8; ++v) next_v(v);   // (requested with the others they spill)
         }
+        keep_here(s);
         __builtin_amdgcn_sched_barrier(0);
         softmax(t, s);
         Split pr[2];                                 // probabilities of the block's 16-key halves
@@ -533,6 +539,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
                         s2[e & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], s2[e & 1], 0, 0, 0);
                 }
                 floatx16 s = s2[0] + s2[1];
+                keep_here(s);
                 softmax(t, s);
                 v_rows(kk);
 #pragma unroll

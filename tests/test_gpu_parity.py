@@ -191,6 +191,28 @@ def test_fp32_infinities(api, d):
     assert (lse.cpu().double() - torch.logsumexp(s, dim=1)).abs().max() < 1e-5
 
 
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_fp32_infinity_in_stage1(api, d):
+    """The same in stage 1, whose waves then take their blocks again: an infinite value that every row sees spoils its own
+    column of Acc only."""
+    N, gen = 300, torch.Generator(device="cuda").manual_seed(d)
+    q, k, v = (torch.randn(1, 1, N, d, generator=gen, device="cuda") for _ in range(3))
+    s = (q[0, 0].double() @ k[0, 0].double().T) / math.sqrt(d)
+    s.masked_fill_(torch.ones(N, N, dtype=torch.bool, device="cuda").triu(1), -math.inf)
+    m = s.max(dim=1).values
+    e = torch.exp(s - m[:, None])
+    acc = e @ v[0, 0].double()
+    v[0, 0, ::32, 5] = math.inf                      # in every block of keys, so in every wave's
+    p = api.make_params(api.Config(block=32, n_init=32, window=32, step=128, theta=1.0), q, k, v, torch.empty_like(q))
+    b = api.alloc_stage_buffers(p)
+    api.anchor_compute(p, q, k, v, b["M"], b["L"], b["Acc"], b["xa"])
+    got = b["Acc"].view(N, d).double()
+    assert (b["M"].double() - m).abs().max() < 2e-5 and (b["L"].double() / e.sum(dim=1) - 1).abs().max() < 2e-5
+    keep = torch.arange(d, device="cuda") != 5
+    assert (got[:, keep] - acc[:, keep]).norm() < 1e-6 * acc[:, keep].norm()
+    assert not got[:, 5].isfinite().any()
+
+
 def test_fp32_rows_beyond_32_bit_offsets(api):
     """Keys 16 MiB apart: 300 of them span 4.7 GiB and are addressed with 64 bits, to the same bits."""
     N, d, gen = 300, 64, torch.Generator(device="cuda").manual_seed(1)

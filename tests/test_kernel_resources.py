@@ -1,5 +1,6 @@
 """What the compiler makes of the engines' kernels: no vector register spilled (a reload is a vector-memory load, and the
-wait for it waits for the tile loads in flight), and as many waves per SIMD as each kernel is written for."""
+wait for it waits for the tile loads in flight), as many waves per SIMD as each kernel is written for, and
+every result of a matrix instruction left alone for the wait states that the hardware does not see to itself."""
 import os
 import re
 import subprocess
@@ -20,6 +21,70 @@ def test_engines_do_not_spill(tmp_path, source, waves):
     assert len(names) >= 3 and len(spills) == len(occupancy) == len(names)
     assert not any(spills), dict(zip(names, spills))
     assert min(occupancy) >= waves, dict(zip(names, occupancy))
+
+
+# Wait states from a matrix instruction to another instruction that touches its result (its 8 or 16 passes and 4 or 2
+# more; an instruction is one state, s_nop n is 1 + n)
+WAIT_STATES = {"v_mfma_f32_32x32x16_bf16": 12, "v_mfma_f32_32x32x2_f32": 18}
+
+
+def _vgprs(operands):
+    found = set()
+    for first, last, one in re.findall(r"\bv\[(\d+):(\d+)\]|\bv(\d+)\b", operands):
+        found |= {int(one)} if one else set(range(int(first), int(last) + 1))
+    return found
+
+
+def _touched_too_early(body):
+    """(matrix instruction, toucher, states) along every path through a kernel's code"""
+    code, labels = [], {}
+    for line in body.split("\n"):
+        line = line.split(";")[0].strip()
+        if line.endswith(":"):
+            labels[line[:-1]] = len(code)
+        elif line and not line.startswith("."):
+            code.append((line.split(None, 1) + [""])[:2])
+    split = lambda operands: [x.strip() for x in re.split(r",(?![^\[]*\])", operands)]
+    early, checked = [], 0
+    for i, (op, operands) in enumerate(code):
+        if not op.startswith("v_mfma"):
+            continue
+        checked += 1
+        result, states, paths, least = _vgprs(split(operands)[0]), WAIT_STATES[op], [(i + 1, 0)], {}
+        while paths:
+            j, w = paths.pop()
+            while j < len(code) and w < states and w < least.get(j, states):
+                least[j] = w
+                o, x = code[j]
+                if o.startswith("v_mfma"):
+                    d, a, b, c = (_vgprs(y) for y in split(x)[:4])
+                    if (a | b) & result or (c & result and c != result):
+                        early.append((op, o + " " + x, w))
+                    if c == result or d == result:
+                        break                        # the next of a chain, which forwards; its own wait covers the rest
+                elif re.match("v_|ds_|buffer_|global_|flat_", o) and _vgprs(x) & result:
+                    early.append((op, o + " " + x, w))
+                    break
+                if o == "s_endpgm":
+                    break
+                if o.startswith("s_cbranch"):
+                    paths.append((labels[x], w + 1))
+                w += int(x, 0) + 1 if o == "s_nop" else 1
+                j = labels[x] if o == "s_branch" else j + 1
+    return early, checked
+
+
+@pytest.mark.parametrize("source", [s for s in build.SOURCES if s != "aa_api.hip"])
+def test_matrix_results_are_awaited(tmp_path, source):
+    asm = str(tmp_path / "x.s")
+    subprocess.check_call(["hipcc", *build.FLAGS, *build.EXTRA.get(source, []), "--cuda-device-only", "-S",
+                           os.path.join(build.CSRC, source), "-o", asm])
+    checked = 0
+    for name, body in re.findall(r"^(_ZN2aa\S+):.*?\n(.*?)^\s*\.section", open(asm).read(), re.M | re.S):
+        early, n = _touched_too_early(body)
+        assert not early, (name, early[:3])
+        checked += n
+    assert checked > 100
 
 
 def test_list_loop_address(tmp_path):
