@@ -3,7 +3,8 @@
 // dense causal comparator -- arXiv 2505.23520) with fp32 inputs, fp32 products and
 // fp32 probabilities, on the bf16 matrix instruction.
 //
-// Products: every fp32 value is the exact sum of three bf16 parts (h, m, l: 3 x 8 bits), and a product of two values
+// Products: an fp32 value is the exact sum of three bf16 parts (h, m, l: 3 x 8 bits; 0 and magnitudes from 2^-110 to 3.39e38,
+// what lies outside is looked for after the loop and falls back to the fp32 instruction), and a product of two values
 // is six products of parts, hh + hm + mh + mm + hl + lh; the other three are below 2^-24 of it.  Six instructions of
 // 32 matrix cycles for 16 columns take 192 cycles where v_mfma_f32_32x32x2_f32 takes 512.  Scores: the hh products have an
 // accumulator of their own, which sees 8 roundings at d = 128 (64 with the fp32 instruction); relative error of the output
@@ -60,8 +61,15 @@ typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float comp(float x, int) { return x; }
 template <class V> __device__ __forceinline__ float comp(const V& x, int i) { return x[i]; }
 
+// A row's two lanes (n, 0) and (n, 1) combined, without a trip through LDS
+template <class Op> __device__ __forceinline__ float both_halves(float x, Op op) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float sum_halves(float x) { return both_halves(x, [](float a, float b) { return a + b; }); }
+
 // Eight fp32 values as three bf16 parts, x = h + m + l exactly (8 + 8 + 8 bits, each rounded to nearest, so the
-// subtractions are exact); finite x below 3.39e38 and parts above the smallest bf16.
+// subtractions are exact) for 0 and |x| from 2^-110 to 3.39e38; below, l lies among bf16's last subnormals and up to 2^-134 is lost.
 struct Split {
     uintx4 h, m, l;
     __device__ __forceinline__ void pair(int i, float x0, float x1) {        // elements 2 i, 2 i + 1
@@ -287,11 +295,15 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
         }
     };
     // rows of loads v .. v + N - 1: every exchange is issued before the first result is waited for
-    auto load_v = [&](int v, auto count) {
+    // src: byte address of lane 4 hf, made opaque for every block: 16 sums are not kept in registers
+    auto v_lane = [&]() -> int {
+        int src = 16 * hf;
+        asm volatile("" : "+v"(src));
+        return src;
+    };
+    auto load_v = [&](int src, int v, auto count) {
         constexpr int N = decltype(count)::value;
         unsigned lo[N], hi[N];
-        int src = 16 * hf;                           // byte address of lane 4 hf, opaque: 16 sums are not kept in registers
-        asm volatile("" : "+v"(src));
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const int from = src + 4 * (8 * ((v + i) >> 2) + ((v + i) & 3));
@@ -323,6 +335,16 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
             if (n % 4 == 0) ((float*)a.qp_hi)[part_index() * D + 16 * j + 8 * hf + n / 4] = sum;
         }
         own[i].pair(0, x[0], x[1]); own[i].pair(1, x[2], x[3]); own[i].pair(2, y[0], y[1]); own[i].pair(3, y[2], y[3]);
+        // Queries outside [2^-100, 2^40] but for 0: a part that is not a number makes the row's results so (see below the loop)
+        float big = 0.f;
+        unsigned small = ~0u;                        // twice the smallest magnitude but 0, less 1
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float c = e < 4 ? x[e & 3] : y[e & 3];
+            big = __builtin_elementwise_maximum(big, fabsf(c));
+            small = min(small, (__float_as_uint(c) << 1) - 1u);
+        }
+        if (small < (__float_as_uint(0x1p-100f) << 1) - 1u || !(big <= 0x1p40f)) own[i].l[0] = 0x7fc07fc0u;
         sm.q[0][j][lane] = own[i].h;
         sm.q[1][j][lane] = own[i].l;
         if (!QREG) sm.q[QREG ? 0 : 2][j][lane] = own[i].m;
@@ -338,6 +360,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
 
     const float c2 = p.sigma * 1.4426950408889634f;  // exp(sigma*x) = exp2(c2*x)
     float m = -INFINITY, l = 0.f;                    // l: this lane's keys only
+    float smin = INFINITY;                           // of the lane's scores, hidden keys' too (loop only)
     floatx16 o[T];
     auto reset = [&]() {
         m = -INFINITY; l = 0.f;
@@ -352,8 +375,14 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
     // the other, 12 instead of 18 in the fp32 form below, where a row's keys 27 and 31 had the score of earlier instructions, and 9
     // instead of 12 in the loop.
     auto keep_here = [](floatx16& s) __attribute__((always_inline)) { asm volatile("" : "+v"(s)); };
-    // scores of block t -> probabilities; updates m and l, rescales o
-    auto softmax = [&](int t, floatx16& s) {
+    // Scores of block t -> probabilities; updates m and l, rescales o.  parts: of the loop, whose wave takes its blocks again if a
+    // score is not a number, so it may get lost here or not; fmaxf, which passes it over, costs an instruction
+    // more for every operand of unknown origin.
+    auto softmax = [&](auto parts, int t, floatx16& s) {
+        if (decltype(parts)::value) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) smin = __builtin_elementwise_minimum(smin, s[v]);
+        }
         if (t < nA) {
             // key j is visible to row r iff j <= r and (j < ninit or j >= W); the lane's part of j,
             // 4 hf, is taken off the limits instead
@@ -377,10 +406,13 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
                     if (8 * (v >> 2) + (v & 3) > jr) s[v] = -INFINITY;
             }
         }
+        const auto larger = [](float a, float b) {
+            return decltype(parts)::value ? __builtin_elementwise_maximum(a, b) : fmaxf(a, b);
+        };
         float mx = s[0];
 #pragma unroll
-        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        for (int v = 1; v < 16; ++v) mx = larger(mx, s[v]);
+        mx = both_halves(mx, larger);
         if (__any(mx > m)) {
             const float mnew = fmaxf(m, mx);
             const float alpha = (mnew == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f((m - mnew) * c2);
@@ -423,6 +455,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
         // Two accumulation chains.  Of the nine products of the parts the three below 2^-24 of the largest are left out.
         floatx16 s2[2] = {kZero16, kZero16};
         v_rows(key);
+        const int src = v_lane();
         key = key_next;
         key_next = key_of(t + 2 * NW);
         k_rows(key);
@@ -432,7 +465,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
             Split& nx = sp[(j + 1) & 1];
             const uintx4 qh = QREG ? qreg[QREG ? j : 0] : sm.q[0][j][lane];
             const uintx4 qm = sm.q[QREG ? 0 : 2][j][lane], ql = sm.q[1][j][lane];
-            const auto next_v = load_v(j * VK, std::integral_constant<int, VK>());
+            const auto next_v = load_v(src, j * VK, std::integral_constant<int, VK>());
             const bool more = j + 1 < KS;
             __builtin_amdgcn_sched_barrier(0);
             load_k(j);                               // of the next block: piece j of this one has been split
@@ -458,14 +491,14 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
         }
         floatx16 s = s2[0] + s2[1];
         {
-            const auto next_v = load_v(8, std::integral_constant<int, 8>());
+            const auto next_v = load_v(src, 8, std::integral_constant<int, 8>());
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int v = 0; v < 8; ++v) next_v(v);   // (requested with the others they spill)
         }
         keep_here(s);
         __builtin_amdgcn_sched_barrier(0);
-        softmax(t, s);
+        softmax(std::true_type(), t, s);
         Split pr[2];                                 // probabilities of the block's 16-key halves
 #pragma unroll
         for (int c = 0; c < 2; ++c)
@@ -516,15 +549,65 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
 #pragma unroll
         for (int c = 0; c < T; ++c) acc0[c] = *(const floatx4*)(a.Accin + ri * D + col0 + 4 * c);
     }
-    // An infinite input, or one that its first part rounds to infinity, has no such parts (inf - inf): a wave whose
-    // results are not all finite takes its blocks again with the fp32 instruction, which gives what infinities give.
+    // What the parts do not hold.  An infinite input, or one that its first part rounds to infinity, has none (inf - inf): results
+    // that are not finite, as with queries out of range.  What lies below 2^-110 loses up to 2^-134:
+    //  - an entry of V: at most 2^-134 l in a result, less than 2^-24 of one that is at least 2^-96 l;
+    //  - an entry of K, with queries of at most 2^40: less than 2^-86 in a score, 2^-23 of a row's largest that is at
+    //    least 2^-63, and nothing in a probability;
+    //  - a probability, 2^100 times smaller than a row's largest or more: less than 2^-48 of every result and key, if no entry of
+    //    V is above 2^86 times the smallest result.
+    // Where a result or a largest score is smaller, but not 0 (made of zeros, as in padded columns; entries below 2^-134 count as
+    // such beside others), where all of a row is 0 or scores lie that far apart, the wave looks whether its rows of V or K
+    // hold such entries.  If so, and where results are not finite, it takes its blocks again with the fp32 instruction.
+    // d = 128, 4000 tokens, 8 heads, dense: 214 us; half of V zeros 206; scores 90 nats apart 320 (every row of V looked at);
+    // V below 2^-115 604 (fp32 instruction alone, with K and V straight to registers: 327 to 343).
     {
-        float z = 0.f * l;
+        const float lt = sum_halves(l);
+        float least = INFINITY, most = 0.f;          // (of numbers only: else these are not)
 #pragma unroll
         for (int db = 0; db < T; ++db)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) z = fmaf(0.f, o[db][v], z);
-        if (__builtin_expect(__any(!(z == 0.f)), 0)) {
+            for (int v = 0; v < 16; v += 2) {
+                const float x = fabsf(o[db][v]), y = fabsf(o[db][v + 1]);
+                least = __builtin_elementwise_minimum(__builtin_elementwise_minimum(x, y), least);
+                most = __builtin_elementwise_maximum(__builtin_elementwise_maximum(x, y), most);
+            }
+        const bool odd = !(__builtin_elementwise_maximum(most, lt) < INFINITY);
+        const bool low_s = m != 0.f && fabsf(m) < 0x1p-63f, deep = (m - smin) * c2 > 100.f;
+        bool again = __any(odd);
+        if (__builtin_expect(__any(odd || least < 0x1p-96f * lt || low_s || deep), 0) && !again) {
+            float small = INFINITY;                  // the smallest result of the row but 0
+#pragma unroll
+            for (int db = 0; db < T; ++db)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) small = o[db][v] != 0.f ? fminf(small, fabsf(o[db][v])) : small;
+            const bool low_o = small < 0x1p-96f * lt || (most == 0.f && lt > 0.f);
+            const float limit = __any(deep) ? 0x1p86f * wave_reduce<1>(small, [](float a, float b) { return fminf(a, b); }) : INFINITY;
+            // an entry below 2^-100 but 0, or above the limit (always_inline: outlined, it would take o through memory)
+            auto holds = [&](const float* rows, long long stride, float top) __attribute__((always_inline)) -> bool {
+                bool found = false;
+#pragma unroll 1
+                for (int t = wave; t < nT && !found; t += NW) {
+                    const int kk = key_of(t);
+                    floatx4 x[KB * D / 256];
+#pragma unroll
+                    for (int i = 0; i < KB * D / 256; ++i) {
+                        const int e = 256 * i + 4 * lane;
+                        x[i] = *(const floatx4*)(rows + __shfl(kk, e / D, 64) * stride + e % D);
+                    }
+#pragma unroll
+                    for (int i = 0; i < KB * D / 256; ++i)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            found |= x[i][c] != 0.f && (fabsf(x[i][c]) < 0x1p-100f || fabsf(x[i][c]) > top);
+                    found = __any(found);
+                }
+                return found;
+            };
+            again = (__any(low_s) && holds(kb_, p.ks[2], INFINITY)) || (__any(low_o || deep) && holds(vb_, p.vs[2], limit));
+        }
+        l = lt;
+        if (__builtin_expect(again, 0)) {
             reset();
 #pragma unroll 1
             for (int t = wave; t < nT; t += NW) {
@@ -540,22 +623,22 @@ __global__ __launch_bounds__(64 * NW, D == 128 || WIDE ? 2 : 3) void engine_fp32
                 }
                 floatx16 s = s2[0] + s2[1];
                 keep_here(s);
-                softmax(t, s);
+                softmax(std::false_type(), t, s);
                 v_rows(kk);
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {       // k slot hf of step v is key 8 (v / 4) + 4 hf + v % 4
-                    load_v(v, std::integral_constant<int, 1>())(0);
+                    load_v(v_lane(), v, std::integral_constant<int, 1>())(0);
 #pragma unroll
                     for (int db = 0; db < T; ++db)
                         o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(comp(vf[v], db), s[v], o[db], 0, 0, 0);
                 }
             }
+            l = sum_halves(l);
         }
     }
 
     // ---- merge the four waves' states.  Wave w finishes O^T registers 4 w .. 4 w + 3 of every column
     // block: of row n the columns T (8 w + 4 hf) .. + 4 T - 1.
-    l += __shfl_xor(l, 32, 64);
     __syncthreads();                                 // the query parts are no longer read
 #pragma unroll
     for (int db = 0; db < T; ++db)

@@ -213,6 +213,74 @@ def test_fp32_infinity_in_stage1(api, d):
     assert not got[:, 5].isfinite().any()
 
 
+def _fp32_state(api, q, k, v):
+    """dense output and lse, and M, L, Acc / L of a call whose one group attends every key"""
+    N, d = q.shape[2:]
+    out = torch.zeros_like(q)
+    p = api.make_params(api.Config(block=32, n_init=32, window=32, step=128, theta=1.0), q, k, v, out)
+    b = api.alloc_stage_buffers(p)
+    api.dense_causal_flash(p, q, k, v, out, b["lse"])
+    api.anchor_compute(p, q, k, v, b["M"], b["L"], b["Acc"], b["xa"])
+    return out[0, 0], b["lse"], b["M"], b["L"], b["Acc"].view(N, d) / b["L"].view(N, 1)
+
+
+def _fp64_state(q, k, v):
+    N, d = q.shape[2:]
+    s = (q[0, 0].double() @ k[0, 0].double().T) / math.sqrt(d)
+    s.masked_fill_(torch.ones(N, N, dtype=torch.bool, device="cuda").triu(1), -math.inf)
+    m = s.max(dim=1).values
+    l = torch.exp(s - m[:, None]).sum(dim=1)
+    out = torch.softmax(s, dim=1) @ v[0, 0].double()
+    return out, torch.logsumexp(s, dim=1), m, l, out
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("eq,ek,ev", [
+    (0, 0, -109), (0, 0, -112), (0, 0, -118), (0, 0, -124),     # V across the line where three bf16 parts hold fewer than 24 bits
+    (0, -112, 0), (0, -122, 0), (-112, 0, 0), (-122, 0, 0), (-55, -60, 0),
+    (-120, 120, 0), (120, -120, 0), (-120, 120, -120), (60, -60, 100), (42, -42, 0), (0, 0, 110)])
+def test_fp32_magnitudes(api, d, eq, ek, ev):
+    """Inputs of any magnitude (powers of two times normal values) at the precision of ordinary ones."""
+    N, gen = 300, torch.Generator(device="cuda").manual_seed(d)
+    q, k, v = (torch.randn(1, 1, N, d, generator=gen, device="cuda") * 2.0 ** e for e in (eq, ek, ev))
+    for name, got, want in zip(("out", "lse", "M", "L", "Acc/L"), _fp32_state(api, q, k, v), _fp64_state(q, k, v)):
+        got = got.reshape(want.shape).double()
+        assert (got - want).norm() < 1e-6 * want.norm(), name       # ordinary magnitudes: up to 2e-7
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_fp32_mixed_magnitudes(api, d):
+    """Zeros, and rows whose results hang on the smallest entries: of V, of K, of the probabilities."""
+    N, gen = 300, torch.Generator(device="cuda").manual_seed(d)
+    q, k, v = (torch.randn(1, 1, N, d, generator=gen, device="cuda") for _ in range(3))
+    plain = _fp32_state(api, q, k, v)
+    vz = v.clone()
+    vz[..., d // 2:] = 0                                             # zero columns of V: the other columns keep their bits
+    got = _fp32_state(api, q, k, vz)
+    assert torch.equal(got[0][:, :d // 2], plain[0][:, :d // 2]) and not got[0][:, d // 2:].any()
+    vt = v.clone()
+    vt[..., d // 2:] *= 2.0 ** -120                                  # tiny columns beside ordinary ones
+    got, want = _fp32_state(api, q, k, vt)[0].double(), _fp64_state(q, k, vt)[0]
+    for c in (slice(0, d // 2), slice(d // 2, d)):
+        assert (got[:, c] - want[:, c]).norm() < 1e-6 * want[:, c].norm()
+    vs = v * 2.0 ** -138                                             # subnormal results: their spacing is 2^-9 of them
+    got, want = _fp32_state(api, q, k, vs)[0].double(), _fp64_state(q, k, vs)[0]
+    assert (got - want).norm() < 1e-2 * want.norm()
+    kt = k.clone()
+    kt[0, 0, :40] *= 2.0 ** -120                                     # the first rows see tiny keys only
+    got, want = _fp32_state(api, q, kt, v), _fp64_state(q, kt, v)
+    assert (got[2][:40].double() - want[2][:40]).norm() < 1e-6 * want[2][:40].norm()
+    assert (got[0].double() - want[0]).norm() < 1e-6 * want[0].norm()
+    # one key 85 nats above the rest, whose values are 2^122 times its own: probabilities of 2^-122 make half of the result
+    q2, k2, v2 = torch.zeros_like(q), torch.zeros_like(k), v.clone()
+    q2[..., 0] = 1.0
+    k2[0, 0, 0, 0] = 85 * math.sqrt(d)
+    v2[0, 0, 1:] *= 2.0 ** 122
+    got, want = _fp32_state(api, q2, k2, v2)[0].double(), _fp64_state(q2, k2, v2)[0]
+    # a probability's relative error is that of its exponent, 122 x 2^-24 times ln 2, twice (product and exponential)
+    assert (got - want).norm() < 2e-5 * want.norm()
+
+
 def test_fp32_rows_beyond_32_bit_offsets(api):
     """Keys 16 MiB apart: 300 of them span 4.7 GiB and are addressed with 64 bits, to the same bits."""
     N, d, gen = 300, 64, torch.Generator(device="cuda").manual_seed(1)
