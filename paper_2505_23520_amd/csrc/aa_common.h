@@ -100,7 +100,8 @@ __device__ __forceinline__ int window_start(const KParams& p, int g) {
 // Work-group id -> (batch, query head, query block).  The hardware deals
 // consecutive work-groups round-robin to the 8 XCDs; this map keeps all query
 // heads of one KV head on one XCD (its K/V stay in that XCD's L2) and hands out
-// the longest query blocks first (causal work grows with the block index).
+// the last query blocks first: the longest of dense attention and of lists, whose work grows with the block index.  (The
+// anchor region's grows with the block's place in its group only.)
 struct Work { int b, h, i; };
 // per_pair: nblk * Hq / Hkv
 __device__ __forceinline__ Work decode_work(const KParams& p, int nblk, const FastDiv& per_pair, unsigned id) {

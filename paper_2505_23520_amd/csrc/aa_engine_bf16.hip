@@ -432,8 +432,8 @@ __global__ __launch_bounds__(256, 3) void engine_bf16_kernel(EngineArgs a) {
 // the other things that stage 2 needs.  The scores are those of engine_bf16_kernel, instruction by instruction, so the maxima
 // are the same bits.  Bound: a block is six tiles at step 1, 3000 matrix cycles a wave, between the latencies of its query rows
 // and of its exports; so a work-group walks every gridDim.x-th block (all blocks cost the same) and requests the next block's
-// query rows ahead of the exports of this one.  16384 tokens, 32 heads: about 60 us with a work-group per block, 50 so (the whole call
-// 2 % faster); its compulsory bytes take 34 us.
+// query rows ahead of the exports of this one.  16384 tokens, 32 heads: 78 us with a work-group per block and exports through LDS, 70
+// so (the walk alone makes the whole call 2 % faster); its compulsory bytes take 34 us.
 __global__ __launch_bounds__(256, 3) void anchor_max_bf16_kernel(EngineArgs a, unsigned total) {
     __shared__ __attribute__((aligned(16))) char Ks0[KBYTES], Ks1[KBYTES];
     __shared__ float red[4], knorm[4], qpart[4][128];
